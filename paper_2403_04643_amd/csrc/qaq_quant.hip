@@ -1854,7 +1854,7 @@ __global__ __launch_bounds__(kThreads) void k_select(QaqSelectArgs a) {
 }
 
 // ---------------------------------------------------------------------------------
-// Canonical export and dequantization (tests, export; not on the decode path).
+// Canonical export (tests, export; not on the decode path) and dequantization.
 // ---------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
@@ -1893,36 +1893,234 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
   }
 }
 
-template <int D>
+// Dequantization.  Bound by the fp16 rows it writes (2 D bytes per token side against D b / 8 read), so
+// everything is arranged for whole-line traffic: a work item is eight channels of a token, D/8 lanes
+// write one row's 2 D consecutive bytes with 16-byte stores, and codes are read in the words they are
+// stored in and spread four at a time by masks, not code by code.  Keys: slot order, an item's word
+// belongs to the token alone.  Values: an item is (unit of 16 tokens, eight channels) -- eight words, each
+// one channel of the 16 tokens, turned into rows by 4x4 byte transposes; the D/8 lanes of a unit read its
+// 4 D bytes between them.
+// 8 sequences x 32 heads x 4096 tokens x 128 channels, all 8-bit (805 MB): 1232 us code by code through
+// an LDS staging tile, 190-205 us (4 TB/s, a copy of that size: 5.1) so.
+
+// eight codes (one per byte, channels in order) -> eight fp16 values, with the outliers among these channels
+// put in: ch0 = first channel, NO2 outlier entries per token (idx: one byte each, 0xff = unused)
+template <int NO2>
+struct DequantToken {
+  float scale, mn;
+  uint32_t idx[(NO2 + 3) / 4 > 0 ? (NO2 + 3) / 4 : 1];
+  uint32_t val[(NO2 + 1) / 2 > 0 ? (NO2 + 1) / 2 : 1];
+  __device__ __forceinline__ uint4 eight(uint32_t lo, uint32_t hi, int ch0) const {
+    uint32_t h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t w = j < 2 ? lo : hi;
+      const float c0 = (float)((w >> (16 * (j & 1))) & 0xffu) + 0.5f, c1 = (float)((w >> (16 * (j & 1) + 8)) & 0xffu) + 0.5f;
+      const float p0 = c0 * scale, p1 = c1 * scale;
+      h[j] = (uint32_t)f2h(p0 + mn) | ((uint32_t)f2h(p1 + mn) << 16);
+    }
+#pragma unroll
+    for (int k = 0; k < NO2; ++k) {
+      const int rel = (int)((idx[k >> 2] >> (8 * (k & 3))) & 0xffu) - ch0;
+      if ((unsigned)rel < 8u) {
+        const uint32_t ov = (val[k >> 1] >> (16 * (k & 1))) & 0xffffu;
+        const uint32_t m = rel & 1 ? 0xffff0000u : 0xffffu, x = ov | (ov << 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] = (rel >> 1) == j ? ((h[j] & ~m) | (x & m)) : h[j];
+      }
+    }
+    return make_uint4(h[0], h[1], h[2], h[3]);
+  }
+};
+
+// NO2: outlier entries per token: 0, 2, or up to 8 (the run-time count v.no2; also the variable-length store)
+template <int D, int NO2>
 __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  TileLds<D>& L = *reinterpret_cast<TileLds<D>*>(smem_raw);
+  constexpr int NI = NO2 ? (NO2 + 3) / 4 : 1, NV = NO2 ? (NO2 + 1) / 2 : 1;
+  constexpr int LPT = D / 8, KS = D / 64;
+  __shared__ float s_scale[QAQ_TT], s_mn[QAQ_TT];
+  __shared__ int s_row[QAQ_TT];                  // by slot: output row, -1 = outside [t0, t1)
+  __shared__ uint32_t s_idx[NI][QAQ_TT], s_val[NV][QAQ_TT];
   const QaqView& v = a.v;
   const int tid = threadIdx.x;
-  const int tile = a.t0 / QAQ_TT + blockIdx.x;
-  const int bh = blockIdx.y, b = bh / v.Hkv, h = bh % v.Hkv;
+  // heads fastest, then tiles (see k_build)
+  const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv;
+  const int tile = a.t0 / QAQ_TT + blockIdx.y;
   const int side = blockIdx.z;
   if (a.out[side] == nullptr) return;
   const int t0 = tile * QAQ_TT;
   const int n_tok = min(qaq_seq_len(v, b, a.len) - t0, QAQ_TT);
   if (n_tok <= 0) return;
-  tile_load<D>(v, side, b, h, tile, n_tok, L);
-  const int nt = a.t1 - a.t0;
-  for (int e = tid; e < n_tok * D; e += kThreads) {
-    const int pos = e / D, d = e % D;
+  const QaqCounts c = qaq_load_counts(v, side, b, h, tile, n_tok);
+  if (tid < n_tok) {
+    const size_t gi = qaq_slot_index(v, b, h, tile, tid);
+    const int pos = v.perm[side][gi];
+    const uint32_t mm = v.mm[side][gi];
+    uint32_t ix[NI], vx[NV];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) ix[k] = 0xffffffffu;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) vx[k] = 0u;
+    if constexpr (NO2 == 2) {
+      ix[0] = *(const uint16_t*)(v.oidx[side] + gi * 2) | 0xffff0000u;
+      vx[0] = *(const uint32_t*)(v.oval[side] + gi * 2);
+    } else if constexpr (NO2 > 2) {
+      size_t e0 = gi * v.no2;
+      int cnt = v.no2;
+      if (v.csr) {
+        const size_t g0 = qaq_slot_index(v, b, h, tile, 0);
+        cnt = v.ocnt[side][g0 + pos];
+        e0 = g0 * v.no2 + v.ostart[side][g0 + pos];
+      }
+#pragma unroll
+      for (int k = 0; k < NO2; ++k)
+        if (k < cnt) {
+          ix[k >> 2] = (ix[k >> 2] & ~(0xffu << (8 * (k & 3)))) | ((uint32_t)v.oidx[side][e0 + k] << (8 * (k & 3)));
+          vx[k >> 1] |= (uint32_t)v.oval[side][e0 + k] << (16 * (k & 1));
+        }
+    }
+    const float mn = h2f((uint16_t)(mm & 0xffffu)), mx = h2f((uint16_t)(mm >> 16));
+    s_scale[tid] = ldexpf(mx - mn, -c.bits_of_slot(tid));
+    s_mn[tid] = mn;
     const int t = t0 + pos;
-    if (t < a.t0 || t >= a.t1) continue;
-    const int bits = L.bits_old[pos];
-    const float mn = h2f((uint16_t)(L.mm[pos] & 0xffffu)), mx = h2f((uint16_t)(L.mm[pos] >> 16));
-    const float range = mx - mn;
-    const float scale = ldexpf(range, -bits);
-    const float half_c = (float)L.stage[pos][d] + 0.5f;
-    const float prod = half_c * scale;
-    float xh = prod + mn;
-    uint16_t hb = f2h(xh);
-    for (int k = 0; k < v.no2; ++k)
-      if (L.oidx[pos][k] == d) hb = L.oval[pos][k];
-    a.out[side][((size_t)bh * nt + (t - a.t0)) * D + d] = __ushort_as_half(hb);
+    s_row[tid] = t >= a.t0 && t < a.t1 ? t - a.t0 : -1;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) s_idx[k][tid] = ix[k];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) s_val[k][tid] = vx[k];
+  }
+  __syncthreads();
+  const uint8_t* base = qaq_tile_codes(v, side, b, h, tile);
+  __half* out = a.out[side] + (size_t)bh * (a.t1 - a.t0) * D;
+  auto put = [&](int slot, int ch0, uint32_t lo, uint32_t hi) {
+    const int row = s_row[slot];
+    if (row < 0) return;
+    DequantToken<NO2> tk;
+    tk.scale = s_scale[slot]; tk.mn = s_mn[slot];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) tk.idx[k] = s_idx[k][slot];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) tk.val[k] = s_val[k][slot];
+    const uint4 x = tk.eight(lo, hi, ch0);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 xv = {x.x, x.y, x.z, x.w};
+    __builtin_nontemporal_store(xv, (u32x4*)(out + (size_t)row * D + ch0));      // written once, read by somebody else
+  };
+  const int n32 = c.n32(), first8 = n32 + c.n4, first1 = c.first1();
+  if (side == 0) {
+    const QaqKRegions r = qaq_k_regions(c, D);
+#pragma unroll 2
+    for (int it = tid; it < n_tok * LPT; it += kThreads) {
+      const int s = it / LPT, c8 = it % LPT;           // channels 8 c8 .. +7: half `hf` of slice q
+      const int hf = c8 & 1, q = ((c8 >> 1) & 3) * KS + (c8 >> 3);
+      uint32_t lo, hi;
+      if (s < n32) {
+        const uint32_t w = *(const uint32_t*)(base + r.r2 + (uint32_t)s * (D / 4) + 4u * (uint32_t)q) >> (4 * hf);
+        lo = w & 0x03030303u; hi = (w >> 2) & 0x03030303u;
+        if (s < c.n3) {
+          const uint32_t l = *(const uint32_t*)(base + r.r1 + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1)) >> (4 * (q & 1) + 2 * hf);
+          lo = (lo << 1) | (l & 0x01010101u); hi = (hi << 1) | ((l >> 1) & 0x01010101u);
+        }
+      } else if (s < first8) {
+        const uint32_t w = *(const uint32_t*)(base + r.r4 + (uint32_t)(s - n32) * (D / 2) + 4u * (uint32_t)(2 * q + hf));
+        lo = w & 0x0f0f0f0fu; hi = (w >> 4) & 0x0f0f0f0fu;
+      } else if (s < first1) {
+        const uint2 w = *(const uint2*)(base + r.r8 + (uint32_t)(s - first8) * D + 16u * (uint32_t)q + 8u * (uint32_t)hf);
+        lo = w.x ^ 0x80808080u; hi = w.y ^ 0x80808080u;
+      } else {
+        const uint32_t l = *(const uint32_t*)(base + r.r1b + (uint32_t)(s - first1) * (D / 8) + 4u * (uint32_t)(q >> 1)) >> (4 * (q & 1) + 2 * hf);
+        lo = l & 0x01010101u; hi = (l >> 1) & 0x01010101u;
+      }
+      put(s, 8 * c8, lo, hi);
+    }
+    return;
+  }
+  const QaqVRegions r = qaq_v_regions(c, D);
+  // the 2-bit field units (and the low bits of the 3-bit tokens among them)
+  for (int it = tid; it < ((n32 + 15) / 16) * LPT; it += kThreads) {
+    const int u = it / LPT, c8 = it % LPT, cg = c8 >> 1, n0 = 8 * (c8 & 1);     // channels 16 cg + n0 .. +7
+    uint32_t w[8], l[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = *(const uint32_t*)(base + r.r2 + (uint32_t)u * (4 * D) + 4u * (uint32_t)((n0 + k) * (D / 16) + cg));
+    const bool low = 16 * u < c.n3;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      l[k] = low ? *(const uint32_t*)(base + r.r1 + (uint32_t)u * (2 * D) + 4u * (uint32_t)((n0 + k) * (D / 32) + (cg >> 1))) >> (4 * (cg & 1)) : 0u;
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+      uint32_t x[4], tl[4], th[4], ll[4], lh[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (w[k] >> (2 * vq)) & 0x03030303u;
+      transpose4(x, tl);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (w[4 + k] >> (2 * vq)) & 0x03030303u;
+      transpose4(x, th);
+      if (low) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = (l[k] >> vq) & 0x01010101u;
+        transpose4(x, ll);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = (l[4 + k] >> vq) & 0x01010101u;
+        transpose4(x, lh);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int s = 16 * u + 4 * vq + j;
+        if (s >= n32) break;
+        uint32_t lo = tl[j], hi = th[j];
+        if (s < c.n3) { lo = (lo << 1) | ll[j]; hi = (hi << 1) | lh[j]; }
+        put(s, 8 * c8, lo, hi);
+      }
+    }
+  }
+  for (int it = tid; it < ((c.n4 + 7) / 8) * LPT; it += kThreads) {
+    const int hu = it / LPT, c8 = it % LPT, cg = c8 >> 1, n0 = 8 * (c8 & 1);
+    uint32_t w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = *(const uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D) + 4u * (uint32_t)((n0 + k) * (D / 16) + cg));
+#pragma unroll
+    for (int vq = 0; vq < 2; ++vq) {
+      uint32_t x[4], tl[4], th[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (w[k] >> (4 * vq)) & 0x0f0f0f0fu;
+      transpose4(x, tl);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (w[4 + k] >> (4 * vq)) & 0x0f0f0f0fu;
+      transpose4(x, th);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i4 = 8 * hu + 4 * vq + j;
+        if (i4 < c.n4) put(n32 + i4, 8 * c8, tl[j], th[j]);
+      }
+    }
+  }
+#pragma unroll 2
+  for (int it = tid; it < c.n8 * LPT; it += kThreads) {        // token-major bytes
+    const int i8 = it / LPT, c8 = it % LPT;
+    const uint2 w = *(const uint2*)(base + r.r8 + (uint32_t)i8 * D + 8u * (uint32_t)c8);
+    put(first8 + i8, 8 * c8, w.x, w.y);
+  }
+  for (int it = tid; it < ((c.n1 + 15) / 16) * LPT; it += kThreads) {
+    const int u = it / LPT, c8 = it % LPT, cg = c8 >> 1, n0 = 8 * (c8 & 1);
+    uint32_t l[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      l[k] = *(const uint32_t*)(base + r.r1b + (uint32_t)u * (2 * D) + 4u * (uint32_t)((n0 + k) * (D / 32) + (cg >> 1))) >> (4 * (cg & 1));
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+      uint32_t x[4], tl[4], th[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (l[k] >> vq) & 0x01010101u;
+      transpose4(x, tl);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (l[4 + k] >> vq) & 0x01010101u;
+      transpose4(x, th);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i1 = 16 * u + 4 * vq + j;
+        if (i1 < c.n1) put(first1 + i1, 8 * c8, tl[j], th[j]);
+      }
+    }
   }
 }
 
@@ -2052,9 +2250,17 @@ hipError_t qaq_launch_export(const QaqExportArgs& a, hipStream_t s) {
 hipError_t qaq_launch_dequant(const QaqDequantArgs& a, hipStream_t s) {
   if (a.t1 <= a.t0) return hipSuccess;
   const int tile_lo = a.t0 / QAQ_TT, tile_hi = (a.t1 - 1) / QAQ_TT;
-  dim3 grid(tile_hi - tile_lo + 1, a.v.B * a.v.Hkv, 2);
-  if (a.v.D == 128) hipLaunchKernelGGL(k_dequant<128>, grid, dim3(kThreads), sizeof(TileLds<128>), s, a);
-  else hipLaunchKernelGGL(k_dequant<64>, grid, dim3(kThreads), sizeof(TileLds<64>), s, a);
+  const dim3 grid(a.v.B * a.v.Hkv, tile_hi - tile_lo + 1, 2), block(kThreads);
+  const int no2 = a.v.csr ? QAQ_MAX_NO2 : a.v.no2;
+  if (a.v.D == 128) {
+    if (no2 == 2) hipLaunchKernelGGL((k_dequant<128, 2>), grid, block, 0, s, a);
+    else if (no2 == 0) hipLaunchKernelGGL((k_dequant<128, 0>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_dequant<128, QAQ_MAX_NO2>), grid, block, 0, s, a);
+  } else {
+    if (no2 == 2) hipLaunchKernelGGL((k_dequant<64, 2>), grid, block, 0, s, a);
+    else if (no2 == 0) hipLaunchKernelGGL((k_dequant<64, 0>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_dequant<64, QAQ_MAX_NO2>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 
