@@ -203,3 +203,25 @@ def test_window_kept_in_fp16(store):
         np.testing.assert_array_equal(bk_g.cpu().numpy(), bk_o)
         np.testing.assert_array_equal(bv_g.cpu().numpy(), bv_o)
     compare_canonical(oc, gc, "after the decode steps")
+
+
+@pytest.mark.parametrize("D,Hkv,G,T,n,gain", [
+    (128, 2, 1, 1025, 8, 1.0),       # one token in the last share of a row, one in its last group of 64
+    (64, 1, 20, 1088, 3, 12.0),      # more query heads than one merge pass takes; peaked rows, groups of very different maxima
+    (64, 3, 2, 64, 8, 30.0),         # one group of 64, rows that end inside it
+    (128, 1, 16, 4161, 1, 6.0),
+])
+def test_score_rows_over_many_shares(D, Hkv, G, T, n, gain):
+    """The rows and the window they leave, where a row is merged from several groups of 64 tokens and written by
+    several workgroups; the window through the widths of the next selection."""
+    sh = W.shape(3, batch=2, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
+    _log(f"prefill rows: {sh} rows={n} gain={gain}")
+    K, V = W.make_kv(3, sh)
+    q_last = np.ascontiguousarray(W.make_queries(3, sh, n=n, seed_offset=4).transpose(1, 2, 0, 3) * F16(gain))
+    oc, gc = make_pair(sh, 0.01, max_tokens=T, window=8, sigma_s_max=1e-3, sigma_x_max=1e-2)
+    rows = gc.prefill_window(dev(q_last), dev(K)).cpu().numpy()
+    _log(f"  worst score error {_check_rows(rows, q_last, K, G):.2e}")
+    bk_g, bv_g = gc.quantize_append_selected(dev(K), dev(V), want_bits=True)
+    bk_o, bv_o, _ = oc.prefill(q_last, K, V, score_rows=[rows[i][..., : T - n + i + 1] for i in range(n)])
+    np.testing.assert_array_equal(bk_g.cpu().numpy(), bk_o)
+    np.testing.assert_array_equal(bv_g.cpu().numpy(), bv_o)
