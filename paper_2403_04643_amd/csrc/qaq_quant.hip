@@ -3,6 +3,7 @@
 // the fp32 operation order of the encoder and decoder is part of the contract
 // (one rounding per operation, round to nearest even).
 #include "qaq_internal.h"
+#include <type_traits>
 
 namespace {
 
@@ -1260,123 +1261,292 @@ __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
 }
 
 // ---------------------------------------------------------------------------------
-// Decode-step update, fast kernel (Section 4.2 "Integration in text generation process": the
-// part of a step after the attention).  Same result as build_tile in mode 2, for the common
-// configuration (one outlier per end, fixed-length side store, widths within {2,3,4,8}), built
-// for what a decode step does to a tile: a few tokens change width, one token is appended to
-// the last tile, everything else stays.  A workgroup evaluates the rules for its tile side,
-// leaves at once if nothing moves, re-assigns slots so that as few tokens move as possible
-// (a token keeps its place inside its region; tiles in which more than kMaxMoved tokens move
-// are handed to the general kernel through a list), and carries only the moved tokens' codes
-// through LDS.  A fifth of
-// the general kernel's LDS and half its registers: eight workgroups per compute unit hide its
-// two dependent round trips to memory.
+// Decode-step update (Section 4.2 "Integration in text generation process": the part of a step
+// after the attention).  Same result as build_tile in mode 2, built for what a decode step does to
+// a tile: a few tokens change width, one token is appended to the last tile, everything else stays.
+//
+// Two wavefronts per tile side, two tokens per lane.  What bounds the update is the chain of dependent
+// steps of a tile side -- metadata, widths, codes of the tokens that move, read-modify-write of the words
+// they go to -- and the instructions spent on all 256 tokens of a tile to move the dozen that change.  Half
+// as many wavefronts as tokens / 64 evaluate what is uniform over the tile half as often and leave room for
+// sixteen tile sides per compute unit (10 KB of LDS, 64 registers), so that all value sides of a 4096-token
+// layer of 256 heads are in flight at once.
+//
+// A tile side with nothing to do is left after one 8-byte load (keys) or after the rules.  Slots are
+// re-assigned so that as few tokens move as possible: a token keeps its index inside its class's
+// region.  A region whose start moves (a class count before it crossed a multiple of 16) is copied as
+// a whole, 16 bytes per lane, up to kMaxCopy bytes of them; only the codes of the tokens that change
+// class, are squeezed out or arrive go through LDS.  Tile sides in which more than kMaxMoved tokens
+// move (a hyper-parameter that jumped) are handed to the general kernel through a list.
 // ---------------------------------------------------------------------------------
-constexpr int kMaxMoved = 64;
+constexpr int kMaxMoved = 60;       // (sixteen tile sides' LDS fit a compute unit)
+constexpr int kMaxCopy = 8192;
+constexpr int kUpdThreads = 128;
 
 template <int D>
 struct UpdLds {
   static constexpr int SROW = D / 4 + 1;   // dwords per staged row (odd stride: rows spread over the banks)
-  float pred[QAQ_TT];                      // value side: predicted score by position
-  uint32_t stage[kMaxMoved * SROW];        // codes of the moved tokens at their new width, byte d = channel d
-  uint32_t mv_a[kMaxMoved];                // moved list: token (thread) index | new slot << 16
-  uint32_t mv_b[kMaxMoved];                // ... old width | new width << 8 | position << 16
+  union {
+    uint32_t stage[kMaxMoved * SROW];      // codes of the moved tokens at their new width; keys: byte d = channel d; values:
+                                           // byte n*(D/16) + g = channel 16*g + n, the order of a unit's words
+    struct {                               // ... before any code is gathered, by position:
+      alignas(16) float pred[QAQ_TT];      // value side: predicted score
+      uint32_t oext[QAQ_TT];               // value side, variable-length side store: largest | smallest outlier << 16 (fp16), all ones: none
+    } p;
+  };
+  uint32_t mv[kMaxMoved];                  // moved list: token | new slot << 8 | position << 16 | old width << 24 | new width << 28
   uint32_t mv_mm[kMaxMoved];               // ... fp16 min | max << 16
   uint8_t cls_new[QAQ_TT];                 // by token: class after this step (0xff: no token)
   uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list, 0xff = what is stored stays
-  uint8_t freeslot[QAQ_TT];                // per class, in slot order: the slots no token keeps
-  uint32_t mask2[16], mask4[32];           // value side: slots to write per unit of 16 (2-bit fields) / half-unit of 8 (4-bit)
-  int wave_cnt[4][4], wave_need[4][4], wave_free[4][4];
-  int wave_moved[4];
-  int wave_wide[4];                        // widenings asked for, per wavefront
-  int wave_any[4];                         // a token of the wavefront changes width or arrives
-  float wave_bound[4], wave_bound2[4];
-  uint32_t new_mm, new_oi, new_ov;         // the appended token: min | max, outlier channels, outlier values
-  uint32_t newrow[D / 4];                  // ... its codes at the widest width, byte d = channel d
+  uint8_t freeslot[QAQ_TT];                // per class: the slots no token keeps, the first wavefront's from the front, the second's from the back
+  uint32_t mask2[16], mask4[32], mask1b[16];   // value side: slots to write per unit of 16 (2-bit fields, 1-bit tokens) or half-unit of 8 (4-bit)
+  unsigned long long written[QAQ_TT / 64 + 1];   // ... bit by slot
+  uint32_t newrow[D / 4];                  // the appended token: its codes at the widest width, byte d = channel d
+  uint32_t new_oi[2], new_ov[4];           // ... outlier channels, outlier values
+  uint32_t new_mm;
+  int new_no;                              // ... outliers (variable-length side store)
+  int w_cls[2][QAQ_NCLASS], w_need[2][QAQ_NCLASS], w_free[2][QAQ_NCLASS];      // per wavefront
+  int w_any[2], w_wide[2], w_moved[2];
+  float w_bnd[2], w_lo[2], w_hi[2];
+  uint8_t units[2][32];                    // ... units with words to write
 };
 
-// unsigned wavefront reductions on the data-parallel-primitive path
+// unsigned wavefront reductions
 __device__ __forceinline__ uint32_t wave_umax(uint32_t x) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) { const uint32_t y = (uint32_t)__shfl_xor((int)x, o); x = x > y ? x : y; }
-  return x;
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 __device__ __forceinline__ uint32_t wave_umin(uint32_t x) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) { const uint32_t y = (uint32_t)__shfl_xor((int)x, o); x = x < y ? x : y; }
-  return x;
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 __device__ __forceinline__ uint16_t key16_bits(uint32_t key) {     // fp16 bits of a key made by order_keys_pair (upper half)
   const uint32_t k = key >> 16;
   return (uint16_t)(k >= 0x8000u ? k - 0x8000u : ((0x8000u - k) | 0x8000u));
 }
 __device__ __forceinline__ uint32_t width_mask(int bits) { return 0x01010101u * ((1u << bits) - 1u); }
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set bits of `mask` below this lane
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
 
-// Four codes (channels 4*c4 .. 4*c4+3, one per byte) of the token in old slot `slot`, keys.  The
-// class only selects addresses, shifts and masks: the loads themselves are unconditional (two, the
-// second one repeating the first where the token has no low-bit plane), so that they are in
-// flight together.
-template <int D>
-__device__ __forceinline__ uint32_t k_old_codes(const uint8_t* base, const QaqCounts& c, const QaqKRegions& r, int slot, int c4) {
+// The window's part of the value rule (Section 4.2) for two consecutive positions of one lane: largest
+// score over this step's row (the maximum over the G query heads, rounded to what the window stores:
+// `s`) and the window's rows.  As qaq_predicted, with loads of two elements (rows start at any multiple of
+// the element: the loads are written as copies, so the compiler knows the alignment), all in flight
+// together: W rows are read whatever the window's length (1, 3, 5 or 8: what it has not is row 0 again).
+// ri: index of the lane's first position inside a ring row; p0: that position inside the tile; lim[r]:
+// positions of the tile that row r covers.
+struct Two { float x[2]; };
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// maximum in one instruction: of a NaN and a number the number, as fmaxf, but without its test for signalling NaNs
+__device__ __forceinline__ float vmaxf(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <int W, typename RAW>
+__device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
+                                             const Two (&g)[4], float (&s)[2], float (&m)[2]) {
+  const size_t ring_row = (size_t)v.B * v.Hkv * v.Tmax;
+  struct R2 { RAW x[2]; } raw[W];
+#pragma unroll
+  for (int r = 0; r < W; ++r) __builtin_memcpy(&raw[r], (const RAW*)v.ring + ((size_t)(r < v.window && r != skip ? r : 0) * ring_row + ri), sizeof(R2));
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    s[e] = qaq_ring_value(v, vmaxf(vmaxf(vmaxf(s[e], g[0].x[e]), vmaxf(g[1].x[e], g[2].x[e])), g[3].x[e]));
+    m[e] = s[e];
+  }
+#pragma unroll
+  for (int r = 0; r < W; ++r) {
+    const int end = r < v.window && r != skip ? lim[r] : 0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const float x = sizeof(RAW) == 4 ? __uint_as_float((uint32_t)raw[r].x[e])
+                    : v.ring_half == 1 ? h2f((uint16_t)raw[r].x[e]) : __uint_as_float((uint32_t)raw[r].x[e] << 16);
+      m[e] = vmaxf(m[e], p0 + e < end ? x : 0.0f);
+    }
+  }
+}
+template <typename RAW>
+__device__ __forceinline__ void predicted2_t(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
+                                             const Two (&g)[4], float (&s)[2], float (&m)[2]) {
+  if (v.window == 1) predicted2_w<1, RAW>(v, lim, skip, ri, p0, g, s, m);
+  else if (v.window <= 3) predicted2_w<3, RAW>(v, lim, skip, ri, p0, g, s, m);
+  else if (v.window <= 5) predicted2_w<5, RAW>(v, lim, skip, ri, p0, g, s, m);
+  else predicted2_w<8, RAW>(v, lim, skip, ri, p0, g, s, m);
+}
+__device__ __forceinline__ void predicted2(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
+                                           const float* row, int G, size_t stride, float (&s)[2], float (&m)[2]) {
+  Two g[4];
+  s[0] = s[1] = 0.0f;                                       // probabilities: >= 0
+#pragma unroll 1
+  for (int g0 = 4; g0 < G; g0 += 4) {                       // query heads beyond the first four
+#pragma unroll
+    for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], row + (size_t)min(g0 + j, G - 1) * stride, sizeof(Two));
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) s[e] = vmaxf(s[e], g[j].x[e]);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], row + (size_t)min(j, G - 1) * stride, sizeof(Two));
+  if (v.ring_half) predicted2_t<uint16_t>(v, lim, skip, ri, p0, g, s, m);
+  else predicted2_t<uint32_t>(v, lim, skip, ri, p0, g, s, m);
+}
+
+// Where four codes of a stored token are and how they are taken out of their words.  The class only
+// selects addresses, shifts and masks: the loads themselves are unconditional, so that those of several items
+// are in flight together.  Keys: channels 4*c4 .. 4*c4+3, in word w, and word l where a 3-bit token has its
+// low bits.  Values: the four consecutive words 4*c .. 4*c+3 of the token's unit, one channel each (one 16-byte
+// load: as four loads of a word each, the channels in order, the kernel took 36.3 instead
+// of 34.8 us at 256 heads x 4096 tokens), or two words of low bits; of an 8-bit token channels 4*c ..
+// 4*c+3, four bytes.
+struct OldCode {
+  uint32_t w, l;       // byte offsets from the tile side
+  int sh, shl;
+  uint32_t msk;
+  bool f3, f8, f1;
+};
+// class of a slot (the classes are numbered in slot order), width of a class: no branches
+template <bool HAS1>
+__device__ __forceinline__ int class_at(const QaqCounts& c, int slot) {
+  const int k = (slot >= c.n3 ? 1 : 0) + (slot >= c.n32() ? 1 : 0) + (slot >= c.n32() + c.n4 ? 1 : 0);
+  return HAS1 ? k + (slot >= c.first1() ? 1 : 0) : k;
+}
+static_assert(QC3 == 0 && QC2 == 1 && QC4 == 2 && QC8 == 3 && QC1 == 4, "classes are numbered in slot order");
+__device__ __forceinline__ int bits_of_class(int k) { return (int)((0x18423u >> (4 * k)) & 15u); }
+template <bool HAS1>
+__device__ __forceinline__ int class_start(const QaqCounts& c, int k) {        // slot less index inside the region
+  const int n32 = c.n32(), first8 = n32 + c.n4, first1 = first8 + c.n8;
+  int r = k == QC4 ? n32 : 0;
+  r = k == QC8 ? first8 : r;
+  if (HAS1) r = k == QC1 ? first1 : r;
+  return r;
+}
+template <bool HAS1>
+__device__ __forceinline__ int class_end(int n3, int n32, int n4, int n8, int n1, int k) {      // end of a class's indices in its region
+  int r = k == QC3 ? n3 : n32;
+  r = k == QC4 ? n4 : r;
+  r = k == QC8 ? n8 : r;
+  if (HAS1) r = k == QC1 ? n1 : r;
+  return r;
+}
+template <int D, bool HAS1>
+__device__ __forceinline__ OldCode k_old_place(const QaqCounts& c, uint32_t r1, uint32_t r4, uint32_t r8, uint32_t r1b, int slot, int c4) {
   constexpr int KS = D / 64;
   const int d = 4 * c4, ks = d / 64, g = (d % 64) / 16, vq = (d % 16) / 4;
-  const int q = g * KS + ks;
-  const int n32 = c.n32();
-  const bool f2 = slot < n32, f3 = slot < c.n3, f4 = !f2 && slot < n32 + c.n4;
-  const uint32_t off = f2 ? r.r2 + (uint32_t)slot * (D / 4) + 4u * (uint32_t)q
-                     : f4 ? r.r4 + (uint32_t)(slot - n32) * (D / 2) + 4u * (uint32_t)(2 * q + (vq >> 1))
-                          : r.r8 + (uint32_t)(slot - n32 - c.n4) * D + 4u * (uint32_t)(4 * q + vq);
-  const uint32_t offl = f3 ? r.r1 + (uint32_t)slot * (D / 8) + 4u * (uint32_t)(q >> 1) : off;
-  const uint32_t w = *(const uint32_t*)(base + off);
-  const uint32_t wl = *(const uint32_t*)(base + offl);
-  const int sh = f2 ? 2 * vq : f4 ? 4 * (vq & 1) : 0;
-  const uint32_t msk = f2 ? 0x03030303u : f4 ? 0x0f0f0f0fu : 0xffffffffu;
-  uint32_t code = ((w >> sh) & msk) ^ (f2 || f4 ? 0u : 0x80808080u);
-  if (f3) code = (code << 1) | ((wl >> (4 * (q & 1) + vq)) & 0x01010101u);
-  return code;
+  const int q = g * KS + ks;                         // element 16*q + 4*vq of the record
+  const int k = class_at<HAS1>(c, slot), idx = slot - class_start<HAS1>(c, k);
+  const int s = (int)((0x30122u >> (4 * k)) & 15u);    // 8 >> s bits per element
+  OldCode o;
+  o.f3 = k == QC3; o.f8 = k == QC8; o.f1 = HAS1 && k == QC1;
+  uint32_t ro = k <= QC2 ? 0u : r8;           // (the 2-bit fields start the tile side)
+  ro = k == QC4 ? r4 : ro;
+  if (HAS1) ro = k == QC1 ? r1b : ro;
+  o.w = ro + (uint32_t)idx * ((uint32_t)D >> s) + ((uint32_t)((16 * q + 4 * vq) >> s) & ~3u);
+  const uint32_t lo = r1 + (uint32_t)slot * (D / 8) + 4u * (uint32_t)(q >> 1);
+  o.l = o.f3 ? lo : o.w;
+  o.shl = 4 * (q & 1) + vq;
+  o.sh = k <= QC2 ? 2 * vq : 0;
+  o.sh = k == QC4 ? 4 * (vq & 1) : o.sh;
+  if (HAS1) o.sh = k == QC1 ? o.shl : o.sh;
+  o.msk = width_mask(8 >> s);
+  return o;
+}
+template <int D, bool HAS1>
+__device__ __forceinline__ OldCode v_old_place(const QaqCounts& c, uint32_t r1, uint32_t r4, uint32_t r8, uint32_t r1b, int slot, int c4) {
+  const int k = class_at<HAS1>(c, slot), idx = slot - class_start<HAS1>(c, k);
+  OldCode o;
+  o.f3 = k == QC3; o.f8 = k == QC8; o.f1 = HAS1 && k == QC1;
+  const int us = k == QC4 ? 3 : 4, u = idx >> us, i = idx - (u << us);
+  // low-bit planes and 1-bit tokens: words 2*c4, 2*c4 + 1 of unit u, in each two channels, 4 bits apart
+  const uint32_t lo = (uint32_t)u * (2u * D) + 8u * (uint32_t)c4;
+  const uint32_t un = (uint32_t)u * (4u * D) + 16u * (uint32_t)c4, row = r8 + (uint32_t)idx * D + 4u * (uint32_t)c4;
+  o.w = un + (k == QC4 ? r4 : 0u);
+  o.w = o.f8 ? row : o.w;
+  if (HAS1) o.w = o.f1 ? r1b + lo : o.w;
+  o.l = o.f3 ? r1 + lo : o.w;
+  o.shl = 8 * (i & 3) + (i >> 2);
+  o.sh = 8 * (i & 3) + (k == QC4 ? 4 : 2) * (i >> 2);
+  o.msk = k == QC4 ? 15u : 3u;
+  return o;
 }
 
-// The same for values (transposed units: one load per channel, and one more per channel for the
-// low-bit plane of a 3-bit token; eight unconditional loads, or one for an 8-bit token).
-template <int D>
-__device__ __forceinline__ uint32_t v_old_codes(const uint8_t* base, const QaqCounts& c, const QaqVRegions& r, int slot, int c4) {
-  const int n32 = c.n32();
-  const int n0 = 4 * (c4 & 3), cg = c4 >> 2;
-  if (slot >= n32 + c.n4) return *(const uint32_t*)(base + r.r8 + (uint32_t)(slot - n32 - c.n4) * D + 4u * (uint32_t)c4);
-  const bool f2 = slot < n32, f3 = slot < c.n3;
-  const int idx = f2 ? slot : slot - n32;
-  const int u = f2 ? idx >> 4 : idx >> 3, i = f2 ? idx & 15 : idx & 7;
-  const uint32_t off = (f2 ? r.r2 : r.r4) + (uint32_t)u * (4u * D) + 4u * (uint32_t)(n0 * (D / 16) + cg);
-  const int sh = f2 ? 8 * (i & 3) + 2 * (i >> 2) : 8 * (i & 3) + 4 * (i >> 2);
-  const uint32_t msk = f2 ? 3u : 15u;
-  // low-bit plane of a 3-bit token: word (n, cg / 2) of unit u, bit 8*(i%4) + 4*(cg%2) + i/4
-  const uint32_t offl = f3 ? r.r1 + (uint32_t)u * (2u * D) + 4u * (uint32_t)(n0 * (D / 32) + (cg >> 1)) : off;
-  const uint32_t stl = f3 ? D / 8 : D / 4;
-  uint32_t w[4], l[4];
+// Value side: the fields of the slots to write are put into the words as they are stored (a word holds
+// one channel of up to 16 tokens; a word of a unit that did not exist starts from zero).  BF: field
+// width; `masks`: slots to write per unit of 16 (BF 4: of 8) from slot0 on, those from n_slots on left out; `n3`: slots
+// below it hold 3-bit codes (BF 2: their upper bits are wanted).  Each wavefront lists the units with
+// work and takes every other group of them, the words of a batch requested together.
+template <int D, int BF>
+__device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks, int units_old, int n_slots, int slot0, int n3, UpdLds<D>& L) {
+  constexpr int LPU = BF == 1 ? D / 8 : D / 4;       // lanes per unit, four consecutive words each
+  constexpr int UPW = 64 / LPU, U = 2, SPU = BF == 4 ? 8 : 16;
+  constexpr uint32_t UB = BF == 1 ? 2 * D : 4 * D;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto mask_of = [&](int u) {
+    const int n = min(max(n_slots - SPU * u, 0), SPU);
+    return masks[u] & ((1u << n) - 1u);
+  };
+  const int n_units = (n_slots + SPU - 1) / SPU;      // at most 16 (BF 4: 32)
+  const unsigned long long work = __ballot(lane < n_units && mask_of(min(lane, 256 / SPU - 1)) != 0u);
+  const int nu = __popcll(work);
+  if (nu == 0) return;
+  if ((work >> lane) & 1ull) L.units[wave][lanes_below(work)] = (uint8_t)lane;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (the wavefront's own list)
+  const int sub = lane / LPU, c = lane % LPU;
+#pragma unroll 1
+  for (int i0 = wave * UPW * U; i0 < nu; i0 += 2 * UPW * U) {
+    u32x4 o[U];
+    int un[U];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = *(const uint32_t*)(base + off + (uint32_t)k * (D / 4));
+    for (int k = 0; k < U; ++k) {
+      un[k] = L.units[wave][min(i0 + k * UPW + sub, nu - 1)];
+      o[k] = ((const u32x4*)(region + (uint32_t)un[k] * UB))[c];
+    }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) l[k] = *(const uint32_t*)(base + offl + (uint32_t)k * stl);
-  uint32_t code = 0u;
+    for (int k = 0; k < U; ++k) {
+      if (i0 + k * UPW + sub >= nu) continue;
+      uint32_t msk = mask_of(un[k]);
+      if (un[k] >= units_old) o[k] = (u32x4)0u;
+      while (msk) {
+        const int i = __ffs(msk) - 1;
+        msk &= msk - 1;
+        const int sl = slot0 + SPU * un[k] + i;
+        const uint32_t* row = &L.stage[(int)L.m_of_slot[sl] * UpdLds<D>::SROW];
+        if (BF == 1) {
+          const uint32_t w0 = row[2 * c], w1 = row[2 * c + 1];      // word e: bytes 2*e and 2*e + 1 of the pair
+          const int bp = 8 * (i & 3) + (i >> 2);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) code |= ((w[k] >> sh) & msk) << (8 * k);
-  if (f3) {
-    const int shl = 8 * (i & 3) + 4 * (cg & 1) + (i >> 2);
-    uint32_t low = 0u;
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t x = (e < 2 ? w0 : w1) >> (16 * (e & 1));
+            o[k][e] = (o[k][e] & ~(0x11u << bp)) | (((x & 1u) | ((x >> 4) & 0x10u)) << bp);
+          }
+        } else {
+          constexpr uint32_t FM = BF == 2 ? 3u : 15u;
+          const uint32_t w = row[c] >> (BF == 2 && sl < n3 ? 1 : 0);
+          const int bp = 8 * (i & 3) + BF * (i >> 2);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) low |= ((l[k] >> shl) & 1u) << (8 * k);
-    code = (code << 1) | low;
+          for (int e = 0; e < 4; ++e) o[k][e] = (o[k][e] & ~(FM << bp)) | (((w >> (8 * e)) & FM) << bp);
+        }
+      }
+      ((u32x4*)(region + (uint32_t)un[k] * UB))[c] = o[k];
+    }
   }
-  return code;
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
+// ONE: one outlier per end in the fixed-length side store; else any count, or the variable-length store.
+// HAS1: the width set contains 1.
+template <int D, bool ONE, bool HAS1>
+__global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   __shared__ UpdLds<D> L;
-  constexpr int SROW = UpdLds<D>::SROW, NQ = D / 16, KS = D / 64;
+  constexpr int SROW = UpdLds<D>::SROW, NQ = D / 16, KS = D / 64, J = QAQ_TT / kUpdThreads, NC = HAS1 ? QAQ_NCLASS : 4;
+  constexpr int NOI = ONE ? 1 : 4;          // words of outlier values per token, pairs of outlier channels
   const QaqView& v = a.v;
   const QaqRuleArgs& ru = a.rule;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tok0 = 64 * J * wave + lane;
   const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv;
   // value sides first: nearly every one of them has work (a token's predicted score moves every
   // step), most key sides leave after one load and fill in behind
@@ -1387,6 +1557,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
   if (bh == 0 && tile == 0 && side == 0 && tid == 0) *a.todo_count_next = 0u;
   if (n_after == 0) return;
+  const bool csr = !ONE && v.csr;
+  const int no2 = ONE ? 2 : v.no2;
   const bool has_new = n_after > n_before;           // the appended token is position n_before of this tile
   const size_t tile_id = qaq_bh(v, b, h) * v.NT + tile;
   // keys: the tile recorded, when it was built, the interval of thresholds for which none of its
@@ -1399,35 +1571,121 @@ __global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
 
   // ---- everything whose address is known up front ------------------------------------------------
   uint8_t* base = qaq_tile_codes(v, side, b, h, tile);
-  // (the stored class counts are asked for with the rest and decoded behind the barrier: made wavefront
-  // constants on the spot, they would be waited for before any other load is issued)
   const uint2 counts_raw = *(const uint2*)(v.counts + (tile_id * 2 + side) * 4);
   const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
-  // thread t is token t: the cached token in old slot t, or (t == n_before) the appended one
-  uint32_t mm = 0, oi = 0, ov = 0;
-  int pos = tid;
-  if (tid < n_before) {
-    mm = v.mm[side][gi0 + tid];
-    pos = v.perm[side][gi0 + tid];
-    oi = *(const uint16_t*)(v.oidx[side] + (gi0 + tid) * 2);
-    ov = *(const uint32_t*)(v.oval[side] + (gi0 + tid) * 2);
+  // token tok0 + 64*j: the cached token in that old slot, or (== n_before) the appended one
+  uint32_t mm[J], oi[J], ov[J];      // (oi, ov: ONE; else the side store is read again for the tokens that move)
+  uint32_t oext[J];                  // value side, not ONE: largest | smallest outlier << 16
+  int pos[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const size_t gi = gi0 + min(tok0 + 64 * j, max(n_before - 1, 0));
+    mm[j] = v.mm[side][gi];
+    pos[j] = v.perm[side][gi];
+    oi[j] = ov[j] = 0u;
+    oext[j] = 0xffffffffu;
+    if (ONE) {
+      oi[j] = *(const uint16_t*)(v.oidx[side] + gi * 2);
+      ov[j] = *(const uint32_t*)(v.oval[side] + gi * 2);
+    }
   }
-  if (side == 1 && tid < n_after) {      // thread t as position t: the window (Section 4.2), this step's row stored
-    const int t = t0 + tid;
+  if (!ONE && !csr && side == 1 && no2 > 0) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const size_t at = (gi0 + min(tok0 + 64 * j, max(n_before - 1, 0))) * no2;
+      const uint32_t* p = (const uint32_t*)(v.oval[1] + at);
+      const uint16_t* pi = (const uint16_t*)(v.oidx[1] + at);
+      uint32_t x[NOI], xi[NOI];
+#pragma unroll
+      for (int k = 0; k < NOI; ++k) { x[k] = p[min(k, no2 / 2 - 1)]; xi[k] = pi[min(k, no2 / 2 - 1)]; }
+      float hi = -INFINITY, lo = INFINITY;
+      bool some = false;
+#pragma unroll
+      for (int k = 0; k < 2 * NOI; ++k) {
+        const float f = h2f((uint16_t)(x[k >> 1] >> (16 * (k & 1))));
+        const bool used = ((xi[k >> 1] >> (8 * (k & 1))) & 0xffu) != 0xffu;
+        hi = fmaxf(hi, used ? f : -INFINITY); lo = fminf(lo, used ? f : INFINITY);
+        some |= used;
+      }
+      oext[j] = some ? (uint32_t)f2h(hi) | ((uint32_t)f2h(lo) << 16) : 0xffffffffu;
+    }
+  }
+  if (side == 1) {      // the window (Section 4.2), this step's row stored: two positions per lane
     const size_t ring_row = (size_t)v.B * v.Hkv * v.Tmax;
-    const size_t ri = qaq_bh(v, b, h) * v.Tmax + t;
-    float s;
-    const float pred = qaq_predicted<true>(v, qaq_rows_covering(v, ru.row_len, b, t), ru.new_row, ri, t, ru.scores, (size_t)b * v.Hq + h * ru.G, ru.G, ru.score_stride, &s);
-    qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri, s);
-    L.pred[tid] = pred;
+    const size_t ri0 = qaq_bh(v, b, h) * v.Tmax + t0;
+    const float* row0 = ru.scores + ((size_t)b * v.Hq + h * ru.G) * ru.score_stride + t0;
+    int lim[QAQ_MAX_WINDOW];
+#pragma unroll
+    for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] = qaq_seq_len(v, b, ru.row_len[r]) - t0;
+    if (len_after >= 2) {
+      // (the lane that the tile's end falls into reads one position further down: the one before it is
+      // another lane's as well, and gets the same value from both)
+      const int p0 = min(2 * tid, n_after - 2);
+      float s[2], m[2];
+      predicted2(v, lim, ru.new_row, ri0 + p0, p0, row0 + p0, ru.G, ru.score_stride, s, m);
+      if (2 * tid < n_after) {
+        const size_t ro = (size_t)ru.new_row * ring_row + ri0 + p0;
+        if (p0 >= 0) {
+          if (v.ring_half == 0) {
+            __builtin_memcpy((float*)v.ring + ro, s, 8);
+          } else {
+            uint16_t hs[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) hs[e] = v.ring_half == 1 ? f2h(s[e]) : qaq_bf16_bits(s[e]);
+            __builtin_memcpy((uint16_t*)v.ring + ro, hs, 4);
+          }
+          L.p.pred[p0] = m[0]; L.p.pred[p0 + 1] = m[1];
+        } else {               // a tile with one token: the position before it is another tile's
+          qaq_ring_store(v, ro + 1, s[1]);
+          L.p.pred[0] = m[1];
+        }
+      }
+    } else if (tid == 0) {          // a sequence of one token
+      float s = 0.0f;
+      for (int g = 0; g < ru.G; ++g) s = fmaxf(s, row0[(size_t)g * ru.score_stride]);
+      s = qaq_ring_value(v, s);
+      L.p.pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t0), ru.new_row, ri0, s);
+      qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri0, s);
+    }
+    if (csr) {
+      // outliers by thresholds: the extremes of every position's run in the tile's pool
+      const size_t pool0 = gi0 * (size_t)no2;
+      int cnt[J], st[J], most = 0;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int p = min(tok0 + 64 * j, max(n_before - 1, 0));
+        cnt[j] = v.ocnt[1][gi0 + p];
+        st[j] = v.ostart[1][gi0 + p];
+      }
+#pragma unroll
+      for (int j = 0; j < J; ++j) { if (tok0 + 64 * j >= n_before) cnt[j] = 0; most = max(most, cnt[j]); }
+      float hi[J], lo[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) { hi[j] = -INFINITY; lo[j] = INFINITY; }
+#pragma unroll 1
+      for (int k0 = 0; k0 < QAQ_MAX_NO2 && __ballot(most > k0) != 0ull; k0 += 4) {
+        uint16_t x[J][4];
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) x[j][k] = v.oval[1][pool0 + (cnt[j] > 0 ? st[j] + min(k0 + k, cnt[j] - 1) : 0)];
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) { const float f = h2f(x[j][k]); hi[j] = fmaxf(hi[j], f); lo[j] = fminf(lo[j], f); }
+      }
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (tok0 + 64 * j < n_before) L.p.oext[tok0 + 64 * j] = cnt[j] > 0 ? (uint32_t)f2h(hi[j]) | ((uint32_t)f2h(lo[j]) << 16) : 0xffffffffu;
+    }
   }
-  L.cls_new[tid] = 0xffu;
-  L.m_of_slot[tid] = 0xffu;
-  if (tid < 32) L.mask4[tid] = 0u;
+#pragma unroll
+  for (int j = 0; j < J; ++j) L.m_of_slot[tok0 + 64 * j] = 0xffu;
 
   // ---- the appended token: outliers, range, codes at the widest width (Section 4.2 "Outliers",
-  // Section 4.1 quantizer), by the last wavefront, two channels per lane -------------------------------
-  if (has_new && wave == 3) {
+  // Section 4.1 quantizer), by the second wavefront, two channels per lane ------------------------------
+  if (has_new && wave == 1) {
+    int new_no = 0;              // outliers found (the variable-length store: as many as pass the thresholds)
     const bool act = 2 * lane < D;
     const uint32_t* src = (const uint32_t*)(a.newx[side] + (size_t)bh * a.n_new * D);
     const uint32_t w = act ? src[lane] : 0u;
@@ -1435,20 +1693,33 @@ __global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
     const uint32_t kk = order_keys_pair(w);
     const int ch0 = 2 * lane, ch1 = 2 * lane + 1;
     const uint32_t k0 = kk << 16, k1 = kk & 0xffff0000u;
-    // largest value, lowest channel first; then the smallest of the rest, lowest channel first
-    const uint32_t A1 = wave_umax(act ? max(k0 | (uint32_t)(127 - ch0), k1 | (uint32_t)(127 - ch1)) : 0u);
-    const int ch_top = 127 - (int)(A1 & 127u);
-    const uint32_t n0 = act && ch0 != ch_top ? (k0 | (uint32_t)ch0) : 0xffffffffu;
-    const uint32_t n1 = act && ch1 != ch_top ? (k1 | (uint32_t)ch1) : 0xffffffffu;
-    const uint32_t B1 = wave_umin(min(n0, n1));
-    const int ch_bot = (int)(B1 & 127u);
+    bool in0 = act, in1 = act;
+    const float thr_lo = csr ? v.othr[(side * v.Hkv + h) * 2] : INFINITY;
+    const float thr_hi = csr ? v.othr[(side * v.Hkv + h) * 2 + 1] : -INFINITY;
+    // the largest values, lowest channel first; then the smallest of the rest, lowest channel first; the
+    // one in lane k is the k-th found
+    uint32_t my_ch = 0xffu, my_val = 0u;
+#pragma unroll 1
+    for (int end = 0; end < 2; ++end)
+#pragma unroll 1
+      for (int k = 0; k < no2 / 2; ++k) {
+        const uint32_t M = end == 0 ? wave_umax(max(in0 ? k0 | (uint32_t)(127 - ch0) : 0u, in1 ? k1 | (uint32_t)(127 - ch1) : 0u))
+                                    : wave_umin(min(in0 ? k0 | (uint32_t)ch0 : 0xffffffffu, in1 ? k1 | (uint32_t)ch1 : 0xffffffffu));
+        const int ch = end == 0 ? 127 - (int)(M & 127u) : (int)(M & 127u);
+        if (!ONE) {               // (the count rule's thresholds are infinite: what no number passes is left out as in a bulk build)
+          const float val = key16_value(M);
+          if (!(end == 0 ? val > thr_hi : val < thr_lo)) break;
+        }
+        const uint32_t wc = (uint32_t)__builtin_amdgcn_readlane((int)w, ch >> 1);
+        if (lane == new_no) { my_ch = (uint32_t)ch; my_val = (wc >> (16 * (ch & 1))) & 0xffffu; }
+        in0 = in0 && ch0 != ch;
+        in1 = in1 && ch1 != ch;
+        ++new_no;
+      }
     // [min, max] of what remains
-    const bool in0 = act && ch0 != ch_top && ch0 != ch_bot, in1 = act && ch1 != ch_top && ch1 != ch_bot;
     const uint32_t A2 = wave_umax(max(in0 ? k0 : 0u, in1 ? k1 : 0u));
     const uint32_t B2 = wave_umin(min(in0 ? k0 : 0xffffffffu, in1 ? k1 : 0xffffffffu));
     const uint32_t mn_b = key16_bits(B2), mx_b = key16_bits(A2);
-    const uint32_t wt = (uint32_t)__shfl((int)w, ch_top >> 1), wb = (uint32_t)__shfl((int)w, ch_bot >> 1);
-    const uint32_t v_top = (wt >> (16 * (ch_top & 1))) & 0xffffu, v_bot = (wb >> (16 * (ch_bot & 1))) & 0xffffu;
     const float mn = h2f((uint16_t)mn_b), mx = h2f((uint16_t)mx_b);
     const float range = mx - mn;
     const float levels = (float)(1 << a.widest);
@@ -1462,11 +1733,19 @@ __global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
       cw = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), e, cw);
     }
     if (act) ((uint16_t*)L.newrow)[lane] = (uint16_t)cw;
-    if (lane == 0) {
-      L.new_mm = mn_b | (mx_b << 16);
-      const bool top_first = ch_top < ch_bot;                 // the side store is ordered by channel
-      L.new_oi = top_first ? ((uint32_t)ch_top | ((uint32_t)ch_bot << 8)) : ((uint32_t)ch_bot | ((uint32_t)ch_top << 8));
-      L.new_ov = top_first ? (v_top | (v_bot << 16)) : (v_bot | (v_top << 16));
+    if (lane == 0) { L.new_mm = mn_b | (mx_b << 16); L.new_no = new_no; }
+    // the side store is ordered by channel (unused places last)
+    int rank = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * NOI; ++k) {
+      const uint32_t ck = (uint32_t)__builtin_amdgcn_readlane((int)my_ch, k);
+      rank += ck < my_ch || (ck == my_ch && k < lane) ? 1 : 0;
+    }
+    if (lane < 2 * NOI) { ((uint8_t*)L.new_oi)[rank] = (uint8_t)my_ch; ((uint16_t*)L.new_ov)[rank] = (uint16_t)my_val; }
+    if (!ONE && side == 1 && lane == 0) {
+      float hi = -INFINITY, lo = INFINITY;
+      for (int k = 0; k < new_no; ++k) { const float f = h2f(((const uint16_t*)L.new_ov)[k]); hi = fmaxf(hi, f); lo = fminf(lo, f); }
+      L.p.oext[n_before] = new_no > 0 ? (uint32_t)f2h(hi) | ((uint32_t)f2h(lo) << 16) : 0xffffffffu;
     }
   }
   __syncthreads();
@@ -1476,337 +1755,457 @@ __global__ __launch_bounds__(kThreads, 8) void k_update(QaqBuildArgs a) {
     const uint32_t c01 = (uint32_t)__builtin_amdgcn_readfirstlane((int)counts_raw.x), c23 = (uint32_t)__builtin_amdgcn_readfirstlane((int)counts_raw.y);
     static_assert(QC3 == 0 && QC2 == 1 && QC4 == 2 && QC8 == 3, "order of the stored counts");
     c_old.n3 = (int)(c01 & 0xffffu); c_old.n2 = (int)(c01 >> 16); c_old.n4 = (int)(c23 & 0xffffu); c_old.n8 = (int)(c23 >> 16);
+    if (HAS1) c_old.n1 = n_before - (c_old.n3 + c_old.n2 + c_old.n4 + c_old.n8);
   }
-  const bool is_new = has_new && tid == n_before;
-  if (is_new) { mm = L.new_mm; oi = L.new_oi; ov = L.new_ov; pos = n_before; }
 
   // ---- widths by the rules of Section 4.1 -----------------------------------------------------------
-  const float mnf = h2f((uint16_t)(mm & 0xffffu)), mxf = h2f((uint16_t)(mm >> 16));
-  const float range = mxf - mnf;
-  int ob = 0, nb = 0;
-  bool changed = false, wider = false;
-  if (tid < n_after) {
-    const float lhs = side == 0 ? range : range * L.pred[pos];
-    const float thr = side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b);
-    int req = ru.bit_set[ru.nbits - 1];
-    for (int i = ru.nbits - 1; i >= 0; --i)
-      if (lhs <= ldexpf(thr, ru.bit_set[i])) req = ru.bit_set[i];
-    if (ru.out_bits[side]) ru.out_bits[side][(size_t)bh * a.len_after + t0 + pos] = (uint8_t)req;
-    if (is_new) {
-      ob = a.widest; nb = req; changed = true;       // encoded at the widest width; narrowing drops low bits
-    } else {
-      ob = c_old.bits_of_slot4(tid);
-      nb = ob;
-      if (req < ob) nb = req;
-      else if (req > ob) { wider = true; if (a.orig[side]) nb = req; }
-      changed = nb != ob;
-    }
-  }
+  const float thr = side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b);
+  float thr_b[NC];             // (entries past the last width repeat it)
+  int wc[NC];                  // width | class << 4
+#pragma unroll
+  for (int i = 0; i < NC; ++i) { thr_b[i] = ldexpf(thr, ru.bit_set[i]); wc[i] = ru.bit_set[i] | (qaq_class_of_bits(ru.bit_set[i]) << 4); }
   const bool served = a.orig[side] != nullptr;
-  note_widenings(L.wave_wide, wider);
-  // ---- new class counts; what the attention kernel and the next step's skip test need of the tile
-  // (ahead of the test whether the tile side has work at all, so that one barrier serves both) ------------
-  const int cls = tid < n_after ? qaq_class_of_bits(nb) : -1;
-  const int ocls = (tid < n_before) ? qaq_class_of_bits(ob) : -1;
+  int cls[J], ocls[J];         // class after and before this step, -1: no token
+  int nb[J], ob[J];
+  float bnd = 0.0f, lo = 0.0f, hi = INFINITY;
+  unsigned long long any = 0ull;
+  int n_wide = 0;
+  int n_cls[QAQ_NCLASS] = {0, 0, 0, 0, 0};
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const unsigned long long bal = __ballot(cls == c);
-    if (lane == 0) L.wave_cnt[c][wave] = __popcll(bal);
-  }
-  if (tid < n_after) L.cls_new[tid] = (uint8_t)cls;
-  if (side == 1) {
-    float bnd = 0.0f;
-    if (tid < n_after) {
-      bnd = ldexpf(range, nb == 3 ? -2 : -nb);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const float o = h2f((uint16_t)(ov >> (16 * k)));
-        bnd = fmaxf(bnd, fmaxf(fabsf(o - mxf), fabsf(o - mnf)) + range);
-      }
+  for (int j = 0; j < J; ++j) {
+    const int tok = tok0 + 64 * j;
+    const bool live = tok < n_after, is_new = has_new && tok == n_before;
+    if (is_new) {
+      mm[j] = L.new_mm;
+      pos[j] = n_before;
+      oi[j] = L.new_oi[0] & 0xffffu; ov[j] = L.new_ov[0];
     }
-    bnd = wave_max(bnd);
-    if (lane == 0) L.wave_bound[wave] = bnd;
-  } else {
-    float lo = 0.0f, hi = INFINITY;
-    if (tid < n_after) {
+    const float mnf = h2f((uint16_t)(mm[j] & 0xffffu)), mxf = h2f((uint16_t)(mm[j] >> 16));
+    const float range = mxf - mnf;
+    const float lhs = side == 0 ? range : range * L.p.pred[pos[j]];
+    int rc = wc[NC - 1];
+#pragma unroll
+    for (int i = NC - 1; i >= 0; --i) rc = lhs <= thr_b[i] ? wc[i] : rc;
+    const int req = rc & 15;
+    if (ru.out_bits[side] && live) ru.out_bits[side][(size_t)bh * a.len_after + t0 + pos[j]] = (uint8_t)req;
+    const int oc = class_at<HAS1>(c_old, tok);
+    ob[j] = bits_of_class(oc);
+    ob[j] = is_new ? a.widest : ob[j];                  // encoded at the widest width; narrowing drops low bits
+    const bool wider = live & !is_new & (req > ob[j]);
+    nb[j] = (wider & !served) ? ob[j] : req;
+    n_wide += __popcll(__ballot(wider));
+    any |= __ballot(live & (is_new | (nb[j] != ob[j])));
+    cls[j] = (wider & !served) ? oc : rc >> 4;
+    cls[j] = live ? cls[j] : -1;
+    ocls[j] = tok < n_before ? oc : -1;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) n_cls[c] += __popcll(__ballot(cls[j] == c));
+    L.cls_new[tok] = (uint8_t)(live ? cls[j] : 0xff);
+    // what the attention kernel and the next step's skip test need of the tile
+    if (side == 1) {
+      float bt = ldexpf(range, nb[j] == 3 ? -2 : -nb[j]);
+      uint32_t x = ONE ? ov[j] : oext[j];           // two numbers the tile's largest correction is between
+      if (!ONE && (csr || is_new)) x = L.p.oext[pos[j]];
+      const float o1 = h2f((uint16_t)(x & 0xffffu)), o0 = h2f((uint16_t)(x >> 16));
+      const float bo = fmaxf(fmaxf(fabsf(o1 - mxf), fabsf(o1 - mnf)), fmaxf(fabsf(o0 - mxf), fabsf(o0 - mnf))) + range;
+      if (ONE || x != 0xffffffffu) bt = fmaxf(bt, bo);
+      if (live) bnd = fmaxf(bnd, bt);
+    } else if (live) {
       int narrower = 0;
-      for (int i = 0; i < ru.nbits; ++i)
-        if (ru.bit_set[i] < nb) narrower = ru.bit_set[i];
-      if (nb < ru.bit_set[ru.nbits - 1]) lo = ldexpf(range, -nb);
-      if (narrower > 0) hi = ldexpf(range, -narrower);
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+        if (ru.bit_set[i] < nb[j]) narrower = ru.bit_set[i];
+      if (nb[j] < ru.bit_set[NC - 1]) lo = fmaxf(lo, ldexpf(range, -nb[j]));
+      if (narrower > 0) hi = fminf(hi, ldexpf(range, -narrower));
     }
-    lo = wave_max(lo); hi = wave_min(hi);
-    if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
   }
-  // (one ballot per wavefront, one barrier, four flags: the library's workgroup OR is a reduction
-  // across lanes and three barriers)
-  const unsigned long long bal_changed = __ballot(changed);
-  if (lane == 0) L.wave_any[wave] = bal_changed != 0ull ? 1 : 0;
+  bnd = wave_max(bnd); lo = wave_max(lo); hi = wave_min(hi);
+  if (lane == 0) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) L.w_cls[wave][c] = n_cls[c];
+    L.w_any[wave] = any != 0ull; L.w_wide[wave] = n_wide;
+    L.w_bnd[wave] = bnd; L.w_lo[wave] = lo; L.w_hi[wave] = hi;
+  }
   __syncthreads();
-  if (!(L.wave_any[0] | L.wave_any[1] | L.wave_any[2] | L.wave_any[3])) {          // nothing moves and nothing is appended
-    if (tid == 0) add_widenings(v, tile_id * 2 + side, L.wave_wide, served);
+  const int all_wide = L.w_wide[0] + L.w_wide[1];
+  if (!(L.w_any[0] | L.w_any[1])) {          // nothing moves and nothing is appended
+    if (tid == 0 && all_wide) v.refused[(tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
     return;
   }
-
+  auto both = [](const int (&x)[2][QAQ_NCLASS], int c) { return __builtin_amdgcn_readfirstlane(x[0][c] + x[1][c]); };
   QaqCounts cn;
-  cn.n3 = L.wave_cnt[QC3][0] + L.wave_cnt[QC3][1] + L.wave_cnt[QC3][2] + L.wave_cnt[QC3][3];
-  cn.n2 = L.wave_cnt[QC2][0] + L.wave_cnt[QC2][1] + L.wave_cnt[QC2][2] + L.wave_cnt[QC2][3];
-  cn.n4 = L.wave_cnt[QC4][0] + L.wave_cnt[QC4][1] + L.wave_cnt[QC4][2] + L.wave_cnt[QC4][3];
-  cn.n8 = L.wave_cnt[QC8][0] + L.wave_cnt[QC8][1] + L.wave_cnt[QC8][2] + L.wave_cnt[QC8][3];
-  cn.n1 = 0;
+  cn.n3 = both(L.w_cls, QC3); cn.n2 = both(L.w_cls, QC2); cn.n4 = both(L.w_cls, QC4); cn.n8 = both(L.w_cls, QC8);
+  cn.n1 = HAS1 ? both(L.w_cls, QC1) : 0;
 
-  // ---- slots.  A token's codes sit at an index inside its class's region (2- and 3-bit tokens: the
-  // slot; 4-bit: slot minus the 2/3-bit tokens; 8-bit: minus the 4-bit ones as well).  A cached token
-  // that stays in its class keeps that index if the region still reaches it; the others -- tokens that
-  // change class, tokens squeezed out, the appended one -- take the free indices of their class in order.
+  // ---- regions.  A token's codes sit at an index inside its class's region (2- and 3-bit tokens: the
+  // slot; the others: the slot less the class's first one).  The 2-bit fields start the tile side; another
+  // region's start moves when the space before it changes.  What it holds for the tokens that stay is then
+  // copied, region by region as long as the copies are small; the tokens of one that is not copied are
+  // written again like any other moved token. -----------------------------------------------------------
   const int n32o = c_old.n32(), n32n = cn.n32();
-  bool mv3, mv4, mv8;       // the region a class alone owns starts elsewhere than before (the 2-bit fields start the tile side)
-  if (side == 0) {
-    const QaqKRegions r0 = qaq_k_regions(c_old, D), r1 = qaq_k_regions(cn, D);
-    mv3 = r0.r1 != r1.r1; mv4 = r0.r4 != r1.r4; mv8 = r0.r8 != r1.r8;
-  } else {
-    const QaqVRegions r0 = qaq_v_regions(c_old, D), r1 = qaq_v_regions(cn, D);
-    mv3 = r0.r1 != r1.r1; mv4 = r0.r4 != r1.r4; mv8 = r0.r8 != r1.r8;
-  }
-  auto old_index = [&](int c, int slot) { return c == QC4 ? slot - n32o : c == QC8 ? slot - n32o - c_old.n4 : slot; };
-  auto new_slot_of = [&](int c, int idx) { return c == QC4 ? n32n + idx : c == QC8 ? n32n + cn.n4 + idx : idx; };
-  // (a region whose start moves -- a count before it crossed a multiple of 16 -- keeps nobody: its
-  // tokens are written again at the new place like any other moved token)
-  auto region_moved = [&](int c) { return (c == QC3 && mv3) || (c == QC4 && mv4) || (c == QC8 && mv8); };
-  bool keep = false;
-  int my_slot = -1;
-  if (ocls >= 0 && cls == ocls && !region_moved(cls)) {
-    const int idx = old_index(cls, tid);
-    keep = cls == QC3 ? idx < cn.n3 : cls == QC2 ? (idx >= cn.n3 && idx < n32n) : cls == QC4 ? idx < cn.n4 : idx < cn.n8;
-    if (keep) my_slot = new_slot_of(cls, idx);
-  }
-  const bool need = cls >= 0 && !keep;
-  // thread s as slot s of the new order: free unless the token that could keep it does
-  int slot_cls = -1;
-  bool is_free = false;
-  if (tid < n_after) {
-    slot_cls = qaq_class_of_bits(cn.bits_of_slot4(tid));
-    const int idx = slot_cls == QC4 ? tid - n32n : slot_cls == QC8 ? tid - n32n - cn.n4 : tid;
-    const int cand = slot_cls == QC4 ? idx + n32o : slot_cls == QC8 ? idx + n32o + c_old.n4 : idx;    // the old slot with that index
-    const bool taken = cand < n_before && !region_moved(slot_cls) && qaq_class_of_bits(c_old.bits_of_slot4(cand)) == slot_cls &&
-                       L.cls_new[cand] == slot_cls;
-    is_free = !taken;
-  }
-  int need_rank = 0, free_rank = 0;
+  uint32_t r_old[QAQ_NCLASS], r_new[QAQ_NCLASS];
+  int cp_end[QAQ_NCLASS];       // 16-byte pieces to copy, summed up to and including the class's region
+  uint32_t lost = 0u;           // bit c: the region of class c moved and is not copied
+  {
+    if (side == 0) {
+      const QaqKRegions r0 = qaq_k_regions(c_old, D), r1 = qaq_k_regions(cn, D);
+      r_old[QC3] = r0.r1; r_old[QC2] = r0.r2; r_old[QC4] = r0.r4; r_old[QC8] = r0.r8; r_old[QC1] = r0.r1b;
+      r_new[QC3] = r1.r1; r_new[QC2] = r1.r2; r_new[QC4] = r1.r4; r_new[QC8] = r1.r8; r_new[QC1] = r1.r1b;
+    } else {
+      const QaqVRegions r0 = qaq_v_regions(c_old, D), r1 = qaq_v_regions(cn, D);
+      r_old[QC3] = r0.r1; r_old[QC2] = r0.r2; r_old[QC4] = r0.r4; r_old[QC8] = r0.r8; r_old[QC1] = r0.r1b;
+      r_new[QC3] = r1.r1; r_new[QC2] = r1.r2; r_new[QC4] = r1.r4; r_new[QC8] = r1.r8; r_new[QC1] = r1.r1b;
+    }
+    const int n3 = min(c_old.n3, cn.n3), n4 = min(c_old.n4, cn.n4), n8 = min(c_old.n8, cn.n8), n1 = min(c_old.n1, cn.n1);
+    int bytes[QAQ_NCLASS];     // (keys: records; values: whole units; both within what the region is sized for)
+    bytes[QC2] = 0;
+    bytes[QC3] = side == 0 ? (n3 * (D / 8) + 15) & ~15 : ((n3 + 15) / 16) * (2 * D);
+    bytes[QC4] = side == 0 ? n4 * (D / 2) : ((n4 + 7) / 8) * (4 * D);
+    bytes[QC8] = n8 * D;
+    bytes[QC1] = side == 0 ? (n1 * (D / 8) + 15) & ~15 : ((n1 + 15) / 16) * (2 * D);
+    int sum = 0;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const unsigned long long bn = __ballot(need && cls == c);
-    const unsigned long long bf = __ballot(is_free && slot_cls == c);
-    if (lane == 0) { L.wave_need[c][wave] = __popcll(bn); L.wave_free[c][wave] = __popcll(bf); }
-    if (need && cls == c) need_rank = __popcll(bn & ((1ull << lane) - 1ull));
-    if (is_free && slot_cls == c) free_rank = __popcll(bf & ((1ull << lane) - 1ull));
+    for (int c = 0; c < NC; ++c) {
+      const bool moved = r_old[c] != r_new[c] && bytes[c] > 0;
+      const bool fits = sum + bytes[c] <= kMaxCopy;
+      if (moved && !fits) lost |= 1u << c;
+      if (moved && fits) sum += bytes[c];
+      cp_end[c] = sum >> 4;
+    }
   }
-  const unsigned long long bal_need = __ballot(need);
-  if (lane == 0) L.wave_moved[wave] = __popcll(bal_need);
+
+  // ---- slots: a cached token that stays in its class keeps its index if the region still reaches it;
+  // the others -- tokens that change class, tokens squeezed out, the appended one -- take the free
+  // indices of their class in order ------------------------------------------------------------------------
+  int my_slot[J], need_rank[J];
+  int need_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, free_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, moved_here = 0;
+  unsigned long long need_bal[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int tok = tok0 + 64 * j;
+    // (conditions as bit operations: no branch is worth its instructions here)
+    const int idx = tok - class_start<HAS1>(c_old, cls[j]);
+    const bool keep = (ocls[j] >= 0) & (cls[j] == ocls[j]) & (((lost >> (cls[j] & 7)) & 1u) == 0u) &
+                      (idx < class_end<HAS1>(cn.n3, n32n, cn.n4, cn.n8, cn.n1, cls[j])) & (idx >= (cls[j] == QC2 ? cn.n3 : 0));
+    my_slot[j] = keep ? idx + class_start<HAS1>(cn, cls[j]) : -1;
+    const bool need = (cls[j] >= 0) & !keep;
+    need_bal[j] = __ballot(need);
+    moved_here += __popcll(need_bal[j]);
+    // slot `tok` of the new order: free unless the token that could keep it does
+    const int slot_cls = class_at<HAS1>(cn, tok);
+    const int cand = tok - class_start<HAS1>(cn, slot_cls) + class_start<HAS1>(c_old, slot_cls);        // the old slot with that index
+    const bool taken = (cand < n_before) & (((lost >> slot_cls) & 1u) == 0u) & (class_at<HAS1>(c_old, cand) == slot_cls) &
+                       ((int)L.cls_new[cand & (QAQ_TT - 1)] == slot_cls);
+    const bool is_free = (tok < n_after) & !taken;
+    int free_at = 0;
+    need_rank[j] = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const unsigned long long bn = __ballot(need & (cls[j] == c)), bf = __ballot(is_free & (slot_cls == c));
+      if (bn) {                                   // uniform; most are empty
+        need_rank[j] = cls[j] == c ? need_base[c] + lanes_below(bn) : need_rank[j];
+        need_base[c] += __popcll(bn);
+      }
+      if (bf) {
+        const int r = free_base[c] + lanes_below(bf);
+        free_at = slot_cls == c ? (wave == 0 ? cn.start(c) + r : cn.start(c) + cn.count(c) - 1 - r) : free_at;
+        free_base[c] += __popcll(bf);
+      }
+    }
+    if (is_free) L.freeslot[free_at] = (uint8_t)tok;
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) { L.w_need[wave][c] = need_base[c]; L.w_free[wave][c] = free_base[c]; }
+    L.w_moved[wave] = moved_here;
+  }
   __syncthreads();
-  const int n_moved = L.wave_moved[0] + L.wave_moved[1] + L.wave_moved[2] + L.wave_moved[3];
+  const int n_moved = __builtin_amdgcn_readfirstlane(L.w_moved[0] + L.w_moved[1]);
   if (n_moved > kMaxMoved) {
     // nothing of the cache has been written yet (the window row and the width outputs are the same
     // numbers when the general kernel writes them again)
     if (tid == 0) a.todo[atomicAdd(a.todo_count, 1u)] = (uint32_t)(tile_id * 2 + side);
     return;
   }
-  if (is_free) {
-    int r = cn.start(slot_cls) + free_rank;
-    for (int w = 0; w < wave; ++w) r += L.wave_free[slot_cls][w];
-    L.freeslot[r] = (uint8_t)tid;
-  }
-  __syncthreads();
-  int m_idx = -1;
-  if (need) {
-    int r = cn.start(cls) + need_rank;
-    for (int w = 0; w < wave; ++w) r += L.wave_need[cls][w];
-    my_slot = L.freeslot[r];
-    m_idx = __popcll(bal_need & ((1ull << lane) - 1ull));
-    for (int w = 0; w < wave; ++w) m_idx += L.wave_moved[w];
-    L.mv_a[m_idx] = (uint32_t)tid | ((uint32_t)my_slot << 16);
-    L.mv_b[m_idx] = (uint32_t)ob | ((uint32_t)nb << 8) | ((uint32_t)pos << 16);
-    L.mv_mm[m_idx] = mm;
-    L.m_of_slot[my_slot] = (uint8_t)m_idx;
-  }
-  __syncthreads();
-
-  // ---- value side: which slots of which units are written ---------------------------------------------
-  if (side == 1) {
-    const bool wr = tid < n_after && L.m_of_slot[tid] != 0xffu;
-    const unsigned long long bal = __ballot(wr && tid < n32n);
-    if (lane < 4) L.mask2[4 * wave + lane] = (uint32_t)(bal >> (16 * lane)) & 0xffffu;
-    if (wr && tid >= n32n && tid < n32n + cn.n4) atomicOr(&L.mask4[(tid - n32n) >> 3], 1u << ((tid - n32n) & 7));
-  }
-
-  // ---- codes of the moved tokens -> LDS, at the new width: four channels per work item -----------------
   {
-    const QaqKRegions rk0 = qaq_k_regions(c_old, D);
-    const QaqVRegions rv0 = qaq_v_regions(c_old, D);
-    for (int it = tid; it < n_moved * (D / 4); it += kThreads) {
-      const int m = it / (D / 4), c4 = it % (D / 4);
-      const uint32_t ma = L.mv_a[m], mb = L.mv_b[m];
-      const int tok = (int)(ma & 0xffffu), o_b = (int)(mb & 0xffu), n_b = (int)((mb >> 8) & 0xffu), p = (int)(mb >> 16);
-      uint32_t codes;
-      if (has_new && tok == n_before) {
-        codes = (L.newrow[c4] >> (o_b - n_b)) & width_mask(n_b);
-      } else if (n_b > o_b) {
-        // wider: from the unquantized copy, with the stored [min, max] (Section 4.2 "Integration")
-        const uint2 raw = *(const uint2*)(a.orig[side] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D + 4 * c4);
-        const uint32_t m2 = L.mv_mm[m];
-        const float mn = h2f((uint16_t)(m2 & 0xffffu)), mx = h2f((uint16_t)(m2 >> 16));
-        const float rg = mx - mn;
-        const float levels = (float)(1 << n_b);
-        const float inv = rg > 0.0f ? levels / rg : 0.0f;
-        const float top_code = levels - 1.0f;
-        codes = 0u;
+    int m0 = wave ? L.w_moved[0] : 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t hw = e < 2 ? raw.x : raw.y;
-          const float diff = h2f((uint16_t)(hw >> (16 * (e & 1)))) - mn;
-          const float prod = diff * inv;
-          codes = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), e, codes);
-        }
-      } else {
-        codes = side == 0 ? k_old_codes<D>(base, c_old, rk0, tok, c4) : v_old_codes<D>(base, c_old, rv0, tok, c4);
-        codes = (codes >> (o_b - n_b)) & width_mask(n_b);
+    for (int j = 0; j < J; ++j) {
+      if ((need_bal[j] >> lane) & 1ull) {
+        const int c = cls[j], r = need_rank[j] + (wave ? L.w_need[0][c] : 0), f0 = L.w_free[0][c];
+        my_slot[j] = L.freeslot[r < f0 ? cn.start(c) + r : cn.start(c) + cn.count(c) - 1 - (r - f0)];
+        const int m = m0 + lanes_below(need_bal[j]);
+        L.mv[m] = (uint32_t)(tok0 + 64 * j) | ((uint32_t)my_slot[j] << 8) | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
+        L.mv_mm[m] = mm[j];
+        L.m_of_slot[my_slot[j]] = (uint8_t)m;
       }
-      L.stage[m * SROW + c4] = codes;
+      m0 += __popcll(need_bal[j]);
+    }
+  }
+  // what is left to write of a token, in one register: position, slot, width; whether slot or width changed
+  uint32_t left[J];
+  constexpr uint32_t kMoves = 1u << 20, kRetag = 1u << 21;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int tok = tok0 + 64 * j;
+    const bool live = tok < n_after, need = ((need_bal[j] >> lane) & 1ull) != 0ull, is_new = has_new & (tok == n_before);
+    left[j] = (uint32_t)pos[j] | ((uint32_t)(my_slot[j] & 0xff) << 8) | ((uint32_t)nb[j] << 16) | ((live & ((my_slot[j] != tok) | need)) ? kMoves : 0u) |
+              ((live & ((nb[j] != ob[j]) | is_new)) ? kRetag : 0u);
+  }
+  __syncthreads();
+
+  // ---- value side: which slots are written, by unit of the region they are in ----------------------------
+  if (side == 1) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const unsigned long long wr = __ballot((tok0 + 64 * j < n_after) & (L.m_of_slot[tok0 + 64 * j] != 0xffu));
+      if (lane == 0) L.written[J * wave + j] = wr;
+    }
+    if (tid == 0) L.written[QAQ_TT / 64] = 0ull;
+    __syncthreads();
+    auto slots_from = [&](int first) -> uint32_t {       // slots [first, first + 16) of those to write
+      const uint32_t* p = (const uint32_t*)L.written + (min(first, QAQ_TT) >> 5);
+      return __builtin_amdgcn_alignbit(p[1], p[0], (uint32_t)first & 31u) & 0xffffu;
+    };
+    if (tid < 16) L.mask2[tid] = slots_from(16 * tid);
+    else if (tid < 48) L.mask4[tid - 16] = slots_from(n32n + 8 * (tid - 16)) & 0xffu;
+    else if (HAS1 && tid < 64) L.mask1b[tid - 48] = slots_from(cn.first1() + 16 * (tid - 48));
+  }
+
+  // ---- codes of the moved tokens -> LDS, at the new width: four channels per work item, two items per
+  // lane at a time, all their loads in flight together ---------------------------------------------------------
+  {
+    constexpr int U = 2;
+    auto gather = [&](auto side_c) {
+    constexpr int SD = decltype(side_c)::value;
+    const int n_items = n_moved * (D / 4);
+    const int new_tok = has_new ? n_before : QAQ_TT;
+#pragma unroll 1
+    for (int i0 = 0; i0 < n_items; i0 += kUpdThreads * U) {
+      u32x4 w[U];
+      u32x2 l[U];
+      uint32_t how[U];          // shifts (w, low bits), field width, class of the stored code
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int it = min(i0 + kUpdThreads * u + tid, n_items - 1);
+        const int m = it / (D / 4), c4 = it % (D / 4);
+        const uint32_t e = L.mv[m];
+        const int tok = (int)(e & 0xffu), o_b = (int)((e >> 24) & 15u), n_b = (int)(e >> 28), p = (int)((e >> 16) & 0xffu);
+        const int slot = min(tok, max(n_before - 1, 0));                 // (the appended token has no old codes: any in-range address)
+        const bool wide = n_b > o_b && tok != new_tok;
+        const OldCode o = SD == 0 ? k_old_place<D, HAS1>(c_old, r_old[QC3], r_old[QC4], r_old[QC8], r_old[QC1], slot, c4)
+                          : v_old_place<D, HAS1>(c_old, r_old[QC3], r_old[QC4], r_old[QC8], r_old[QC1], slot, c4);
+        how[u] = (uint32_t)o.sh | ((uint32_t)o.shl << 8) | (o.f3 ? 1u << 16 : 0u) | (o.f8 ? 1u << 17 : 0u) | (o.f1 ? 1u << 18 : 0u) | ((o.msk & 0xffu) << 20);
+        // wider: from the unquantized copy, with the stored [min, max] (Section 4.2 "Integration")
+        const uint8_t* src = wide ? (const uint8_t*)(a.orig[side] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D + 4 * c4) : base + o.w;
+        if (SD == 0) {
+          w[u].x = *(const uint32_t*)src;
+          w[u].y = *(const uint32_t*)(wide ? src + 4 : base + o.l);
+        } else {
+          // (sixteen bytes in all cases: of the copy's row the ones that hold the lane's eight, of an 8-bit
+          // row those that hold its four, of low bits those that hold its eight)
+          w[u] = *(const u32x4*)((uintptr_t)src & ~(uintptr_t)15);
+          l[u] = *(const u32x2*)(base + (o.l & ~7u));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int it = i0 + kUpdThreads * u + tid;
+        if (it >= n_items) continue;
+        const int m = it / (D / 4), c4 = it % (D / 4);
+        const uint32_t e = L.mv[m];
+        const int tok = (int)(e & 0xffu), o_b = (int)((e >> 24) & 15u), n_b = (int)(e >> 28);
+        const uint32_t sh = how[u] & 0xffu, shl = (how[u] >> 8) & 0xffu;
+        const bool f3 = how[u] & (1u << 16), f8 = how[u] & (1u << 17), f1 = how[u] & (1u << 18);
+        uint32_t codes = 0u;
+        bool by_channel = true;          // channels 4*c4 .. 4*c4+3; else (values) words 4*c4 .. 4*c4+3 of a unit
+        if (tok == new_tok) {
+          codes = (L.newrow[c4] >> (o_b - n_b)) & width_mask(n_b);
+        } else if (n_b > o_b) {
+          const uint32_t m2 = L.mv_mm[m];
+          const float mn = h2f((uint16_t)(m2 & 0xffffu)), mx = h2f((uint16_t)(m2 >> 16));
+          const float rg = mx - mn;
+          const float levels = (float)(1 << n_b);
+          const float inv = rg > 0.0f ? levels / rg : 0.0f;
+          const float top_code = levels - 1.0f;
+          const bool up = SD == 1 && (c4 & 1);            // (a row of the copy is 16-byte aligned: the caller's buffer is)
+          const uint32_t h2[2] = {up ? w[u].z : w[u].x, up ? w[u].w : w[u].y};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float diff = h2f((uint16_t)(h2[q >> 1] >> (16 * (q & 1)))) - mn;
+            const float prod = diff * inv;
+            codes = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), q, codes);
+          }
+        } else {
+          if (SD == 0) {
+            codes = ((w[u].x >> sh) & ((how[u] >> 20) * 0x01010101u)) ^ (f8 ? 0x80808080u : 0u);
+            if (f3) codes = (codes << 1) | ((w[u].y >> shl) & 0x01010101u);
+          } else if (f8) {
+            const uint32_t lo = c4 & 1 ? w[u].y : w[u].x, hi = c4 & 1 ? w[u].w : w[u].z;
+            codes = c4 & 2 ? hi : lo;
+          } else {
+            by_channel = false;
+            const uint32_t a0 = HAS1 && f1 ? (c4 & 1 ? w[u].z : w[u].x) : l[u].x, a1 = HAS1 && f1 ? (c4 & 1 ? w[u].w : w[u].y) : l[u].y;
+            const uint32_t t0l = a0 >> shl, t1l = a1 >> shl;      // bits 0 and 4 of each: the four channels' low bits
+            const uint32_t low = (t0l & 1u) | ((t0l << 4) & 0x100u) | ((t1l << 16) & 0x10000u) | ((t1l << 20) & 0x1000000u);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) codes |= ((w[u][k] >> sh) & (how[u] >> 20)) << (8 * k);
+            if (f3) codes = (codes << 1) | low;
+            if (HAS1 && f1) codes = low;
+          }
+          codes = (codes >> (o_b - n_b)) & width_mask(n_b);
+        }
+        if (SD == 0 || !by_channel) {
+          L.stage[m * SROW + c4] = codes;
+        } else {
+          uint8_t* row = (uint8_t*)&L.stage[m * SROW] + 4 * (c4 & 3) * (D / 16) + (c4 >> 2);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) row[k * (D / 16)] = (uint8_t)(codes >> (8 * k));
+        }
+      }
+    }
+    };
+    if (side == 0) gather(std::integral_constant<int, 0>{});
+    else gather(std::integral_constant<int, 1>{});
+  }
+
+  // ---- regions that start elsewhere: read as a whole, then written --------------------------------------
+  const int n_cp = cp_end[NC - 1];
+  if (n_cp > 0) {
+    constexpr int CP = kMaxCopy / (16 * kUpdThreads);
+    u32x4 x[CP];
+    uint32_t dst[CP];
+#pragma unroll
+    for (int k = 0; k < CP; ++k) {
+      const int i = min(kUpdThreads * k + tid, n_cp - 1);
+      uint32_t so = 0u, d = 0u;
+#pragma unroll
+      for (int c = NC - 1; c >= 0; --c)          // the class whose share holds piece i
+        if (i < cp_end[c]) {
+          const uint32_t first = 16u * (uint32_t)(i - (c > 0 ? cp_end[c > 0 ? c - 1 : 0] : 0));
+          so = r_old[c] + first; d = r_new[c] + first;
+        }
+      dst[k] = d;
+      x[k] = *(const u32x4*)(base + so);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();           // old and new places may overlap: everything read before anything is written
+#pragma unroll
+    for (int k = 0; k < CP; ++k)
+      if (kUpdThreads * k + tid < n_cp) *(u32x4*)(base + dst[k]) = x[k];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // ... and written before words of it are read again
+  }
+  uint32_t oi_mv[J][NOI], ov_mv[J][NOI];
+  if (!ONE && !csr) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int tok = tok0 + 64 * j;
+      const size_t gi = gi0 + min(tok, max(n_before - 1, 0));
+      if (left[j] & kMoves) {
+#pragma unroll
+        for (int k = 0; k < NOI; ++k)
+          if (2 * k < no2) {
+            oi_mv[j][k] = tok == n_before ? ((const uint16_t*)L.new_oi)[k] : *(const uint16_t*)(v.oidx[side] + gi * no2 + 2 * k);
+            ov_mv[j][k] = tok == n_before ? L.new_ov[k] : *(const uint32_t*)(v.oval[side] + gi * no2 + 2 * k);
+          }
+      }
     }
   }
   __syncthreads();      // every read of the old layout is done
 
-  // ---- metadata: tokens whose slot changed (moved ones, and 4-/8-bit tokens behind a moved class
-  // border), widths by position, class counts, the tile's bounds --------------------------------------
-  if (tid < n_after && (my_slot != tid || need)) {
-    const size_t gi = gi0 + my_slot;
-    v.mm[side][gi] = mm;
-    v.perm[side][gi] = (uint8_t)pos;
-    *(uint16_t*)(v.oidx[side] + gi * 2) = (uint16_t)oi;
-    *(uint32_t*)(v.oval[side] + gi * 2) = ov;
+  // ---- metadata: tokens whose slot changed (moved ones, and tokens behind a moved class border),
+  // widths by position, class counts, the tile's bounds ------------------------------------------------
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int p = (int)(left[j] & 0xffu);
+    if (left[j] & kMoves) {
+      const size_t gi = gi0 + ((left[j] >> 8) & 0xffu);
+      v.mm[side][gi] = mm[j];
+      v.perm[side][gi] = (uint8_t)p;
+      if (ONE) {
+        *(uint16_t*)(v.oidx[side] + gi * 2) = (uint16_t)oi[j];
+        *(uint32_t*)(v.oval[side] + gi * 2) = ov[j];
+      } else {
+#pragma unroll
+        for (int k = 0; k < NOI; ++k)
+          if (!csr && 2 * k < no2) {
+            *(uint16_t*)(v.oidx[side] + gi * no2 + 2 * k) = (uint16_t)oi_mv[j][k];
+            *(uint32_t*)(v.oval[side] + gi * no2 + 2 * k) = ov_mv[j][k];
+          }
+      }
+    }
+    if (left[j] & kRetag) v.tags[side][gi0 + p] = (uint8_t)((left[j] >> 16) & 15u);
   }
-  if (tid < n_after && (changed || is_new)) v.tags[side][gi0 + pos] = (uint8_t)nb;
+  if (csr && has_new) {        // the appended token's run goes behind the tile's last one
+    const size_t pool0 = gi0 * (size_t)no2;
+    const int st = n_before > 0 ? (int)v.ostart[side][gi0 + n_before - 1] + (int)v.ocnt[side][gi0 + n_before - 1] : 0;
+    const int new_no = L.new_no;
+    if (tid == 0) { v.ostart[side][gi0 + n_before] = (uint16_t)st; v.ocnt[side][gi0 + n_before] = (uint8_t)new_no; }
+    if (tid < new_no) {
+      v.oidx[side][pool0 + st + tid] = ((const uint8_t*)L.new_oi)[tid];
+      v.oval[side][pool0 + st + tid] = ((const uint16_t*)L.new_ov)[tid];
+    }
+  }
   if (tid == 0) {
     uint16_t* cp = v.counts + ((tile_id * 2 + side) * 4);
     cp[QC3] = (uint16_t)cn.n3; cp[QC2] = (uint16_t)cn.n2; cp[QC4] = (uint16_t)cn.n4; cp[QC8] = (uint16_t)cn.n8;
-    if (side == 1)
-      v.vbound[tile_id] = fmaxf(fmaxf(L.wave_bound[0], L.wave_bound[1]), fmaxf(L.wave_bound[2], L.wave_bound[3]));
-    else
-      ((float2*)v.kthr)[tile_id] = make_float2(fmaxf(fmaxf(L.wave_bound[0], L.wave_bound[1]), fmaxf(L.wave_bound[2], L.wave_bound[3])),
-                                               fminf(fminf(L.wave_bound2[0], L.wave_bound2[1]), fminf(L.wave_bound2[2], L.wave_bound2[3])));
+    if (side == 1) v.vbound[tile_id] = fmaxf(L.w_bnd[0], L.w_bnd[1]);
+    else ((float2*)v.kthr)[tile_id] = make_float2(fmaxf(L.w_lo[0], L.w_lo[1]), fminf(L.w_hi[0], L.w_hi[1]));
+    if (all_wide) v.refused[(tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
   }
-  if (tid == 0) add_widenings(v, tile_id * 2 + side, L.wave_wide, served);
 
   // ---- codes of the moved tokens -> their new places ----------------------------------------------------
   if (side == 0) {
-    const QaqKRegions r = qaq_k_regions(cn, D);
-    for (int it = tid; it < n_moved * NQ; it += kThreads) {
+    for (int it = tid; it < n_moved * NQ; it += kUpdThreads) {
       const int m = it / NQ, q = it % NQ;
-      const uint32_t ma = L.mv_a[m];
-      const int sl = (int)(ma >> 16), n_b = (int)((L.mv_b[m] >> 8) & 0xffu);
+      const uint32_t e = L.mv[m];
+      const int sl = (int)((e >> 8) & 0xffu), n_b = (int)(e >> 28);
       const uint32_t* row = &L.stage[m * SROW + 16 * (q % KS) + 4 * (q / KS)];
+      const uint32_t* row1 = &L.stage[m * SROW + 16 * ((q | 1) % KS) + 4 * ((q | 1) / KS)];       // slices q and q+1 of 1-bit fields share a word
       if (n_b <= 3) {
-        const int sh = n_b == 3 ? 1 : 0;
-        uint32_t w = 0;
+        if (!HAS1 || n_b > 1) {
+          const int sh = n_b == 3 ? 1 : 0;
+          uint32_t w = 0;
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq) w |= ((row[vq] >> sh) & 0x03030303u) << (2 * vq);
-        *(uint32_t*)(base + r.r2 + (uint32_t)sl * (D / 4) + 4u * (uint32_t)q) = w;
-        if (n_b == 3 && !(q & 1)) {       // the low bits of slices q and q+1 share a word
-          const uint32_t* row1 = &L.stage[m * SROW + 16 * ((q + 1) % KS) + 4 * ((q + 1) / KS)];
+          for (int vq = 0; vq < 4; ++vq) w |= ((row[vq] >> sh) & 0x03030303u) << (2 * vq);
+          *(uint32_t*)(base + r_new[QC2] + (uint32_t)sl * (D / 4) + 4u * (uint32_t)q) = w;
+        }
+        if (n_b != 2 && !(q & 1)) {
           uint32_t w1 = 0;
 #pragma unroll
           for (int vq = 0; vq < 4; ++vq) w1 |= ((row[vq] & 0x01010101u) << vq) | ((row1[vq] & 0x01010101u) << (4 + vq));
-          *(uint32_t*)(base + r.r1 + (uint32_t)sl * (D / 8) + 4u * (uint32_t)(q >> 1)) = w1;
+          const uint32_t at = HAS1 && n_b == 1 ? r_new[QC1] + (uint32_t)(sl - cn.first1()) * (D / 8) : r_new[QC3] + (uint32_t)sl * (D / 8);
+          *(uint32_t*)(base + at + 4u * (uint32_t)(q >> 1)) = w1;
         }
       } else if (n_b == 4) {
         const uint2 w = make_uint2((row[0] & 0x0f0f0f0fu) | ((row[1] & 0x0f0f0f0fu) << 4), (row[2] & 0x0f0f0f0fu) | ((row[3] & 0x0f0f0f0fu) << 4));
-        *(uint2*)(base + r.r4 + (uint32_t)(sl - n32n) * (D / 2) + 8u * (uint32_t)q) = w;
+        *(uint2*)(base + r_new[QC4] + (uint32_t)(sl - n32n) * (D / 2) + 8u * (uint32_t)q) = w;
       } else {
-        *(uint4*)(base + r.r8 + (uint32_t)(sl - n32n - cn.n4) * D + 16u * (uint32_t)q) =
+        *(uint4*)(base + r_new[QC8] + (uint32_t)(sl - n32n - cn.n4) * D + 16u * (uint32_t)q) =
             make_uint4(row[0] ^ 0x80808080u, row[1] ^ 0x80808080u, row[2] ^ 0x80808080u, row[3] ^ 0x80808080u);
       }
     }
     return;
   }
-  // value side: a stored word holds one channel of up to 16 tokens, so the fields of the written slots
-  // are put into the words as they are stored (a word of a unit that did not exist starts from zero;
-  // so does one whose region moved: then no token was kept in it and every slot of it is written)
-  {
-    const QaqVRegions r = qaq_v_regions(cn, D), r0 = qaq_v_regions(c_old, D);
-    const int units2_old = (n32o + 15) / 16;
-    const int units1_old = r.r1 == r0.r1 ? (c_old.n3 + 15) / 16 : 0;
-    const int half4_old = r.r4 == r0.r4 ? (c_old.n4 + 7) / 8 : 0;
-    for (int it = tid; it < ((n32n + 15) / 16) * (D / 4); it += kThreads) {
-      const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-      uint32_t msk = L.mask2[u];
-      if (!msk) continue;
-      uint32_t* wp = (uint32_t*)(base + r.r2 + (uint32_t)u * (4 * D)) + (4 * (c4 & 3)) * (D / 16) + cg;
-      uint32_t o[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = u < units2_old ? wp[k * (D / 16)] : 0u;
-      while (msk) {
-        const int i = __ffs(msk) - 1;
-        msk &= msk - 1;
-        const int sl = 16 * u + i;
-        const uint32_t w = (L.stage[L.m_of_slot[sl] * SROW + c4] >> (sl < cn.n3 ? 1 : 0)) & 0x03030303u;
-        const int bp = 8 * (i & 3) + 2 * (i >> 2);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(3u << bp)) | (((w >> (8 * k)) & 3u) << bp);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wp[k * (D / 16)] = o[k];
-    }
-    for (int it = tid; it < ((cn.n3 + 15) / 16) * (D / 8); it += kThreads) {
-      const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
-      const int in3 = cn.n3 - 16 * u;                      // slots of this unit inside the 3-bit class
-      uint32_t msk = L.mask2[u] & (in3 >= 16 ? 0xffffu : (1u << in3) - 1u);
-      if (!msk) continue;
-      uint32_t* wp = (uint32_t*)(base + r.r1 + (uint32_t)u * (2 * D)) + (4 * n4) * (D / 32) + cgp;
-      uint32_t o[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = u < units1_old ? wp[k * (D / 32)] : 0u;
-      while (msk) {
-        const int i = __ffs(msk) - 1;
-        msk &= msk - 1;
-        const int mi = L.m_of_slot[16 * u + i];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const uint32_t w = L.stage[mi * SROW + 4 * (2 * cgp + hh) + n4] & 0x01010101u;
-          const int bp = 8 * (i & 3) + 4 * hh + (i >> 2);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(1u << bp)) | (((w >> (8 * k)) & 1u) << bp);
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wp[k * (D / 32)] = o[k];
-    }
-    for (int it = tid; it < ((cn.n4 + 7) / 8) * (D / 4); it += kThreads) {
-      const int hu = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-      uint32_t msk = L.mask4[hu];
-      if (!msk) continue;
-      uint32_t* wp = (uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D)) + (4 * (c4 & 3)) * (D / 16) + cg;
-      uint32_t o[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = hu < half4_old ? wp[k * (D / 16)] : 0u;
-      while (msk) {
-        const int i = __ffs(msk) - 1;
-        msk &= msk - 1;
-        const uint32_t w = L.stage[L.m_of_slot[n32n + 8 * hu + i] * SROW + c4] & 0x0f0f0f0fu;
-        const int bp = 8 * (i & 3) + 4 * (i >> 2);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(15u << bp)) | (((w >> (8 * k)) & 15u) << bp);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wp[k * (D / 16)] = o[k];
-    }
-    for (int it = tid; it < n_moved * (D / 16); it += kThreads) {        // 8-bit tokens: token-major bytes, 16 per item
+  // value side: the words of the units with slots to write
+  // (the slots that are written were marked before the codes were gathered: barriers since)
+  auto old_units = [&](int c, int n) { return (lost >> c) & 1u ? 0 : n; };
+  if (n32n > 0) put_units<D, 2>(base + r_new[QC2], L.mask2, (n32o + 15) / 16, n32n, 0, cn.n3, L);
+  if (cn.n3 > 0) put_units<D, 1>(base + r_new[QC3], L.mask2, old_units(QC3, (min(c_old.n3, cn.n3) + 15) / 16), cn.n3, 0, 0, L);
+  if (cn.n4 > 0) put_units<D, 4>(base + r_new[QC4], L.mask4, old_units(QC4, (min(c_old.n4, cn.n4) + 7) / 8), cn.n4, n32n, 0, L);
+  if (HAS1 && cn.n1 > 0) put_units<D, 1>(base + r_new[QC1], L.mask1b, old_units(QC1, (min(c_old.n1, cn.n1) + 15) / 16), cn.n1, cn.first1(), 0, L);
+  if (cn.n8 > 0)
+    for (int it = tid; it < n_moved * (D / 16); it += kUpdThreads) {        // 8-bit tokens: token-major bytes, 16 per item
       const int m = it / (D / 16), dq = 4 * (it % (D / 16));
-      if (((L.mv_b[m] >> 8) & 0xffu) != 8u) continue;
-      const int sl = (int)(L.mv_a[m] >> 16);
-      const uint32_t* row = &L.stage[m * SROW + dq];
-      *(uint4*)(base + r.r8 + (uint32_t)(sl - n32n - cn.n4) * D + 4u * (uint32_t)dq) = make_uint4(row[0], row[1], row[2], row[3]);
+      const uint32_t e = L.mv[m];
+      if ((e >> 28) != 8u) continue;
+      const int sl = (int)((e >> 8) & 0xffu);
+      const uint8_t* row = (const uint8_t*)&L.stage[m * SROW] + (dq >> 2);      // channel group dq / 4
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int n = 0; n < 16; ++n) w[n >> 2] |= (uint32_t)row[n * (D / 16)] << (8 * (n & 3));
+      *(uint4*)(base + r_new[QC8] + (uint32_t)(sl - n32n - cn.n4) * D + 4u * (uint32_t)dq) = make_uint4(w[0], w[1], w[2], w[3]);
     }
-  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -2210,25 +2609,27 @@ hipError_t qaq_launch_build(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t qaq_launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_t s) {
-  if (ntiles <= 0) return hipSuccess;
-  QaqBuildArgs a = a_in;
-  const bool fast = a.mode == 2 && a.v.no2 == 2 && !a.v.csr && !a.v.has1 && a.todo && a.todo_count && a.todo_count_next;
-  if (!fast) {
-    a.todo = nullptr;
-    return qaq_launch_build(a, ntiles, s);
-  }
+template <int D, bool ONE, bool HAS1>
+static hipError_t launch_update(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
   const dim3 grid(a.v.B * a.v.Hkv, ntiles, 2);
-  if (a.v.D == 128) hipLaunchKernelGGL(k_update<128>, grid, dim3(kThreads), 0, s, a);
-  else hipLaunchKernelGGL(k_update<64>, grid, dim3(kThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL((k_update<D, ONE, HAS1>), grid, dim3(kUpdThreads), 0, s, a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // the tile sides the fast kernel handed over (their number is only known on the device)
+  // the tile sides it handed over (their number is only known on the device)
   const long long sides = (long long)a.v.B * a.v.Hkv * ntiles * 2;
-  const dim3 grid2((unsigned)(sides < 512 ? sides : 512));
-  if (a.v.D == 128) hipLaunchKernelGGL((k_build_listed<128, true, false>), grid2, dim3(kThreads), 0, s, a);
-  else hipLaunchKernelGGL((k_build_listed<64, true, false>), grid2, dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < 512 ? sides : 512)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
+}
+
+hipError_t qaq_launch_update(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
+  if (ntiles <= 0) return hipSuccess;
+  const bool one = a.v.no2 == 2 && !a.v.csr;
+  if (a.v.D == 128) {
+    if (a.v.has1) return one ? launch_update<128, true, true>(a, ntiles, s) : launch_update<128, false, true>(a, ntiles, s);
+    return one ? launch_update<128, true, false>(a, ntiles, s) : launch_update<128, false, false>(a, ntiles, s);
+  }
+  if (a.v.has1) return one ? launch_update<64, true, true>(a, ntiles, s) : launch_update<64, false, true>(a, ntiles, s);
+  return one ? launch_update<64, true, false>(a, ntiles, s) : launch_update<64, false, false>(a, ntiles, s);
 }
 
 hipError_t qaq_launch_select(const QaqSelectArgs& a, hipStream_t s) {
