@@ -257,6 +257,7 @@ struct QaqBuildArgs {
   const __half* orig[2];       // requantize: [B,Hkv,orig_tokens,D] or null
   __half* orig_put[2];         // same buffers when the appended tokens are to be written into them, else null
   int orig_tokens;             // token extent of the unquantized copies (>= len)
+  int max_moved;               // decode-step update: tokens of a tile side the kernel has staging memory for (set by the launcher)
   // decode-step update: tile sides the fast kernel leaves to the general one, (unit * NT + tile) * 2 + side
   uint32_t* todo;
   uint32_t* todo_count;        // the counter this step appends through (zero when the step starts)

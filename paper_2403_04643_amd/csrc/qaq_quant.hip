@@ -1279,25 +1279,19 @@ __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
 // class, are squeezed out or arrive go through LDS.  Tile sides in which more than kMaxMoved tokens
 // move (a hyper-parameter that jumped) are handed to the general kernel through a list.
 // ---------------------------------------------------------------------------------
-constexpr int kMaxMoved = 60;       // (sixteen tile sides' LDS fit a compute unit)
+constexpr int kMinMoved = 60;       // (sixteen tile sides' LDS fit a compute unit)
 constexpr int kMaxCopy = 8192;
 constexpr int kUpdThreads = 128;
 
+// Beside this block a tile side has LDS for the codes of `a.max_moved` tokens (dynamic, sized at launch): that many
+// staged rows, then a list word and a [min, max] for each.  Before any code is gathered the space holds, by position,
+// the value side's predicted scores and (variable-length side store) largest | smallest outlier << 16.
 template <int D>
 struct UpdLds {
+  // keys: byte d of a staged row = channel d; values: byte n*(D/16) + g = channel 16*g + n, the order of a unit's words
   static constexpr int SROW = D / 4 + 1;   // dwords per staged row (odd stride: rows spread over the banks)
-  union {
-    uint32_t stage[kMaxMoved * SROW];      // codes of the moved tokens at their new width; keys: byte d = channel d; values:
-                                           // byte n*(D/16) + g = channel 16*g + n, the order of a unit's words
-    struct {                               // ... before any code is gathered, by position:
-      alignas(16) float pred[QAQ_TT];      // value side: predicted score
-      uint32_t oext[QAQ_TT];               // value side, variable-length side store: largest | smallest outlier << 16 (fp16), all ones: none
-    } p;
-  };
-  uint32_t mv[kMaxMoved];                  // moved list: token | new slot << 8 | position << 16 | old width << 24 | new width << 28
-  uint32_t mv_mm[kMaxMoved];               // ... fp16 min | max << 16
-  uint8_t cls_new[QAQ_TT];                 // by token: class after this step (0xff: no token)
-  uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list, 0xff = what is stored stays
+  static constexpr int PER_TOKEN = 4 * SROW + 8;
+  uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list; before that 1 = a token keeps the slot
   uint8_t freeslot[QAQ_TT];                // per class: the slots no token keeps, the first wavefront's from the front, the second's from the back
   uint32_t mask2[16], mask4[32], mask1b[16];   // value side: slots to write per unit of 16 (2-bit fields, 1-bit tokens) or half-unit of 8 (4-bit)
   unsigned long long written[QAQ_TT / 64 + 1];   // ... bit by slot
@@ -1336,8 +1330,8 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set
 // `s`) and the window's rows.  As qaq_predicted, with loads of two elements (rows start at any multiple of
 // the element: the loads are written as copies, so the compiler knows the alignment), all in flight
 // together: W rows are read whatever the window's length (1, 3, 5 or 8: what it has not is row 0 again).
-// ri: index of the lane's first position inside a ring row; p0: that position inside the tile; lim[r]:
-// positions of the tile that row r covers.
+// ri0: index inside a ring row that p0 >= 0 (the lane's first position) counts from, row0: the same of the scores; lim[r]:
+// positions from there on that row r covers.
 struct Two { float x[2]; };
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -1348,12 +1342,13 @@ __device__ __forceinline__ float vmaxf(float a, float b) {
   return r;
 }
 template <int W, typename RAW>
-__device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
+__device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri0, int p0,
                                              const Two (&g)[4], float (&s)[2], float (&m)[2]) {
   const size_t ring_row = (size_t)v.B * v.Hkv * v.Tmax;
   struct R2 { RAW x[2]; } raw[W];
 #pragma unroll
-  for (int r = 0; r < W; ++r) __builtin_memcpy(&raw[r], (const RAW*)v.ring + ((size_t)(r < v.window && r != skip ? r : 0) * ring_row + ri), sizeof(R2));
+  for (int r = 0; r < W; ++r)
+    __builtin_memcpy(&raw[r], (const uint8_t*)((const RAW*)v.ring + (size_t)(r < v.window && r != skip ? r : 0) * ring_row + ri0) + (uint32_t)(p0 * (int)sizeof(RAW)), sizeof(R2));
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     s[e] = qaq_ring_value(v, vmaxf(vmaxf(vmaxf(s[e], g[0].x[e]), vmaxf(g[1].x[e], g[2].x[e])), g[3].x[e]));
@@ -1362,54 +1357,47 @@ __device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[
 #pragma unroll
   for (int r = 0; r < W; ++r) {
     const int end = r < v.window && r != skip ? lim[r] : 0;
+    float xs[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const float x = sizeof(RAW) == 4 ? __uint_as_float((uint32_t)raw[r].x[e])
                     : v.ring_half == 1 ? h2f((uint16_t)raw[r].x[e]) : __uint_as_float((uint32_t)raw[r].x[e] << 16);
-      m[e] = vmaxf(m[e], p0 + e < end ? x : 0.0f);
+      xs[e] = x;
+    }
+    if (end >= QAQ_TT) {                                    // (uniform; what a row does not cover is left out)
+      m[0] = vmaxf(m[0], xs[0]); m[1] = vmaxf(m[1], xs[1]);
+    } else if (end > 0) {
+      m[0] = vmaxf(m[0], p0 < end ? xs[0] : 0.0f); m[1] = vmaxf(m[1], p0 + 1 < end ? xs[1] : 0.0f);
     }
   }
 }
 template <typename RAW>
-__device__ __forceinline__ void predicted2_t(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
+__device__ __forceinline__ void predicted2_t(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri0, int p0,
                                              const Two (&g)[4], float (&s)[2], float (&m)[2]) {
-  if (v.window == 1) predicted2_w<1, RAW>(v, lim, skip, ri, p0, g, s, m);
-  else if (v.window <= 3) predicted2_w<3, RAW>(v, lim, skip, ri, p0, g, s, m);
-  else if (v.window <= 5) predicted2_w<5, RAW>(v, lim, skip, ri, p0, g, s, m);
-  else predicted2_w<8, RAW>(v, lim, skip, ri, p0, g, s, m);
+  if (v.window == 1) predicted2_w<1, RAW>(v, lim, skip, ri0, p0, g, s, m);
+  else if (v.window <= 3) predicted2_w<3, RAW>(v, lim, skip, ri0, p0, g, s, m);
+  else if (v.window <= 5) predicted2_w<5, RAW>(v, lim, skip, ri0, p0, g, s, m);
+  else predicted2_w<8, RAW>(v, lim, skip, ri0, p0, g, s, m);
 }
-__device__ __forceinline__ void predicted2(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri, int p0,
-                                           const float* row, int G, size_t stride, float (&s)[2], float (&m)[2]) {
+__device__ __forceinline__ void predicted2(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri0, int p0,
+                                           const float* row0, int G, size_t stride, float (&s)[2], float (&m)[2]) {
   Two g[4];
   s[0] = s[1] = 0.0f;                                       // probabilities: >= 0
 #pragma unroll 1
   for (int g0 = 4; g0 < G; g0 += 4) {                       // query heads beyond the first four
 #pragma unroll
-    for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], row + (size_t)min(g0 + j, G - 1) * stride, sizeof(Two));
+    for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], (const uint8_t*)(row0 + (size_t)min(g0 + j, G - 1) * stride) + (uint32_t)(4 * p0), sizeof(Two));
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int e = 0; e < 2; ++e) s[e] = vmaxf(s[e], g[j].x[e]);
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], row + (size_t)min(j, G - 1) * stride, sizeof(Two));
-  if (v.ring_half) predicted2_t<uint16_t>(v, lim, skip, ri, p0, g, s, m);
-  else predicted2_t<uint32_t>(v, lim, skip, ri, p0, g, s, m);
+  for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], (const uint8_t*)(row0 + (size_t)min(j, G - 1) * stride) + (uint32_t)(4 * p0), sizeof(Two));
+  if (v.ring_half) predicted2_t<uint16_t>(v, lim, skip, ri0, p0, g, s, m);
+  else predicted2_t<uint32_t>(v, lim, skip, ri0, p0, g, s, m);
 }
 
-// Where four codes of a stored token are and how they are taken out of their words.  The class only
-// selects addresses, shifts and masks: the loads themselves are unconditional, so that those of several items
-// are in flight together.  Keys: channels 4*c4 .. 4*c4+3, in word w, and word l where a 3-bit token has its
-// low bits.  Values: the four consecutive words 4*c .. 4*c+3 of the token's unit, one channel each (one 16-byte
-// load: as four loads of a word each, the channels in order, the kernel took 36.3 instead
-// of 34.8 us at 256 heads x 4096 tokens), or two words of low bits; of an 8-bit token channels 4*c ..
-// 4*c+3, four bytes.
-struct OldCode {
-  uint32_t w, l;       // byte offsets from the tile side
-  int sh, shl;
-  uint32_t msk;
-  bool f3, f8, f1;
-};
 // class of a slot (the classes are numbered in slot order), width of a class: no branches
 template <bool HAS1>
 __device__ __forceinline__ int class_at(const QaqCounts& c, int slot) {
@@ -1426,53 +1414,10 @@ __device__ __forceinline__ int class_start(const QaqCounts& c, int k) {        /
   if (HAS1) r = k == QC1 ? first1 : r;
   return r;
 }
-template <bool HAS1>
-__device__ __forceinline__ int class_end(int n3, int n32, int n4, int n8, int n1, int k) {      // end of a class's indices in its region
-  int r = k == QC3 ? n3 : n32;
-  r = k == QC4 ? n4 : r;
-  r = k == QC8 ? n8 : r;
-  if (HAS1) r = k == QC1 ? n1 : r;
-  return r;
-}
-template <int D, bool HAS1>
-__device__ __forceinline__ OldCode k_old_place(const QaqCounts& c, uint32_t r1, uint32_t r4, uint32_t r8, uint32_t r1b, int slot, int c4) {
-  constexpr int KS = D / 64;
-  const int d = 4 * c4, ks = d / 64, g = (d % 64) / 16, vq = (d % 16) / 4;
-  const int q = g * KS + ks;                         // element 16*q + 4*vq of the record
-  const int k = class_at<HAS1>(c, slot), idx = slot - class_start<HAS1>(c, k);
-  const int s = (int)((0x30122u >> (4 * k)) & 15u);    // 8 >> s bits per element
-  OldCode o;
-  o.f3 = k == QC3; o.f8 = k == QC8; o.f1 = HAS1 && k == QC1;
-  uint32_t ro = k <= QC2 ? 0u : r8;           // (the 2-bit fields start the tile side)
-  ro = k == QC4 ? r4 : ro;
-  if (HAS1) ro = k == QC1 ? r1b : ro;
-  o.w = ro + (uint32_t)idx * ((uint32_t)D >> s) + ((uint32_t)((16 * q + 4 * vq) >> s) & ~3u);
-  const uint32_t lo = r1 + (uint32_t)slot * (D / 8) + 4u * (uint32_t)(q >> 1);
-  o.l = o.f3 ? lo : o.w;
-  o.shl = 4 * (q & 1) + vq;
-  o.sh = k <= QC2 ? 2 * vq : 0;
-  o.sh = k == QC4 ? 4 * (vq & 1) : o.sh;
-  if (HAS1) o.sh = k == QC1 ? o.shl : o.sh;
-  o.msk = width_mask(8 >> s);
-  return o;
-}
-template <int D, bool HAS1>
-__device__ __forceinline__ OldCode v_old_place(const QaqCounts& c, uint32_t r1, uint32_t r4, uint32_t r8, uint32_t r1b, int slot, int c4) {
-  const int k = class_at<HAS1>(c, slot), idx = slot - class_start<HAS1>(c, k);
-  OldCode o;
-  o.f3 = k == QC3; o.f8 = k == QC8; o.f1 = HAS1 && k == QC1;
-  const int us = k == QC4 ? 3 : 4, u = idx >> us, i = idx - (u << us);
-  // low-bit planes and 1-bit tokens: words 2*c4, 2*c4 + 1 of unit u, in each two channels, 4 bits apart
-  const uint32_t lo = (uint32_t)u * (2u * D) + 8u * (uint32_t)c4;
-  const uint32_t un = (uint32_t)u * (4u * D) + 16u * (uint32_t)c4, row = r8 + (uint32_t)idx * D + 4u * (uint32_t)c4;
-  o.w = un + (k == QC4 ? r4 : 0u);
-  o.w = o.f8 ? row : o.w;
-  if (HAS1) o.w = o.f1 ? r1b + lo : o.w;
-  o.l = o.f3 ? r1 + lo : o.w;
-  o.shl = 8 * (i & 3) + (i >> 2);
-  o.sh = 8 * (i & 3) + (k == QC4 ? 4 : 2) * (i >> 2);
-  o.msk = k == QC4 ? 15u : 3u;
-  return o;
+// bits [from, to) of a 64-bit mask, the ends clamped to it
+__device__ __forceinline__ unsigned long long span_mask(int from, int to) {
+  from = min(max(from, 0), 64); to = min(max(to, 0), 64);
+  return to > from ? (~0ull >> (64 - (to - from))) << from : 0ull;
 }
 
 // Value side: the fields of the slots to write are put into the words as they are stored (a word holds
@@ -1481,11 +1426,11 @@ __device__ __forceinline__ OldCode v_old_place(const QaqCounts& c, uint32_t r1, 
 // below it hold 3-bit codes (BF 2: their upper bits are wanted).  Each wavefront lists the units with
 // work and takes every other group of them, the words of a batch requested together.
 template <int D, int BF>
-__device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks, int units_old, int n_slots, int slot0, int n3, UpdLds<D>& L) {
+__device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks, int units_old, int n_slots, int slot0, int n3, const uint32_t* stage, UpdLds<D>& L) {
   constexpr int LPU = BF == 1 ? D / 8 : D / 4;       // lanes per unit, four consecutive words each
   constexpr int UPW = 64 / LPU, U = 2, SPU = BF == 4 ? 8 : 16;
   constexpr uint32_t UB = BF == 1 ? 2 * D : 4 * D;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   auto mask_of = [&](int u) {
     const int n = min(max(n_slots - SPU * u, 0), SPU);
     return masks[u] & ((1u << n) - 1u);
@@ -1504,7 +1449,7 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       un[k] = L.units[wave][min(i0 + k * UPW + sub, nu - 1)];
-      o[k] = ((const u32x4*)(region + (uint32_t)un[k] * UB))[c];
+      o[k] = *(const u32x4*)(region + (uint32_t)(un[k] * (int)UB + 16 * c));
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
@@ -1515,7 +1460,7 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
         const int i = __ffs(msk) - 1;
         msk &= msk - 1;
         const int sl = slot0 + SPU * un[k] + i;
-        const uint32_t* row = &L.stage[(int)L.m_of_slot[sl] * UpdLds<D>::SROW];
+        const uint32_t* row = &stage[(int)L.m_of_slot[sl] * UpdLds<D>::SROW];
         if (BF == 1) {
           const uint32_t w0 = row[2 * c], w1 = row[2 * c + 1];      // word e: bytes 2*e and 2*e + 1 of the pair
           const int bp = 8 * (i & 3) + (i >> 2);
@@ -1532,7 +1477,7 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
           for (int e = 0; e < 4; ++e) o[k][e] = (o[k][e] & ~(FM << bp)) | (((w >> (8 * e)) & FM) << bp);
         }
       }
-      ((u32x4*)(region + (uint32_t)un[k] * UB))[c] = o[k];
+      *(u32x4*)(region + (uint32_t)(un[k] * (int)UB + 16 * c)) = o[k];
     }
   }
 }
@@ -1542,11 +1487,16 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   __shared__ UpdLds<D> L;
+  extern __shared__ uint32_t stage[];        // [max_moved][SROW], then the moved list
   constexpr int SROW = UpdLds<D>::SROW, NQ = D / 16, KS = D / 64, J = QAQ_TT / kUpdThreads, NC = HAS1 ? QAQ_NCLASS : 4;
   constexpr int NOI = ONE ? 1 : 4;          // words of outlier values per token, pairs of outlier channels
+  uint32_t* const mv = stage + a.max_moved * SROW;      // moved list: token | new slot << 8 | position << 16 | old width << 24 | new width << 28
+  uint32_t* const mv_mm = mv + a.max_moved;             // ... fp16 min | max << 16
+  float* const pred = (float*)stage;                    // value side, until the codes are gathered: predicted scores
+  uint32_t* const oext_at = stage + QAQ_TT;             // ... extremes of the outliers
   const QaqView& v = a.v;
   const QaqRuleArgs& ru = a.rule;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tok0 = 64 * J * wave + lane;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), tok0 = 64 * J * wave + lane;
   const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv;
   // value sides first: nearly every one of them has work (a token's predicted score moves every
   // step), most key sides leave after one load and fill in behind
@@ -1579,14 +1529,14 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   int pos[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const size_t gi = gi0 + min(tok0 + 64 * j, max(n_before - 1, 0));
-    mm[j] = v.mm[side][gi];
-    pos[j] = v.perm[side][gi];
+    const uint32_t s = (uint32_t)min(tok0 + 64 * j, max(n_before - 1, 0));
+    mm[j] = *(const uint32_t*)((const uint8_t*)(v.mm[side] + gi0) + 4u * s);       // (uniform base, 32-bit lane offset)
+    pos[j] = *(v.perm[side] + gi0 + s);
     oi[j] = ov[j] = 0u;
     oext[j] = 0xffffffffu;
     if (ONE) {
-      oi[j] = *(const uint16_t*)(v.oidx[side] + gi * 2);
-      ov[j] = *(const uint32_t*)(v.oval[side] + gi * 2);
+      oi[j] = *(const uint16_t*)(v.oidx[side] + gi0 * 2 + 2u * s);
+      ov[j] = *(const uint32_t*)((const uint8_t*)(v.oval[side] + gi0 * 2) + 4u * s);
     }
   }
   if (!ONE && !csr && side == 1 && no2 > 0) {
@@ -1620,31 +1570,34 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     if (len_after >= 2) {
       // (the lane that the tile's end falls into reads one position further down: the one before it is
       // another lane's as well, and gets the same value from both)
-      const int p0 = min(2 * tid, n_after - 2);
+      // (lane offsets are unsigned: in a tile with one token everything counts from the position before it)
+      const int p0 = min(2 * tid, n_after - 2), back = n_after < 2 ? 1 : 0;
+#pragma unroll
+      for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] += back;
       float s[2], m[2];
-      predicted2(v, lim, ru.new_row, ri0 + p0, p0, row0 + p0, ru.G, ru.score_stride, s, m);
+      predicted2(v, lim, ru.new_row, ri0 - back, p0 + back, row0 - back, ru.G, ru.score_stride, s, m);
       if (2 * tid < n_after) {
         const size_t ro = (size_t)ru.new_row * ring_row + ri0 + p0;
         if (p0 >= 0) {
           if (v.ring_half == 0) {
-            __builtin_memcpy((float*)v.ring + ro, s, 8);
+            __builtin_memcpy((uint8_t*)((float*)v.ring + (size_t)ru.new_row * ring_row + ri0) + (uint32_t)(4 * p0), s, 8);
           } else {
             uint16_t hs[2];
 #pragma unroll
             for (int e = 0; e < 2; ++e) hs[e] = v.ring_half == 1 ? f2h(s[e]) : qaq_bf16_bits(s[e]);
             __builtin_memcpy((uint16_t*)v.ring + ro, hs, 4);
           }
-          L.p.pred[p0] = m[0]; L.p.pred[p0 + 1] = m[1];
+          pred[p0] = m[0]; pred[p0 + 1] = m[1];
         } else {               // a tile with one token: the position before it is another tile's
           qaq_ring_store(v, ro + 1, s[1]);
-          L.p.pred[0] = m[1];
+          pred[0] = m[1];
         }
       }
     } else if (tid == 0) {          // a sequence of one token
       float s = 0.0f;
       for (int g = 0; g < ru.G; ++g) s = fmaxf(s, row0[(size_t)g * ru.score_stride]);
       s = qaq_ring_value(v, s);
-      L.p.pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t0), ru.new_row, ri0, s);
+      pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t0), ru.new_row, ri0, s);
       qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri0, s);
     }
     if (csr) {
@@ -1676,11 +1629,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       }
 #pragma unroll
       for (int j = 0; j < J; ++j)
-        if (tok0 + 64 * j < n_before) L.p.oext[tok0 + 64 * j] = cnt[j] > 0 ? (uint32_t)f2h(hi[j]) | ((uint32_t)f2h(lo[j]) << 16) : 0xffffffffu;
+        if (tok0 + 64 * j < n_before) oext_at[tok0 + 64 * j] = cnt[j] > 0 ? (uint32_t)f2h(hi[j]) | ((uint32_t)f2h(lo[j]) << 16) : 0xffffffffu;
     }
   }
 #pragma unroll
-  for (int j = 0; j < J; ++j) L.m_of_slot[tok0 + 64 * j] = 0xffu;
+  for (int j = 0; j < J; ++j) L.m_of_slot[tok0 + 64 * j] = 0u;
 
   // ---- the appended token: outliers, range, codes at the widest width (Section 4.2 "Outliers",
   // Section 4.1 quantizer), by the second wavefront, two channels per lane ------------------------------
@@ -1745,7 +1698,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     if (!ONE && side == 1 && lane == 0) {
       float hi = -INFINITY, lo = INFINITY;
       for (int k = 0; k < new_no; ++k) { const float f = h2f(((const uint16_t*)L.new_ov)[k]); hi = fmaxf(hi, f); lo = fminf(lo, f); }
-      L.p.oext[n_before] = new_no > 0 ? (uint32_t)f2h(hi) | ((uint32_t)f2h(lo) << 16) : 0xffffffffu;
+      oext_at[n_before] = new_no > 0 ? (uint32_t)f2h(hi) | ((uint32_t)f2h(lo) << 16) : 0xffffffffu;
     }
   }
   __syncthreads();
@@ -1765,12 +1718,13 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 #pragma unroll
   for (int i = 0; i < NC; ++i) { thr_b[i] = ldexpf(thr, ru.bit_set[i]); wc[i] = ru.bit_set[i] | (qaq_class_of_bits(ru.bit_set[i]) << 4); }
   const bool served = a.orig[side] != nullptr;
-  int cls[J], ocls[J];         // class after and before this step, -1: no token
+  int cls[J];                  // class after this step, -1: no token
+  unsigned long long same_cls[J];   // cached tokens that stay in their class
   int nb[J], ob[J];
   float bnd = 0.0f, lo = 0.0f, hi = INFINITY;
   unsigned long long any = 0ull;
   int n_wide = 0;
-  int n_cls[QAQ_NCLASS] = {0, 0, 0, 0, 0};
+  unsigned long long bal_cls[NC][J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const int tok = tok0 + 64 * j;
@@ -1782,7 +1736,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     }
     const float mnf = h2f((uint16_t)(mm[j] & 0xffffu)), mxf = h2f((uint16_t)(mm[j] >> 16));
     const float range = mxf - mnf;
-    const float lhs = side == 0 ? range : range * L.p.pred[pos[j]];
+    const float lhs = side == 0 ? range : range * pred[pos[j]];
     int rc = wc[NC - 1];
 #pragma unroll
     for (int i = NC - 1; i >= 0; --i) rc = lhs <= thr_b[i] ? wc[i] : rc;
@@ -1797,15 +1751,14 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     any |= __ballot(live & (is_new | (nb[j] != ob[j])));
     cls[j] = (wider & !served) ? oc : rc >> 4;
     cls[j] = live ? cls[j] : -1;
-    ocls[j] = tok < n_before ? oc : -1;
+    same_cls[j] = __ballot((tok < n_before) & (cls[j] == oc));
 #pragma unroll
-    for (int c = 0; c < NC; ++c) n_cls[c] += __popcll(__ballot(cls[j] == c));
-    L.cls_new[tok] = (uint8_t)(live ? cls[j] : 0xff);
+    for (int c = 0; c < NC; ++c) bal_cls[c][j] = __ballot(cls[j] == c);
     // what the attention kernel and the next step's skip test need of the tile
     if (side == 1) {
       float bt = ldexpf(range, nb[j] == 3 ? -2 : -nb[j]);
       uint32_t x = ONE ? ov[j] : oext[j];           // two numbers the tile's largest correction is between
-      if (!ONE && (csr || is_new)) x = L.p.oext[pos[j]];
+      if (!ONE && (csr || is_new)) x = oext_at[pos[j]];
       const float o1 = h2f((uint16_t)(x & 0xffffu)), o0 = h2f((uint16_t)(x >> 16));
       const float bo = fmaxf(fmaxf(fabsf(o1 - mxf), fabsf(o1 - mnf)), fmaxf(fabsf(o0 - mxf), fabsf(o0 - mnf))) + range;
       if (ONE || x != 0xffffffffu) bt = fmaxf(bt, bo);
@@ -1822,7 +1775,12 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   bnd = wave_max(bnd); lo = wave_max(lo); hi = wave_min(hi);
   if (lane == 0) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) L.w_cls[wave][c] = n_cls[c];
+    for (int c = 0; c < NC; ++c) {
+      int n = 0;
+#pragma unroll
+      for (int j = 0; j < J; ++j) n += __popcll(bal_cls[c][j]);
+      L.w_cls[wave][c] = n;
+    }
     L.w_any[wave] = any != 0ull; L.w_wide[wave] = n_wide;
     L.w_bnd[wave] = bnd; L.w_lo[wave] = lo; L.w_hi[wave] = hi;
   }
@@ -1877,43 +1835,63 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   // ---- slots: a cached token that stays in its class keeps its index if the region still reaches it;
   // the others -- tokens that change class, tokens squeezed out, the appended one -- take the free
   // indices of their class in order ------------------------------------------------------------------------
+  // (whole wavefronts at a time, as masks: an old slot can be kept if it lies in a range that follows from the
+  // class counts alone)
   int my_slot[J], need_rank[J];
   int need_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, free_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, moved_here = 0;
-  unsigned long long need_bal[J];
+  unsigned long long need_bal[J], keep_bal[J];
+  const int shift4 = n32n - n32o, shift8 = shift4 + cn.n4 - c_old.n4, shift1 = shift8 + cn.n8 - c_old.n8;     // new slot less old slot of a kept token
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const int tok = tok0 + 64 * j;
-    // (conditions as bit operations: no branch is worth its instructions here)
-    const int idx = tok - class_start<HAS1>(c_old, cls[j]);
-    const bool keep = (ocls[j] >= 0) & (cls[j] == ocls[j]) & (((lost >> (cls[j] & 7)) & 1u) == 0u) &
-                      (idx < class_end<HAS1>(cn.n3, n32n, cn.n4, cn.n8, cn.n1, cls[j])) & (idx >= (cls[j] == QC2 ? cn.n3 : 0));
-    my_slot[j] = keep ? idx + class_start<HAS1>(cn, cls[j]) : -1;
-    const bool need = (cls[j] >= 0) & !keep;
-    need_bal[j] = __ballot(need);
-    moved_here += __popcll(need_bal[j]);
-    // slot `tok` of the new order: free unless the token that could keep it does
-    const int slot_cls = class_at<HAS1>(cn, tok);
-    const int cand = tok - class_start<HAS1>(cn, slot_cls) + class_start<HAS1>(c_old, slot_cls);        // the old slot with that index
-    const bool taken = (cand < n_before) & (((lost >> slot_cls) & 1u) == 0u) & (class_at<HAS1>(c_old, cand) == slot_cls) &
-                       ((int)L.cls_new[cand & (QAQ_TT - 1)] == slot_cls);
-    const bool is_free = (tok < n_after) & !taken;
-    int free_at = 0;
-    need_rank[j] = 0;
+    const int w0 = 64 * (J * wave + j);
+    unsigned long long can = 0ull;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const unsigned long long bn = __ballot(need & (cls[j] == c)), bf = __ballot(is_free & (slot_cls == c));
+      const int s0 = c_old.start(c), idx0 = c == QC2 ? max(cn.n3, c_old.n3) : s0;
+      const int end_new = c == QC3 ? cn.n3 : c == QC2 ? n32n : s0 + cn.count(c);
+      if (!((lost >> c) & 1u)) can |= span_mask(idx0 - w0, min(s0 + c_old.count(c), end_new) - w0);
+    }
+    keep_bal[j] = same_cls[j] & can;
+    const int tok = tok0 + 64 * j;
+    int to = cls[j] == QC4 ? tok + shift4 : tok;
+    to = cls[j] == QC8 ? tok + shift8 : to;
+    if (HAS1) to = cls[j] == QC1 ? tok + shift1 : to;
+    my_slot[j] = to;
+    need_rank[j] = 0;
+    need_bal[j] = 0ull;
+    if ((keep_bal[j] >> lane) & 1ull) L.m_of_slot[to] = 1u;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const unsigned long long bn = bal_cls[c][j] & ~keep_bal[j];
+      need_bal[j] |= bn;
       if (bn) {                                   // uniform; most are empty
         need_rank[j] = cls[j] == c ? need_base[c] + lanes_below(bn) : need_rank[j];
         need_base[c] += __popcll(bn);
       }
+    }
+    moved_here += __popcll(need_bal[j]);
+  }
+  __syncthreads();
+  unsigned long long free_bal[J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int w0 = 64 * (J * wave + j);
+    const unsigned long long open = __ballot(L.m_of_slot[tok0 + 64 * j] == 0u);
+    free_bal[j] = open & span_mask(-w0, n_after - w0);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int s0 = cn.start(c), n = cn.count(c);
+      const unsigned long long bf = open & span_mask(s0 - w0, s0 + n - w0);
       if (bf) {
         const int r = free_base[c] + lanes_below(bf);
-        free_at = slot_cls == c ? (wave == 0 ? cn.start(c) + r : cn.start(c) + cn.count(c) - 1 - r) : free_at;
+        if ((bf >> lane) & 1ull) L.freeslot[wave == 0 ? s0 + r : s0 + n - 1 - r] = (uint8_t)(tok0 + 64 * j);
         free_base[c] += __popcll(bf);
       }
     }
-    if (is_free) L.freeslot[free_at] = (uint8_t)tok;
+    // every free slot is taken by a token that moves: the slots to write
+    if (lane == 0) L.written[J * wave + j] = free_bal[j];
   }
+  if (tid == 0) L.written[QAQ_TT / 64] = 0ull;
   if (lane == 0) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) { L.w_need[wave][c] = need_base[c]; L.w_free[wave][c] = free_base[c]; }
@@ -1921,7 +1899,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   }
   __syncthreads();
   const int n_moved = __builtin_amdgcn_readfirstlane(L.w_moved[0] + L.w_moved[1]);
-  if (n_moved > kMaxMoved) {
+  if (n_moved > a.max_moved) {
     // nothing of the cache has been written yet (the window row and the width outputs are the same
     // numbers when the general kernel writes them again)
     if (tid == 0) a.todo[atomicAdd(a.todo_count, 1u)] = (uint32_t)(tile_id * 2 + side);
@@ -1935,8 +1913,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
         const int c = cls[j], r = need_rank[j] + (wave ? L.w_need[0][c] : 0), f0 = L.w_free[0][c];
         my_slot[j] = L.freeslot[r < f0 ? cn.start(c) + r : cn.start(c) + cn.count(c) - 1 - (r - f0)];
         const int m = m0 + lanes_below(need_bal[j]);
-        L.mv[m] = (uint32_t)(tok0 + 64 * j) | ((uint32_t)my_slot[j] << 8) | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
-        L.mv_mm[m] = mm[j];
+        mv[m] = (uint32_t)(tok0 + 64 * j) | ((uint32_t)my_slot[j] << 8) | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
+        mv_mm[m] = mm[j];
         L.m_of_slot[my_slot[j]] = (uint8_t)m;
       }
       m0 += __popcll(need_bal[j]);
@@ -1956,13 +1934,6 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 
   // ---- value side: which slots are written, by unit of the region they are in ----------------------------
   if (side == 1) {
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const unsigned long long wr = __ballot((tok0 + 64 * j < n_after) & (L.m_of_slot[tok0 + 64 * j] != 0xffu));
-      if (lane == 0) L.written[J * wave + j] = wr;
-    }
-    if (tid == 0) L.written[QAQ_TT / 64] = 0ull;
-    __syncthreads();
     auto slots_from = [&](int first) -> uint32_t {       // slots [first, first + 16) of those to write
       const uint32_t* p = (const uint32_t*)L.written + (min(first, QAQ_TT) >> 5);
       return __builtin_amdgcn_alignbit(p[1], p[0], (uint32_t)first & 31u) & 0xffffu;
@@ -1972,98 +1943,141 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     else if (HAS1 && tid < 64) L.mask1b[tid - 48] = slots_from(cn.first1() + 16 * (tid - 48));
   }
 
-  // ---- codes of the moved tokens -> LDS, at the new width: four channels per work item, two items per
-  // lane at a time, all their loads in flight together ---------------------------------------------------------
+  // ---- codes of the moved tokens -> LDS, at the new width: sixteen channels per work item --------------------
+  // (all loads of an item without a condition, so that they are in flight together: the class selects addresses,
+  // shifts and masks.  Four channels per item cost as many instructions per item.)
   {
-    constexpr int U = 2;
-    auto gather = [&](auto side_c) {
-    constexpr int SD = decltype(side_c)::value;
-    const int n_items = n_moved * (D / 4);
+    constexpr int LPT = D / 16;
+    const int n_items = n_moved * LPT;
     const int new_tok = has_new ? n_before : QAQ_TT;
-#pragma unroll 1
-    for (int i0 = 0; i0 < n_items; i0 += kUpdThreads * U) {
-      u32x4 w[U];
-      u32x2 l[U];
-      uint32_t how[U];          // shifts (w, low bits), field width, class of the stored code
+    // sixteen values of the unquantized copy at the token's [min, max] (Section 4.2 "Integration"), four codes per word
+    auto encode16 = [&](const u32x4& x0, const u32x4& x1, uint32_t m2, int n_b, uint32_t (&codes)[4]) {
+      const float mn = h2f((uint16_t)(m2 & 0xffffu)), mx = h2f((uint16_t)(m2 >> 16));
+      const float rg = mx - mn;
+      const float levels = (float)(1 << n_b);
+      const float inv = rg > 0.0f ? levels / rg : 0.0f;
+      const float top_code = levels - 1.0f;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int it = min(i0 + kUpdThreads * u + tid, n_items - 1);
-        const int m = it / (D / 4), c4 = it % (D / 4);
-        const uint32_t e = L.mv[m];
+      for (int k = 0; k < 4; ++k) {
+        codes[k] = 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t hw = k < 2 ? x0[2 * k + (e >> 1)] : x1[2 * (k - 2) + (e >> 1)];
+          const float diff = h2f((uint16_t)(hw >> (16 * (e & 1)))) - mn;
+          const float prod = diff * inv;
+          codes[k] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), e, codes[k]);
+        }
+      }
+    };
+    auto gather = [&](auto side_c) {
+      constexpr int SD = decltype(side_c)::value;
+#pragma unroll 1
+      for (int it = tid; it < n_items; it += kUpdThreads) {
+        int c = it % LPT;
+        asm volatile("" : "+v"(c));        // (nothing that follows from it is worth a register across the loop)
+        const int m = it / LPT;
+        const uint32_t e = mv[m];
         const int tok = (int)(e & 0xffu), o_b = (int)((e >> 24) & 15u), n_b = (int)(e >> 28), p = (int)((e >> 16) & 0xffu);
         const int slot = min(tok, max(n_before - 1, 0));                 // (the appended token has no old codes: any in-range address)
-        const bool wide = n_b > o_b && tok != new_tok;
-        const OldCode o = SD == 0 ? k_old_place<D, HAS1>(c_old, r_old[QC3], r_old[QC4], r_old[QC8], r_old[QC1], slot, c4)
-                          : v_old_place<D, HAS1>(c_old, r_old[QC3], r_old[QC4], r_old[QC8], r_old[QC1], slot, c4);
-        how[u] = (uint32_t)o.sh | ((uint32_t)o.shl << 8) | (o.f3 ? 1u << 16 : 0u) | (o.f8 ? 1u << 17 : 0u) | (o.f1 ? 1u << 18 : 0u) | ((o.msk & 0xffu) << 20);
-        // wider: from the unquantized copy, with the stored [min, max] (Section 4.2 "Integration")
-        const uint8_t* src = wide ? (const uint8_t*)(a.orig[side] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D + 4 * c4) : base + o.w;
-        if (SD == 0) {
-          w[u].x = *(const uint32_t*)src;
-          w[u].y = *(const uint32_t*)(wide ? src + 4 : base + o.l);
-        } else {
-          // (sixteen bytes in all cases: of the copy's row the ones that hold the lane's eight, of an 8-bit
-          // row those that hold its four, of low bits those that hold its eight)
-          w[u] = *(const u32x4*)((uintptr_t)src & ~(uintptr_t)15);
-          l[u] = *(const u32x2*)(base + (o.l & ~7u));
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int it = i0 + kUpdThreads * u + tid;
-        if (it >= n_items) continue;
-        const int m = it / (D / 4), c4 = it % (D / 4);
-        const uint32_t e = L.mv[m];
-        const int tok = (int)(e & 0xffu), o_b = (int)((e >> 24) & 15u), n_b = (int)(e >> 28);
-        const uint32_t sh = how[u] & 0xffu, shl = (how[u] >> 8) & 0xffu;
-        const bool f3 = how[u] & (1u << 16), f8 = how[u] & (1u << 17), f1 = how[u] & (1u << 18);
-        uint32_t codes = 0u;
-        bool by_channel = true;          // channels 4*c4 .. 4*c4+3; else (values) words 4*c4 .. 4*c4+3 of a unit
-        if (tok == new_tok) {
-          codes = (L.newrow[c4] >> (o_b - n_b)) & width_mask(n_b);
-        } else if (n_b > o_b) {
-          const uint32_t m2 = L.mv_mm[m];
-          const float mn = h2f((uint16_t)(m2 & 0xffffu)), mx = h2f((uint16_t)(m2 >> 16));
-          const float rg = mx - mn;
-          const float levels = (float)(1 << n_b);
-          const float inv = rg > 0.0f ? levels / rg : 0.0f;
-          const float top_code = levels - 1.0f;
-          const bool up = SD == 1 && (c4 & 1);            // (a row of the copy is 16-byte aligned: the caller's buffer is)
-          const uint32_t h2[2] = {up ? w[u].z : w[u].x, up ? w[u].w : w[u].y};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float diff = h2f((uint16_t)(h2[q >> 1] >> (16 * (q & 1)))) - mn;
-            const float prod = diff * inv;
-            codes = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), q, codes);
+        const bool fresh = tok == new_tok, wide = n_b > o_b && !fresh;
+        const int k = class_at<HAS1>(c_old, slot), idx = slot - class_start<HAS1>(c_old, k);
+        const bool f3 = k == QC3, f8 = k == QC8, f1 = HAS1 && k == QC1, f4 = k == QC4;
+        const int drop = o_b - n_b;
+        const uint32_t keep_bits = width_mask(n_b);
+        uint32_t codes[4];
+        if constexpr (SD == 0) {
+          // keys: slice c of the record, channels 64*ks + 16*g ..: one word, two or four, and for a 3-bit token half a
+          // word of low bits; of the copy's row 32 bytes
+          const int ch0 = 64 * (c % KS) + 16 * (c / KS);
+          uint32_t ro = k <= QC2 ? 0u : r_old[QC8];
+          ro = f4 ? r_old[QC4] : ro;
+          if (HAS1) ro = f1 ? r_old[QC1] : ro;
+          const int s8 = (int)((0x30122u >> (4 * k)) & 15u);           // 8 >> s8 bits per channel
+          const uint32_t at = ro + (uint32_t)idx * ((uint32_t)D >> s8) + ((uint32_t)(16 * c) >> s8 & ~3u);
+          const uint32_t lo_at = f3 ? r_old[QC3] + (uint32_t)slot * (D / 8) + 4u * (uint32_t)(c >> 1) : at;
+          const uint32_t st1 = f4 || f8 ? 4u : 0u, st2 = f8 ? 4u : 0u;
+          uint32_t w[4];
+          w[0] = *(const uint32_t*)(base + at);
+          w[1] = *(const uint32_t*)(base + (at + st1));
+          w[2] = *(const uint32_t*)(base + (at + 2u * st2));
+          w[3] = *(const uint32_t*)(base + (at + 3u * st2));
+          uint32_t low = *(const uint32_t*)(base + lo_at);
+          u32x4 x0 = (u32x4)0u, x1 = (u32x4)0u;
+          if (wide) {
+            const u32x4* src = (const u32x4*)(a.orig[0] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D + ch0);
+            x0 = src[0]; x1 = src[1];
           }
-        } else {
-          if (SD == 0) {
-            codes = ((w[u].x >> sh) & ((how[u] >> 20) * 0x01010101u)) ^ (f8 ? 0x80808080u : 0u);
-            if (f3) codes = (codes << 1) | ((w[u].y >> shl) & 0x01010101u);
-          } else if (f8) {
-            const uint32_t lo = c4 & 1 ? w[u].y : w[u].x, hi = c4 & 1 ? w[u].w : w[u].z;
-            codes = c4 & 2 ? hi : lo;
+          if (fresh) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) codes[q] = (L.newrow[ch0 / 4 + q] >> drop) & keep_bits;
+          } else if (wide) {
+            encode16(x0, x1, mv_mm[m], n_b, codes);
           } else {
-            by_channel = false;
-            const uint32_t a0 = HAS1 && f1 ? (c4 & 1 ? w[u].z : w[u].x) : l[u].x, a1 = HAS1 && f1 ? (c4 & 1 ? w[u].w : w[u].y) : l[u].y;
-            const uint32_t t0l = a0 >> shl, t1l = a1 >> shl;      // bits 0 and 4 of each: the four channels' low bits
-            const uint32_t low = (t0l & 1u) | ((t0l << 4) & 0x100u) | ((t1l << 16) & 0x10000u) | ((t1l << 20) & 0x1000000u);
+            if (HAS1 && f1) low = w[0];
+            low >>= 4 * (c & 1);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) codes |= ((w[u][k] >> sh) & (how[u] >> 20)) << (8 * k);
-            if (f3) codes = (codes << 1) | low;
-            if (HAS1 && f1) codes = low;
+            for (int q = 0; q < 4; ++q) {
+              uint32_t x = f8 ? w[q] ^ 0x80808080u : f4 ? (w[q >> 1] >> (4 * (q & 1))) & 0x0f0f0f0fu : (w[0] >> (2 * q)) & 0x03030303u;
+              const uint32_t lb = (low >> q) & 0x01010101u;
+              if (f3) x = (x << 1) | lb;
+              if (HAS1 && f1) x = lb;
+              codes[q] = (x >> drop) & keep_bits;
+            }
           }
-          codes = (codes >> (o_b - n_b)) & width_mask(n_b);
-        }
-        if (SD == 0 || !by_channel) {
-          L.stage[m * SROW + c4] = codes;
-        } else {
-          uint8_t* row = (uint8_t*)&L.stage[m * SROW] + 4 * (c4 & 3) * (D / 16) + (c4 >> 2);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) row[k * (D / 16)] = (uint8_t)(codes >> (8 * k));
+          for (int q = 0; q < 4; ++q) stage[m * SROW + ch0 / 4 + q] = codes[q];
+        } else {
+          // values: words 16*c .. 16*c+15 of the token's unit, a channel each, and for a 3-bit token eight words of low
+          // bits, two channels each; of an 8-bit row or of the copy's row the channels 16*c ..
+          const int us = f4 ? 3 : 4, u = idx >> us, i = idx - (u << us);
+          const uint32_t lo = (uint32_t)u * (2u * D) + 32u * (uint32_t)c;
+          uint32_t at = (uint32_t)u * (4u * D) + 64u * (uint32_t)c + (f4 ? r_old[QC4] : 0u);
+          at = f8 ? r_old[QC8] + (uint32_t)idx * D + 16u * (uint32_t)c : at;
+          const uint32_t lo_at = HAS1 && f1 ? r_old[QC1] + lo : f3 ? r_old[QC3] + lo : at & ~31u;
+          if (HAS1) at = f1 ? lo_at : at;
+          const bool unit = !f8 && !f1;
+          u32x4 w[4], l[2];
+          w[0] = *(const u32x4*)(base + at);
+          w[1] = *(const u32x4*)(base + (at + (unit ? 16u : 0u)));
+          w[2] = *(const u32x4*)(base + (at + (unit ? 32u : 0u)));
+          w[3] = *(const u32x4*)(base + (at + (unit ? 48u : 0u)));
+          l[0] = *(const u32x4*)(base + lo_at);
+          l[1] = *(const u32x4*)(base + (lo_at + (f3 || f1 ? 16u : 0u)));
+          if (wide) {
+            const u32x4* src = (const u32x4*)(a.orig[1] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D + 16 * c);
+            w[0] = src[0]; w[1] = src[1];
+          }
+          uint8_t* row = (uint8_t*)&stage[m * SROW];
+          if (fresh || wide || f8) {             // by channel: channel 16*c + n goes to byte n*(D/16) + c
+            if (fresh) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) codes[q] = (L.newrow[4 * c + q] >> drop) & keep_bits;
+            } else if (wide) {
+              encode16(w[0], w[1], mv_mm[m], n_b, codes);
+            } else {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) codes[q] = (w[0][q] >> drop) & keep_bits;
+            }
+#pragma unroll
+            for (int n = 0; n < 16; ++n) row[n * (D / 16) + c] = (uint8_t)(codes[n >> 2] >> (8 * (n & 3)));
+          } else {
+            const int sh = 8 * (i & 3) + (f4 ? 4 : 2) * (i >> 2), shl = 8 * (i & 3) + (i >> 2);
+            const uint32_t msk = f4 ? 15u : 3u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              uint32_t x = 0u;
+#pragma unroll
+              for (int n = 0; n < 4; ++n) x |= ((w[q][n] >> sh) & msk) << (8 * n);
+              if (f3 || f1) {                       // bits 0 and 4 of a word: two channels
+                const uint32_t l0 = l[q >> 1][2 * (q & 1)] >> shl, l1 = l[q >> 1][2 * (q & 1) + 1] >> shl;
+                const uint32_t lb = (l0 & 1u) | ((l0 << 4) & 0x100u) | ((l1 << 16) & 0x10000u) | ((l1 << 20) & 0x1000000u);
+                x = f1 ? lb : (x << 1) | lb;
+              }
+              stage[m * SROW + 4 * c + q] = (x >> drop) & keep_bits;
+            }
+          }
         }
       }
-    }
     };
     if (side == 0) gather(std::integral_constant<int, 0>{});
     else gather(std::integral_constant<int, 1>{});
@@ -2158,10 +2172,10 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   if (side == 0) {
     for (int it = tid; it < n_moved * NQ; it += kUpdThreads) {
       const int m = it / NQ, q = it % NQ;
-      const uint32_t e = L.mv[m];
+      const uint32_t e = mv[m];
       const int sl = (int)((e >> 8) & 0xffu), n_b = (int)(e >> 28);
-      const uint32_t* row = &L.stage[m * SROW + 16 * (q % KS) + 4 * (q / KS)];
-      const uint32_t* row1 = &L.stage[m * SROW + 16 * ((q | 1) % KS) + 4 * ((q | 1) / KS)];       // slices q and q+1 of 1-bit fields share a word
+      const uint32_t* row = &stage[m * SROW + 16 * (q % KS) + 4 * (q / KS)];
+      const uint32_t* row1 = &stage[m * SROW + 16 * ((q | 1) % KS) + 4 * ((q | 1) / KS)];       // slices q and q+1 of 1-bit fields share a word
       if (n_b <= 3) {
         if (!HAS1 || n_b > 1) {
           const int sh = n_b == 3 ? 1 : 0;
@@ -2190,17 +2204,17 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   // value side: the words of the units with slots to write
   // (the slots that are written were marked before the codes were gathered: barriers since)
   auto old_units = [&](int c, int n) { return (lost >> c) & 1u ? 0 : n; };
-  if (n32n > 0) put_units<D, 2>(base + r_new[QC2], L.mask2, (n32o + 15) / 16, n32n, 0, cn.n3, L);
-  if (cn.n3 > 0) put_units<D, 1>(base + r_new[QC3], L.mask2, old_units(QC3, (min(c_old.n3, cn.n3) + 15) / 16), cn.n3, 0, 0, L);
-  if (cn.n4 > 0) put_units<D, 4>(base + r_new[QC4], L.mask4, old_units(QC4, (min(c_old.n4, cn.n4) + 7) / 8), cn.n4, n32n, 0, L);
-  if (HAS1 && cn.n1 > 0) put_units<D, 1>(base + r_new[QC1], L.mask1b, old_units(QC1, (min(c_old.n1, cn.n1) + 15) / 16), cn.n1, cn.first1(), 0, L);
+  if (n32n > 0) put_units<D, 2>(base + r_new[QC2], L.mask2, (n32o + 15) / 16, n32n, 0, cn.n3, stage, L);
+  if (cn.n3 > 0) put_units<D, 1>(base + r_new[QC3], L.mask2, old_units(QC3, (min(c_old.n3, cn.n3) + 15) / 16), cn.n3, 0, 0, stage, L);
+  if (cn.n4 > 0) put_units<D, 4>(base + r_new[QC4], L.mask4, old_units(QC4, (min(c_old.n4, cn.n4) + 7) / 8), cn.n4, n32n, 0, stage, L);
+  if (HAS1 && cn.n1 > 0) put_units<D, 1>(base + r_new[QC1], L.mask1b, old_units(QC1, (min(c_old.n1, cn.n1) + 15) / 16), cn.n1, cn.first1(), 0, stage, L);
   if (cn.n8 > 0)
     for (int it = tid; it < n_moved * (D / 16); it += kUpdThreads) {        // 8-bit tokens: token-major bytes, 16 per item
       const int m = it / (D / 16), dq = 4 * (it % (D / 16));
-      const uint32_t e = L.mv[m];
+      const uint32_t e = mv[m];
       if ((e >> 28) != 8u) continue;
       const int sl = (int)((e >> 8) & 0xffu);
-      const uint8_t* row = (const uint8_t*)&L.stage[m * SROW] + (dq >> 2);      // channel group dq / 4
+      const uint8_t* row = (const uint8_t*)&stage[m * SROW] + (dq >> 2);      // channel group dq / 4
       uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int n = 0; n < 16; ++n) w[n >> 2] |= (uint32_t)row[n * (D / 16)] << (8 * (n & 3));
@@ -2610,13 +2624,21 @@ hipError_t qaq_launch_build(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
 }
 
 template <int D, bool ONE, bool HAS1>
-static hipError_t launch_update(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
-  const dim3 grid(a.v.B * a.v.Hkv, ntiles, 2);
-  hipLaunchKernelGGL((k_update<D, ONE, HAS1>), grid, dim3(kUpdThreads), 0, s, a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // the tile sides it handed over (their number is only known on the device)
+static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_t s) {
+  QaqBuildArgs a = a_in;
   const long long sides = (long long)a.v.B * a.v.Hkv * ntiles * 2;
+  // LDS for moved tokens: what is left of a compute unit's 160 KB when all value sides are resident at once (the key
+  // sides, few of which have work, take the places that become free), from kMinMoved -- sixteen tile sides -- up to a
+  // whole tile, which leaves nothing for the general kernel to do
+  const long long resident = (sides / 2 + 255) / 256;
+  const int room = (int)(160 * 1024 / (resident < 16 ? resident : 16)) / 1280 * 1280 - (int)sizeof(UpdLds<D>);      // (LDS is handed out 1280 bytes at a time)
+  a.max_moved = room / UpdLds<D>::PER_TOKEN;
+  if (a.max_moved < kMinMoved) a.max_moved = kMinMoved;
+  if (a.max_moved > QAQ_TT) a.max_moved = QAQ_TT;
+  hipLaunchKernelGGL((k_update<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(kUpdThreads), (size_t)a.max_moved * UpdLds<D>::PER_TOKEN, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.max_moved == QAQ_TT) return e;
+  // the tile sides it handed over (their number is only known on the device)
   hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < 512 ? sides : 512)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
