@@ -505,6 +505,7 @@ struct ValRegs {
 // no test for it: as a run-time flag it cost the call 0.4 us).
 template <int D, int NO2, int PP, bool H1>
 __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_attn_tile(QaqAttnArgs a) {   // four wavefronts per SIMD
+  qaq_request_arguments<0, sizeof(QaqAttnArgs)>();
   constexpr int P = PP == 5 ? 4 : PP;
   constexpr bool LDS_LOGITS = PP != 5;
   constexpr int KS = D / 64;

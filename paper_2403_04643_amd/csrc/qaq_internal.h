@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/qaq.h"
@@ -230,7 +231,27 @@ __device__ __forceinline__ float wave_min(float x) {
 }
 #endif
 
-// What the width rules need (Section 4.1 written as comparisons, Section 4.2 window).
+// Ask for the kernel's arguments at once, a word of each 64-byte line of [FROM, TO).  They come from memory that
+// nothing has cached yet; read as the code gets to them, the lines are as many round trips one behind the other
+// (seven before the first load of k_attn_tile: four calls at 8 x 32 heads x 4096 tokens 125.2 us that way, 120.8 with the
+// lines asked for together; 24 steps of a small model 520 and 509 us; the kernels that do not call it did not gain).  At most 28 lines.
+template <int FROM, int TO>
+__device__ __forceinline__ void qaq_request_arguments() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int L0 = FROM / 64, N = (TO + 63) / 64 - L0;
+  static_assert(N >= 1 && N <= 28, "argument lines");
+  const __attribute__((address_space(4))) uint32_t* k = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t x[28];
+#pragma unroll
+  for (int i = 0; i < 28; ++i) x[i] = k[16 * (L0 + (i < N ? i : 0))];
+  asm volatile("" :: "s"(x[0]), "s"(x[1]), "s"(x[2]), "s"(x[3]), "s"(x[4]), "s"(x[5]), "s"(x[6]), "s"(x[7]), "s"(x[8]), "s"(x[9]),
+               "s"(x[10]), "s"(x[11]), "s"(x[12]), "s"(x[13]), "s"(x[14]), "s"(x[15]), "s"(x[16]), "s"(x[17]), "s"(x[18]), "s"(x[19]),
+               "s"(x[20]), "s"(x[21]), "s"(x[22]), "s"(x[23]), "s"(x[24]), "s"(x[25]), "s"(x[26]), "s"(x[27]));
+#endif
+}
+
+// What the width rules need (Section 4.1 written as comparisons, Section 4.2 window).  (The tables come last: what every
+// workgroup reads is then on few lines, see qaq_request_arguments.)
 struct QaqRuleArgs {
   int G;                   // query heads per KV head
   const float* scores;     // [B,Hq,score_stride] or null
@@ -239,9 +260,9 @@ struct QaqRuleArgs {
   int row_len[QAQ_MAX_WINDOW];  // tokens covered by each ring row, 0 = unused
   int nbits;
   int bit_set[5];
-  float tau_k[QAQ_MAX_THR];        // key-rule threshold per KV head; per (sequence, KV head) in a cache with different lengths
-  float c_v[QAQ_MAX_RAGGED_BATCH]; // value-rule threshold; per sequence in such a cache, else entry 0
   uint8_t* out_bits[2];    // [B,Hkv,len] or null
+  float c_v[QAQ_MAX_RAGGED_BATCH]; // value-rule threshold; per sequence in a cache with different lengths, else entry 0
+  float tau_k[QAQ_MAX_THR];        // key-rule threshold per KV head; per (sequence, KV head) in such a cache
 };
 __device__ __forceinline__ float qaq_tau_k(const QaqRuleArgs& r, const QaqView& v, int b, int h) { return r.tau_k[v.ragged ? b * v.Hkv + h : h]; }
 __device__ __forceinline__ float qaq_c_v(const QaqRuleArgs& r, const QaqView& v, int b) { return r.c_v[v.ragged ? b : 0]; }
@@ -250,7 +271,6 @@ struct QaqBuildArgs {
   QaqView v;
   int mode;          // 0 = append, 1 = requantize, 2 = decode-step update (append one token, select, requantize),
                      // 3 = append at the widths the rules give from the window as it stands
-  QaqRuleArgs rule;  // modes 2 and 3
   int len_before, len_after, tile0, n_new, widest;
   const __half* newx[2];       // append: [B,Hkv,n_new,D]
   const uint8_t* newbits[2];   // append: [B,Hkv,n_new] or null; requantize: [B,Hkv,len] or null
@@ -262,6 +282,7 @@ struct QaqBuildArgs {
   uint32_t* todo;
   uint32_t* todo_count;        // the counter this step appends through (zero when the step starts)
   uint32_t* todo_count_next;   // the next step's counter (this step clears it)
+  QaqRuleArgs rule;            // modes 2 and 3
 };
 
 struct QaqSelectArgs {
@@ -273,9 +294,9 @@ struct QaqSelectArgs {
   int row_len[QAQ_MAX_WINDOW];  // tokens covered by each ring row, 0 = unused
   int nbits;
   int bit_set[5];
-  float tau_k[QAQ_MAX_THR];        // as in QaqRuleArgs
-  float c_v[QAQ_MAX_RAGGED_BATCH];
   uint8_t* out_bits[2];    // [B,Hkv,len]
+  float c_v[QAQ_MAX_RAGGED_BATCH]; // as in QaqRuleArgs
+  float tau_k[QAQ_MAX_THR];
 };
 
 struct QaqAttnArgs {

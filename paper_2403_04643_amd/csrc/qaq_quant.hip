@@ -1244,6 +1244,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 // head, which ran 30 % slower.
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
+  qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, tau_k) + 128 * sizeof(float)>();
   build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z);
 }
 
@@ -1486,6 +1487,8 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
 // HAS1: the width set contains 1.
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
+  // (and the key thresholds of the first 128 heads)
+  qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, tau_k) + 128 * sizeof(float)>();
   __shared__ UpdLds<D> L;
   extern __shared__ uint32_t stage[];        // [max_moved][SROW], then the moved list
   constexpr int SROW = UpdLds<D>::SROW, NQ = D / 16, KS = D / 64, J = QAQ_TT / kUpdThreads, NC = HAS1 ? QAQ_NCLASS : 4;
@@ -2226,6 +2229,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 // Width selection (Section 4.1 bit rules written as comparisons, Section 4.2 window).
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_select(QaqSelectArgs a) {
+  qaq_request_arguments<0, offsetof(QaqSelectArgs, tau_k) + 128 * sizeof(float)>();
   __shared__ float rk[QAQ_TT], rv[QAQ_TT];
   const QaqView& v = a.v;
   const int tid = threadIdx.x;
