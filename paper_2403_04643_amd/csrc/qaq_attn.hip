@@ -484,6 +484,23 @@ struct ValRegs {
   }
 };
 
+// Workgroups are dealt to the eight dies round-robin, and each die has an L2 of its own.  Where `share`
+// workgroups read the same codes (the query heads of a KV head, or groups of them, at one part of the
+// tiles), they are given linear indices eight apart: one die, and next to one another in time, so that all
+// but the first are served by its L2.  lin: linear workgroup index of `total`; -> which of the `share`, and the
+// index of what they share.  (k_attn_gqa at 16 x 64 heads on 8, 8192 tokens fetched 197 MB with the two of a KV
+// head on different dies.)
+__device__ __forceinline__ void die_neighbours(int lin, int total, int share, int& member, int& item) {
+  const int whole = total / (8 * share) * (8 * share);
+  if (lin < whole) {
+    const int a = lin / (8 * share), r = lin - a * (8 * share);
+    member = r >> 3; item = 8 * a + (r & 7);
+  } else {                        // what does not fill eight groups
+    const int r = lin - whole;
+    member = r % share; item = whole / share + r / share;
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // One workgroup: one (sequence, query head), part `chunk` of its tiles: the tiles are split
 // into nparts runs whose lengths differ by at most one, the longer runs last (the last tile
@@ -514,7 +531,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   __shared__ TileLds<D> S_all[P ? P : 1];
   extern __shared__ float lg_all[];         // fused form: raw logits [part][iteration][position]
   const QaqView& v = a.v;
-  const int chunk = P ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8)) : (int)blockIdx.x;
+  int chunk = P ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8)) : (int)blockIdx.x;
   TileLds<D>& S = S_all[P ? chunk : 0];
   const int tid = threadIdx.x & (kThreads - 1), lane = tid & 63, wave = tid >> 6;
   const int nn = lane & 15, g = lane >> 4;
@@ -530,6 +547,13 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   // of the (sequence, query head) pairs.
   int bq = blockIdx.y;
   if (P && a.G > 1 && (gridDim.y & 7) == 0) bq = (int)(blockIdx.y & 7) * (int)(gridDim.y >> 3) + (int)(blockIdx.y >> 3);
+  if (!P && a.G > 1) {
+    int g, item;
+    die_neighbours((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y), a.G, g, item);
+    const int bh = item / a.nparts;
+    chunk = item - bh * a.nparts;
+    bq = bh * a.G + g;
+  }
   const int b = bq / v.Hq, hq = bq % v.Hq, h = hq / a.G;
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
   const int ntile = (len + QAQ_TT - 1) / QAQ_TT;
@@ -1086,12 +1110,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   constexpr int CGW = NCG / 4;
   __shared__ GqaLds<D> S;
   const QaqView& v = a.v;
-  const int chunk = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nn = lane & 15, g = lane >> 4;
-  const int NG = a.G / kHG;
-  const int unit = blockIdx.y;
-  const int b = unit / (v.Hkv * NG), h = (unit / NG) % v.Hkv, hg = unit % NG;
+  int hg, item;
+  die_neighbours((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y), a.G / kHG, hg, item);
+  const int bh = item / a.nparts, chunk = item - bh * a.nparts;
+  const int b = bh / v.Hkv, h = bh % v.Hkv;
   const int bq0 = b * v.Hq + h * a.G + kHG * hg;           // first of the four query heads
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
   const int ntile = (len + QAQ_TT - 1) / QAQ_TT;
