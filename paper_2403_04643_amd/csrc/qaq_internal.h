@@ -218,6 +218,17 @@ __device__ __forceinline__ float wave_sum(float x) {
                : "+v"(x));
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
+__device__ __forceinline__ int wave_isum(int x) {
+  asm volatile(QAQ_DPP_STEP("v_add_u32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_u32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_u32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_u32_dpp", "row_mirror row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_u32_dpp", "row_bcast:15 row_mask:0xa bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_u32_dpp", "row_bcast:31 row_mask:0xc bank_mask:0xf")
+               "s_nop 1"
+               : "+v"(x));
+  return __builtin_amdgcn_readlane(x, 63);
+}
 __device__ __forceinline__ float wave_min(float x) {
   asm volatile(QAQ_DPP_STEP("v_min_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
                QAQ_DPP_STEP("v_min_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
