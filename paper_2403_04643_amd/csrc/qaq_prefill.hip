@@ -7,9 +7,8 @@
 // fp32).  k_prefill_logits reads every key once: a wavefront keeps 64 keys in registers as B
 // operands and sweeps the query rows of the head over them in blocks of 16.  It leaves
 // logit/sqrt(D) (minus infinity where a token lies after the query's position) in the score
-// buffer, and for every query row the maximum and the sum of exponentials over its 64 keys;
-// k_prefill_softmax merges these, turns each row into scores in place and writes the maximum
-// over the query heads of a KV head into the ring rows.
+// buffer; k_prefill_softmax turns each row into scores in place and, where a KV head has one query head,
+// fills the window's rows; where it has several, k_prefill_ring writes their maximum there.
 #include "qaq_internal.h"
 
 namespace {
@@ -17,38 +16,21 @@ namespace {
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;
-constexpr int kChunk = 64;         // keys per wavefront of the logits kernel = tokens per (maximum, sum) pair
-constexpr int kShare = 4;          // tokens per thread of the softmax kernel
+constexpr int kShare = 4;          // tokens per thread of the kernel that fills the window's rows
 
 // tokens a query row attends to: row i belongs to position T - n + i of a prompt of T tokens
 __device__ __forceinline__ int row_length(int T, int n, int i) { return T - n + i + 1; }
 
-// The (maximum, sum) pairs of score row i of (sequence, query head) bq: NT tiles x 4 pairs.  They lie where
-// the attention call keeps its partial results (D + 4 floats per tile and query head; 8 rows x 4 x 2
-// are at most 64), which nobody needs while a prompt is encoded.
-__device__ __forceinline__ float2* row_pairs(const QaqView& v, int bq, int i) {
-  static_assert(QAQ_MAX_WINDOW * (QAQ_TT / kChunk) * 2 <= 64 + 4, "the pairs fit the attention call's partials");
-  return (float2*)(v.partial + (size_t)bq * v.NT * (v.D + 4)) + (size_t)i * v.NT * (QAQ_TT / kChunk);
-}
-
-// maximum / sum over the 16 lanes of a row, in every one of them
-__device__ __forceinline__ float row16_max(float x) {
-  asm volatile(QAQ_DPP_STEP("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_max_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_max_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_max_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf")
-               "s_nop 1"
-               : "+v"(x));
-  return x;
-}
-__device__ __forceinline__ float row16_sum(float x) {
-  asm volatile(QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_add_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf")
-               QAQ_DPP_STEP("v_add_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf")
-               "s_nop 1"
-               : "+v"(x));
-  return x;
+__device__ __forceinline__ float block_reduce(float x, bool is_max, float* red) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const float y = __shfl_xor(x, o);
+    x = is_max ? fmaxf(x, y) : x + y;
+  }
+  __syncthreads();                 // red[] may still be read from the previous reduction
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  return is_max ? fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) : (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 template <int D>
@@ -87,104 +69,93 @@ __global__ __launch_bounds__(kThreads) void k_prefill_logits(QaqPrefillArgs a) {
         if (!live) qa[s] = (h8)(_Float16)0;
       }
     }
-    f4 acc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      acc[g] = (f4){0.0f, 0.0f, 0.0f, 0.0f};
+      f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int s = 0; s < NS; ++s) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], key[g][s], acc[g], 0, 0, 0);
-    }
-    // element j of a result: query row 4kb + j of the block, key `col` of group g
+      for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[s], key[g][s], acc, 0, 0, 0);
+      const int t = t_wave + 16 * g + col;
+      if (t < a.T) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = r0 + 4 * kb + j;
-      const int rc = min(r, R - 1);
-      const int hq = h * a.G + rc / a.n_rows, i = rc % a.n_rows;
-      const int len = row_length(T_seq, a.n_rows, i);
-      float* row = a.scores + (((size_t)i * v.B + b) * v.Hq + hq) * a.T;
-      float x[4], m = -INFINITY;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int t = t_wave + 16 * g + col;
-        x[g] = t < len ? acc[g][j] * scale : -INFINITY;
-        m = fmaxf(m, x[g]);
-        if (r < R && t < a.T) row[t] = x[g];
+        for (int j = 0; j < 4; ++j) {      // element j of the result: query row 4kb + j of the block, key `col`
+          const int r = r0 + 4 * kb + j;
+          if (r < R) {
+            const int hq = h * a.G + r / a.n_rows, i = r % a.n_rows;
+            a.scores[(((size_t)i * v.B + b) * v.Hq + hq) * a.T + t] =
+                t < row_length(T_seq, a.n_rows, i) ? acc[j] * scale : -INFINITY;
+          }
+        }
       }
-      m = row16_max(m);
-      float l = 0.0f;
-      if (m > -INFINITY) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) l += expf(x[g] - m);        // exp(-inf) = 0 past the row's end
-      }
-      l = row16_sum(l);
-      if (col == 0 && r < R) row_pairs(v, b * v.Hq + hq, i)[t_wave / kChunk] = make_float2(m, l);
     }
   }
 }
 
-// Softmax of the score rows in place, and the ring rows: one workgroup per (share of 4 x 256 tokens,
-// prompt row, (sequence, KV head)), for all G query heads of the KV head, so that the ring entry --
-// the maximum over them -- is written once.  Every workgroup merges the heads' (maximum, sum) pairs for
-// itself (a wavefront per head, 8 bytes per 64 tokens, from the L2).  Bound by HBM: a score is read
-// and written once.  Before, one workgroup took the whole row, head after head, and read what exceeded 4096
-// tokens three times: 16 x 64 heads, 8192 tokens, 5 rows 256 us, now 60; 8 x 32 heads, 4096 tokens
-// 18 -> 16 us; 2 x 32 heads, 12001 tokens 37 -> 14 us.
-constexpr int kMaxMergeHeads = 16;         // query heads merged per pass over the pairs (more: further passes)
+// Softmax of the score rows in place: one workgroup per (query head, prompt row).  Bound by HBM: a thread keeps its
+// logits -- every 256th of the row -- in registers, KEEP of them (16, 32 or 64 by the row's length), so that up to
+// 16384 tokens a score is read once and written once.  The sum's order is part of what the scores are to the last bit:
+// a score that decides a width must not depend on how a row is shared out.  Before, one workgroup took the rows of all
+// G heads one after the other, with 16 logits in registers: 16 x 64 heads, 8192 tokens, 5 rows 256 us, now 59 (and 27 for
+// the window's rows); 8 x 32 heads, 4096 tokens 18 -> 13; 2 x 32 heads, 12001 tokens 37 -> 18.
+template <int KEEP>
 __global__ __launch_bounds__(kThreads) void k_prefill_softmax(QaqPrefillArgs a) {
-  __shared__ float s_m[kMaxMergeHeads], s_l[kMaxMergeHeads];
+  __shared__ float red[4];
   const QaqView& v = a.v;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv;      // heads fastest (see k_build)
-  const int i = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int bq = blockIdx.x, b = bq / v.Hq, hq = bq % v.Hq, i = blockIdx.y;      // heads fastest (see k_build)
   const int len = row_length(qaq_seq_len(v, b, a.T), a.n_rows, i);
-  const int n_pair = (a.T + kChunk - 1) / kChunk;
-  const int t0 = blockIdx.y * (kShare * kThreads) + tid;
-  float best[kShare];
+  float* row = a.scores + ((size_t)i * v.B * v.Hq + bq) * a.T;
+  float mine[KEEP];
 #pragma unroll
-  for (int k = 0; k < kShare; ++k) best[k] = 0.0f;
-  for (int g0 = 0; g0 < a.G; g0 += kMaxMergeHeads) {
-    const int ng = min(a.G - g0, kMaxMergeHeads);
-    if (g0) __syncthreads();
-    for (int g = wave; g < ng; g += 4) {
-      const float2* pairs = row_pairs(v, b * v.Hq + h * a.G + g0 + g, i);
-      float m = -INFINITY, l = 0.0f;
-      for (int p = lane; p < n_pair; p += 64) {
-        const float2 x = pairs[p];
-        if (x.x > -INFINITY) {
-          const float mm = fmaxf(m, x.x);
-          l = l * expf(m - mm) + x.y * expf(x.x - mm);
-          m = mm;
-        }
-      }
-      const float M = wave_max(m);
-      const float Lw = wave_sum(m > -INFINITY ? l * expf(m - M) : 0.0f);
-      if (lane == 0) { s_m[g] = M; s_l[g] = Lw; }
-    }
-    __syncthreads();
-#pragma unroll 2
-    for (int g = 0; g < ng; ++g) {
-      float* row = a.scores + (((size_t)i * v.B + b) * v.Hq + (h * a.G + g0 + g)) * a.T;
-      const float m = s_m[g], l = s_l[g];
-      float x[kShare];
+  for (int k = 0; k < KEEP; ++k) {
+    const int t = tid + k * kThreads;
+    mine[k] = t < len ? row[t] : -INFINITY;
+  }
+  float m = -INFINITY;
 #pragma unroll
-      for (int k = 0; k < kShare; ++k) {
-        const int t = t0 + k * kThreads;
-        x[k] = t < len ? row[t] : -INFINITY;
-      }
+  for (int k = 0; k < KEEP; ++k) m = fmaxf(m, mine[k]);
+  for (int t = tid + KEEP * kThreads; t < len; t += kThreads) m = fmaxf(m, row[t]);
+  m = block_reduce(m, true, red);
+  float l = 0.0f;
 #pragma unroll
-      for (int k = 0; k < kShare; ++k) {
-        const int t = t0 + k * kThreads;
-        const float s = t < len ? expf(x[k] - m) / l : 0.0f;
-        if (t < a.T) row[t] = s;
-        best[k] = fmaxf(best[k], s);
-      }
+  for (int k = 0; k < KEEP; ++k) {
+    mine[k] = expf(mine[k] - m);                    // exp(-inf) = 0 past the row's end
+    l += mine[k];
+  }
+  for (int t = tid + KEEP * kThreads; t < len; t += kThreads) l += expf(row[t] - m);
+  l = block_reduce(l, false, red);
+  const bool ring = a.G == 1;                       // (else the maximum over the heads goes there: k_prefill_ring)
+  const size_t ring0 = (size_t)i * ((size_t)v.B * v.Hkv * v.Tmax) + (size_t)bq * v.Tmax;
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    const int t = tid + k * kThreads;
+    if (t < a.T) {
+      const float s = t < len ? mine[k] / l : 0.0f;
+      row[t] = s;
+      if (ring && t < len) qaq_ring_store(v, ring0 + t, s);
     }
   }
+  for (int t = tid + KEEP * kThreads; t < a.T; t += kThreads) {
+    const float s = t < len ? expf(row[t] - m) / l : 0.0f;
+    row[t] = s;
+    if (ring && t < len) qaq_ring_store(v, ring0 + t, s);
+  }
+}
+
+// Grouped queries: the window's rows, the maximum of the scores over the G query heads of a KV head (what the kernel
+// before has just written: from the last-level cache).
+__global__ __launch_bounds__(kThreads) void k_prefill_ring(QaqPrefillArgs a) {
+  const QaqView& v = a.v;
+  const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv, i = blockIdx.z;
+  const int len = row_length(qaq_seq_len(v, b, a.T), a.n_rows, i);
+  const float* row = a.scores + (((size_t)i * v.B + b) * v.Hq + h * a.G) * a.T;
   const size_t ring0 = (size_t)i * ((size_t)v.B * v.Hkv * v.Tmax) + qaq_bh(v, b, h) * v.Tmax;
-#pragma unroll
   for (int k = 0; k < kShare; ++k) {
-    const int t = t0 + k * kThreads;
-    if (t < len) qaq_ring_store(v, ring0 + t, best[k]);
+    const int t = (blockIdx.y * kShare + k) * kThreads + threadIdx.x;
+    if (t >= len) return;
+    float s = 0.0f;                                 // probabilities: >= 0
+#pragma unroll 8
+    for (int g = 0; g < a.G; ++g) s = fmaxf(s, row[(size_t)g * a.T + t]);
+    qaq_ring_store(v, ring0 + t, s);
   }
 }
 
@@ -198,7 +169,13 @@ hipError_t qaq_launch_prefill_window(const QaqPrefillArgs& a, hipStream_t s) {
   else return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  const dim3 rows(v.B * v.Hq, a.n_rows), block(kThreads);
+  if (a.T <= 16 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<16>, rows, block, 0, s, a);
+  else if (a.T <= 32 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<32>, rows, block, 0, s, a);
+  else hipLaunchKernelGGL(k_prefill_softmax<64>, rows, block, 0, s, a);
+  e = hipGetLastError();
+  if (e != hipSuccess || a.G == 1) return e;
   const int share = kShare * kThreads;
-  hipLaunchKernelGGL(k_prefill_softmax, dim3(v.B * v.Hkv, (a.T + share - 1) / share, a.n_rows), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(k_prefill_ring, dim3(v.B * v.Hkv, (a.T + share - 1) / share, a.n_rows), block, 0, s, a);
   return hipGetLastError();
 }
