@@ -1,0 +1,61 @@
+"""The fused decode step where many tokens move: hyper-parameters that jump from step to step, so that class counts
+cross the borders their regions are sized by, regions move, and a tile side has more tokens to move than the launch
+has staging memory for.  The same step in separate calls (append, selection, requantization) goes through the
+general kernels and must leave the same cache, bit for bit."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2403_04643_amd import qaq  # noqa: E402
+
+
+def _thresholds(x):
+    flat = x.float().transpose(0, 1).reshape(x.shape[1], -1).sort(dim=1).values
+    n = flat.shape[1]
+    return torch.stack([flat[:, n // 100], flat[:, n - 1 - n // 100]], dim=1).cpu().tolist()
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,T,steps,bit_set,n_o,thresholds,window,store", [
+    (2, 3, 1, 128, 253, 6, (2, 3, 4, 8), 1, False, 5, {}),             # a tile border; the second tile starts with one token
+    (1, 2, 4, 64, 1, 5, (2, 3, 4, 8), 0, False, 3, {"window_fp16": True}),   # one to six tokens
+    (2, 2, 5, 128, 509, 5, (1, 2, 3, 4, 8), 2, False, 8, {}),          # the 1-bit class, four outliers per token
+    (1, 3, 2, 64, 300, 5, (1, 2, 8), 3, False, 1, {"window_bf16": True}),
+    (2, 2, 1, 128, 511, 4, (2, 3, 4, 8), 4, True, 5, {}),              # the variable-length side store
+    (8, 32, 1, 128, 1299, 3, (2, 3, 4, 8), 1, False, 5, {}),           # 1536 value sides: staging for part of a tile, the rest handed over
+    (8, 32, 1, 64, 1100, 3, (1, 2, 3, 4, 8), 2, False, 2, {}),
+])
+def test_update_equals_separate_calls_when_many_tokens_move(B, Hkv, G, D, T, steps, bit_set, n_o, thresholds, window, store):
+    print(f"update moves: B={B} Hkv={Hkv} G={G} D={D} T={T} set={bit_set} n_o={n_o} thr={thresholds}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * T + D)
+    cap = T + steps
+    std = torch.exp(torch.rand((1, Hkv, 1, D), device="cuda", generator=gen) * 2.0)
+    k, v = ((torch.randn((B, Hkv, cap, D), device="cuda", generator=gen) * std).half() for _ in range(2))
+    thr = [_thresholds(k), _thresholds(v)] if thresholds else None
+    caches = [qaq.Cache(qaq.make_config(B, Hkv * G, Hkv, D, cap, [1.0] * Hkv, bit_set=bit_set, n_outlier_per_side=n_o, window=window,
+                                        outlier_thresholds=thr, sigma_s_max=1e-3, sigma_x_max=1e-2, **store)) for _ in range(2)]
+    fused, apart = caches
+    for c in caches:
+        c.quantize_append(k[:, :, :T].contiguous(), v[:, :, :T].contiguous())
+    k_copy, v_copy = (torch.cat([x[:, :, :T], torch.zeros_like(x[:, :, T:])], dim=2) for x in (k, v))
+    widths = set()
+    for j in range(steps):
+        n = T + j + 1
+        s = torch.rand((B, Hkv * G, n), device="cuda", generator=gen).pow_(6)
+        s = (s / s.sum(-1, keepdim=True)).contiguous()
+        for c in caches:      # finer and coarser in turn, by a factor that takes tokens over one class and more
+            c.set_sigmas(*((2e-5, 2e-3), (2e-3, 8e-2), (2e-4, 1e-2))[j % 3])
+        kn, vn = k[:, :, T + j].contiguous(), v[:, :, T + j].contiguous()
+        kb, vb = fused.decode_update(s, kn, vn, k_copy, v_copy, want_bits=True)
+        apart.quantize_append(kn[:, :, None].contiguous(), vn[:, :, None].contiguous())
+        kb2, vb2 = apart.select_bits(s)
+        apart.requantize(kb2, vb2, k, v)
+        assert torch.equal(kb, kb2) and torch.equal(vb, vb2), f"step {j}: widths"
+        for side in (0, 1):
+            a, b = fused.export_canonical(side), apart.export_canonical(side)
+            for name in a:
+                assert torch.equal(a[name].view(torch.uint8), b[name].view(torch.uint8)), f"step {j} side {side}: {name}"
+        widths |= set(torch.cat([kb.flatten(), vb.flatten()]).unique().tolist())
+    assert torch.equal(k_copy, k) and torch.equal(v_copy, v), "the appended rows belong into the copies"
+    assert len(widths) > 1
