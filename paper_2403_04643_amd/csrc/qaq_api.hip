@@ -19,7 +19,6 @@ struct qaq_cache {
   int max_shortfall;               // 0: every sequence has `len` positions; else sequence b has max(len - view.shortfall[b], 0)
   int n_o;
   int ring_next;                   // ring row that the next score row goes to
-  int update_parity;               // which of the two hand-over counters the next decode-step update uses
   int row_len[QAQ_MAX_WINDOW];     // tokens covered by each ring row (0 = empty)
   double sigma_s, sigma_x;
   std::vector<hipEvent_t> prof_ev;  // 4 events per profiled attention call
@@ -194,7 +193,6 @@ int qaq_create(const qaq_config* cfg, void* dev_arena, size_t arena_bytes, qaq_c
   c->len = 0;
   c->max_shortfall = 0;
   c->ring_next = 0;
-  c->update_parity = 0;
   std::memset(c->row_len, 0, sizeof(c->row_len));
   c->sigma_s = cfg->sigma_s_max;
   c->sigma_x = cfg->sigma_x_max;
@@ -423,11 +421,9 @@ int qaq_decode_update(qaq_cache* c, const float* dev_scores, const void* dev_k_n
   threshold_tables(c, a.len_after, r.tau_k, r.c_v);
   r.out_bits[0] = dev_k_bits; r.out_bits[1] = dev_v_bits;
   a.todo = c->view.todo;
-  a.todo_count = c->view.todo_count + c->update_parity;
-  a.todo_count_next = c->view.todo_count + (1 - c->update_parity);
+  a.todo_count = c->view.todo_count;
   hipError_t e = qaq_launch_update(a, (a.len_after + QAQ_TT - 1) / QAQ_TT, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_decode_update");
-  c->update_parity ^= 1;
   c->row_len[r.new_row] = a.len_after;
   c->ring_next = (r.new_row + 1) % c->dims.window;
   c->len = a.len_after;
@@ -604,9 +600,9 @@ int qaq_stats(qaq_cache* c, qaq_stats_t* out, void* stream) {
   std::memset(out, 0, sizeof(*out));
   out->tokens = c->len;
   long long buf[16] = {0};
-  uint32_t handed[2] = {0, 0};
+  uint32_t handed = 0;
   hipError_t e = qaq_launch_stats(c->view, c->len, (hipStream_t)stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(handed, c->view.todo_count, sizeof(handed), hipMemcpyDeviceToHost, (hipStream_t)stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(&handed, c->view.todo_count + 1, sizeof(handed), hipMemcpyDeviceToHost, (hipStream_t)stream);
   if (e == hipSuccess) e = hipMemcpyAsync(buf, c->view.statbuf, sizeof(buf), hipMemcpyDeviceToHost, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_stats");
@@ -625,7 +621,7 @@ int qaq_stats(qaq_cache* c, qaq_stats_t* out, void* stream) {
   long long seq_tokens = 0;
   for (int b = 0; b < c->dims.B; ++b) seq_tokens += seq_len(c, b, c->len);
   out->fp16_bytes = seq_tokens * c->dims.Hkv * D * 2 * 2;
-  out->update_handovers = (long long)handed[0] + handed[1];     // (the counter of the step to come is zero)
+  out->update_handovers = handed;
   out->refused_upgrades = buf[12];
   out->served_upgrades = buf[13];
   return QAQ_OK;

@@ -31,7 +31,7 @@ struct QaqView {
   long long* statbuf;
   unsigned int* refused;   // per tile side: [0] widenings refused for want of the unquantized copy, [1] widenings served
   uint32_t* todo;          // [B][Hkv][NT][2] list of tile sides a decode-step update hands to the general kernel
-  uint32_t* todo_count;    // [2] entries of the list; the two counters serve alternate steps
+  uint32_t* todo_count;    // [3] entries of the list (zero between steps), entries the last step made, workgroups that are done with theirs
   int B, Hq, Hkv, D, Tmax, NT, no2, window;
   int has1;                // the width set contains 1: kernels take their five-class variants
   int csr;                 // outliers by thresholds: oidx / oval are per-tile pools in position order, addressed
@@ -291,8 +291,7 @@ struct QaqBuildArgs {
   int max_moved;               // decode-step update: tokens of a tile side the kernel has staging memory for (set by the launcher)
   // decode-step update: tile sides the fast kernel leaves to the general one, (unit * NT + tile) * 2 + side
   uint32_t* todo;
-  uint32_t* todo_count;        // the counter this step appends through (zero when the step starts)
-  uint32_t* todo_count_next;   // the next step's counter (this step clears it)
+  uint32_t* todo_count;        // (QaqView::todo_count)
   QaqRuleArgs rule;            // modes 2 and 3
 };
 

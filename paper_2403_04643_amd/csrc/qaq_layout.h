@@ -184,7 +184,7 @@ struct QaqArena {
   size_t refused;     // u32  [B][Hkv][NT][2 sides][2] widenings refused / served, counted per tile side by the
                       // workgroup that owns it (plain read-modify-write: no atomics)
   size_t todo;        // u32  [B][Hkv][NT][2] tile sides a decode-step update leaves to the general build kernel
-  size_t todo_count;  // u32  [2]
+  size_t todo_count;  // u32  [3] its length, and what goes with it
   // variable-length side store (outliers by thresholds) only: oidx / oval are then per-tile pools
   // of 256 * no2 entries filled in position order
   size_t ostart[2];   // u16  [B][Hkv][Tmax]  by position: first entry of the token in its tile's pool
@@ -214,7 +214,7 @@ inline QaqArena qaq_carve(const QaqDims& d) {
   a.statbuf = off; off = qaq_up256(off + 32 * 8);
   a.refused = off; off = qaq_up256(off + bh * d.NT * 2 * 2 * 4);
   a.todo = off; off = qaq_up256(off + bh * d.NT * 2 * 4);
-  a.todo_count = off; off = qaq_up256(off + 2 * 4);
+  a.todo_count = off; off = qaq_up256(off + 3 * 4);
   a.ostart[0] = a.ostart[1] = a.ocnt[0] = a.ocnt[1] = a.othr = 0;
   if (d.csr) {
     for (int s = 0; s < 2; ++s) { a.ostart[s] = off; off = qaq_up256(off + bh * d.Tmax * 2); }

@@ -1248,8 +1248,10 @@ __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
   build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z);
 }
 
-// The same for a list of tile sides (a.todo: entries (unit * NT + tile) * 2 + side, a.todo_count of
-// them, both in device memory): a one-dimensional grid whose workgroups share out the entries.
+// The same for a list of tile sides (a.todo: entries (unit * NT + tile) * 2 + side, a.todo_count[0] of
+// them, both in device memory): a one-dimensional grid whose workgroups share out the entries.  The last
+// workgroup to finish leaves the list empty for the next step, whichever step that is (a captured run of
+// steps may be replayed from its start); a workgroup that starts after that had no entry anyway.
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
   const uint32_t n = *a.todo_count;
@@ -1258,6 +1260,10 @@ __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
     const uint32_t e = a.todo[i];
     build_tile<D, ONE, HAS1>(a, (int)((e >> 1) / (uint32_t)a.v.NT), (int)((e >> 1) % (uint32_t)a.v.NT), (int)(e & 1u));
     __syncthreads();        // the next tile side reuses the staging memory
+  }
+  // (every wavefront of a workgroup with entries has read the count: there was a barrier since)
+  if (blockIdx.x < n && threadIdx.x == 0 && atomicAdd(&a.todo_count[2], 1u) + 1u == min(n, gridDim.x)) {
+    a.todo_count[0] = 0u; a.todo_count[1] = n; a.todo_count[2] = 0u;
   }
 }
 
@@ -1512,7 +1518,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   const int len_before = qaq_seq_len(v, b, a.len_before), len_after = qaq_seq_len(v, b, a.len_after);   // of this sequence
   const int n_before = min(max(len_before - t0, 0), QAQ_TT);
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
-  if (bh == 0 && tile == 0 && side == 0 && tid == 0) *a.todo_count_next = 0u;
+  if (bh == 0 && tile == 0 && side == 0 && tid == 0) a.todo_count[1] = 0u;      // (k_build_listed, if it has entries, leaves their number)
   if (n_after == 0) return;
   const bool csr = !ONE && v.csr;
   const int no2 = ONE ? 2 : v.no2;
@@ -2593,7 +2599,7 @@ __global__ void k_init(QaqView v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) v.counts[i] = 0;
   if (blockIdx.x == 0 && threadIdx.x < 32) v.statbuf[threadIdx.x] = 0;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < (size_t)v.B * v.Hkv * v.NT * 4; i += (size_t)gridDim.x * blockDim.x) v.refused[i] = 0;
-  if (blockIdx.x == 0 && threadIdx.x < 2) v.todo_count[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 3) v.todo_count[threadIdx.x] = 0;
 }
 
 __global__ void k_clear_stats(QaqView v) {

@@ -59,3 +59,53 @@ def test_update_equals_separate_calls_when_many_tokens_move(B, Hkv, G, D, T, ste
         widths |= set(torch.cat([kb.flatten(), vb.flatten()]).unique().tolist())
     assert torch.equal(k_copy, k) and torch.equal(v_copy, v), "the appended rows belong into the copies"
     assert len(widths) > 1
+
+
+@pytest.mark.parametrize("B,Hkv,D,T,bit_set,n_o,thresholds", [
+    (8, 32, 128, 1290, (2, 3, 4, 8), 1, False),
+    (8, 32, 128, 1290, (2, 3, 4, 8), 4, True),
+    (8, 32, 64, 3000, (1, 2, 3, 4, 8), 2, False),
+])
+def test_captured_steps_can_be_replayed(B, Hkv, D, T, bit_set, n_o, thresholds):
+    """A prompt and an odd number of steps, the last of which hands tile sides to the general kernel, captured once and
+    replayed: nothing of one replay may be left in what the next one starts from."""
+    print(f"replayed steps: B={B} Hkv={Hkv} D={D} T={T} set={bit_set} n_o={n_o} thr={thresholds}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T + D + n_o)
+    steps, cap = 3, T + 3
+    std = torch.exp(torch.rand((1, Hkv, 1, D), device="cuda", generator=gen) * 2.0)
+    k, v = ((torch.randn((B, Hkv, cap, D), device="cuda", generator=gen) * std).half() for _ in range(2))
+    thr = [_thresholds(k), _thresholds(v)] if thresholds else None
+    eager, replayed = (qaq.Cache(qaq.make_config(B, Hkv, Hkv, D, cap, [1.0] * Hkv, bit_set=bit_set, n_outlier_per_side=n_o, window=3,
+                                                 outlier_thresholds=thr)) for _ in range(2))
+    kp, vp = k[:, :, :T].contiguous(), v[:, :, :T].contiguous()
+    new = [(k[:, :, T + j].contiguous(), v[:, :, T + j].contiguous()) for j in range(steps)]
+    scores = []
+    for j in range(steps):
+        s = torch.rand((B, Hkv, T + j + 1), device="cuda", generator=gen).pow_(6)
+        scores.append((s / s.sum(-1, keepdim=True)).contiguous())
+
+    def run(c):
+        c.reset()
+        c.quantize_append(kp, vp)
+        for j in range(steps):
+            c.set_sigmas(*((2e-4, 1e-2), (2e-5, 2e-3), (2e-3, 8e-2))[j])
+            c.decode_update(scores[j], *new[j], k, v)
+
+    run(eager)
+    handed = eager.stats().update_handovers
+    print(f"  handed over in the last step: {handed}", flush=True)
+    assert handed > 0
+    want = [eager.export_canonical(side) for side in (0, 1)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(replayed)
+    for rep in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert replayed.stats().update_handovers == handed, f"replay {rep}"
+        for side in (0, 1):
+            got = replayed.export_canonical(side)
+            for name in got:
+                assert torch.equal(got[name].view(torch.uint8), want[side][name].view(torch.uint8)), f"replay {rep} side {side}: {name}"
