@@ -273,7 +273,7 @@ size_t qaq_static_scratch_limit(void);
 
 /* Midpoint reconstruction of positions [t0, t1) with outliers restored exactly
  * (Section 4.1 / 4.2), rounded to fp16.  dev_k_out/dev_v_out: fp16 [B, Hkv, t1-t0, D],
- * either may be NULL. */
+ * either may be NULL; no more than an fp16's alignment is asked of them. */
 int qaq_dequantize(qaq_cache* c, int32_t t0, int32_t t1, void* dev_k_out, void* dev_v_out,
                    void* stream);
 

@@ -2429,9 +2429,10 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) tk.val[k] = s_val[k][slot];
     const uint4 x = tk.eight(lo, hi, ch0);
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 xv = {x.x, x.y, x.z, x.w};
-    __builtin_nontemporal_store(xv, (u32x4*)(out + (size_t)row * D + ch0));      // written once, read by somebody else
+    // (the output may start at any fp16: the type says so, and it still is one 16-byte store)
+    typedef uint32_t u32x4_of_halves __attribute__((ext_vector_type(4), aligned(2)));
+    const u32x4_of_halves xv = {x.x, x.y, x.z, x.w};
+    __builtin_nontemporal_store(xv, (u32x4_of_halves*)(out + (size_t)row * D + ch0));      // written once, read by somebody else
   };
   const int n32 = c.n32(), first8 = n32 + c.n4, first1 = c.first1();
   if (side == 0) {
