@@ -114,8 +114,16 @@ __device__ __forceinline__ uint32_t digits_packed(int x) { return ((uint32_t)x +
 // Digits of a weight (0 <= w <= 2^28: the top byte needs no offset), and the exchange by which each lane of a quad
 // -- four consecutive slots -- ends with one digit of all four, a word of a digit row: lane i with digit i.  (As four
 // byte stores per lane, digits in base 128 for want of a cheap signed split, two layers at 16 x 64 heads on 8, 8192 tokens took
-// 186.3 instead of 184.0 us, four calls at 8 x 32 heads x 4096 120.6 instead of 120.1.)
+// 186.3 instead of 184.0 us, four calls at 8 x 32 heads x 4096 120.6 instead of 120.1.  The forms of k_attn_tile for several
+// outliers per end store bytes: at their register budget the selectors and the row's address are spilled words, 7 -> 13 of
+// them in the widest form, and one call at 8 x 32 heads x 4096 with two outliers per end took 49.7 us, 44.4 so; 16 x 16 x 8192
+// 104.7 and 91.4.)
 __device__ __forceinline__ uint32_t weight_digits(uint32_t w) { return (w + 0x00808080u) ^ 0x00808080u; }
+template <int N>
+__device__ __forceinline__ void put_digits(int8_t (&rows)[4][N], int at, uint32_t digits) {
+  rows[0][at] = (int8_t)digits; rows[1][at] = (int8_t)(digits >> 8);
+  rows[2][at] = (int8_t)(digits >> 16); rows[3][at] = (int8_t)(digits >> 24);
+}
 struct DigitExchange {
   uint32_t sel1, sel2;
   __device__ __forceinline__ explicit DigitExchange(int lane)
@@ -683,6 +691,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 
 
   const DigitExchange exchange(lane);
+  constexpr bool BYTES = NO2 > 2;       // digits stored as bytes (see DigitExchange)
   // carried across the tiles
   float m_run = -INFINITY;          // reference of everything below
   float l_run = 0.0f, bias_run = 0.0f;    // per thread: softmax sum and constant terms of its slots
@@ -872,24 +881,22 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       const bool fx = live && smax > 0.0f;
       const int vg = (s & 15) >> 2;
       const uint32_t W2 = (fx && s < n32V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift2(vg) + (s < cV.n3 ? 1 : 0))) : 0u;
-      *(uint32_t*)&S.wl2[s & 3][s & ~3] = exchange(weight_digits(W2));
+      if constexpr (BYTES) put_digits(S.wl2, s, weight_digits(W2));
+      else *(uint32_t*)&S.wl2[s & 3][s & ~3] = exchange(weight_digits(W2));
       // (the value phase reads these two tables in blocks of 64 slots, as far as the class reaches:
       // slots of later blocks need no digits, not even zeros)
       if (s < ((cV.n3 + 63) & ~63)) {
         const uint32_t W1 = (fx && s < cV.n3) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift1(vg))) : 0u;
-        *(uint32_t*)&S.wl1[s & 3][s & ~3] = exchange(weight_digits(W1));
+        if constexpr (BYTES) put_digits(S.wl1, s, weight_digits(W1));
+        else *(uint32_t*)&S.wl1[s & 3][s & ~3] = exchange(weight_digits(W1));
       }
       if (((s - n32V) & (QAQ_TT - 1)) < ((cV.n4 + 63) & ~63)) {
         const int i4 = (s - n32V) & (QAQ_TT - 1);
-        const uint32_t W4 = weight_digits((fx && s >= n32V && s < first8V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp)) : 0u);
-        S.wl4[0][i4] = (int8_t)W4; S.wl4[1][i4] = (int8_t)(W4 >> 8);
-        S.wl4[2][i4] = (int8_t)(W4 >> 16); S.wl4[3][i4] = (int8_t)(W4 >> 24);
+        put_digits(S.wl4, i4, weight_digits((fx && s >= n32V && s < first8V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp)) : 0u));
       }
       if (H1 && cV.n1 > 0) {
         const int i1 = (s - first1V) & (QAQ_TT - 1);
-        const uint32_t W1 = weight_digits((fx && s >= first1V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift1((i1 & 15) >> 2))) : 0u);
-        S.wl1b[0][i1] = (int8_t)W1; S.wl1b[1][i1] = (int8_t)(W1 >> 8);
-        S.wl1b[2][i1] = (int8_t)(W1 >> 16); S.wl1b[3][i1] = (int8_t)(W1 >> 24);
+        put_digits(S.wl1b, i1, weight_digits((fx && s >= first1V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift1((i1 & 15) >> 2))) : 0u));
       }
     }
     lds_barrier();
@@ -1463,9 +1470,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
           *(uint32_t*)&S.wl1[j][s & 3][s & ~3] = exchange(weight_digits(W1));
         }
         if (i4 < ((cV.n4 + 63) & ~63)) {
-          const uint32_t W4 = weight_digits((fx && s >= n32V && s < first8V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp)) : 0u);
-          S.wl4[j][0][i4] = (int8_t)W4; S.wl4[j][1][i4] = (int8_t)(W4 >> 8);
-          S.wl4[j][2][i4] = (int8_t)(W4 >> 16); S.wl4[j][3][i4] = (int8_t)(W4 >> 24);
+          put_digits(S.wl4[j], i4, weight_digits((fx && s >= n32V && s < first8V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp)) : 0u));
         }
       }
     }
