@@ -507,7 +507,8 @@ struct ValRegs {
 // tiles), they are given linear indices eight apart: one die, and next to one another in time, so that all
 // but the first are served by its L2.  lin: linear workgroup index of `total`; -> which of the `share`, and the
 // index of what they share.  (k_attn_gqa at 16 x 64 heads on 8, 8192 tokens fetched 197 MB with the two of a KV
-// head on different dies.)
+// head on different dies.  With a multiple of eight parts they are on one die as they are, and the divisions here would only
+// cost: see the launcher.)
 __device__ __forceinline__ void die_neighbours(int lin, int total, int share, int& member, int& item) {
   const int whole = total / (8 * share) * (8 * share);
   if (lin < whole) {
@@ -565,7 +566,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   // of the (sequence, query head) pairs.
   int bq = blockIdx.y;
   if (P && a.G > 1 && (gridDim.y & 7) == 0) bq = (int)(blockIdx.y & 7) * (int)(gridDim.y >> 3) + (int)(blockIdx.y >> 3);
-  if (!P && a.G > 1) {
+  if (!P && a.neighbours) {
     int g, item;
     die_neighbours((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y), a.G, g, item);
     const int bh = item / a.nparts;
@@ -1130,9 +1131,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   // two layers at 16 x 64 heads on 8, 8192 tokens; in k_attn_tile the same costs registers it has not: 120.0 -> 128.0 us)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nn = lane & 15, g = lane >> 4;
-  int hg, item;
-  die_neighbours((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y), a.G / kHG, hg, item);
-  const int bh = item / a.nparts, chunk = item - bh * a.nparts;
+  const int NG = a.G / kHG;
+  int chunk = blockIdx.x, bh = (int)blockIdx.y / NG, hg = (int)blockIdx.y - bh * NG;
+  if (a.neighbours) {
+    int item;
+    die_neighbours((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y), NG, hg, item);
+    bh = item / a.nparts; chunk = item - bh * a.nparts;
+  }
   const int b = bh / v.Hkv, h = bh % v.Hkv;
   const int bq0 = b * v.Hq + h * a.G + kHG * hg;           // first of the four query heads
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
@@ -1797,6 +1802,11 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   a.lds_logits = a.nparts * a.ntc <= kFusedMaxTiles || !a.scores;
   const bool fused = !gqa && ntile > 0 && a.nparts <= 4 && (!a.v.ragged || ntile_shortest >= a.nparts) &&
                      (a.lds_logits || a.nparts == 4);
+  // Which workgroups share a die (die_neighbours), where several read the same codes: nothing to do if the parts are a
+  // multiple of eight (4 x 16 heads on 8, 8192 tokens, 16 parts: 21.7 us with the re-ordering, 21.4 without), and not where
+  // a part is one tile and the grid small, the codes too few for it to matter (1 x 28 on 4 x 7000: 16.6 and 16.1; the other
+  // way, 5 parts of 16 tiles at 8 x 24 on 4: 32.0 and 34.1; 20 parts of 20 at 4 x 32 on 4 in k_attn_gqa: 21.1 and 21.4).
+  a.neighbours = !fused && a.G > (gqa ? kHG : 1) && (a.nparts & 7) != 0 && (a.ntc > 1 || (gqa && a.nparts * units >= 2 * n_cu));
   if (kernels) *kernels = ntile > 0 ? (fused ? 1 : 2) : 0;
   if (static_scratch && !fused) {
     if ((size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float) > kStaticScratchBytes) {

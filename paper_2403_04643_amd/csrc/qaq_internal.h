@@ -325,6 +325,7 @@ struct QaqAttnArgs {
   int lds_logits;         // fused form: the head's raw logits fit the workgroup's LDS (set by the launcher); else they wait in the score buffer
   float* partial;         // two-kernel form: [B*Hq][part_stride][D+4] partial results (max, sum, X) of the parts
   int part_stride;        // partials reserved per (sequence, query head)
+  int neighbours;         // two-kernel form: workgroups that read the same codes get indices eight apart (set by the launcher)
 };
 
 struct QaqPrefillArgs {
