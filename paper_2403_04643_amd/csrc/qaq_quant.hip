@@ -1244,7 +1244,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 // head, which ran 30 % slower.
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
-  qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, tau_k) + 128 * sizeof(float)>();
+  qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
   build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z);
 }
 
@@ -2239,7 +2239,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 // Width selection (Section 4.1 bit rules written as comparisons, Section 4.2 window).
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_select(QaqSelectArgs a) {
-  qaq_request_arguments<0, offsetof(QaqSelectArgs, tau_k) + 128 * sizeof(float)>();
+  qaq_request_arguments<0, offsetof(QaqSelectArgs, tau_k)>();
   __shared__ float rk[QAQ_TT], rv[QAQ_TT];
   const QaqView& v = a.v;
   const int tid = threadIdx.x;
