@@ -1,4 +1,5 @@
 // Host side of libqaq: argument checking, cache bookkeeping, thresholds, launches.
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -123,6 +124,21 @@ bool first_append_too_short(const qaq_cache* c, int n_new) {
 }
 
 }  // namespace
+
+// (asked once: hipGetDeviceProperties is not a call to make in every step.  Two threads that come first at the same
+// time find and store the same number.)
+int qaq_compute_units() {
+  static std::atomic<int> n_cu{0};
+  int n = n_cu.load(std::memory_order_relaxed);
+  if (n == 0) {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
+    if (n <= 0) n = 256;
+    n_cu.store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
 
 // ---- streaming yardsticks ------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

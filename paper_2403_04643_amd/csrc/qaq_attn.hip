@@ -1778,13 +1778,7 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // parts per (sequence, query head): as many as keep the whole grid resident at once (four
   // workgroups per compute unit), so that no second, partly filled round of workgroups trails
   // the first; every part gets floor or ceil of ntile/nparts tiles
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n_cu = prop.multiProcessorCount;
-    if (n_cu <= 0) n_cu = 256;
-  }
+  const int n_cu = qaq_compute_units();
   // grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form
   const bool gqa = a.G >= kHG && a.G % kHG == 0 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0);
   const int units = gqa ? BQ / kHG : BQ;

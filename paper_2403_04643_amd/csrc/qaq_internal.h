@@ -263,6 +263,19 @@ __device__ __forceinline__ void qaq_request_arguments() {
 #endif
 }
 
+// The kernel's arguments, as memory the compiler knows nothing about yet (still constant and the same for all lanes):
+// what a loop reads through the result is read again in every round, not held across it.
+template <typename ARGS>
+__device__ __forceinline__ const ARGS* qaq_arguments_anew() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const __attribute__((address_space(4))) ARGS* p = (const __attribute__((address_space(4))) ARGS*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return (const ARGS*)p;
+#else
+  return nullptr;
+#endif
+}
+
 // What the width rules need (Section 4.1 written as comparisons, Section 4.2 window).  (The tables come last: what every
 // workgroup reads is then on few lines, see qaq_request_arguments.)
 struct QaqRuleArgs {
@@ -354,6 +367,7 @@ struct QaqDequantArgs {
   __half* out[2];
 };
 
+int qaq_compute_units();      // of the GPU the process started on
 // launchers (each returns the hipError_t of the launch)
 hipError_t qaq_launch_init(const QaqView& v, hipStream_t s);
 hipError_t qaq_launch_build(const QaqBuildArgs& a, int ntiles, hipStream_t s);

@@ -341,9 +341,8 @@ struct TokenEncoder {
 // the cached tokens whose codes are read again (L.need == 1); whole words / units that hold
 // none of them are not touched.
 template <int D, int MAXO, bool HAS1>
-__device__ void unpack_tile(int side, const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L) {
+__device__ void unpack_tile(int side, const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
-  const int tid = threadIdx.x;
   const int n32 = c.n32();
   if (side == 0) {
     const QaqKRegions r = qaq_k_regions(c, D);
@@ -401,10 +400,10 @@ __device__ void unpack_tile(int side, const uint8_t* base, const QaqCounts& c, B
 // channels), and every code is read with the per-element accessor of the layout -- a tile in
 // a decode step moves a handful of tokens, far fewer than its units hold.
 template <int D, int MAXO, bool HAS1>
-__device__ void unpack_moved_v(const uint8_t* base, const QaqCounts& c, int n_moved, BuildLds<D, MAXO>& L) {
+__device__ void unpack_moved_v(const uint8_t* base, const QaqCounts& c, int n_moved, BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW;
   const QaqVRegions r = qaq_v_regions(c, D);
-  for (int e = threadIdx.x; e < n_moved * (D / 4); e += kThreads) {
+  for (int e = tid; e < n_moved * (D / 4); e += kThreads) {
     const int m = e / (D / 4), c4 = e % (D / 4);
     const int pos = L.freeslot[m], slot = L.kept[m];
     uint32_t w = 0;
@@ -419,9 +418,8 @@ __device__ void unpack_moved_v(const uint8_t* base, const QaqCounts& c, int n_mo
 // c0 = the class counts the tile had before (all zero for a tile that did not exist): a
 // word whose tokens all keep slot and width, in a region that has not moved, is left alone.
 template <int D, int MAXO, bool HAS1>
-__device__ void pack_tile(int side, uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L) {
+__device__ void pack_tile(int side, uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
-  const int tid = threadIdx.x;
   const int n32 = c.n32();
   const bool had = c0.total() > 0;
   const bool same32 = had && c0.n32() == n32;
@@ -614,9 +612,8 @@ __device__ void pack_tile(int side, uint8_t* base, const QaqCounts& c, const Qaq
 // or whose region has moved, starts from zero -- then the masks hold all its slots).  Fields
 // of slots past the end of a region are left as they are: no reader looks at them.
 template <int D, int MAXO, bool HAS1>
-__device__ void pack_masked_v(uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L) {
+__device__ void pack_masked_v(uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW;
-  const int tid = threadIdx.x;
   const int n32 = c.n32(), n32o = c0.n32();
   const QaqVRegions r = qaq_v_regions(c, D), r0 = qaq_v_regions(c0, D);
   const bool same1 = r.r1 == r0.r1;
@@ -732,9 +729,9 @@ __device__ void pack_masked_v(uint8_t* base, const QaqCounts& c, const QaqCounts
 // tile side's own counters (kind 0 = refused for want of the unquantized copy, 1 = served).
 // A tile side is only ever written by the workgroup that owns it, so no atomics are needed;
 // the accounting kernel sums the counters.
-__device__ __forceinline__ void note_widenings(int* per_wave, bool wider) {
+__device__ __forceinline__ void note_widenings(int* per_wave, bool wider, int tid) {
   const unsigned long long bal = __ballot(wider);
-  if ((threadIdx.x & 63) == 0) per_wave[threadIdx.x >> 6] = __popcll(bal);
+  if ((tid & 63) == 0) per_wave[tid >> 6] = __popcll(bal);
 }
 __device__ __forceinline__ void add_widenings(const QaqView& v, size_t tile_side, const int* per_wave, bool served) {
   const int n = per_wave[0] + per_wave[1] + per_wave[2] + per_wave[3];
@@ -742,9 +739,9 @@ __device__ __forceinline__ void add_widenings(const QaqView& v, size_t tile_side
 }
 
 // HAS1: the width set contains 1 (five classes); without it the fifth class costs nothing.
-// One tile side (unit bh, tile, side) of a build.
+// One tile side (unit bh, tile, side) of a build; tid: the thread (an argument: see k_build_listed).
 template <int D, bool ONE, bool HAS1>
-__device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, const int tile, const int side) {
+__device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, const int tile, const int side, const int tid) {
   constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2;
   __shared__ BuildLds<D, MAXO> L;
   constexpr int NC = HAS1 ? QAQ_NCLASS : 4;
@@ -753,7 +750,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 
   const QaqView& v = a.v;
   const bool csr = !ONE && v.csr;     // (the one-per-end build never has the variable-length side store)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   const int b = bh / v.Hkv, h = bh % v.Hkv;
   const int t0 = tile * QAQ_TT;
   const int len_before = qaq_seq_len(v, b, a.len_before), len_after = qaq_seq_len(v, b, a.len_after);   // of this sequence
@@ -825,7 +822,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
       if (req < oldb) changed = true;
       else if (req > oldb) { wider = true; if (a.orig[side]) changed = true; }
     }
-    note_widenings(L.wave_wide, wider);
+    note_widenings(L.wave_wide, wider, tid);
     const bool any = __syncthreads_or(changed ? 1 : 0) != 0;
     if (tid == 0) add_widenings(v, (qaq_bh(v, b, h) * v.NT + tile) * 2 + side, L.wave_wide, a.orig[side] != nullptr);
     if (!any) return;
@@ -879,7 +876,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
       if (req_rule < oldb) changed = true;
       else if (req_rule > oldb) { wider = true; if (a.orig[side]) changed = true; }
     }
-    note_widenings(L.wave_wide, wider);
+    note_widenings(L.wave_wide, wider, tid);
     const bool has_new = len_before >= t0 && len_before < t0 + QAQ_TT;
     const bool any = __syncthreads_or(changed ? 1 : 0) != 0;
     if (tid == 0) add_widenings(v, (qaq_bh(v, b, h) * v.NT + tile) * 2 + side, L.wave_wide, a.orig[side] != nullptr);
@@ -1176,8 +1173,8 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     }
     __syncthreads();
     if (had) {
-      if (side == 0) unpack_tile<D, MAXO, HAS1>(side, base, c_old, L);
-      else unpack_moved_v<D, MAXO, HAS1>(base, c_old, n_moved, L);
+      if (side == 0) unpack_tile<D, MAXO, HAS1>(side, base, c_old, L, tid);
+      else unpack_moved_v<D, MAXO, HAS1>(base, c_old, n_moved, L, tid);
       __syncthreads();
     }
   }
@@ -1235,8 +1232,8 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
           make_float2(fmaxf(fmaxf(L.wave_bound[0], L.wave_bound[1]), fmaxf(L.wave_bound[2], L.wave_bound[3])),
                       fminf(fminf(L.wave_bound2[0], L.wave_bound2[1]), fminf(L.wave_bound2[2], L.wave_bound2[3])));
   }
-  if (side == 1 && n_before > 0) pack_masked_v<D, MAXO, HAS1>(base, cn, c_old, L);
-  else pack_tile<D, MAXO, HAS1>(side, base, cn, c_old, L);
+  if (side == 1 && n_before > 0) pack_masked_v<D, MAXO, HAS1>(base, cn, c_old, L, tid);
+  else pack_tile<D, MAXO, HAS1>(side, base, cn, c_old, L, tid);
 }
 
 // Grid (units, tiles, 2 sides) -- heads are the fastest grid dimension: with tiles fastest and a
@@ -1245,24 +1242,35 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
-  build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z);
+  build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z, (int)threadIdx.x);
 }
 
 // The same for a list of tile sides (a.todo: entries (unit * NT + tile) * 2 + side, a.todo_count[0] of
 // them, both in device memory): a one-dimensional grid whose workgroups share out the entries.  The last
 // workgroup to finish leaves the list empty for the next step, whichever step that is (a captured run of
 // steps may be replayed from its start); a workgroup that starts after that had no entry anyway.
+//
+// Bound by the workgroups in flight, i.e. by registers: left to itself the compiler keeps everything that
+// follows from the thread or from the kernel's arguments in registers across the loop (142-247 of them, and
+// 127-185 scalars spilled).  So each round takes the thread's index and the arguments as if they were new: 81-199
+// registers, no scratch.  With the grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands every side over
+// takes 430 us where it took 633 (128 channels; 64 channels 432 -> 280, with the 1-bit width 482 -> 303).
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
   const uint32_t n = *a.todo_count;
+  if (blockIdx.x >= n) return;
+  qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
 #pragma unroll 1
   for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
     const uint32_t e = a.todo[i];
-    build_tile<D, ONE, HAS1>(a, (int)((e >> 1) / (uint32_t)a.v.NT), (int)((e >> 1) % (uint32_t)a.v.NT), (int)(e & 1u));
+    const QaqBuildArgs* args = qaq_arguments_anew<QaqBuildArgs>();
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    build_tile<D, ONE, HAS1>(*args, (int)((e >> 1) / (uint32_t)args->v.NT), (int)((e >> 1) % (uint32_t)args->v.NT), (int)(e & 1u), tid);
     __syncthreads();        // the next tile side reuses the staging memory
   }
   // (every wavefront of a workgroup with entries has read the count: there was a barrier since)
-  if (blockIdx.x < n && threadIdx.x == 0 && atomicAdd(&a.todo_count[2], 1u) + 1u == min(n, gridDim.x)) {
+  if (threadIdx.x == 0 && atomicAdd(&a.todo_count[2], 1u) + 1u == min(n, gridDim.x)) {
     a.todo_count[0] = 0u; a.todo_count[1] = n; a.todo_count[2] = 0u;
   }
 }
@@ -1290,9 +1298,9 @@ __global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
 // 42.1 -> 33.4 us, 16 x 8 heads x 8192 with 8 query heads each 39.3 -> 32.0, 8 heads x 512 tokens 11.9 -> 11.4; with
 // outliers by thresholds (the general kernel until then) 3 x 16 heads x 2500 34 -> 15.9.
 // ---------------------------------------------------------------------------------
-constexpr int kMinMoved = 60;       // (sixteen tile sides' LDS fit a compute unit)
 constexpr int kMaxCopy = 8192;
 constexpr int kUpdThreads = 128;
+constexpr int kUpdResident = 16;    // tile sides a compute unit takes: two wavefronts of at most 64 registers each
 
 // Beside this block a tile side has LDS for the codes of `a.max_moved` tokens (dynamic, sized at launch): that many
 // staged rows, then a list word and a [min, max] for each.  Before any code is gathered the space holds, by position,
@@ -2643,19 +2651,26 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_
   QaqBuildArgs a = a_in;
   const long long sides = (long long)a.v.B * a.v.Hkv * ntiles * 2;
   // LDS for moved tokens: what is left of a compute unit's 160 KB when all value sides are resident at once (the key
-  // sides, few of which have work, take the places that become free), from kMinMoved -- sixteen tile sides -- up to a
-  // whole tile, which leaves nothing for the general kernel to do (a batch of six with unequal prompts, 72 heads in all:
-  // 20.4 + 13.8 us with staging for 60 tokens and the second launch, 17.4 us without)
-  const long long resident = (sides / 2 + 255) / 256;
-  const int room = (int)(160 * 1024 / (resident < 16 ? resident : 16)) / 1280 * 1280 - (int)sizeof(UpdLds<D>);      // (LDS is handed out 1280 bytes at a time)
+  // sides, few of which have work, take the places that become free), from a sixteenth -- 64 tokens of 128 channels, 119
+  // of 64 -- up to a whole tile, which leaves nothing for the general kernel to do (a batch of six with unequal prompts,
+  // 72 heads in all: 20.4 + 13.8 us with staging for 60 tokens and the second launch, 17.4 us without)
+  constexpr int lds = 160 * 1024, grain = 1280;       // (LDS is handed out 1280 bytes at a time)
+  constexpr int least = (lds / kUpdResident / grain * grain - (int)sizeof(UpdLds<D>)) / UpdLds<D>::PER_TOKEN;
+  static_assert(least * UpdLds<D>::PER_TOKEN >= 2 * QAQ_TT * 4, "the space also holds two words per position before any code is staged");
+  const int cus = qaq_compute_units();
+  const long long resident = (sides / 2 + cus - 1) / cus;
+  const int room = lds / (int)(resident < kUpdResident ? resident : kUpdResident) / grain * grain - (int)sizeof(UpdLds<D>);
   a.max_moved = room / UpdLds<D>::PER_TOKEN;
-  if (a.max_moved < kMinMoved) a.max_moved = kMinMoved;
   if (a.max_moved > QAQ_TT) a.max_moved = QAQ_TT;
   hipLaunchKernelGGL((k_update<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(kUpdThreads), (size_t)a.max_moved * UpdLds<D>::PER_TOKEN, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.max_moved == QAQ_TT) return e;
-  // the tile sides it handed over (their number is only known on the device)
-  hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < 512 ? sides : 512)), dim3(kThreads), 0, s, a);
+  // The tile sides it handed over (their number is only known on the device): as many workgroups as a compute unit holds
+  // at the kernel's registers and LDS.  An empty list costs the same with 512 and with 1536 of them (4.6 us, the launch);
+  // handed-over sides take 2/3 (128 channels) and half (64) of the time they take with two per compute unit.
+  constexpr int per_cu = D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4);
+  const long long most = (long long)per_cu * cus;
+  hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < most ? sides : most)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

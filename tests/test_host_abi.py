@@ -193,6 +193,10 @@ def test_decode_path_kernels_do_not_spill():
 @pytest.mark.parametrize("key,max_vgpr,max_scratch", [
     ("k_attn_tileILi128ELi8E", 128, 48),      # several outliers per end, or outliers by thresholds: a few words spilled, and no more
     ("k_attn_tileILi64ELi8E", 128, 0),
+    ("k_build_listedILi128ELb1E", 128, 0),    # four, two, five and four workgroups per compute unit, as the launch counts on
+    ("k_build_listedILi128ELb0E", 256, 0),
+    ("k_build_listedILi64ELb1E", 96, 0),
+    ("k_build_listedILi64ELb0E", 128, 0),
 ])
 def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
     """The same for kernels off the benchmark's shape that sit at the edge of their budget: one register more in each
