@@ -22,6 +22,11 @@ struct qaq_cache {
   int ring_next;                   // ring row that the next score row goes to
   int row_len[QAQ_MAX_WINDOW];     // tokens covered by each ring row (0 = empty)
   double sigma_s, sigma_x;
+  // What a decode-step update is about to find (a matter of speed only): value threshold that the widths of the cached
+  // tokens follow (0: of none), the one of the last selection, and the cached tokens whose widths follow no rule
+  float ruled_c_v, selected_c_v;
+  int unruled;
+  long long update_whole;          // tile sides of the last update if the general kernel did all of it, else 0
   std::vector<hipEvent_t> prof_ev;  // 4 events per profiled attention call
   int prof_n;
   std::vector<int> prof_kernels;    // dispatches each profiled call made
@@ -93,6 +98,25 @@ void thresholds(const qaq_cache* c, int T, float* tau_k, float* c_v) {
     tau_k[h] = (float)(2.0 * std::sqrt(3.0) * std::sqrt(var_k));
   }
   *c_v = (float)(2.0 * std::sqrt(3.0) * c->sigma_x / std::sqrt((double)(T < 1 ? 1 : T)));
+}
+
+float value_threshold(const qaq_cache* c, int T) { return (float)(c->sigma_x / std::sqrt((double)(T < 1 ? 1 : T))); }   // (in proportion to it)
+
+// Share of a tile side's tokens that a decode-step update at the value threshold c_v can be expected to move, by what has
+// changed since the widths were last chosen: tokens came at other widths than the rules', the threshold fell (quality), or --
+// with the 1-bit width, whose borders are where most ranges are -- it rose.  (Other rises move few tokens, and key thresholds
+// half of the sides: not counted.)  The factors are fits to where the decode-step kernel with what it hands over takes as long
+// as the general kernel alone; 8 x 32 heads x 4000 tokens, us, the one | the other, 64 channels (119 tokens staged per side)
+// and 128 (64 staged): 256 tokens of the prompt at the widest width 86 | 108, 222 | 176; 1000: 169 | 116, 352 | 204 (1-bit
+// width).  Threshold x 0.83: 78 | 109, 252 | 184; x 0.75: 141 | 113, 256 | 191 (x 0.71).  1-bit width, threshold x 1.1: 91 | 134,
+// 246 | 196; x 1.2: 185 | 140, 285 | 207.
+float expected_moves(const qaq_cache* c, float c_v) {
+  float share = c->len > 0 ? 4.0f * (float)c->unruled / (float)c->len : 0.0f;
+  if (c->ruled_c_v > 0.0f && c_v > 0.0f) {
+    const float octaves = std::log2(c_v / c->ruled_c_v);
+    share = std::fmax(share, octaves < 0.0f ? -1.18f * octaves : c->view.has1 ? 2.0f * octaves : 0.0f);
+  }
+  return share;
 }
 
 int seq_len(const qaq_cache* c, int b, int len_longest) {
@@ -212,6 +236,9 @@ int qaq_create(const qaq_config* cfg, void* dev_arena, size_t arena_bytes, qaq_c
   std::memset(c->row_len, 0, sizeof(c->row_len));
   c->sigma_s = cfg->sigma_s_max;
   c->sigma_x = cfg->sigma_x_max;
+  c->ruled_c_v = c->selected_c_v = 0.0f;
+  c->unruled = 0;
+  c->update_whole = 0;
   c->prof_n = 0;
   uint8_t* base = (uint8_t*)dev_arena;
   QaqView& v = c->view;
@@ -270,6 +297,8 @@ int qaq_reset(qaq_cache* c) {
   std::memset(c->view.shortfall, 0, sizeof(c->view.shortfall));
   c->ring_next = 0;
   std::memset(c->row_len, 0, sizeof(c->row_len));
+  c->ruled_c_v = c->selected_c_v = 0.0f;
+  c->unruled = 0;
   return QAQ_OK;
 }
 
@@ -350,6 +379,7 @@ int qaq_quantize_append(qaq_cache* c, const void* dev_k, const void* dev_v, int3
   hipError_t e = qaq_launch_build(a, tile_last - a.tile0 + 1, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_quantize_append");
   c->len = a.len_after;
+  c->unruled += n_new;
   return QAQ_OK;
 }
 
@@ -371,6 +401,7 @@ int qaq_select_bits(qaq_cache* c, const float* dev_scores, uint8_t* dev_k_bits, 
   a.out_bits[0] = dev_k_bits; a.out_bits[1] = dev_v_bits;
   hipError_t e = qaq_launch_select(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_select_bits");
+  c->selected_c_v = value_threshold(c, c->len);
   if (dev_scores) {
     c->row_len[a.new_row] = c->len;
     c->ring_next = (a.new_row + 1) % c->dims.window;
@@ -398,6 +429,10 @@ int qaq_requantize(qaq_cache* c, const uint8_t* dev_k_bits, const uint8_t* dev_v
   a.orig_tokens = orig_tokens;
   hipError_t e = qaq_launch_build(a, (c->len + QAQ_TT - 1) / QAQ_TT, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_requantize");
+  if (dev_v_bits) {                // (taken for the last selection's)
+    c->ruled_c_v = c->selected_c_v;
+    c->unruled = 0;
+  }
   return QAQ_OK;
 }
 
@@ -438,8 +473,14 @@ int qaq_decode_update(qaq_cache* c, const float* dev_scores, const void* dev_k_n
   r.out_bits[0] = dev_k_bits; r.out_bits[1] = dev_v_bits;
   a.todo = c->view.todo;
   a.todo_count = c->view.todo_count;
-  hipError_t e = qaq_launch_update(a, (a.len_after + QAQ_TT - 1) / QAQ_TT, (hipStream_t)stream);
+  const float c_v = value_threshold(c, a.len_after);
+  const int ntiles = (a.len_after + QAQ_TT - 1) / QAQ_TT;
+  bool whole = false;
+  hipError_t e = qaq_launch_update(a, ntiles, expected_moves(c, c_v), &whole, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_decode_update");
+  c->update_whole = whole ? 2ll * c->dims.B * c->dims.Hkv * ntiles : 0;
+  c->ruled_c_v = c_v;
+  c->unruled = 0;
   c->row_len[r.new_row] = a.len_after;
   c->ring_next = (r.new_row + 1) % c->dims.window;
   c->len = a.len_after;
@@ -502,6 +543,7 @@ int qaq_quantize_append_selected(qaq_cache* c, const void* dev_k, const void* de
   const int tile_last = (a.len_after - 1) / QAQ_TT;
   hipError_t e = qaq_launch_build(a, tile_last - a.tile0 + 1, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "qaq_quantize_append_selected");
+  if (c->len == 0) c->ruled_c_v = value_threshold(c, a.len_after);
   c->len = a.len_after;
   return QAQ_OK;
 }
@@ -637,7 +679,7 @@ int qaq_stats(qaq_cache* c, qaq_stats_t* out, void* stream) {
   long long seq_tokens = 0;
   for (int b = 0; b < c->dims.B; ++b) seq_tokens += seq_len(c, b, c->len);
   out->fp16_bytes = seq_tokens * c->dims.Hkv * D * 2 * 2;
-  out->update_handovers = handed;
+  out->update_handovers = c->update_whole ? c->update_whole : (long long)handed;
   out->refused_upgrades = buf[12];
   out->served_upgrades = buf[13];
   return QAQ_OK;

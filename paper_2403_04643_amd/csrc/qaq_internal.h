@@ -371,9 +371,10 @@ int qaq_compute_units();      // of the GPU the process started on
 // launchers (each returns the hipError_t of the launch)
 hipError_t qaq_launch_init(const QaqView& v, hipStream_t s);
 hipError_t qaq_launch_build(const QaqBuildArgs& a, int ntiles, hipStream_t s);
-// decode-step update (a.mode == 2): the fast kernel where the configuration has one, followed by the
-// general kernel on the tile sides it handed over; else the general kernel on every tile side
-hipError_t qaq_launch_update(const QaqBuildArgs& a, int ntiles, hipStream_t s);
+// decode-step update (a.mode == 2): the decode-step kernel, followed by the general kernel on the tile sides it may have
+// handed over; the general kernel on every tile side (*whole) where more tokens are expected to move than a side can stage
+// (moving: which share of them)
+hipError_t qaq_launch_update(const QaqBuildArgs& a, int ntiles, float moving, bool* whole, hipStream_t s);
 hipError_t qaq_launch_select(const QaqSelectArgs& a, hipStream_t s);
 // ev: NULL, or four events that take the start and the end of the dispatch of the tile kernel
 // ([0], [1]) and of the merge kernel ([2], [3], two-kernel form only); *kernels = dispatches

@@ -2647,7 +2647,7 @@ hipError_t qaq_launch_build(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
 }
 
 template <int D, bool ONE, bool HAS1>
-static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_t s) {
+static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float moving, bool* whole, hipStream_t s) {
   QaqBuildArgs a = a_in;
   const long long sides = (long long)a.v.B * a.v.Hkv * ntiles * 2;
   // LDS for moved tokens: what is left of a compute unit's 160 KB when all value sides are resident at once (the key
@@ -2662,6 +2662,8 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_
   const int room = lds / (int)(resident < kUpdResident ? resident : kUpdResident) / grain * grain - (int)sizeof(UpdLds<D>);
   a.max_moved = room / UpdLds<D>::PER_TOKEN;
   if (a.max_moved > QAQ_TT) a.max_moved = QAQ_TT;
+  *whole = a.max_moved < QAQ_TT && moving * QAQ_TT >= (float)a.max_moved;
+  if (*whole) return qaq_launch_build(a_in, ntiles, s);
   hipLaunchKernelGGL((k_update<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(kUpdThreads), (size_t)a.max_moved * UpdLds<D>::PER_TOKEN, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.max_moved == QAQ_TT) return e;
@@ -2674,15 +2676,15 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, hipStream_
   return hipGetLastError();
 }
 
-hipError_t qaq_launch_update(const QaqBuildArgs& a, int ntiles, hipStream_t s) {
+hipError_t qaq_launch_update(const QaqBuildArgs& a, int ntiles, float moving, bool* whole, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const bool one = a.v.no2 == 2 && !a.v.csr;
   if (a.v.D == 128) {
-    if (a.v.has1) return one ? launch_update<128, true, true>(a, ntiles, s) : launch_update<128, false, true>(a, ntiles, s);
-    return one ? launch_update<128, true, false>(a, ntiles, s) : launch_update<128, false, false>(a, ntiles, s);
+    if (a.v.has1) return one ? launch_update<128, true, true>(a, ntiles, moving, whole, s) : launch_update<128, false, true>(a, ntiles, moving, whole, s);
+    return one ? launch_update<128, true, false>(a, ntiles, moving, whole, s) : launch_update<128, false, false>(a, ntiles, moving, whole, s);
   }
-  if (a.v.has1) return one ? launch_update<64, true, true>(a, ntiles, s) : launch_update<64, false, true>(a, ntiles, s);
-  return one ? launch_update<64, true, false>(a, ntiles, s) : launch_update<64, false, false>(a, ntiles, s);
+  if (a.v.has1) return one ? launch_update<64, true, true>(a, ntiles, moving, whole, s) : launch_update<64, false, true>(a, ntiles, moving, whole, s);
+  return one ? launch_update<64, true, false>(a, ntiles, moving, whole, s) : launch_update<64, false, false>(a, ntiles, moving, whole, s);
 }
 
 hipError_t qaq_launch_select(const QaqSelectArgs& a, hipStream_t s) {
