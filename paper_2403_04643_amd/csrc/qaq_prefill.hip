@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_prefill_softmax(QaqPrefillArgs a) 
   __shared__ float red[4];
   const QaqView& v = a.v;
   const int tid = threadIdx.x;
-  const int bq = blockIdx.x, b = bq / v.Hq, hq = bq % v.Hq, i = blockIdx.y;      // heads fastest (see k_build)
+  const int bq = blockIdx.x, b = bq / v.Hq, i = blockIdx.y;      // heads fastest (see k_build)
   const int len = row_length(qaq_seq_len(v, b, a.T), a.n_rows, i);
   float* row = a.scores + ((size_t)i * v.B * v.Hq + bq) * a.T;
   float mine[KEEP];

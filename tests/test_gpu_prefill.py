@@ -206,14 +206,14 @@ def test_window_kept_in_fp16(store):
 
 
 @pytest.mark.parametrize("D,Hkv,G,T,n,gain", [
-    (128, 2, 1, 1025, 8, 1.0),       # one token in the last share of a row, one in its last group of 64
-    (64, 1, 20, 1088, 3, 12.0),      # more query heads than one merge pass takes; peaked rows, groups of very different maxima
-    (64, 3, 2, 64, 8, 30.0),         # one group of 64, rows that end inside it
-    (128, 1, 16, 4161, 1, 6.0),
+    (128, 2, 1, 1025, 8, 1.0),       # a thread's fifth logit exists in one thread
+    (64, 1, 20, 1088, 3, 12.0),      # many query heads per KV head; peaked rows
+    (64, 3, 2, 64, 8, 30.0),         # less than a workgroup, rows that end inside it
+    (128, 1, 16, 4161, 1, 6.0),      # past the shortest form's registers
 ])
 def test_score_rows_over_many_shares(D, Hkv, G, T, n, gain):
-    """The rows and the window they leave, where a row is merged from several groups of 64 tokens and written by
-    several workgroups; the window through the widths of the next selection."""
+    """The rows and the window they leave, over row lengths, query heads per KV head and peaked rows; the window through
+    the widths of the next selection."""
     sh = W.shape(3, batch=2, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
     _log(f"prefill rows: {sh} rows={n} gain={gain}")
     K, V = W.make_kv(3, sh)
@@ -225,3 +225,40 @@ def test_score_rows_over_many_shares(D, Hkv, G, T, n, gain):
     bk_o, bv_o, _ = oc.prefill(q_last, K, V, score_rows=[rows[i][..., : T - n + i + 1] for i in range(n)])
     np.testing.assert_array_equal(bk_g.cpu().numpy(), bk_o)
     np.testing.assert_array_equal(bv_g.cpu().numpy(), bv_o)
+
+
+@pytest.mark.parametrize("D,Hkv,G,T,n,shortfall", [
+    (64, 2, 1, 4096, 2, None),              # the last row of 16 logits per thread, and the first of 32 ...
+    (64, 1, 3, 4097, 2, None),
+    (64, 1, 2, 8192, 2, None),
+    (128, 2, 1, 8193, 3, None),             # ... of 64
+    (64, 1, 1, 16384, 2, None),
+    (64, 1, 1, 16385, 2, None),             # one logit, and a row of them, that no register holds
+    (64, 1, 4, 16641, 2, None),
+    (64, 1, 1, 16900, 2, (0, 600)),         # the shorter sequence's row ends inside the registers
+    (64, 1, 2, 8300, 2, (0, 8200)),
+])
+def test_rows_at_the_borders_of_the_register_forms(D, Hkv, G, T, n, shortfall):
+    """The softmax keeps a row's logits in registers, 16, 32 or 64 per thread, and reads again what they do not hold: rows
+    and window around each border, sequences of one length and of two."""
+    B = len(shortfall) if shortfall else 1
+    sh = W.shape(3, batch=B, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
+    _log(f"prefill rows: {sh} rows={n} shortfall={shortfall}")
+    K, V = W.make_kv(3, sh)
+    q_last = np.ascontiguousarray(W.make_queries(3, sh, n=n, seed_offset=4).transpose(1, 2, 0, 3) * F16(4.0))
+    _, gc = make_pair(sh, 0.01, max_tokens=T, window=4, sigma_s_max=1e-3, sigma_x_max=1e-2)
+    if shortfall:
+        gc.set_shortfall(shortfall)
+    rows = gc.prefill_window(dev(q_last), dev(K)).cpu().numpy()
+    bk_g, bv_g = (x.cpu().numpy() for x in gc.quantize_append_selected(dev(K), dev(V), want_bits=True))
+    lengths = [T - s for s in shortfall] if shortfall else [T]
+    for b, length in enumerate(lengths):
+        one = W.shape(3, batch=1, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=length)
+        Kb, Vb, qb = (np.ascontiguousarray(x[b:b + 1]) for x in (K[:, :, :length], V[:, :, :length], q_last))
+        got = rows[:, b:b + 1]
+        assert (got[..., length:] == 0).all()
+        _log(f"  sequence {b}: worst score error {_check_rows(got[..., :length], qb, Kb, G):.2e}")
+        oc, _ = make_pair(one, 0.01, window=4, sigma_s_max=1e-3, sigma_x_max=1e-2)
+        bk_o, bv_o, _ = oc.prefill(qb, Kb, Vb, score_rows=[got[i][..., : length - n + i + 1] for i in range(n)])
+        np.testing.assert_array_equal(bk_g[b:b + 1, :, :length], bk_o)
+        np.testing.assert_array_equal(bv_g[b:b + 1, :, :length], bv_o)

@@ -197,6 +197,11 @@ def test_decode_path_kernels_do_not_spill():
     ("k_build_listedILi128ELb0E", 256, 0),
     ("k_build_listedILi64ELb1E", 96, 0),
     ("k_build_listedILi64ELb0E", 128, 0),
+    ("k_attn_gqaILi128ELi2E", 168, 8),        # three workgroups per compute unit; two words, none of them inside the tile loop
+    ("k_attn_gqaILi128ELi0E", 168, 0),
+    ("k_attn_gqaILi64E", 168, 0),
+    ("k_dequantILi128ELi2E", 128, 0),
+    ("k_prefill_softmaxILi64E", 256, 0),      # 64 logits per thread
 ])
 def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
     """The same for kernels off the benchmark's shape that sit at the edge of their budget: one register more in each
