@@ -2336,7 +2336,7 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
 // one channel of the 16 tokens, turned into rows by 4x4 byte transposes; the D/8 lanes of a unit read its
 // 4 D bytes between them.
 // 8 sequences x 32 heads x 4096 tokens x 128 channels, all 8-bit (805 MB): 1232 us code by code through
-// an LDS staging tile, 190-205 us (4 TB/s, a copy of that size: 5.1) so.
+// an LDS staging tile, 209 us (3.8 TB/s; a 4 GiB copy: 4.85) so; all 3-bit 1325 and 130.
 
 // eight codes (one per byte, channels in order) -> eight fp16 values, with the outliers among these channels
 // put in: ch0 = first channel, NO2 outlier entries per token (idx: one byte each, 0xff = unused)
