@@ -149,7 +149,7 @@ __device__ __forceinline__ void transpose4(const uint32_t (&w)[4], uint32_t (&t)
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);      // (within quads every lane has a source)
 }
 // Reductions over the four consecutive lanes (one quad) that share a token; every lane
 // of the quad ends up with the result.
@@ -194,6 +194,49 @@ __device__ __forceinline__ uint32_t order_keys_pair(uint32_t two_halves) {
   const us2 t = (mag ^ sg) - sg;                                                      // +-magnitude, two's complement
   return __builtin_bit_cast(uint32_t, (us2)(t + (us2)0x8000u));
 }
+// ... and as signed 16-bit numbers (magnitude, or minus magnitude), for the packed maximum and minimum
+__device__ __forceinline__ ss2 signed_keys_pair(uint32_t two_halves) {
+  const ss2 b = __builtin_bit_cast(ss2, two_halves);
+  const ss2 sg = b >> (ss2)15;
+  return ((b & (ss2)0x7fff) ^ sg) - sg;
+}
+__device__ __forceinline__ ss2 pk_max(ss2 a, ss2 b) { return __builtin_elementwise_max(a, b); }
+__device__ __forceinline__ ss2 pk_min(ss2 a, ss2 b) { return __builtin_elementwise_min(a, b); }
+__device__ __forceinline__ uint32_t signed_key_bits(int key) { return (uint32_t)(key < 0 ? 0x8000 - key : key); }   // fp16 bits (of +0 for a zero)
+// maximum, minimum in one instruction: of a NaN and a number the number, as fmaxf, but without its test for signalling NaNs
+__device__ __forceinline__ float vmaxf(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float vminf(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// An element of a pair of fp16 less a float, rounded once (the fp16 number is exact in fp32): one instruction
+__device__ __forceinline__ float half_minus(uint32_t pair, bool upper, float x) {
+  float r;
+  if (upper) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(x));
+  else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pair), "v"(x));
+  return r;
+}
+// floor of eight numbers, clamped to [0, 255], as the bytes of two words.  v_cvt_pk_u8_f32 rounds as the mode register
+// says and saturates: rounding toward zero for the eight of them takes the place of eight floors (below zero both give 0).
+__device__ __forceinline__ void floor_bytes(const float (&x)[8], uint32_t& w0, uint32_t& w1) {
+  asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
+      "v_cvt_pk_u8_f32 %0, %2, 0, 0\n\t"
+      "v_cvt_pk_u8_f32 %1, %6, 0, 0\n\t"
+      "v_cvt_pk_u8_f32 %0, %3, 1, %0\n\t"
+      "v_cvt_pk_u8_f32 %1, %7, 1, %1\n\t"
+      "v_cvt_pk_u8_f32 %0, %4, 2, %0\n\t"
+      "v_cvt_pk_u8_f32 %1, %8, 2, %1\n\t"
+      "v_cvt_pk_u8_f32 %0, %5, 3, %0\n\t"
+      "v_cvt_pk_u8_f32 %1, %9, 3, %1\n\t"
+      "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
+      : "=&v"(w0), "=&v"(w1)
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]));
+}
 // value of a key made from order_keys_pair (upper 16 bits; the low bits carry a channel number)
 __device__ __forceinline__ float key16_value(uint32_t key) {
   const uint32_t k = key >> 16;
@@ -207,6 +250,12 @@ __device__ __forceinline__ float key16_value(uint32_t key) {
 // (Section 4.2): the n_o largest, then the n_o smallest of the rest, ties to the lower
 // channel; [min,max] over what remains; then the midpoint quantizer of Section 4.1:
 // code = clamp(floor((x-min)*2^B/range)).
+//
+// Bound by vector instructions: a bulk build spends four fifths of its on the search and the codes.  So the search
+// works on pairs of 16-bit keys and looks for the channels afterwards (282 instructions for a quad's lane with 32
+// elements; 395 with the channel in the low bits of 32-bit keys), and a code takes three instructions, not six.
+// Vector instructions per wavefront of a bulk build 3240 -> 2600: 2 x 32 heads x 12001 tokens 167 -> 140 us,
+// 8 x 32 heads x 4096 in three chunks 229 -> 197.
 // ---------------------------------------------------------------------------------
 template <int D, bool ONE>   // ONE: exactly one outlier per end (the common case) has its own, shorter search
 struct TokenEncoder {
@@ -239,38 +288,84 @@ struct TokenEncoder {
                                              uint8_t* oidx_row, uint16_t* oval_row, uint32_t* stage_row,
                                              float thr_lo = INFINITY, float thr_hi = -INFINITY) {
     float mn, mx;
+    bool finite = false;      // all values known to be
     if (fresh) {
-      uint32_t key_mx, key_mn;
       if constexpr (ONE) {
-        // largest and second largest key, smallest and second smallest key, in one sweep
-        uint32_t a1 = 0u, a2 = 0u, b1 = 0xffffffffu, b2 = 0xffffffffu;
+        // The two largest and the two smallest values, as packed 16-bit keys: four words at a time are sorted (ten
+        // instructions for eight elements), their ends merged into the running ones; then over the halves of the
+        // words and the lanes of the quad (there the largest and minus the smallest in one word).
+        ss2 k[4 * NCH], A1, A2, B1, B2;
 #pragma unroll
-        for (int i = 0; i < NCH; ++i)
-#pragma unroll
-          for (int e2 = 0; e2 < 4; ++e2) {
-            const uint32_t w = e2 == 0 ? raw[i].x : e2 == 1 ? raw[i].y : e2 == 2 ? raw[i].z : raw[i].w;
-            const uint32_t kk = order_keys_pair(w);     // keys of elements 2*e2 (low half) and 2*e2+1 (high half)
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-              const uint32_t k = hf ? (kk & 0xffff0000u) : (kk << 16);
-              const int ch = channel(c, i, 2 * e2 + hf);
-              const uint32_t kx = k | (uint32_t)(127 - ch), kn = k | (uint32_t)ch;
-              a2 = umed3(a1, a2, kx); a1 = a1 > kx ? a1 : kx;
-              b2 = umed3(b1, b2, kn); b1 = b1 < kn ? b1 : kn;
-            }
+        for (int i = 0; i < NCH; ++i) {
+          const ss2 x = k[4 * i] = signed_keys_pair(raw[i].x), y = k[4 * i + 1] = signed_keys_pair(raw[i].y);
+          const ss2 z = k[4 * i + 2] = signed_keys_pair(raw[i].z), w = k[4 * i + 3] = signed_keys_pair(raw[i].w);
+          const ss2 h0 = pk_max(x, y), l0 = pk_min(x, y), h1 = pk_max(z, w), l1 = pk_min(z, w);
+          const ss2 s3 = pk_max(h0, h1), s0 = pk_min(l0, l1), m0 = pk_min(h0, h1), m1 = pk_max(l0, l1);
+          const ss2 s2 = pk_max(m0, m1), s1 = pk_min(m0, m1);
+          if (i == 0) { A1 = s3; A2 = s2; B1 = s0; B2 = s1; }
+          else {
+            A2 = pk_max(pk_min(A1, s3), pk_max(A2, s2)); A1 = pk_max(A1, s3);
+            B2 = pk_min(pk_max(B1, s0), pk_min(B2, s1)); B1 = pk_min(B1, s0);
           }
-        const uint32_t A1 = quad_umax(a1), A2 = quad_umax(a1 == A1 ? a2 : a1);
-        const uint32_t B1 = quad_umin(b1), B2 = quad_umin(b1 == B1 ? b2 : b1);
-        const int ch_top = 127 - (int)(A1 & 127u);
-        // the smallest of the rest is the overall smallest unless that is the top element
-        // itself (all values equal): then it is the runner-up
-        const uint32_t Bb = (int)(B1 & 127u) == ch_top ? B2 : B1;
-        const int ch_bot = (int)(Bb & 127u);
-        if (((ch_top >> 3) & 3) == c) { oidx_row[0] = (uint8_t)ch_top; oval_row[0] = outlier_bits(raw, c, ch_top, key16_value(A1)); }
-        if (((ch_bot >> 3) & 3) == c) { oidx_row[1] = (uint8_t)ch_bot; oval_row[1] = outlier_bits(raw, c, ch_bot, key16_value(Bb)); }
-        // what remains: its largest value is the runner-up of the maximum search, its smallest
-        // the runner-up of the minimum search (equal values make the choice of element moot)
-        mx = key16_value(A2); mn = key16_value(B2);
+        }
+        A2 = pk_max(pk_min(A1, A1.yx), pk_max(A2, A2.yx)); A1 = pk_max(A1, A1.yx);
+        B2 = pk_min(pk_max(B1, B1.yx), pk_min(B2, B2.yx)); B1 = pk_min(B1, B1.yx);
+        B1 = -B1; B2 = -B2;
+        uint32_t e1 = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, B1), __builtin_bit_cast(uint32_t, A1), 0x05040100u);
+        uint32_t e2 = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, B2), __builtin_bit_cast(uint32_t, A2), 0x05040100u);
+#pragma unroll
+        for (int step = 0; step < 2; ++step) {
+          const ss2 y1 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e1) : dpp_u<0xB1>(e1)), y2 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e2) : dpp_u<0xB1>(e2));
+          const ss2 x1 = __builtin_bit_cast(ss2, e1), x2 = __builtin_bit_cast(ss2, e2);
+          e2 = __builtin_bit_cast(uint32_t, pk_max(pk_min(x1, y1), pk_max(x2, y2)));
+          e1 = __builtin_bit_cast(uint32_t, pk_max(x1, y1));
+        }
+        const int top1 = (int)(int16_t)(e1 & 0xffffu), bot1 = -((int)e1 >> 16);
+        finite = top1 < 0x7c00 && bot1 > -0x7c00;
+        // Lowest channel that holds an end: per word one bit of each half, then the first over the quad
+        const uint32_t top_pair = __builtin_amdgcn_perm(0u, (uint32_t)top1, 0x01000100u), bot_pair = __builtin_amdgcn_perm(0u, (uint32_t)bot1, 0x01000100u);
+        uint32_t not_top = 0u, not_bot = 0u;
+        uint32_t ones = 0x10001u;
+        asm("" : "+s"(ones));              // (known to be ones, the minimum becomes two compares and two selects)
+        const us2 one = __builtin_bit_cast(us2, ones);
+#pragma unroll
+        for (int j = 0; j < 4 * NCH; ++j) {
+          const uint32_t kw = __builtin_bit_cast(uint32_t, k[j]);
+          not_top = (not_top << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, kw ^ top_pair), one));
+          not_bot = (not_bot << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, kw ^ bot_pair), one));
+        }
+        auto first_channel = [&](uint32_t misses) -> uint32_t {      // bit 4 NCH - 1 of a half: its first element
+          constexpr uint32_t ALL = (1u << (4 * NCH)) - 1u;
+          const uint32_t hits = misses ^ (ALL * 0x10001u);
+          const uint32_t lo = hits << 16, e_lo = 2u * (uint32_t)__builtin_clz(lo | 1u) , e_hi = 2u * (uint32_t)__builtin_clz(hits | 1u) + 1u;
+          const uint32_t e = (e_lo < e_hi ? e_lo : e_hi) - 2u * (16u - 4 * NCH);
+          const uint32_t ch = ((e & ~7u) << 2) + (uint32_t)(8 * c) + (e & 7u);
+          return quad_umin(e < (uint32_t)EPL ? ch : 0xffu);
+        };
+        const uint32_t ch_top = first_channel(not_top);
+        // the smallest of the rest is the overall smallest unless that is the top element itself: all values are
+        // equal then, and it is the second of them
+        const uint32_t ch_bot = top1 == bot1 ? 1u : first_channel(not_bot);
+        uint32_t v_top = signed_key_bits(top1), v_bot = signed_key_bits(bot1);
+        if (top1 == 0 || bot1 == 0) {          // the key does not keep the sign of a zero: the bits as they are stored
+          uint32_t t = 0u, bt = 0u;
+#pragma unroll
+          for (int i = 0; i < NCH; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              if (channel(c, i, e) == (int)ch_top) t = half_bits(raw, i, e);
+              if (channel(c, i, e) == (int)ch_bot) bt = half_bits(raw, i, e);
+            }
+          v_top = quad_umax(t); v_bot = quad_umax(bt);
+        }
+        if (c == 0) {          // the side store's row, by channel
+          const bool first = ch_top < ch_bot;
+          *(uint16_t*)oidx_row = (uint16_t)(first ? ch_top | (ch_bot << 8) : ch_bot | (ch_top << 8));
+          *(uint32_t*)oval_row = first ? v_top | (v_bot << 16) : v_bot | (v_top << 16);
+        }
+        // what remains: its largest value is the runner-up of the largest, its smallest of the smallest
+        // (equal values make the choice of element moot)
+        mx = h2f((uint16_t)signed_key_bits((int)(int16_t)(e2 & 0xffffu))); mn = h2f((uint16_t)signed_key_bits(-((int)e2 >> 16)));
       } else {
         uint32_t kx[EPL], kn[EPL];
 #pragma unroll
@@ -308,7 +403,7 @@ struct TokenEncoder {
         uint32_t m1 = 0u, m0 = 0xffffffffu;
 #pragma unroll
         for (int j = 0; j < EPL; ++j) { m1 = m1 > kx[j] ? m1 : kx[j]; m0 = m0 < kn[j] ? m0 : kn[j]; }
-        key_mx = quad_umax(m1); key_mn = quad_umin(m0);
+        const uint32_t key_mx = quad_umax(m1), key_mn = quad_umin(m0);
         mx = key_value(key_mx); mn = key_value(key_mn);
       }
       if (c == 0) *mm_pos = (uint32_t)f2h(mn) | ((uint32_t)f2h(mx) << 16);
@@ -321,18 +416,26 @@ struct TokenEncoder {
     const float levels = (float)(1 << bits);
     const float inv = range > 0.0f ? levels / range : 0.0f;   // an empty range gives code 0 everywhere
     const float top_code = levels - 1.0f;
+    // (eight bits, the widest width, at which new tokens are encoded: the byte conversion's own clamp is the quantizer's,
+    // but for a NaN, whose code is the top one)
+    const bool clamps = __ballot(bits < 8 || !finite) != 0ull;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      uint32_t w[2] = {0u, 0u};
+      float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float diff = h2f((uint16_t)half_bits(raw, i, e)) - mn;
-        const float prod = diff * inv;
-        // the byte conversion saturates: a negative product (an outlier below min) gives 0
-        w[e >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(floorf(prod), top_code), e & 3, w[e >> 2]);
+        const uint32_t w = e < 2 ? raw[i].x : e < 4 ? raw[i].y : e < 6 ? raw[i].z : raw[i].w;
+        const float diff = half_minus(w, e & 1, mn);
+        x[e] = diff * inv;
       }
-      stage_row[2 * (4 * i + c)] = w[0];
-      stage_row[2 * (4 * i + c) + 1] = w[1];
+      if (clamps) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = vminf(x[e], top_code);
+      }
+      uint32_t w0, w1;
+      floor_bytes(x, w0, w1);
+      stage_row[2 * (4 * i + c)] = w0;
+      stage_row[2 * (4 * i + c) + 1] = w1;
     }
   }
 };
@@ -935,22 +1038,25 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     const int NP = (n_enc + TPP - 1) / TPP;
     const int c = tid & 3, gt = tid >> 2;
     auto position = [&](int pass) { const int e = pass * TPP + gt; return listed ? (int)L.freeslot[min(e, QAQ_TT - 1)] : e; };
+    // rows by position of this tile (the new tokens' first row is that of position n_before)
+    const uint8_t* const new_rows = (const uint8_t*)a.newx[side] + ((long long)bh * a.n_new + (t0 - len_before)) * (2 * D);
+    const uint8_t* const old_rows = (const uint8_t*)a.orig[side] + ((long long)bh * a.orig_tokens + t0) * (2 * D);
+    uint8_t* const put_rows = a.orig_put[side] ? (uint8_t*)a.orig_put[side] + ((long long)bh * a.orig_tokens + t0) * (2 * D) : nullptr;
     auto fetch = [&](int pass, uint4 (&raw)[Enc::NCH]) -> int {   // 0 = nothing to do, 1 = fresh, 2 = widen
       if (pass >= NP || pass * TPP + gt >= n_enc) return 0;
       const int p = position(pass);
       const bool fresh = p >= n_before;
-      const __half* src = fresh ? a.newx[side] + ((size_t)bh * a.n_new + (t0 + p - len_before)) * D
-                                : a.orig[side] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D;
+      const uint32_t at = (uint32_t)p * (2 * D) + 16u * (uint32_t)c;
+      const uint8_t* src = (fresh ? new_rows : old_rows) + at;
 #pragma unroll
       for (int i = 0; i < Enc::NCH; ++i) {      // read once: streaming loads
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        const u32x4 t = __builtin_nontemporal_load((const u32x4*)src + (4 * i + c));
+        const u32x4 t = __builtin_nontemporal_load((const u32x4*)(src + 64 * i));
         raw[i] = make_uint4(t.x, t.y, t.z, t.w);
       }
-      if (fresh && a.orig_put[side]) {     // keep the unquantized token for later widening
-        uint4* dst = (uint4*)(a.orig_put[side] + ((size_t)bh * a.orig_tokens + (t0 + p)) * D);
+      if (fresh && put_rows) {             // keep the unquantized token for later widening
 #pragma unroll
-        for (int i = 0; i < Enc::NCH; ++i) dst[4 * i + c] = raw[i];
+        for (int i = 0; i < Enc::NCH; ++i) *(uint4*)(put_rows + at + 64 * i) = raw[i];
       }
       return fresh ? 1 : 2;
     };
@@ -982,8 +1088,8 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     L.bits_new[tid] = (uint8_t)w;
   }
 
-  // side store of fresh tokens: order by channel
-  if (tid >= n_before && tid < n_after && v.no2 > 1) {
+  // side store of fresh tokens: order by channel (the one-per-end encoder leaves it so)
+  if (!ONE && tid >= n_before && tid < n_after && v.no2 > 1) {
     for (int i = 1; i < v.no2; ++i) {
       const uint8_t ki = L.oidx[tid][i];
       const uint16_t vi = L.oval[tid][i];
@@ -1255,8 +1361,10 @@ __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
 // 127-185 scalars spilled).  So each round takes the thread's index and the arguments as if they were new: 81-199
 // registers, no scratch.  With the grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands every side over
 // takes 430 us where it took 633 (128 channels; 64 channels 432 -> 280, with the 1-bit width 482 -> 303).
+template <int D, bool ONE>
+constexpr int listed_per_cu() { return D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4); }      // workgroups a compute unit takes
 template <int D, bool ONE, bool HAS1>
-__global__ __launch_bounds__(kThreads) void k_build_listed(QaqBuildArgs a) {
+__global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_listed(QaqBuildArgs a) {
   const uint32_t n = *a.todo_count;
   if (blockIdx.x >= n) return;
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
@@ -1354,12 +1462,6 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set
 struct Two { float x[2]; };
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-// maximum in one instruction: of a NaN and a number the number, as fmaxf, but without its test for signalling NaNs
-__device__ __forceinline__ float vmaxf(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
 template <int W, typename RAW>
 __device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri0, int p0,
                                              const Two (&g)[4], float (&s)[2], float (&m)[2]) {
@@ -2670,8 +2772,7 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float movi
   // The tile sides it handed over (their number is only known on the device): as many workgroups as a compute unit holds
   // at the kernel's registers and LDS.  An empty list costs the same with 512 and with 1536 of them (4.6 us, the launch);
   // handed-over sides take 2/3 (128 channels) and half (64) of the time they take with two per compute unit.
-  constexpr int per_cu = D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4);
-  const long long most = (long long)per_cu * cus;
+  const long long most = (long long)listed_per_cu<D, ONE>() * cus;
   hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < most ? sides : most)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
