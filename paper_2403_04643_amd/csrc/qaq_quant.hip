@@ -115,7 +115,7 @@ struct BuildLds {
   uint8_t shf[QAQ_TT];                     // by position: low bits a staged code still has to drop (narrowing);
                                            // bit 7: the token keeps its slot and its width (what is stored for it stays valid)
   uint8_t kept[QAQ_TT];                    // by slot: a token stays here
-  uint16_t pos_of_slot[QAQ_TT];
+  alignas(16) uint16_t pos_of_slot[QAQ_TT];   // (a tile that held nothing: byte offset of the staged row)
   uint16_t slot_of_pos[QAQ_TT];
   uint16_t freeslot[QAQ_TT];               // per class, in slot order: the slots nobody keeps
   uint16_t pos_old[QAQ_TT];                // position of the token that held a slot before
@@ -135,6 +135,11 @@ struct BuildLds {
 };
 constexpr int kKeptFlag = 0x80;
 
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set bits of `mask` below this lane
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // rows of four bytes <-> columns of four bytes: t[k] byte j = w[j] byte k
 __device__ __forceinline__ void transpose4(const uint32_t (&w)[4], uint32_t (&t)[4]) {
   const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);   // w0.b0 w1.b0 w0.b1 w1.b1
@@ -214,6 +219,11 @@ __device__ __forceinline__ float vminf(float a, float b) {
   asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+// Larger and smaller of two pairs of fp16, one instruction (of a NaN and a number the number); `pk_hmaximum`: the NaN.
+__device__ __forceinline__ uint32_t pk_hmax(uint32_t a, uint32_t b) { uint32_t r; asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ uint32_t pk_hmin(uint32_t a, uint32_t b) { uint32_t r; asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b)); return r; }
+__device__ __forceinline__ uint32_t pk_hmaximum(uint32_t a, uint32_t b, uint32_t c) { uint32_t r; asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
+__device__ __forceinline__ uint32_t halves_swapped(uint32_t x) { return __builtin_amdgcn_alignbit(x, x, 16u); }
 // An element of a pair of fp16 less a float, rounded once (the fp16 number is exact in fp32): one instruction
 __device__ __forceinline__ float half_minus(uint32_t pair, bool upper, float x) {
   float r;
@@ -251,11 +261,10 @@ __device__ __forceinline__ float key16_value(uint32_t key) {
 // channel; [min,max] over what remains; then the midpoint quantizer of Section 4.1:
 // code = clamp(floor((x-min)*2^B/range)).
 //
-// Bound by vector instructions: a bulk build spends four fifths of its on the search and the codes.  So the search
-// works on pairs of 16-bit keys and looks for the channels afterwards (282 instructions for a quad's lane with 32
-// elements; 395 with the channel in the low bits of 32-bit keys), and a code takes three instructions, not six.
-// Vector instructions per wavefront of a bulk build 3240 -> 2600: 2 x 32 heads x 12001 tokens 167 -> 140 us,
-// 8 x 32 heads x 4096 in three chunks 229 -> 197.
+// Bound by vector instructions: a bulk build spends four fifths of its on the search and the codes.  So the search works
+// on pairs of fp16 values and looks for the channels afterwards (228 instructions for a quad's lane with 32 elements; 282 on
+// integer keys, 395 with the channel in the low bits of 32-bit keys), and a code takes three instructions, not six.  Figures:
+// see fresh_tile.
 // ---------------------------------------------------------------------------------
 template <int D, bool ONE>   // ONE: exactly one outlier per end (the common case) has its own, shorter search
 struct TokenEncoder {
@@ -281,6 +290,128 @@ struct TokenEncoder {
     return (uint16_t)hv;
   }
 
+  // The pair of values `pair` (both halves the same) among the words x: the lowest channel that holds it, over the quad;
+  // 255 or more if none does
+  template <typename WORD>
+  __device__ static __forceinline__ uint32_t first_channel(WORD word, int c, uint32_t pair, us2 one) {
+    constexpr uint32_t ALL = (1u << (4 * NCH)) - 1u;
+    uint32_t misses = 0u;                   // per word one bit of each half, the first word's in bit 4 NCH - 1 of it
+#pragma unroll
+    for (int j = 0; j < 4 * NCH; ++j)
+      asm("v_lshl_or_b32 %0, %1, 1, %2" : "=v"(misses) : "v"(misses), "v"(__builtin_elementwise_min(__builtin_bit_cast(us2, word(j) ^ pair), one)));
+    const uint32_t hits = misses ^ (ALL * 0x10001u);
+    const uint32_t e_lo = 2u * (uint32_t)__builtin_clz((hits << 16) | 1u), e_hi = 2u * (uint32_t)__builtin_clz(hits | 1u) + 1u;
+    const uint32_t e = (e_lo < e_hi ? e_lo : e_hi) - 2u * (16u - 4 * NCH);
+    const uint32_t ch = ((e & ~7u) << 2) + (uint32_t)(8 * c) + (e & 7u);
+    return quad_umin(e < (uint32_t)EPL ? ch : 0xffu);
+  }
+  __device__ static __forceinline__ uint32_t word_of(const uint4 (&raw)[NCH], int j) {
+    return (j & 3) == 0 ? raw[j >> 2].x : (j & 3) == 1 ? raw[j >> 2].y : (j & 3) == 2 ? raw[j >> 2].z : raw[j >> 2].w;
+  }
+
+  // One outlier per end: the largest and the smallest value of a token and the runners-up.  The two largest and the two
+  // smallest come from four words at a time, sorted as pairs (ten instructions for eight elements) and merged into the
+  // running ones; then over the halves of the words and the lanes of the quad (there the largest and minus the smallest
+  // in one word); the channels are looked up afterwards.  On the fp16 values themselves where the ends are ordinary
+  // numbers; where an end is a zero (two bit patterns) or not finite, or a value is not a number, on integer keys.
+  __device__ static __forceinline__ void ends_of_token(const uint4 (&raw)[NCH], int c, uint8_t* oidx_row, uint16_t* oval_row, float& mn, float& mx, bool& finite) {
+    uint32_t ones = 0x10001u;
+    asm("" : "+s"(ones));              // (known to be ones, the minimum with them becomes two compares and two selects)
+    const us2 one = __builtin_bit_cast(us2, ones);
+    uint32_t A1 = 0u, A2 = 0u, B1 = 0u, B2 = 0u, any = 0u;      // (any: the largest, or a NaN if there is one)
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const uint32_t x = raw[i].x, y = raw[i].y, z = raw[i].z, w = raw[i].w;
+      const uint32_t h0 = pk_hmax(x, y), l0 = pk_hmin(x, y), h1 = pk_hmax(z, w), l1 = pk_hmin(z, w);
+      const uint32_t s3 = pk_hmax(h0, h1), s0 = pk_hmin(l0, l1), m0 = pk_hmin(h0, h1), m1 = pk_hmax(l0, l1);
+      const uint32_t s2 = pk_hmax(m0, m1), s1 = pk_hmin(m0, m1);
+      if (i == 0) { A1 = s3; A2 = s2; B1 = s0; B2 = s1; any = pk_hmaximum(x, y, z); any = pk_hmaximum(any, w, w); }
+      else {
+        A2 = pk_hmax(pk_hmin(A1, s3), pk_hmax(A2, s2)); A1 = pk_hmax(A1, s3);
+        B2 = pk_hmin(pk_hmax(B1, s0), pk_hmin(B2, s1)); B1 = pk_hmin(B1, s0);
+        any = pk_hmaximum(any, x, y); any = pk_hmaximum(any, z, w);
+      }
+    }
+    const uint32_t As = halves_swapped(A1), Bs = halves_swapped(B1);
+    A2 = pk_hmax(pk_hmin(A1, As), pk_hmax(A2, halves_swapped(A2)));
+    B2 = pk_hmin(pk_hmax(B1, Bs), pk_hmin(B2, halves_swapped(B2)));
+    B1 = pk_hmin(B1, Bs);
+    any = pk_hmaximum(any, any, halves_swapped(any));
+    uint32_t e1 = __builtin_amdgcn_perm(B1, any, 0x05040100u) ^ 0x80000000u;
+    uint32_t e2 = __builtin_amdgcn_perm(B2, A2, 0x05040100u) ^ 0x80000000u;
+#pragma unroll
+    for (int step = 0; step < 2; ++step) {
+      const uint32_t y1 = step ? dpp_u<0x4E>(e1) : dpp_u<0xB1>(e1), y2 = step ? dpp_u<0x4E>(e2) : dpp_u<0xB1>(e2);
+      e2 = pk_hmax(pk_hmin(e1, y1), pk_hmax(e2, y2));
+      e1 = pk_hmaximum(e1, y1, y1);
+    }
+    const us2 mag = __builtin_bit_cast(us2, e1 & 0x7fff7fffu) - one;              // magnitudes of the ends, less one
+    const us2 most = __builtin_elementwise_max(mag, mag.yx);
+    uint32_t ch_top, ch_bot, v_top, v_bot;
+    if (__ballot(most.x >= 0x7bffu) == 0ull) {
+      const uint32_t top_pair = __builtin_amdgcn_perm(0u, e1, 0x01000100u), bot_pair = __builtin_amdgcn_perm(0u, e1, 0x03020302u) ^ 0x80008000u;
+      auto word = [&](int j) { return word_of(raw, j); };
+      ch_top = first_channel(word, c, top_pair, one);
+      ch_bot = first_channel(word, c, bot_pair, one);
+      // the smallest of the rest is the overall smallest unless that is the top element itself: all values are equal
+      // then, and it is the second of them
+      if (top_pair == bot_pair) ch_bot = 1u;
+      v_top = e1 & 0xffffu; v_bot = (e1 >> 16) ^ 0x8000u;
+      // what remains: its largest value is the runner-up of the largest, its smallest of the smallest (equal values make
+      // the choice of element moot; a zero without its sign)
+      mx = h2f((uint16_t)(e2 & 0xffffu)) + 0.0f; mn = h2f((uint16_t)((e2 >> 16) ^ 0x8000u)) + 0.0f;
+      finite = true;
+    } else {
+      ends_by_keys(raw, c, one, ch_top, ch_bot, v_top, v_bot, mn, mx, finite);
+    }
+    if (c == 0) {          // the side store's row, by channel
+      const bool first = ch_top < ch_bot;
+      *(uint16_t*)oidx_row = (uint16_t)(first ? ch_top | (ch_bot << 8) : ch_bot | (ch_top << 8));
+      *(uint32_t*)oval_row = first ? v_top | (v_bot << 16) : v_bot | (v_top << 16);
+    }
+  }
+  // The same for any bit patterns, on signed 16-bit keys (signed_keys_pair)
+  __device__ static __forceinline__ void ends_by_keys(const uint4 (&raw)[NCH], int c, us2 one, uint32_t& ch_top, uint32_t& ch_bot, uint32_t& v_top, uint32_t& v_bot,
+                                                      float& mn, float& mx, bool& finite) {
+    ss2 A1, A2;      // largest and runner-up; in the upper half, of the numbers with their signs changed
+    A1 = A2 = (ss2)(short)-0x8000;
+#pragma unroll 1
+    for (int j = 0; j < 4 * NCH; ++j) {
+      uint32_t w = 0u;
+#pragma unroll
+      for (int i = 0; i < 4 * NCH; ++i) w = i == j ? word_of(raw, i) : w;
+      const ss2 k = signed_keys_pair(w);
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const ss2 x = hf ? ss2{k.y, (short)-k.y} : ss2{k.x, (short)-k.x};
+        A2 = pk_max(pk_min(A1, x), A2); A1 = pk_max(A1, x);
+      }
+    }
+#pragma unroll
+    for (int step = 0; step < 2; ++step) {
+      const uint32_t e1 = __builtin_bit_cast(uint32_t, A1), e2 = __builtin_bit_cast(uint32_t, A2);
+      const ss2 y1 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e1) : dpp_u<0xB1>(e1)), y2 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e2) : dpp_u<0xB1>(e2));
+      A2 = pk_max(pk_min(A1, y1), pk_max(A2, y2)); A1 = pk_max(A1, y1);
+    }
+    const int top = A1.x, bot = -A1.y;
+    finite = top < 0x7c00 && bot > -0x7c00;
+    const uint32_t top_pair = __builtin_amdgcn_perm(0u, (uint32_t)top, 0x01000100u), bot_pair = __builtin_amdgcn_perm(0u, (uint32_t)bot, 0x01000100u);
+    auto word = [&](int j) { return __builtin_bit_cast(uint32_t, signed_keys_pair(word_of(raw, j))); };
+    ch_top = first_channel(word, c, top_pair, one);
+    ch_bot = top == bot ? 1u : first_channel(word, c, bot_pair, one);
+    // (the key does not keep the sign of a zero: the bits as they are stored)
+    v_top = v_bot = 0u;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (channel(c, i, e) == (int)ch_top) v_top = half_bits(raw, i, e);
+        if (channel(c, i, e) == (int)ch_bot) v_bot = half_bits(raw, i, e);
+      }
+    v_top = quad_umax(v_top); v_bot = quad_umax(v_bot);
+    mx = h2f((uint16_t)signed_key_bits(A2.x)); mn = h2f((uint16_t)signed_key_bits(-A2.y));
+  }
+
   // thr_lo, thr_hi: an outlier must lie below thr_lo resp. above thr_hi (+inf, -inf: the count
   // rule, every candidate passes); a side stops at its first candidate that does not, and the
   // rows of the side store are filled from the front, the rest marked unused (channel 255)
@@ -291,81 +422,7 @@ struct TokenEncoder {
     bool finite = false;      // all values known to be
     if (fresh) {
       if constexpr (ONE) {
-        // The two largest and the two smallest values, as packed 16-bit keys: four words at a time are sorted (ten
-        // instructions for eight elements), their ends merged into the running ones; then over the halves of the
-        // words and the lanes of the quad (there the largest and minus the smallest in one word).
-        ss2 k[4 * NCH], A1, A2, B1, B2;
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-          const ss2 x = k[4 * i] = signed_keys_pair(raw[i].x), y = k[4 * i + 1] = signed_keys_pair(raw[i].y);
-          const ss2 z = k[4 * i + 2] = signed_keys_pair(raw[i].z), w = k[4 * i + 3] = signed_keys_pair(raw[i].w);
-          const ss2 h0 = pk_max(x, y), l0 = pk_min(x, y), h1 = pk_max(z, w), l1 = pk_min(z, w);
-          const ss2 s3 = pk_max(h0, h1), s0 = pk_min(l0, l1), m0 = pk_min(h0, h1), m1 = pk_max(l0, l1);
-          const ss2 s2 = pk_max(m0, m1), s1 = pk_min(m0, m1);
-          if (i == 0) { A1 = s3; A2 = s2; B1 = s0; B2 = s1; }
-          else {
-            A2 = pk_max(pk_min(A1, s3), pk_max(A2, s2)); A1 = pk_max(A1, s3);
-            B2 = pk_min(pk_max(B1, s0), pk_min(B2, s1)); B1 = pk_min(B1, s0);
-          }
-        }
-        A2 = pk_max(pk_min(A1, A1.yx), pk_max(A2, A2.yx)); A1 = pk_max(A1, A1.yx);
-        B2 = pk_min(pk_max(B1, B1.yx), pk_min(B2, B2.yx)); B1 = pk_min(B1, B1.yx);
-        B1 = -B1; B2 = -B2;
-        uint32_t e1 = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, B1), __builtin_bit_cast(uint32_t, A1), 0x05040100u);
-        uint32_t e2 = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, B2), __builtin_bit_cast(uint32_t, A2), 0x05040100u);
-#pragma unroll
-        for (int step = 0; step < 2; ++step) {
-          const ss2 y1 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e1) : dpp_u<0xB1>(e1)), y2 = __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(e2) : dpp_u<0xB1>(e2));
-          const ss2 x1 = __builtin_bit_cast(ss2, e1), x2 = __builtin_bit_cast(ss2, e2);
-          e2 = __builtin_bit_cast(uint32_t, pk_max(pk_min(x1, y1), pk_max(x2, y2)));
-          e1 = __builtin_bit_cast(uint32_t, pk_max(x1, y1));
-        }
-        const int top1 = (int)(int16_t)(e1 & 0xffffu), bot1 = -((int)e1 >> 16);
-        finite = top1 < 0x7c00 && bot1 > -0x7c00;
-        // Lowest channel that holds an end: per word one bit of each half, then the first over the quad
-        const uint32_t top_pair = __builtin_amdgcn_perm(0u, (uint32_t)top1, 0x01000100u), bot_pair = __builtin_amdgcn_perm(0u, (uint32_t)bot1, 0x01000100u);
-        uint32_t not_top = 0u, not_bot = 0u;
-        uint32_t ones = 0x10001u;
-        asm("" : "+s"(ones));              // (known to be ones, the minimum becomes two compares and two selects)
-        const us2 one = __builtin_bit_cast(us2, ones);
-#pragma unroll
-        for (int j = 0; j < 4 * NCH; ++j) {
-          const uint32_t kw = __builtin_bit_cast(uint32_t, k[j]);
-          not_top = (not_top << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, kw ^ top_pair), one));
-          not_bot = (not_bot << 1) | __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, kw ^ bot_pair), one));
-        }
-        auto first_channel = [&](uint32_t misses) -> uint32_t {      // bit 4 NCH - 1 of a half: its first element
-          constexpr uint32_t ALL = (1u << (4 * NCH)) - 1u;
-          const uint32_t hits = misses ^ (ALL * 0x10001u);
-          const uint32_t lo = hits << 16, e_lo = 2u * (uint32_t)__builtin_clz(lo | 1u) , e_hi = 2u * (uint32_t)__builtin_clz(hits | 1u) + 1u;
-          const uint32_t e = (e_lo < e_hi ? e_lo : e_hi) - 2u * (16u - 4 * NCH);
-          const uint32_t ch = ((e & ~7u) << 2) + (uint32_t)(8 * c) + (e & 7u);
-          return quad_umin(e < (uint32_t)EPL ? ch : 0xffu);
-        };
-        const uint32_t ch_top = first_channel(not_top);
-        // the smallest of the rest is the overall smallest unless that is the top element itself: all values are
-        // equal then, and it is the second of them
-        const uint32_t ch_bot = top1 == bot1 ? 1u : first_channel(not_bot);
-        uint32_t v_top = signed_key_bits(top1), v_bot = signed_key_bits(bot1);
-        if (top1 == 0 || bot1 == 0) {          // the key does not keep the sign of a zero: the bits as they are stored
-          uint32_t t = 0u, bt = 0u;
-#pragma unroll
-          for (int i = 0; i < NCH; ++i)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              if (channel(c, i, e) == (int)ch_top) t = half_bits(raw, i, e);
-              if (channel(c, i, e) == (int)ch_bot) bt = half_bits(raw, i, e);
-            }
-          v_top = quad_umax(t); v_bot = quad_umax(bt);
-        }
-        if (c == 0) {          // the side store's row, by channel
-          const bool first = ch_top < ch_bot;
-          *(uint16_t*)oidx_row = (uint16_t)(first ? ch_top | (ch_bot << 8) : ch_bot | (ch_top << 8));
-          *(uint32_t*)oval_row = first ? v_top | (v_bot << 16) : v_bot | (v_top << 16);
-        }
-        // what remains: its largest value is the runner-up of the largest, its smallest of the smallest
-        // (equal values make the choice of element moot)
-        mx = h2f((uint16_t)signed_key_bits((int)(int16_t)(e2 & 0xffffu))); mn = h2f((uint16_t)signed_key_bits(-((int)e2 >> 16)));
+        ends_of_token(raw, c, oidx_row, oval_row, mn, mx, finite);
       } else {
         uint32_t kx[EPL], kn[EPL];
 #pragma unroll
@@ -440,62 +497,59 @@ struct TokenEncoder {
   }
 };
 
-// Stored code planes of one tile side -> staged bytes (old widths, nothing dropped yet), for
+// Keys: stored code planes of one tile side -> staged bytes (old widths, nothing dropped yet), for
 // the cached tokens whose codes are read again (L.need == 1); whole words / units that hold
 // none of them are not touched.
 template <int D, int MAXO, bool HAS1>
-__device__ void unpack_tile(int side, const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
+__device__ void unpack_k(const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
   const int n32 = c.n32();
-  if (side == 0) {
-    const QaqKRegions r = qaq_k_regions(c, D);
-    for (int it = tid; it < n32 * NQ; it += kThreads) {
-      const int s = it / NQ, q = it % NQ;
-      const int pos = L.pos_old[s];
-      if (L.need[pos] != 1) continue;
-      const bool three = s < c.n3;
-      const uint32_t w2 = *(const uint32_t*)(base + r.r2 + 4u * (uint32_t)it);
-      uint32_t w1 = 0;
-      if (three) w1 = *(const uint32_t*)(base + r.r1 + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1)) >> (4 * (q & 1));
-      uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
+  const QaqKRegions r = qaq_k_regions(c, D);
+  for (int it = tid; it < n32 * NQ; it += kThreads) {
+    const int s = it / NQ, q = it % NQ;
+    const int pos = L.pos_old[s];
+    if (L.need[pos] != 1) continue;
+    const bool three = s < c.n3;
+    const uint32_t w2 = *(const uint32_t*)(base + r.r2 + 4u * (uint32_t)it);
+    uint32_t w1 = 0;
+    if (three) w1 = *(const uint32_t*)(base + r.r1 + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1)) >> (4 * (q & 1));
+    uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        uint32_t code = (w2 >> (2 * v)) & 0x03030303u;
-        if (three) code = (code << 1) | ((w1 >> v) & 0x01010101u);
-        row[v] = code;
-      }
-    }
-    for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
-      const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
-      const int pos = L.pos_old[n32 + i4];
-      if (L.need[pos] != 1) continue;
-      const uint32_t w = *(const uint32_t*)(base + r.r4 + 4u * (uint32_t)it);
-      uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
-      row[0] = w & 0x0f0f0f0fu;
-      row[1] = (w >> 4) & 0x0f0f0f0fu;
-    }
-    for (int it = tid; it < c.n8 * (D / 4); it += kThreads) {
-      const int i8 = it / (D / 4), jj = it % (D / 4), q = jj >> 2, v = jj & 3;
-      const int pos = L.pos_old[n32 + c.n4 + i8];
-      if (L.need[pos] != 1) continue;
-      const uint32_t w = *(const uint32_t*)(base + r.r8 + 4u * (uint32_t)it);
-      L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + v] = w ^ 0x80808080u;
-    }
-    for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
-      const int i1 = it / (D / 32), jj = it % (D / 32);
-      const int pos = L.pos_old[c.first1() + i1];
-      if (L.need[pos] != 1) continue;
-      const uint32_t w = *(const uint32_t*)(base + r.r1b + 4u * (uint32_t)it);
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int q = 2 * jj + hh;
-        uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) row[v] = (w >> (4 * hh + v)) & 0x01010101u;
-      }
+    for (int v = 0; v < 4; ++v) {
+      uint32_t code = (w2 >> (2 * v)) & 0x03030303u;
+      if (three) code = (code << 1) | ((w1 >> v) & 0x01010101u);
+      row[v] = code;
     }
   }
-  // (value side: unpack_moved_v)
+  for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
+    const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
+    const int pos = L.pos_old[n32 + i4];
+    if (L.need[pos] != 1) continue;
+    const uint32_t w = *(const uint32_t*)(base + r.r4 + 4u * (uint32_t)it);
+    uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
+    row[0] = w & 0x0f0f0f0fu;
+    row[1] = (w >> 4) & 0x0f0f0f0fu;
+  }
+  for (int it = tid; it < c.n8 * (D / 4); it += kThreads) {
+    const int i8 = it / (D / 4), jj = it % (D / 4), q = jj >> 2, v = jj & 3;
+    const int pos = L.pos_old[n32 + c.n4 + i8];
+    if (L.need[pos] != 1) continue;
+    const uint32_t w = *(const uint32_t*)(base + r.r8 + 4u * (uint32_t)it);
+    L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + v] = w ^ 0x80808080u;
+  }
+  for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
+    const int i1 = it / (D / 32), jj = it % (D / 32);
+    const int pos = L.pos_old[c.first1() + i1];
+    if (L.need[pos] != 1) continue;
+    const uint32_t w = *(const uint32_t*)(base + r.r1b + 4u * (uint32_t)it);
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int q = 2 * jj + hh;
+      uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) row[v] = (w >> (4 * hh + v)) & 0x01010101u;
+    }
+  }
 }
 
 // Value side: codes of the cached tokens that move, token by token.  The list holds their
@@ -516,194 +570,80 @@ __device__ void unpack_moved_v(const uint8_t* base, const QaqCounts& c, int n_mo
   }
 }
 
-// Staged bytes -> stored code planes of one tile side, in the new slot order; codes that
+// Keys: staged bytes -> stored code planes of one tile side, in the new slot order; codes that
 // narrow drop their low bits here (the coarser grid's segments contain the finer one's).
-// c0 = the class counts the tile had before (all zero for a tile that did not exist): a
+// c0 = the class counts the tile had before: a
 // word whose tokens all keep slot and width, in a region that has not moved, is left alone.
 template <int D, int MAXO, bool HAS1>
-__device__ void pack_tile(int side, uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
+__device__ void pack_k(uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
   constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
   const int n32 = c.n32();
-  const bool had = c0.total() > 0;
-  const bool same32 = had && c0.n32() == n32;
-  if (side == 0) {
-    const QaqKRegions r = qaq_k_regions(c, D), r0 = qaq_k_regions(c0, D);
-    const bool same1 = had && r.r1 == r0.r1;
-    const bool same4 = same32 && r.r4 == r0.r4;
-    const bool same8 = same4 && c0.n4 == c.n4 && r.r8 == r0.r8;
-    for (int it = tid; it < n32 * NQ; it += kThreads) {
-      const int s = it / NQ, q = it % NQ;
-      const int pos = L.pos_of_slot[s];
-      const int f = L.shf[pos];
-      if (had && (f & kKeptFlag)) continue;
-      const int sh = (f & 7) + (s < c.n3 ? 1 : 0);
-      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-      uint32_t w = 0;
+  const bool same32 = c0.n32() == n32;
+  const QaqKRegions r = qaq_k_regions(c, D), r0 = qaq_k_regions(c0, D);
+  const bool same1 = r.r1 == r0.r1;
+  const bool same4 = same32 && r.r4 == r0.r4;
+  const bool same8 = same4 && c0.n4 == c.n4 && r.r8 == r0.r8;
+  for (int it = tid; it < n32 * NQ; it += kThreads) {
+    const int s = it / NQ, q = it % NQ;
+    const int pos = L.pos_of_slot[s];
+    const int f = L.shf[pos];
+    if (f & kKeptFlag) continue;
+    const int sh = (f & 7) + (s < c.n3 ? 1 : 0);
+    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
+    uint32_t w = 0;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x03030303u) << (2 * v);
-      *(uint32_t*)(base + r.r2 + 4u * (uint32_t)it) = w;
-    }
-    for (int it = tid; it < c.n3 * (D / 32); it += kThreads) {
-      const int s = it / (D / 32), jj = it % (D / 32);
-      const int pos = L.pos_of_slot[s];
-      const int f = L.shf[pos];
-      if (same1 && (f & kKeptFlag)) continue;
-      const int sh = f & 7;
-      uint32_t w = 0;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int q = 2 * jj + hh;
-        const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
-      }
-      *(uint32_t*)(base + r.r1 + 4u * (uint32_t)it) = w;
-    }
-    for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
-      const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
-      const int pos = L.pos_of_slot[n32 + i4];
-      const int f = L.shf[pos];
-      if (same4 && (f & kKeptFlag)) continue;
-      const int sh = f & 7;
-      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
-      *(uint32_t*)(base + r.r4 + 4u * (uint32_t)it) = ((row[0] >> sh) & 0x0f0f0f0fu) | (((row[1] >> sh) & 0x0f0f0f0fu) << 4);
-    }
-    for (int it = tid; it < c.n8 * NQ; it += kThreads) {        // one slice (16 bytes) per item
-      const int i8 = it / NQ, q = it % NQ;
-      const int pos = L.pos_of_slot[n32 + c.n4 + i8];
-      if (same8 && (L.shf[pos] & kKeptFlag)) continue;
-      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-      *(uint4*)(base + r.r8 + 16u * (uint32_t)it) =
-          make_uint4(row[0] ^ 0x80808080u, row[1] ^ 0x80808080u, row[2] ^ 0x80808080u, row[3] ^ 0x80808080u);
-    }
-    const bool same1b = same8 && c0.n8 == c.n8;           // then r1b has not moved either
-    for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
-      const int i1 = it / (D / 32), jj = it % (D / 32);
-      const int pos = L.pos_of_slot[c.first1() + i1];
-      const int f = L.shf[pos];
-      if (same1b && (f & kKeptFlag)) continue;
-      const int sh = f & 7;
-      uint32_t w = 0;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int q = 2 * jj + hh;
-        const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
-      }
-      *(uint32_t*)(base + r.r1b + 4u * (uint32_t)it) = w;
-    }
-    return;
+    for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x03030303u) << (2 * v);
+    *(uint32_t*)(base + r.r2 + 4u * (uint32_t)it) = w;
   }
-  const QaqVRegions r = qaq_v_regions(c, D), r0 = qaq_v_regions(c0, D);
-  const bool same8 = same32 && r.r4 == r0.r4 && c0.n4 == c.n4 && r.r8 == r0.r8;
-  // every unit is written (a tile that held nothing; see pack_masked_v for a rebuild)
-  for (int it = tid; it < ((n32 + 15) / 16) * (D / 4); it += kThreads) {
-    const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-    uint32_t o[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      uint32_t w[4], t[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int s = 16 * u + 4 * v + j;
-        w[j] = 0;
-        if (s < n32) {
-          const int pos = L.pos_of_slot[s];
-          w[j] = (L.stage[pos * SROW + c4] >> ((L.shf[pos] & 7) + (s < c.n3 ? 1 : 0))) & 0x03030303u;
-        }
-      }
-      transpose4(w, t);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] |= t[k] << (2 * v);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *(uint32_t*)(base + r.r2 + (uint32_t)u * (4 * D) + 4u * (uint32_t)((4 * (c4 & 3) + k) * (D / 16) + cg)) = o[k];
-  }
-  for (int it = tid; it < ((c.n3 + 15) / 16) * (D / 8); it += kThreads) {
-    const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
-    uint32_t o[4] = {0u, 0u, 0u, 0u};
+  for (int it = tid; it < c.n3 * (D / 32); it += kThreads) {
+    const int s = it / (D / 32), jj = it % (D / 32);
+    const int pos = L.pos_of_slot[s];
+    const int f = L.shf[pos];
+    if (same1 && (f & kKeptFlag)) continue;
+    const int sh = f & 7;
+    uint32_t w = 0;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int c4 = 4 * (2 * cgp + hh) + n4;
+      const int q = 2 * jj + hh;
+      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        uint32_t w[4], t[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int s = 16 * u + 4 * v + j;
-          w[j] = 0;
-          if (s < c.n3) {
-            const int pos = L.pos_of_slot[s];
-            w[j] = (L.stage[pos * SROW + c4] >> (L.shf[pos] & 7)) & 0x01010101u;
-          }
-        }
-        transpose4(w, t);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] |= t[k] << (4 * hh + v);
-      }
+      for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *(uint32_t*)(base + r.r1 + (uint32_t)u * (2 * D) + 4u * (uint32_t)((4 * n4 + k) * (D / 32) + cgp)) = o[k];
+    *(uint32_t*)(base + r.r1 + 4u * (uint32_t)it) = w;
   }
-  for (int it = tid; it < ((c.n4 + 7) / 8) * (D / 4); it += kThreads) {
-    const int hu = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-    uint32_t o[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int g2 = 0; g2 < 2; ++g2) {
-      uint32_t w[4], t[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int i4 = 8 * hu + 4 * g2 + j;
-        w[j] = 0;
-        if (i4 < c.n4) {
-          const int pos = L.pos_of_slot[n32 + i4];
-          w[j] = (L.stage[pos * SROW + c4] >> (L.shf[pos] & 7)) & 0x0f0f0f0fu;
-        }
-      }
-      transpose4(w, t);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] |= t[k] << (4 * g2);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *(uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D) + 4u * (uint32_t)((4 * (c4 & 3) + k) * (D / 16) + cg)) = o[k];
+  for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
+    const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
+    const int pos = L.pos_of_slot[n32 + i4];
+    const int f = L.shf[pos];
+    if (same4 && (f & kKeptFlag)) continue;
+    const int sh = f & 7;
+    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
+    *(uint32_t*)(base + r.r4 + 4u * (uint32_t)it) = ((row[0] >> sh) & 0x0f0f0f0fu) | (((row[1] >> sh) & 0x0f0f0f0fu) << 4);
   }
-  for (int it = tid; it < c.n8 * (D / 16); it += kThreads) {    // 16 bytes per item
-    const int i8 = it / (D / 16), dq = 4 * (it % (D / 16));
+  for (int it = tid; it < c.n8 * NQ; it += kThreads) {        // one slice (16 bytes) per item
+    const int i8 = it / NQ, q = it % NQ;
     const int pos = L.pos_of_slot[n32 + c.n4 + i8];
     if (same8 && (L.shf[pos] & kKeptFlag)) continue;
-    const uint32_t* row = &L.stage[pos * SROW + dq];
-    *(uint4*)(base + r.r8 + 16u * (uint32_t)it) = make_uint4(row[0], row[1], row[2], row[3]);
+    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
+    *(uint4*)(base + r.r8 + 16u * (uint32_t)it) =
+        make_uint4(row[0] ^ 0x80808080u, row[1] ^ 0x80808080u, row[2] ^ 0x80808080u, row[3] ^ 0x80808080u);
   }
-  for (int it = tid; HAS1 && it < ((c.n1 + 15) / 16) * (D / 8); it += kThreads) {
-    const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
-    uint32_t o[4] = {0u, 0u, 0u, 0u};
+  const bool same1b = same8 && c0.n8 == c.n8;           // then r1b has not moved either
+  for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
+    const int i1 = it / (D / 32), jj = it % (D / 32);
+    const int pos = L.pos_of_slot[c.first1() + i1];
+    const int f = L.shf[pos];
+    if (same1b && (f & kKeptFlag)) continue;
+    const int sh = f & 7;
+    uint32_t w = 0;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int c4 = 4 * (2 * cgp + hh) + n4;
+      const int q = 2 * jj + hh;
+      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        uint32_t w[4], t[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int i1 = 16 * u + 4 * v + j;
-          w[j] = 0;
-          if (i1 < c.n1) {
-            const int pos = L.pos_of_slot[c.first1() + i1];
-            w[j] = (L.stage[pos * SROW + c4] >> (L.shf[pos] & 7)) & 0x01010101u;
-          }
-        }
-        transpose4(w, t);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] |= t[k] << (4 * hh + v);
-      }
+      for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *(uint32_t*)(base + r.r1b + (uint32_t)u * (2 * D) + 4u * (uint32_t)((4 * n4 + k) * (D / 32) + cgp)) = o[k];
+    *(uint32_t*)(base + r.r1b + 4u * (uint32_t)it) = w;
   }
 }
 
@@ -841,12 +781,353 @@ __device__ __forceinline__ void add_widenings(const QaqView& v, size_t tile_side
   if (n) v.refused[tile_side * 2 + (served ? 1 : 0)] += (unsigned int)n;
 }
 
+// What the general and the fresh build have in common, for one position's thread.
+// Width by the rules of Section 4.1: the narrowest that satisfies lhs <= threshold * 2^B, else the widest
+__device__ __forceinline__ int rule_width(const QaqRuleArgs& ru, float lhs, float thr) {
+  int w = ru.bit_set[ru.nbits - 1];
+  for (int i = ru.nbits - 1; i >= 0; --i)
+    if (lhs <= ldexpf(thr, ru.bit_set[i])) w = ru.bit_set[i];
+  return w;
+}
+// Side store's row of a fresh token: order by channel (the one-per-end encoder leaves it so)
+__device__ __forceinline__ void sort_side_store(uint8_t* idx, uint16_t* val, int no2) {
+  for (int i = 1; i < no2; ++i) {
+    const uint8_t ki = idx[i];
+    const uint16_t vi = val[i];
+    int j = i - 1;
+    while (j >= 0 && idx[j] > ki) { idx[j + 1] = idx[j]; val[j + 1] = val[j]; --j; }
+    idx[j + 1] = ki;
+    val[j + 1] = vi;
+  }
+}
+// Values: what the attention kernel needs as the fixed-point range of a tile -- the largest per-token step range/2^B (a 3-bit
+// code is split into planes, the upper one weighs twice the step) and the largest magnitude an outlier correction (stored value
+// minus reconstruction) can have
+__device__ __forceinline__ float value_bound(int bits, float mn, float mx, const uint8_t* idx, const uint16_t* val, int no2) {
+  const float range = mx - mn;
+  float bnd = ldexpf(range, bits == 3 ? -2 : -bits);
+  for (int k = 0; k < no2; ++k) {
+    if (idx[k] == 0xffu) continue;        // (variable-length side store: an unused place)
+    const float ov = h2f(val[k]);
+    bnd = fmaxf(bnd, fmaxf(fabsf(ov - mx), fabsf(ov - mn)) + range);
+  }
+  return bnd;
+}
+// Keys: thresholds for which the token keeps its width (Section 4.1 key rule as the comparison range <= threshold * 2^B): a token
+// at width B widens below range / 2^B and narrows from range / 2^B' on, B' the next narrower width; the power-of-two scalings are exact
+__device__ __forceinline__ void key_interval(const QaqRuleArgs& ru, int bits, float range, float& lo, float& hi) {
+  int narrower = 0;
+  for (int i = 0; i < ru.nbits; ++i)
+    if (ru.bit_set[i] < bits) narrower = ru.bit_set[i];
+  if (bits < ru.bit_set[ru.nbits - 1]) lo = ldexpf(range, -bits);
+  if (narrower > 0) hi = ldexpf(range, -narrower);
+}
+// Variable-length side store: the entries of the new tokens (positions n_before .. n_after - 1) go behind the tile's last one, in
+// position order (a prefix sum of their counts)
+template <int D, int MAXO>
+__device__ __forceinline__ void put_new_runs(const QaqView& v, int side, size_t gi0, int n_before, int n_after, BuildLds<D, MAXO>& L, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  const size_t pool0 = gi0 * (size_t)v.no2;
+  const bool fresh = tid >= n_before && tid < n_after;
+  int cnt = 0;
+  if (fresh)
+    for (int k = 0; k < v.no2; ++k) cnt += L.oidx[tid][k] != 0xffu;
+  int inc = cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  if (lane == 63) L.wave_ocnt[wave] = inc;
+  __syncthreads();
+  int start = inc - cnt;
+  for (int w = 0; w < wave; ++w) start += L.wave_ocnt[w];
+  if (n_before > 0) start += (int)v.ostart[side][gi0 + n_before - 1] + (int)v.ocnt[side][gi0 + n_before - 1];
+  if (fresh) {
+    v.ostart[side][gi0 + tid] = (uint16_t)start;
+    v.ocnt[side][gi0 + tid] = (uint8_t)cnt;
+    for (int k = 0; k < cnt; ++k) {          // the row is sorted by channel, unused places last
+      v.oidx[side][pool0 + start + k] = L.oidx[tid][k];
+      v.oval[side][pool0 + start + k] = L.oval[tid][k];
+    }
+  }
+}
+// Class counts and bounds of a tile side (one thread; per wavefront: the value bound, or the ends of the key interval)
+__device__ __forceinline__ void put_tile_summary(const QaqView& v, int side, size_t tile_id, const QaqCounts& cn, const float* bound, const float* bound2) {
+  uint16_t* cp = v.counts + (tile_id * 2 + side) * 4;
+  cp[QC3] = (uint16_t)cn.n3; cp[QC2] = (uint16_t)cn.n2; cp[QC4] = (uint16_t)cn.n4; cp[QC8] = (uint16_t)cn.n8;
+  const float most = fmaxf(fmaxf(bound[0], bound[1]), fmaxf(bound[2], bound[3]));
+  if (side == 1) v.vbound[tile_id] = most;
+  else ((float2*)v.kthr)[tile_id] = make_float2(most, fminf(fminf(bound2[0], bound2[1]), fminf(bound2[2], bound2[3])));
+}
+
+// ---------------------------------------------------------------------------------
+// A tile side that held nothing (bulk appends, prompt encoding, the first token of a tile).  Every token is encoded at
+// eight bits, so the stored fields of every class are the same upper bits of a staged byte and the planes are put together
+// by shifts that take all tokens of a word along (top_fields), one 4x4 byte transpose per four channels of 16 values; there is
+// nothing to keep, to read back or to compare with, so none of the general path's bookkeeping.
+//
+// Bound by vector instructions (the search and the codes, see TokenEncoder), then by the fp16 rows it reads.  Vector instructions
+// per wavefront 3240 -> 2600 by the encoder, -> 2020 by this form (through the general path before): 2 x 32 heads x 12001
+// tokens 167 -> 140 -> 113 us = 4.1 TB/s, 16 x 8 heads x 8192 216 -> 152, 8 x 32 heads x 4096 at eight bits, in three chunks,
+// 229 -> 197 -> 187.
+// ---------------------------------------------------------------------------------
+
+// FW upper bits below bit 8 - SKIP of the bytes of N = 8 / FW words -> fields of one word, the first word's lowest
+template <int FW, int SKIP, int N>
+__device__ __forceinline__ uint32_t top_fields(const uint32_t (&w)[N]) {
+  constexpr uint32_t M = 0x01010101u * (((1u << FW) - 1u) << (8 - FW));
+  uint32_t x = w[0] << SKIP;
+#pragma unroll
+  for (int i = 1; i < N; ++i) x = ((x >> FW) & ~M) | ((w[i] << SKIP) & M);
+  return x;      // (what a shift brings in from the next byte is replaced in the same step; N steps replace every bit)
+}
+
+template <int D, int MAXO, bool HAS1>
+__device__ __forceinline__ void pack_fresh(int side, uint8_t* base, const QaqCounts& c, const BuildLds<D, MAXO>& L, int tid) {
+  constexpr int NQ = D / 16, KS = D / 64;
+  const int n32 = c.n32();
+  const uint8_t* const staged = (const uint8_t*)L.stage;
+  auto row_of = [&](int slot) { return (const uint32_t*)(staged + L.pos_of_slot[slot]); };
+  if (side == 0) {
+    const QaqKRegions r = qaq_k_regions(c, D);
+    auto slice = [&](const uint32_t* row, int q) { return row + (16 * (q % KS) + 4 * (q / KS)); };
+    for (int it = tid; it < n32 * (D / 64); it += kThreads) {          // four slices of a token: 16 bytes
+      const uint32_t* row = row_of(it / (D / 64));
+      const int q0 = 4 * (it % (D / 64));
+      uint32_t o[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t* p = slice(row, q0 + k);
+        const uint32_t w[4] = {p[0], p[1], p[2], p[3]};
+        o[k] = top_fields<2, 0>(w);
+      }
+      *(uint4*)(base + r.r2 + 16u * (uint32_t)it) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+    auto low_word = [&](const uint32_t* row, int jj, auto skip) {      // slices 2 jj and 2 jj + 1, one bit each
+      const uint32_t *p = slice(row, 2 * jj), *p1 = slice(row, 2 * jj + 1);
+      const uint32_t w[8] = {p[0], p[1], p[2], p[3], p1[0], p1[1], p1[2], p1[3]};
+      return top_fields<1, decltype(skip)::value>(w);
+    };
+    for (int it = tid; it < c.n3 * (D / 32); it += kThreads)
+      *(uint32_t*)(base + r.r1 + 4u * (uint32_t)it) = low_word(row_of(it / (D / 32)), it % (D / 32), std::integral_constant<int, 2>{});
+    for (int it = tid; it < c.n4 * (D / 32); it += kThreads) {         // two slices: 16 bytes
+      const uint32_t* row = row_of(n32 + it / (D / 32));
+      const uint32_t *p = slice(row, 2 * (it % (D / 32))), *p1 = slice(row, 2 * (it % (D / 32)) + 1);
+      const uint32_t a[2] = {p[0], p[1]}, b[2] = {p[2], p[3]}, a1[2] = {p1[0], p1[1]}, b1[2] = {p1[2], p1[3]};
+      *(uint4*)(base + r.r4 + 16u * (uint32_t)it) = make_uint4(top_fields<4, 0>(a), top_fields<4, 0>(b), top_fields<4, 0>(a1), top_fields<4, 0>(b1));
+    }
+    for (int it = tid; it < c.n8 * NQ; it += kThreads) {
+      const uint32_t* p = slice(row_of(n32 + c.n4 + it / NQ), it % NQ);
+      *(uint4*)(base + r.r8 + 16u * (uint32_t)it) = make_uint4(p[0] ^ 0x80808080u, p[1] ^ 0x80808080u, p[2] ^ 0x80808080u, p[3] ^ 0x80808080u);
+    }
+    for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads)
+      *(uint32_t*)(base + r.r1b + 4u * (uint32_t)it) = low_word(row_of(c.first1() + it / (D / 32)), it % (D / 32), std::integral_constant<int, 0>{});
+    return;
+  }
+  // values: fields of slots past the end of a region are whatever those slots hold (no reader looks at them)
+  const QaqVRegions r = qaq_v_regions(c, D);
+  for (int it = tid; it < ((n32 + 15) / 16) * (D / 4); it += kThreads) {
+    const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
+    const uint4* offs = (const uint4*)&L.pos_of_slot[16 * u];
+    const uint4 oa = offs[0], ob = offs[1];
+    const uint32_t off[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
+    uint32_t w[16], m[4], o[4];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = *(const uint32_t*)(staged + ((off[i >> 1] >> (16 * (i & 1))) & 0xffffu) + 4 * c4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t x[4] = {w[j], w[4 + j], w[8 + j], w[12 + j]};
+      m[j] = top_fields<2, 0>(x);
+    }
+    transpose4(m, o);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      *(uint32_t*)(base + r.r2 + (uint32_t)u * (4 * D) + 4u * (uint32_t)((4 * (c4 & 3) + k) * (D / 16) + cg)) = o[k];
+  }
+  auto low_units = [&](uint32_t region, int first, int n, auto skip) {      // one bit of every token of units of 16 slots
+    for (int it = tid; it < ((n + 15) / 16) * (D / 8); it += kThreads) {
+      const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
+      uint32_t m[4], o[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint32_t x[8];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const uint32_t* row = row_of(min(first + 16 * u + 4 * v + j, QAQ_TT - 1)) + (8 * cgp + n4);
+          x[v] = row[0]; x[4 + v] = row[4];
+        }
+        m[j] = top_fields<1, decltype(skip)::value>(x);
+      }
+      transpose4(m, o);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        *(uint32_t*)(base + region + (uint32_t)u * (2 * D) + 4u * (uint32_t)((4 * n4 + k) * (D / 32) + cgp)) = o[k];
+    }
+  };
+  low_units(r.r1, 0, c.n3, std::integral_constant<int, 2>{});
+  for (int it = tid; it < ((c.n4 + 7) / 8) * (D / 4); it += kThreads) {
+    const int hu = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
+    uint32_t m[4], o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int s0 = n32 + 8 * hu + j;
+      const uint32_t x[2] = {row_of(min(s0, QAQ_TT - 1))[c4], row_of(min(s0 + 4, QAQ_TT - 1))[c4]};
+      m[j] = top_fields<4, 0>(x);
+    }
+    transpose4(m, o);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      *(uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D) + 4u * (uint32_t)((4 * (c4 & 3) + k) * (D / 16) + cg)) = o[k];
+  }
+  for (int it = tid; it < c.n8 * (D / 16); it += kThreads) {
+    const uint32_t* p = row_of(n32 + c.n4 + it / (D / 16)) + 4 * (it % (D / 16));
+    *(uint4*)(base + r.r8 + 16u * (uint32_t)it) = make_uint4(p[0], p[1], p[2], p[3]);
+  }
+  if (HAS1) low_units(r.r1b, c.first1(), c.n1, std::integral_constant<int, 0>{});
+}
+
+template <int D, bool ONE, bool HAS1>
+__device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, const int bh, const int tile, const int side, const int tid) {
+  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2, NC = HAS1 ? QAQ_NCLASS : 4, ROW = 4 * BuildLds<D, MAXO>::SROW;
+  typedef TokenEncoder<D, ONE> Enc;
+  const QaqView& v = a.v;
+  const QaqRuleArgs& ru = a.rule;
+  const bool csr = !ONE && v.csr;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int b = bh / v.Hkv, h = bh % v.Hkv, t0 = tile * QAQ_TT;
+  const int len_before = qaq_seq_len(v, b, a.len_before), n_new0 = t0 - len_before;      // (position 0 is new token n_new0)
+  const int n = min(qaq_seq_len(v, b, a.len_after) - t0, QAQ_TT);
+  const size_t tile_id = qaq_bh(v, b, h) * v.NT + tile, gi0 = qaq_slot_index(v, b, h, tile, 0);
+
+  // encode: a quad of lanes per token, 64 tokens per pass, the next pass's rows requested before the current one's are used
+  const uint8_t* const rows = (const uint8_t*)a.newx[side] + ((long long)bh * a.n_new + n_new0) * (2 * D);
+  uint8_t* const put = a.orig_put[side] ? (uint8_t*)a.orig_put[side] + ((long long)bh * a.orig_tokens + t0) * (2 * D) : nullptr;
+  const float thr_lo = csr ? v.othr[(side * v.Hkv + h) * 2] : INFINITY, thr_hi = csr ? v.othr[(side * v.Hkv + h) * 2 + 1] : -INFINITY;
+  constexpr int TPP = kThreads / 4;
+  const int NP = (n + TPP - 1) / TPP, c = tid & 3, gt = tid >> 2;
+  auto fetch = [&](int pass, uint4 (&raw)[Enc::NCH]) {
+    const int p = pass * TPP + gt;
+    const uint32_t at = (uint32_t)min(p, n - 1) * (2 * D) + 16u * (uint32_t)c;
+#pragma unroll
+    for (int i = 0; i < Enc::NCH; ++i) {        // read once: streaming loads
+      const u32x4 t = __builtin_nontemporal_load((const u32x4*)(rows + (at + 64 * i)));
+      raw[i] = make_uint4(t.x, t.y, t.z, t.w);
+    }
+    if (put && p < n) {                         // keep the unquantized token for later widening
+#pragma unroll
+      for (int i = 0; i < Enc::NCH; ++i) *(uint4*)(put + (at + 64 * i)) = raw[i];
+    }
+  };
+  auto encode = [&](int pass, const uint4 (&raw)[Enc::NCH]) {
+    const int p = pass * TPP + gt;
+    if (p < n) Enc::run(raw, c, true, 8, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
+  };
+  uint4 cur[Enc::NCH], nxt[Enc::NCH];
+  fetch(0, cur);
+  // the window's part of the value rule (thread t: position t), or the widths given
+  float pred = 0.0f;
+  int bits = a.widest;
+  if (a.mode >= 2 && side == 1 && tid < n) {
+    const int t = t0 + tid;
+    const size_t ri = qaq_bh(v, b, h) * v.Tmax + t;
+    float s = 0.0f;
+    if (a.mode == 2)
+      for (int g = 0; g < ru.G; ++g) s = fmaxf(s, ru.scores[((size_t)b * v.Hq + (h * ru.G + g)) * ru.score_stride + t]);
+    s = qaq_ring_value(v, s);
+    pred = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t), ru.new_row, ri, s);
+    if (a.mode == 2) qaq_ring_store(v, (size_t)ru.new_row * ((size_t)v.B * v.Hkv * v.Tmax) + ri, s);
+  } else if (a.mode == 0 && a.newbits[side] && tid < n) {
+    bits = a.newbits[side][(size_t)bh * a.n_new + (n_new0 + tid)];
+  }
+#pragma unroll 1
+  for (int pass = 0; pass < NP; ++pass) {
+    if (pass + 1 < NP) fetch(pass + 1, nxt);
+    encode(pass, cur);
+#pragma unroll
+    for (int i = 0; i < Enc::NCH; ++i) cur[i] = nxt[i];
+  }
+  L.pos_of_slot[tid] = 0;        // (slots past the last token: any staged row)
+  __syncthreads();
+
+  // widths, the tile's bounds, classes (thread t: position t)
+  int cls = -1;
+  {
+    float bnd = 0.0f, lo = 0.0f, hi = INFINITY;
+    if (tid < n) {
+      const uint32_t m = L.mm[tid];
+      const float mn = h2f((uint16_t)(m & 0xffffu)), mx = h2f((uint16_t)(m >> 16)), range = mx - mn;
+      if (a.mode >= 2) {
+        bits = rule_width(ru, side == 0 ? range : range * pred, side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b));
+        if (ru.out_bits[side]) ru.out_bits[side][(a.mode == 2 ? (size_t)bh * a.len_after + t0 : (size_t)bh * a.n_new + n_new0) + tid] = (uint8_t)bits;
+      }
+      v.tags[side][gi0 + tid] = (uint8_t)bits;
+      cls = qaq_class_of_bits(bits);
+      if (!ONE) sort_side_store(L.oidx[tid], L.oval[tid], v.no2);
+      if (side == 1) bnd = value_bound(bits, mn, mx, L.oidx[tid], L.oval[tid], v.no2);
+      else key_interval(ru, bits, range, lo, hi);
+    }
+    if (side == 1) {
+      bnd = wave_max(bnd);
+      if (lane == 0) L.wave_bound[wave] = bnd;
+    } else {
+      lo = wave_max(lo); hi = wave_min(hi);
+      if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
+    }
+  }
+  // slots: by class, in position order inside a class
+  int rank = 0;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const unsigned long long bal = __ballot(cls == k);
+    if (lane == 0) L.wave_cnt[k][wave] = __popcll(bal);
+    rank = cls == k ? lanes_below(bal) : rank;
+  }
+  __syncthreads();
+  QaqCounts cn;
+  {
+    int m[QAQ_NCLASS];
+    m[QC1] = 0;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      int before = 0, all = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) { const int x = __builtin_amdgcn_readfirstlane(L.wave_cnt[k][w]); before += w < wave ? x : 0; all += x; }
+      m[k] = all;
+      rank += cls == k ? before : 0;
+    }
+    cn.n3 = m[QC3]; cn.n2 = m[QC2]; cn.n4 = m[QC4]; cn.n8 = m[QC8]; cn.n1 = m[QC1];
+  }
+  if (cls >= 0) {
+    const int sl = cn.start(cls) + rank;
+    L.pos_of_slot[sl] = (uint16_t)(tid * ROW);
+    L.kept[sl] = (uint8_t)tid;
+  }
+  __syncthreads();
+  if (tid < n) {                // metadata, in slot order
+    const int p = L.kept[tid];
+    v.mm[side][gi0 + tid] = L.mm[p];
+    v.perm[side][gi0 + tid] = (uint8_t)p;
+    if (ONE) {
+      *(uint16_t*)(v.oidx[side] + (gi0 + tid) * 2) = *(const uint16_t*)L.oidx[p];
+      *(uint32_t*)(v.oval[side] + (gi0 + tid) * 2) = *(const uint32_t*)L.oval[p];
+    } else {
+      for (int k = 0; k < v.no2 && !csr; ++k) {
+        v.oidx[side][(gi0 + tid) * v.no2 + k] = L.oidx[p][k];
+        v.oval[side][(gi0 + tid) * v.no2 + k] = L.oval[p][k];
+      }
+    }
+  }
+  if (csr) put_new_runs<D, MAXO>(v, side, gi0, 0, n, L, tid);
+  if (tid == 0) put_tile_summary(v, side, tile_id, cn, L.wave_bound, L.wave_bound2);
+  pack_fresh<D, MAXO, HAS1>(side, qaq_tile_codes(v, side, b, h, tile), cn, L, tid);
+}
+
 // HAS1: the width set contains 1 (five classes); without it the fifth class costs nothing.
 // One tile side (unit bh, tile, side) of a build; tid: the thread (an argument: see k_build_listed).
 template <int D, bool ONE, bool HAS1>
-__device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, const int tile, const int side, const int tid) {
+__device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, const int bh, const int tile, const int side, const int tid) {
   constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2;
-  __shared__ BuildLds<D, MAXO> L;
   constexpr int NC = HAS1 ? QAQ_NCLASS : 4;
   auto bits_at = [](const QaqCounts& c, int s) { return HAS1 ? c.bits_of_slot(s) : c.bits_of_slot4(s); };
   constexpr int SROW = BuildLds<D, MAXO>::SROW;
@@ -859,7 +1140,6 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   const int len_before = qaq_seq_len(v, b, a.len_before), len_after = qaq_seq_len(v, b, a.len_after);   // of this sequence
   const int n_before = min(max(len_before - t0, 0), QAQ_TT);
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
-  if (n_after == 0) return;
   const int n_o = v.no2 / 2;
 
   if (a.mode == 1 && a.newbits[side] == nullptr) return;   // requantize: nothing to do for this side
@@ -880,23 +1160,19 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   // slot-order metadata, and for a requantize the widths that decide whether the tile is
   // touched at all), so that a rebuild costs two dependent round trips to memory, not three
   uint8_t* base = qaq_tile_codes(v, side, b, h, tile);
-  QaqCounts c_old;
-  c_old.n3 = c_old.n2 = c_old.n4 = c_old.n8 = c_old.n1 = 0;
+  QaqCounts c_old = qaq_load_counts(v, side, b, h, tile, n_before);
+  if (!HAS1) c_old.n1 = 0;
   int pos_old = 0;
   uint32_t mm_old = 0;
   uint8_t oi_old[MAXO];
   uint16_t ov_old[MAXO];
-  if (n_before > 0) {
-    c_old = qaq_load_counts(v, side, b, h, tile, n_before);
-    if (!HAS1) c_old.n1 = 0;
-    if (tid < n_before) {
-      const size_t gi = qaq_slot_index(v, b, h, tile, tid);
-      pos_old = v.perm[side][gi];
-      mm_old = v.mm[side][gi];
+  if (tid < n_before) {
+    const size_t gi = qaq_slot_index(v, b, h, tile, tid);
+    pos_old = v.perm[side][gi];
+    mm_old = v.mm[side][gi];
 #pragma unroll
-      for (int k = 0; k < MAXO; ++k)
-        if (k < v.no2 && !csr) { oi_old[k] = v.oidx[side][gi * v.no2 + k]; ov_old[k] = v.oval[side][gi * v.no2 + k]; }
-    }
+    for (int k = 0; k < MAXO; ++k)
+      if (k < v.no2 && !csr) { oi_old[k] = v.oidx[side][gi * v.no2 + k]; ov_old[k] = v.oval[side][gi * v.no2 + k]; }
   }
   // decode-step update: the inputs of the width rules that are indexed by position (this
   // step's scores, the window rows) are requested now as well; the value side keeps the window
@@ -932,7 +1208,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   }
 
   // metadata by position
-  if (n_before > 0 && tid < n_before) {
+  if (tid < n_before) {
     L.mm[pos_old] = mm_old;
     L.pos_of_slot[tid] = (uint16_t)pos_old;
     L.pos_old[tid] = (uint16_t)pos_old;
@@ -944,7 +1220,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   }
   // variable-length side store: the tile's pool is in position order and a token's entries never
   // move; thread `tid` fetches those of position tid (unused places of its row: channel 255)
-  const size_t pool0 = qaq_slot_index(v, b, h, tile, 0) * (size_t)v.no2;
+  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0), pool0 = gi0 * (size_t)v.no2;
   if (csr && tid < n_before) {
     const size_t pi = qaq_slot_index(v, b, h, tile, tid);
     const int cnt = v.ocnt[side][pi], st = v.ostart[side][pi];
@@ -959,22 +1235,16 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 
   // decode-step update: widths of the cached positions by the rules; the tile is left alone
   // if none of them moves and the new token is not in it
-  auto rule_width = [&](uint32_t m) {
-    const QaqRuleArgs& ru = a.rule;
+  auto ruled_width = [&](uint32_t m) {
     const float range = h2f((uint16_t)(m >> 16)) - h2f((uint16_t)(m & 0xffffu));
-    const float lhs = side == 0 ? range : range * pred;
-    const float thr = side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b);
-    int w = ru.bit_set[ru.nbits - 1];
-    for (int i = ru.nbits - 1; i >= 0; --i)
-      if (lhs <= ldexpf(thr, ru.bit_set[i])) w = ru.bit_set[i];
-    return w;
+    return rule_width(a.rule, side == 0 ? range : range * pred, side == 0 ? qaq_tau_k(a.rule, v, b, h) : qaq_c_v(a.rule, v, b));
   };
   int req_rule = 0;
   if (a.mode == 2) {
     bool changed = false, wider = false;
     if (tid < n_before) {
       const int oldb = L.bits_old[tid];
-      req_rule = rule_width(L.mm[tid]);
+      req_rule = ruled_width(L.mm[tid]);
       if (a.rule.out_bits[side]) a.rule.out_bits[side][(size_t)bh * a.len_after + t0 + tid] = (uint8_t)req_rule;
       if (req_rule < oldb) changed = true;
       else if (req_rule > oldb) { wider = true; if (a.orig[side]) changed = true; }
@@ -1009,35 +1279,28 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     L.bits_new[tid] = (uint8_t)nb;
     L.shf[tid] = (uint8_t)drop;
   }
-  // In a tile that has cached tokens the few positions to encode are gathered into a list,
-  // so that they fill the encoder's passes densely; a tile with none (most value-side tiles
-  // of a decode step without the unquantized copies) goes on after one barrier.
-  const bool listed = n_before > 0;
-  unsigned long long enc_bal = 0ull;
-  if (listed) {
-    enc_bal = __ballot(enc);
-    if (lane == 0) L.wave_need[0][wave] = __popcll(enc_bal);    // (this array's other use comes two barriers later)
-  }
+  // The few positions to encode are gathered into a list, so that they fill the encoder's passes
+  // densely; a tile with none (most value-side tiles of a decode step without the unquantized
+  // copies) goes on after one barrier.
+  const unsigned long long enc_bal = __ballot(enc);
+  if (lane == 0) L.wave_need[0][wave] = __popcll(enc_bal);    // (this array's other use comes two barriers later)
   __syncthreads();
 
   // encode: a quad of lanes per token, 64 tokens per pass; the rows of the next pass are
   // requested before the current pass is computed
-  int n_enc = n_after;
-  if (listed) {
+  const int n_enc = L.wave_need[0][0] + L.wave_need[0][1] + L.wave_need[0][2] + L.wave_need[0][3];
+  if (n_enc > 0) {                           // uniform: every thread has the same sum
     int off = 0;
     for (int w = 0; w < wave; ++w) off += L.wave_need[0][w];
     if (enc) L.freeslot[off + __popcll(enc_bal & ((1ull << lane) - 1ull))] = (uint16_t)tid;
-    n_enc = L.wave_need[0][0] + L.wave_need[0][1] + L.wave_need[0][2] + L.wave_need[0][3];
-    if (n_enc > 0) __syncthreads();          // uniform: every thread has the same sum
-  }
-  if (n_enc > 0) {
+    __syncthreads();
     typedef TokenEncoder<D, ONE> Enc;
     const float thr_lo = csr ? v.othr[(side * v.Hkv + h) * 2] : INFINITY;
     const float thr_hi = csr ? v.othr[(side * v.Hkv + h) * 2 + 1] : -INFINITY;
     constexpr int TPP = kThreads / 4;     // tokens per pass
     const int NP = (n_enc + TPP - 1) / TPP;
     const int c = tid & 3, gt = tid >> 2;
-    auto position = [&](int pass) { const int e = pass * TPP + gt; return listed ? (int)L.freeslot[min(e, QAQ_TT - 1)] : e; };
+    auto position = [&](int pass) { return (int)L.freeslot[min(pass * TPP + gt, QAQ_TT - 1)]; };
     // rows by position of this tile (the new tokens' first row is that of position n_before)
     const uint8_t* const new_rows = (const uint8_t*)a.newx[side] + ((long long)bh * a.n_new + (t0 - len_before)) * (2 * D);
     const uint8_t* const old_rows = (const uint8_t*)a.orig[side] + ((long long)bh * a.orig_tokens + t0) * (2 * D);
@@ -1050,7 +1313,6 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
       const uint8_t* src = (fresh ? new_rows : old_rows) + at;
 #pragma unroll
       for (int i = 0; i < Enc::NCH; ++i) {      // read once: streaming loads
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         const u32x4 t = __builtin_nontemporal_load((const u32x4*)(src + 64 * i));
         raw[i] = make_uint4(t.x, t.y, t.z, t.w);
       }
@@ -1079,7 +1341,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   // decode-step update, append by the rules: the width of a new token from the range the
   // encoder has just found (it was encoded at the widest width; narrowing drops low bits)
   if ((a.mode == 2 || a.mode == 3) && tid >= n_before && tid < n_after) {
-    const int w = rule_width(L.mm[tid]);
+    const int w = ruled_width(L.mm[tid]);
     if (a.rule.out_bits[side]) {
       if (a.mode == 2) a.rule.out_bits[side][(size_t)bh * a.len_after + t0 + tid] = (uint8_t)w;
       else a.rule.out_bits[side][(size_t)bh * a.n_new + (t0 + tid - len_before)] = (uint8_t)w;
@@ -1088,66 +1350,30 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     L.bits_new[tid] = (uint8_t)w;
   }
 
-  // side store of fresh tokens: order by channel (the one-per-end encoder leaves it so)
-  if (!ONE && tid >= n_before && tid < n_after && v.no2 > 1) {
-    for (int i = 1; i < v.no2; ++i) {
-      const uint8_t ki = L.oidx[tid][i];
-      const uint16_t vi = L.oval[tid][i];
-      int j = i - 1;
-      while (j >= 0 && L.oidx[tid][j] > ki) {
-        L.oidx[tid][j + 1] = L.oidx[tid][j];
-        L.oval[tid][j + 1] = L.oval[tid][j];
-        --j;
-      }
-      L.oidx[tid][j + 1] = ki;
-      L.oval[tid][j + 1] = vi;
-    }
-  }
+  if (!ONE && tid >= n_before && tid < n_after) sort_side_store(L.oidx[tid], L.oval[tid], v.no2);
 
-  // values: what the attention kernel needs as the fixed-point range of a tile -- the largest
-  // per-token step range/2^B (a 3-bit code is split into planes, the upper one weighs twice the
-  // step) and the largest magnitude an outlier correction (stored value minus reconstruction) can have
-  if (side == 1) {
-    float bnd = 0.0f;
+  // the tile's bounds
+  {
+    float bnd = 0.0f, lo = 0.0f, hi = INFINITY;
     if (tid < n_after) {
-      const int bits = L.bits_new[tid];
       const float mn = h2f((uint16_t)(L.mm[tid] & 0xffffu)), mx = h2f((uint16_t)(L.mm[tid] >> 16));
-      const float range = mx - mn;
-      bnd = ldexpf(range, bits == 3 ? -2 : -bits);
-      for (int k = 0; k < v.no2; ++k) {
-        if (L.oidx[tid][k] == 0xffu) continue;        // (variable-length side store: an unused place)
-        const float ov = h2f(L.oval[tid][k]);
-        bnd = fmaxf(bnd, fmaxf(fabsf(ov - mx), fabsf(ov - mn)) + range);
-      }
+      if (side == 1) bnd = value_bound(L.bits_new[tid], mn, mx, L.oidx[tid], L.oval[tid], v.no2);
+      else key_interval(a.rule, L.bits_new[tid], mx - mn, lo, hi);
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) bnd = fmaxf(bnd, __shfl_xor(bnd, o));
-    if (lane == 0) L.wave_bound[wave] = bnd;
-  } else {
-    // keys: thresholds for which every token keeps its width (Section 4.1 key rule as the
-    // comparison range <= threshold * 2^B): a token at width B widens below range / 2^B and
-    // narrows from range / 2^B' on, B' the next narrower width; the power-of-two scalings are exact
-    float lo = 0.0f, hi = INFINITY;
-    if (tid < n_after) {
-      const int bits = L.bits_new[tid];
-      const float range = h2f((uint16_t)(L.mm[tid] >> 16)) - h2f((uint16_t)(L.mm[tid] & 0xffffu));
-      int narrower = 0;
-      for (int i = 0; i < a.rule.nbits; ++i)
-        if (a.rule.bit_set[i] < bits) narrower = a.rule.bit_set[i];
-      if (bits < a.rule.bit_set[a.rule.nbits - 1]) lo = ldexpf(range, -bits);
-      if (narrower > 0) hi = ldexpf(range, -narrower);
+    if (side == 1) {
+      bnd = wave_max(bnd);
+      if (lane == 0) L.wave_bound[wave] = bnd;
+    } else {
+      lo = wave_max(lo); hi = wave_min(hi);
+      if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) { lo = fmaxf(lo, __shfl_xor(lo, o)); hi = fminf(hi, __shfl_xor(hi, o)); }
-    if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
   }
 
   // Slots: class by class (3, 2, 4, 8).  A cached token whose class is unchanged and whose
   // old slot still lies in its class's range stays where it is; the others (new tokens, tokens
   // that change class, tokens squeezed out by a moved class boundary) take the remaining
-  // slots of their class, in position order.  A freshly built tile thus comes out sorted by
-  // position inside each class, and a rebuild moves only as many tokens as it has to -- what
-  // is stored for the tokens that stay is not written again.
+  // slots of their class, in position order: a rebuild moves only as many tokens as it has to
+  // -- what is stored for the tokens that stay is not written again.
   const int cls = tid < n_after ? qaq_class_of_bits(L.bits_new[tid]) : -1;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -1167,22 +1393,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     cn.n3 = n[QC3]; cn.n2 = n[QC2]; cn.n4 = n[QC4]; cn.n8 = n[QC8]; cn.n1 = n[QC1];
   }
   int old_slot = -1;              // cached tokens: the slot held so far
-  if (n_before == 0) {
-    // nothing cached: a plain stable counting sort (rank inside the wavefront + wavefront offsets)
-    int my_rank = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const unsigned long long bal = __ballot(cls == c);
-      if (cls == c) my_rank = __popcll(bal & ((1ull << lane) - 1ull));
-    }
-    if (cls >= 0) {
-      int sl = cn.start(cls) + my_rank;
-      for (int w = 0; w < wave; ++w) sl += L.wave_cnt[cls][w];
-      L.slot_of_pos[tid] = (uint16_t)sl;
-      L.pos_of_slot[sl] = (uint16_t)tid;
-    }
-    __syncthreads();
-  } else {
+  {
     const bool was_cached = tid < n_before;
     old_slot = was_cached ? (int)L.slot_of_pos[tid] : -1;
     bool keep = false;
@@ -1233,18 +1444,17 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
   // the tokens to read back into a list.
   int n_moved = 0;
   {
-    const bool had = n_before > 0;
     const int n32 = cn.n32(), n32o = c_old.n32();
     bool same1, same4, same8;
     if (side == 0) {
       const QaqKRegions r = qaq_k_regions(cn, D), r0 = qaq_k_regions(c_old, D);
-      same1 = had && r.r1 == r0.r1;
-      same4 = had && n32 == n32o && r.r4 == r0.r4;
+      same1 = r.r1 == r0.r1;
+      same4 = n32 == n32o && r.r4 == r0.r4;
       same8 = same4 && c_old.n4 == cn.n4 && r.r8 == r0.r8;
     } else {
       const QaqVRegions r = qaq_v_regions(cn, D), r0 = qaq_v_regions(c_old, D);
-      same1 = had && r.r1 == r0.r1;
-      same4 = had && n32 == n32o && r.r4 == r0.r4;
+      same1 = r.r1 == r0.r1;
+      same4 = n32 == n32o && r.r4 == r0.r4;
       same8 = same4 && c_old.n4 == cn.n4 && r.r8 == r0.r8;
     }
     const bool same1b = same8 && c_old.n8 == cn.n8;
@@ -1252,7 +1462,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
       return !(L.shf[pos] & kKeptFlag) || (c == QC3 && !same1) || (c == QC4 && !same4) || (c == QC8 && !same8) ||
              (HAS1 && c == QC1 && !same1b);
     };
-    if (side == 1 && had) {
+    if (side == 1) {
       // by slot of the new layout
       const bool wr = tid < n_after && written(L.pos_of_slot[tid], qaq_class_of_bits(bits_at(cn, tid)));
       const unsigned long long bal = __ballot(wr && tid < n32);
@@ -1264,7 +1474,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     int nd = 0;
     if (tid < n_before) nd = L.bits_new[tid] > L.bits_old[tid] ? 2 : written(tid, cls) ? 1 : 0;
     if (tid < n_after) L.need[tid] = (uint8_t)nd;
-    if (side == 1 && had) {
+    if (side == 1) {
       const unsigned long long bal = __ballot(nd == 1);
       if (lane == 0) L.wave_cnt[0][wave] = __popcll(bal);
       __syncthreads();
@@ -1278,11 +1488,9 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
       n_moved = L.wave_cnt[0][0] + L.wave_cnt[0][1] + L.wave_cnt[0][2] + L.wave_cnt[0][3];
     }
     __syncthreads();
-    if (had) {
-      if (side == 0) unpack_tile<D, MAXO, HAS1>(side, base, c_old, L, tid);
-      else unpack_moved_v<D, MAXO, HAS1>(base, c_old, n_moved, L, tid);
-      __syncthreads();
-    }
+    if (side == 0) unpack_k<D, MAXO, HAS1>(base, c_old, L, tid);
+    else unpack_moved_v<D, MAXO, HAS1>(base, c_old, n_moved, L, tid);
+    __syncthreads();
   }
 
   // metadata in slot order, widths by position, class counts
@@ -1297,49 +1505,10 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
     }
     v.tags[side][qaq_slot_index(v, b, h, tile, tid)] = L.bits_new[tid];
   }
-  if (csr && n_after > n_before) {
-    // variable-length side store: the new tokens' entries go behind the tile's last one, in
-    // position order (a prefix sum of their counts)
-    const bool fresh = tid >= n_before && tid < n_after;
-    int cnt = 0;
-    if (fresh)
-      for (int k = 0; k < v.no2; ++k) cnt += L.oidx[tid][k] != 0xffu;
-    int inc = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(inc, o);
-      if (lane >= o) inc += y;
-    }
-    if (lane == 63) L.wave_ocnt[wave] = inc;
-    __syncthreads();
-    int start = inc - cnt;
-    for (int w = 0; w < wave; ++w) start += L.wave_ocnt[w];
-    if (n_before > 0) {
-      const size_t pl = qaq_slot_index(v, b, h, tile, n_before - 1);
-      start += (int)v.ostart[side][pl] + (int)v.ocnt[side][pl];
-    }
-    if (fresh) {
-      const size_t pi = qaq_slot_index(v, b, h, tile, tid);
-      v.ostart[side][pi] = (uint16_t)start;
-      v.ocnt[side][pi] = (uint8_t)cnt;
-      for (int k = 0; k < cnt; ++k) {          // the row is sorted by channel, unused places last
-        v.oidx[side][pool0 + start + k] = L.oidx[tid][k];
-        v.oval[side][pool0 + start + k] = L.oval[tid][k];
-      }
-    }
-  }
-  if (tid == 0) {
-    uint16_t* cp = v.counts + (((qaq_bh(v, b, h) * v.NT + tile) * 2 + side) * 4);
-    cp[QC3] = (uint16_t)cn.n3; cp[QC2] = (uint16_t)cn.n2; cp[QC4] = (uint16_t)cn.n4; cp[QC8] = (uint16_t)cn.n8;
-    if (side == 1)
-      v.vbound[qaq_bh(v, b, h) * v.NT + tile] = fmaxf(fmaxf(L.wave_bound[0], L.wave_bound[1]), fmaxf(L.wave_bound[2], L.wave_bound[3]));
-    else
-      ((float2*)v.kthr)[qaq_bh(v, b, h) * v.NT + tile] =
-          make_float2(fmaxf(fmaxf(L.wave_bound[0], L.wave_bound[1]), fmaxf(L.wave_bound[2], L.wave_bound[3])),
-                      fminf(fminf(L.wave_bound2[0], L.wave_bound2[1]), fminf(L.wave_bound2[2], L.wave_bound2[3])));
-  }
-  if (side == 1 && n_before > 0) pack_masked_v<D, MAXO, HAS1>(base, cn, c_old, L, tid);
-  else pack_tile<D, MAXO, HAS1>(side, base, cn, c_old, L, tid);
+  if (csr && n_after > n_before) put_new_runs<D, MAXO>(v, side, gi0, n_before, n_after, L, tid);
+  if (tid == 0) put_tile_summary(v, side, qaq_bh(v, b, h) * v.NT + tile, cn, L.wave_bound, L.wave_bound2);
+  if (side == 1) pack_masked_v<D, MAXO, HAS1>(base, cn, c_old, L, tid);
+  else pack_k<D, MAXO, HAS1>(base, cn, c_old, L, tid);
 }
 
 // Grid (units, tiles, 2 sides) -- heads are the fastest grid dimension: with tiles fastest and a
@@ -1348,7 +1517,11 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, const int bh, 
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
-  build_tile<D, ONE, HAS1>(a, (int)blockIdx.x, a.tile0 + (int)blockIdx.y, (int)blockIdx.z, (int)threadIdx.x);
+  __shared__ BuildLds<D, ONE ? 2 : QAQ_MAX_NO2> L;
+  const int tile = a.tile0 + (int)blockIdx.y, t0 = tile * QAQ_TT, b = (int)blockIdx.x / a.v.Hkv;
+  if (qaq_seq_len(a.v, b, a.len_after) <= t0) return;
+  if (qaq_seq_len(a.v, b, a.len_before) <= t0) fresh_tile<D, ONE, HAS1>(a, L, (int)blockIdx.x, tile, (int)blockIdx.z, (int)threadIdx.x);
+  else build_tile<D, ONE, HAS1>(a, L, (int)blockIdx.x, tile, (int)blockIdx.z, (int)threadIdx.x);
 }
 
 // The same for a list of tile sides (a.todo: entries (unit * NT + tile) * 2 + side, a.todo_count[0] of
@@ -1365,6 +1538,7 @@ template <int D, bool ONE>
 constexpr int listed_per_cu() { return D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4); }      // workgroups a compute unit takes
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_listed(QaqBuildArgs a) {
+  __shared__ BuildLds<D, ONE ? 2 : QAQ_MAX_NO2> L;
   const uint32_t n = *a.todo_count;
   if (blockIdx.x >= n) return;
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
@@ -1374,7 +1548,7 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
     const QaqBuildArgs* args = qaq_arguments_anew<QaqBuildArgs>();
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    build_tile<D, ONE, HAS1>(*args, (int)((e >> 1) / (uint32_t)args->v.NT), (int)((e >> 1) % (uint32_t)args->v.NT), (int)(e & 1u), tid);
+    build_tile<D, ONE, HAS1>(*args, L, (int)((e >> 1) / (uint32_t)args->v.NT), (int)((e >> 1) % (uint32_t)args->v.NT), (int)(e & 1u), tid);
     __syncthreads();        // the next tile side reuses the staging memory
   }
   // (every wavefront of a workgroup with entries has read the count: there was a barrier since)
@@ -1448,9 +1622,6 @@ __device__ __forceinline__ uint16_t key16_bits(uint32_t key) {     // fp16 bits 
   return (uint16_t)(k >= 0x8000u ? k - 0x8000u : ((0x8000u - k) | 0x8000u));
 }
 __device__ __forceinline__ uint32_t width_mask(int bits) { return 0x01010101u * ((1u << bits) - 1u); }
-__device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set bits of `mask` below this lane
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
 
 // The window's part of the value rule (Section 4.2) for two consecutive positions of one lane: largest
 // score over this step's row (the maximum over the G query heads, rounded to what the window stores:
@@ -1460,8 +1631,6 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set
 // ri0: index inside a ring row that p0 >= 0 (the lane's first position) counts from, row0: the same of the scores; lim[r]:
 // positions from there on that row r covers.
 struct Two { float x[2]; };
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <int W, typename RAW>
 __device__ __forceinline__ void predicted2_w(const QaqView& v, const int (&lim)[QAQ_MAX_WINDOW], int skip, size_t ri0, int p0,
                                              const Two (&g)[4], float (&s)[2], float (&m)[2]) {
