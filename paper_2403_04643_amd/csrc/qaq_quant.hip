@@ -1578,7 +1578,8 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 //
 // Measured, kernel trace, against four wavefronts per tile side with one token per lane: 8 x 32 heads x 4096 tokens
 // 42.1 -> 33.4 us, 16 x 8 heads x 8192 with 8 query heads each 39.3 -> 32.0, 8 heads x 512 tokens 11.9 -> 11.4; with
-// outliers by thresholds (the general kernel until then) 3 x 16 heads x 2500 34 -> 15.9.
+// outliers by thresholds (the general kernel until then) 3 x 16 heads x 2500 34 -> 15.9.  Of that the slots were 10 us,
+// 580 scalar instructions per wavefront for masks class by class; as compares per lane and one list of free slots: 33.4 -> 30.
 // ---------------------------------------------------------------------------------
 constexpr int kMaxCopy = 8192;
 constexpr int kUpdThreads = 128;
@@ -1593,15 +1594,17 @@ struct UpdLds {
   static constexpr int SROW = D / 4 + 1;   // dwords per staged row (odd stride: rows spread over the banks)
   static constexpr int PER_TOKEN = 4 * SROW + 8;
   uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list; before that 1 = a token keeps the slot
-  uint8_t freeslot[QAQ_TT];                // per class: the slots no token keeps, the first wavefront's from the front, the second's from the back
+  uint8_t freeslot[QAQ_TT];                // the slots no token keeps, in order: the first wavefront's from the front, the second's from the back
   uint32_t mask2[16], mask4[32], mask1b[16];   // value side: slots to write per unit of 16 (2-bit fields, 1-bit tokens) or half-unit of 8 (4-bit)
   unsigned long long written[QAQ_TT / 64 + 1];   // ... bit by slot
   uint32_t newrow[D / 4];                  // the appended token: its codes at the widest width, byte d = channel d
   uint32_t new_oi[2], new_ov[4];           // ... outlier channels, outlier values
   uint32_t new_mm;
   int new_no;                              // ... outliers (variable-length side store)
-  int w_cls[2][QAQ_NCLASS], w_need[2][QAQ_NCLASS], w_free[2][QAQ_NCLASS];      // per wavefront
+  int w_cls[2][QAQ_NCLASS];                // per wavefront
   int w_any[2], w_wide[2], w_moved[2];
+  int free0;                               // free slots among the first wavefront's
+  int first_free[QAQ_NCLASS];              // per class: free slots before its first slot (256 added: to be counted on from free0)
   float w_bnd[2], w_lo[2], w_hi[2];
   uint8_t units[2][32];                    // ... units with words to write
 };
@@ -1704,11 +1707,6 @@ __device__ __forceinline__ int class_start(const QaqCounts& c, int k) {        /
   if (HAS1) r = k == QC1 ? first1 : r;
   return r;
 }
-// bits [from, to) of a 64-bit mask, the ends clamped to it
-__device__ __forceinline__ unsigned long long span_mask(int from, int to) {
-  from = min(max(from, 0), 64); to = min(max(to, 0), 64);
-  return to > from ? (~0ull >> (64 - (to - from))) << from : 0ull;
-}
 
 // Value side: the fields of the slots to write are put into the words as they are stored (a word holds
 // one channel of up to 16 tokens; a word of a unit that did not exist starts from zero).  BF: field
@@ -1794,7 +1792,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   // step), most key sides leave after one load and fill in behind
   const int tile = blockIdx.y, side = 1 - (int)blockIdx.z;
   const int t0 = tile * QAQ_TT;
-  const int len_before = qaq_seq_len(v, b, a.len_before), len_after = qaq_seq_len(v, b, a.len_after);   // of this sequence
+  const int shorter = v.ragged ? v.shortfall[b] : 0;      // than the longest sequence
+  const int len_before = max(a.len_before - shorter, 0), len_after = max(a.len_after - shorter, 0);   // of this sequence
   const int n_before = min(max(len_before - t0, 0), QAQ_TT);
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
   if (bh == 0 && tile == 0 && side == 0 && tid == 0) a.todo_count[1] = 0u;      // (k_build_listed, if it has entries, leaves their number)
@@ -1858,7 +1857,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     const float* row0 = ru.scores + ((size_t)b * v.Hq + h * ru.G) * ru.score_stride + t0;
     int lim[QAQ_MAX_WINDOW];
 #pragma unroll
-    for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] = qaq_seq_len(v, b, ru.row_len[r]) - t0;
+    for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] = max(ru.row_len[r] - shorter, 0) - t0;
     if (len_after >= 2) {
       // (the lane that the tile's end falls into reads one position further down: the one before it is
       // another lane's as well, and gets the same value from both)
@@ -2064,7 +2063,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       if (narrower > 0) hi = fminf(hi, ldexpf(range, -narrower));
     }
   }
-  bnd = wave_max(bnd); lo = wave_max(lo); hi = wave_min(hi);
+  if (side == 1) bnd = wave_max(bnd);
+  else { lo = wave_max(lo); hi = wave_min(hi); }
   if (lane == 0) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -2124,73 +2124,35 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     }
   }
 
-  // ---- slots: a cached token that stays in its class keeps its index if the region still reaches it;
-  // the others -- tokens that change class, tokens squeezed out, the appended one -- take the free
-  // indices of their class in order ------------------------------------------------------------------------
-  // (whole wavefronts at a time, as masks: an old slot can be kept if it lies in a range that follows from the
-  // class counts alone)
-  int my_slot[J], need_rank[J];
-  int need_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, free_base[QAQ_NCLASS] = {0, 0, 0, 0, 0}, moved_here = 0;
-  unsigned long long need_bal[J], keep_bal[J];
+  // ---- slots: a cached token that stays in its class keeps its index if the region still reaches it; the others --
+  // tokens that change class, tokens squeezed out, the appended one -- take the free slots of their class in order.
+  // Which old slots can be kept follows from the class counts alone; free slots are in class order as they are, so
+  // they make one list, and only the tokens that move ask where their class begins in it. -------------------------
   const int shift4 = n32n - n32o, shift8 = shift4 + cn.n4 - c_old.n4, shift1 = shift8 + cn.n8 - c_old.n8;     // new slot less old slot of a kept token
+  auto kept_end = [&](int c, int first, int n_old, int n_new) { return (lost >> c) & 1u ? first : first + min(n_old, n_new); };
+  const int f8 = n32o + c_old.n4, f1 = f8 + c_old.n8;
+  const int e3 = kept_end(QC3, 0, c_old.n3, cn.n3), s2 = max(cn.n3, c_old.n3), e2 = min(n32o, n32n);
+  const int e4 = kept_end(QC4, n32o, c_old.n4, cn.n4), e8 = kept_end(QC8, f8, c_old.n8, cn.n8), e1 = kept_end(QC1, f1, c_old.n1, cn.n1);
+  int my_slot[J];
+  unsigned long long need_bal[J], live_bal[J];
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const int w0 = 64 * (J * wave + j);
-    unsigned long long can = 0ull;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int s0 = c_old.start(c), idx0 = c == QC2 ? max(cn.n3, c_old.n3) : s0;
-      const int end_new = c == QC3 ? cn.n3 : c == QC2 ? n32n : s0 + cn.count(c);
-      if (!((lost >> c) & 1u)) can |= span_mask(idx0 - w0, min(s0 + c_old.count(c), end_new) - w0);
-    }
-    keep_bal[j] = same_cls[j] & can;
     const int tok = tok0 + 64 * j;
-    int to = cls[j] == QC4 ? tok + shift4 : tok;
-    to = cls[j] == QC8 ? tok + shift8 : to;
-    if (HAS1) to = cls[j] == QC1 ? tok + shift1 : to;
+    bool can = (tok < e3) | ((tok >= s2) & (tok < e2)) | ((tok >= n32o) & (tok < e4)) | ((tok >= f8) & (tok < e8));
+    if (HAS1) can |= (tok >= f1) & (tok < e1);
+    int to = tok + (tok >= n32o ? shift4 : 0);
+    to = tok >= f8 ? tok + shift8 : to;
+    if (HAS1) to = tok >= f1 ? tok + shift1 : to;
     my_slot[j] = to;
-    need_rank[j] = 0;
-    need_bal[j] = 0ull;
-    if ((keep_bal[j] >> lane) & 1ull) L.m_of_slot[to] = 1u;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const unsigned long long bn = bal_cls[c][j] & ~keep_bal[j];
-      need_bal[j] |= bn;
-      if (bn) {                                   // uniform; most are empty
-        need_rank[j] = cls[j] == c ? need_base[c] + lanes_below(bn) : need_rank[j];
-        need_base[c] += __popcll(bn);
-      }
-    }
-    moved_here += __popcll(need_bal[j]);
+    const unsigned long long keep_bal = same_cls[j] & __ballot(can);
+    live_bal[j] = __ballot(tok < n_after);
+    need_bal[j] = live_bal[j] & ~keep_bal;
+    if ((keep_bal >> lane) & 1ull) L.m_of_slot[to] = 1u;
   }
+  if (lane == 0) L.w_moved[wave] = __popcll(need_bal[0]) + __popcll(need_bal[J - 1]);
+  static_assert(J == 2, "");
   __syncthreads();
-  unsigned long long free_bal[J];
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int w0 = 64 * (J * wave + j);
-    const unsigned long long open = __ballot(L.m_of_slot[tok0 + 64 * j] == 0u);
-    free_bal[j] = open & span_mask(-w0, n_after - w0);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int s0 = cn.start(c), n = cn.count(c);
-      const unsigned long long bf = open & span_mask(s0 - w0, s0 + n - w0);
-      if (bf) {
-        const int r = free_base[c] + lanes_below(bf);
-        if ((bf >> lane) & 1ull) L.freeslot[wave == 0 ? s0 + r : s0 + n - 1 - r] = (uint8_t)(tok0 + 64 * j);
-        free_base[c] += __popcll(bf);
-      }
-    }
-    // every free slot is taken by a token that moves: the slots to write
-    if (lane == 0) L.written[J * wave + j] = free_bal[j];
-  }
-  if (tid == 0) L.written[QAQ_TT / 64] = 0ull;
-  if (lane == 0) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) { L.w_need[wave][c] = need_base[c]; L.w_free[wave][c] = free_base[c]; }
-    L.w_moved[wave] = moved_here;
-  }
-  __syncthreads();
-  const int n_moved = __builtin_amdgcn_readfirstlane(L.w_moved[0] + L.w_moved[1]);
+  const int moved0 = __builtin_amdgcn_readfirstlane(L.w_moved[0]), n_moved = moved0 + __builtin_amdgcn_readfirstlane(L.w_moved[1]);
   if (n_moved > a.max_moved) {
     // nothing of the cache has been written yet (the window row and the width outputs are the same
     // numbers when the general kernel writes them again)
@@ -2198,18 +2160,72 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     return;
   }
   {
-    int m0 = wave ? L.w_moved[0] : 0;
+    int m = wave ? moved0 : 0, r = 0;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      if ((need_bal[j] >> lane) & 1ull) {
-        const int c = cls[j], r = need_rank[j] + (wave ? L.w_need[0][c] : 0), f0 = L.w_free[0][c];
-        my_slot[j] = L.freeslot[r < f0 ? cn.start(c) + r : cn.start(c) + cn.count(c) - 1 - (r - f0)];
-        const int m = m0 + lanes_below(need_bal[j]);
-        mv[m] = (uint32_t)(tok0 + 64 * j) | ((uint32_t)my_slot[j] << 8) | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
-        mv_mm[m] = mm[j];
-        L.m_of_slot[my_slot[j]] = (uint8_t)m;
+      const int slot = tok0 + 64 * j;
+      const unsigned long long free_bal = __ballot(L.m_of_slot[slot] == 0u) & live_bal[j];
+      const int below = r + lanes_below(free_bal);
+      if ((free_bal >> lane) & 1ull) L.freeslot[wave == 0 ? below : QAQ_TT - 1 - below] = (uint8_t)slot;
+      if (slot == cn.n3 || slot == n32n || slot == n32n + cn.n4) {      // (a class that has no slot is never asked for)
+        const int x = below + (wave ? QAQ_TT : 0);
+        if (slot == cn.n3) L.first_free[QC2] = x;
+        if (slot == n32n) L.first_free[QC4] = x;
+        if (slot == n32n + cn.n4) L.first_free[QC8] = x;
       }
-      m0 += __popcll(need_bal[j]);
+      if (HAS1 && slot == cn.first1()) L.first_free[QC1] = below + (wave ? QAQ_TT : 0);
+      r += __popcll(free_bal);
+      // every free slot is taken by a token that moves: the slots to write
+      if (lane == 0) L.written[J * wave + j] = free_bal;
+      if ((need_bal[j] >> lane) & 1ull) {
+        const int at = m + lanes_below(need_bal[j]);
+        mv[at] = (uint32_t)slot | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
+        mv_mm[at] = mm[j];
+      }
+      m += __popcll(need_bal[j]);
+    }
+    if (tid == 0) { L.written[QAQ_TT / 64] = 0ull; L.free0 = r; }
+  }
+  __syncthreads();
+  if (wave == 0) {            // the moved tokens' slots, a token per lane
+    const int free0 = __builtin_amdgcn_readfirstlane(L.free0);
+    int used[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) used[c] = 0;
+#pragma unroll 1
+    for (int m0 = 0; m0 < n_moved; m0 += 64) {
+      const bool live = m0 + lane < n_moved;
+      const int m = min(m0 + lane, n_moved - 1);
+      const uint32_t e = mv[m];
+      const int c = live ? qaq_class_of_bits((int)(e >> 28)) : -1;
+      int rank = 0;
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const unsigned long long bal = __ballot(c == k);
+        rank = c == k ? used[k] + lanes_below(bal) : rank;
+        used[k] += __popcll(bal);
+      }
+      const int x = c > 0 ? L.first_free[c] : 0;
+      const int f = (x & (QAQ_TT - 1)) + (x >= QAQ_TT ? free0 : 0) + rank;
+      const int slot = L.freeslot[f < free0 ? f : QAQ_TT - 1 - (f - free0)];
+      if (live) { mv[m] = e | ((uint32_t)slot << 8); L.m_of_slot[slot] = (uint8_t)m; }
+    }
+  } else if (side == 1) {     // value side: which slots are written, by unit of the region they are in
+    auto slots_from = [&](int first) -> uint32_t {       // slots [first, first + 16) of those to write
+      const uint32_t* p = (const uint32_t*)L.written + (min(first, QAQ_TT) >> 5);
+      return __builtin_amdgcn_alignbit(p[1], p[0], (uint32_t)first & 31u) & 0xffffu;
+    };
+    if (lane < 16) L.mask2[lane] = slots_from(16 * lane);
+    else if (lane < 48) L.mask4[lane - 16] = slots_from(n32n + 8 * (lane - 16)) & 0xffu;
+    else if (HAS1) L.mask1b[lane - 48] = slots_from(cn.first1() + 16 * (lane - 48));
+  }
+  __syncthreads();
+  {
+    int m = wave ? moved0 : 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if ((need_bal[j] >> lane) & 1ull) my_slot[j] = (int)((mv[m + lanes_below(need_bal[j])] >> 8) & 0xffu);
+      m += __popcll(need_bal[j]);
     }
   }
   // what is left to write of a token, in one register: position, slot, width; whether slot or width changed
@@ -2221,18 +2237,6 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     const bool live = tok < n_after, need = ((need_bal[j] >> lane) & 1ull) != 0ull, is_new = has_new & (tok == n_before);
     left[j] = (uint32_t)pos[j] | ((uint32_t)(my_slot[j] & 0xff) << 8) | ((uint32_t)nb[j] << 16) | ((live & ((my_slot[j] != tok) | need)) ? kMoves : 0u) |
               ((live & ((nb[j] != ob[j]) | is_new)) ? kRetag : 0u);
-  }
-  __syncthreads();
-
-  // ---- value side: which slots are written, by unit of the region they are in ----------------------------
-  if (side == 1) {
-    auto slots_from = [&](int first) -> uint32_t {       // slots [first, first + 16) of those to write
-      const uint32_t* p = (const uint32_t*)L.written + (min(first, QAQ_TT) >> 5);
-      return __builtin_amdgcn_alignbit(p[1], p[0], (uint32_t)first & 31u) & 0xffffu;
-    };
-    if (tid < 16) L.mask2[tid] = slots_from(16 * tid);
-    else if (tid < 48) L.mask4[tid - 16] = slots_from(n32n + 8 * (tid - 16)) & 0xffu;
-    else if (HAS1 && tid < 64) L.mask1b[tid - 48] = slots_from(cn.first1() + 16 * (tid - 48));
   }
 
   // ---- codes of the moved tokens -> LDS, at the new width: sixteen channels per work item --------------------
