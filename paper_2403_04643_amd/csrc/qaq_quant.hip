@@ -2610,8 +2610,11 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
 // belongs to the token alone.  Values: an item is (unit of 16 tokens, eight channels) -- eight words, each
 // one channel of the 16 tokens, turned into rows by 4x4 byte transposes; the D/8 lanes of a unit read its
 // 4 D bytes between them.
-// 8 sequences x 32 heads x 4096 tokens x 128 channels, all 8-bit (805 MB): 1232 us code by code through
-// an LDS staging tile, 209 us (3.8 TB/s; a 4 GiB copy: 4.85) so; all 3-bit 1325 and 130.
+// The stores want wavefronts in flight more than long ones: loops are not unrolled, so that 64 registers (80 where a token has
+// more than two outliers) let 32 of them live on a compute unit; unrolled they took 104 and half as many did.
+// 8 sequences x 32 heads x 4096 tokens x 128 channels, all 8-bit (805 MB): 1232 us code by code through an LDS staging
+// tile, 209 us (3.8 TB/s; a 4 GiB copy: 4.85) with whole words at 16 wavefronts, 175 (4.6) at 32; widths of mean 2.5 / 2.1
+// (615 MB) 203 -> 101; 64 channels, mean 4 / 3, 112 -> 68; three outliers per end 250 -> 174.
 
 // eight codes (one per byte, channels in order) -> eight fp16 values, with the outliers among these channels
 // put in: ch0 = first channel, NO2 outlier entries per token (idx: one byte each, 0xff = unused)
@@ -2645,7 +2648,7 @@ struct DequantToken {
 
 // NO2: outlier entries per token: 0, 2, or up to 8 (the run-time count v.no2; also the variable-length store)
 template <int D, int NO2>
-__global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
+__global__ __launch_bounds__(kThreads, (NO2 > 2 ? 6 : 8)) void k_dequant(QaqDequantArgs a) {
   constexpr int NI = NO2 ? (NO2 + 3) / 4 : 1, NV = NO2 ? (NO2 + 1) / 2 : 1;
   constexpr int LPT = D / 8, KS = D / 64;
   __shared__ float s_scale[QAQ_TT], s_mn[QAQ_TT];
@@ -2720,7 +2723,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
   const int n32 = c.n32(), first8 = n32 + c.n4, first1 = c.first1();
   if (side == 0) {
     const QaqKRegions r = qaq_k_regions(c, D);
-#pragma unroll 2
+#pragma unroll 1
     for (int it = tid; it < n_tok * LPT; it += kThreads) {
       const int s = it / LPT, c8 = it % LPT;           // channels 8 c8 .. +7: half `hf` of slice q
       const int hf = c8 & 1, q = ((c8 >> 1) & 3) * KS + (c8 >> 3);
@@ -2757,7 +2760,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       l[k] = low ? *(const uint32_t*)(base + r.r1 + (uint32_t)u * (2 * D) + 4u * (uint32_t)((n0 + k) * (D / 32) + (cg >> 1))) >> (4 * (cg & 1)) : 0u;
-#pragma unroll
+#pragma unroll 1
     for (int vq = 0; vq < 4; ++vq) {
       uint32_t x[4], tl[4], th[4], ll[4], lh[4];
 #pragma unroll
@@ -2789,7 +2792,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
     uint32_t w[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) w[k] = *(const uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D) + 4u * (uint32_t)((n0 + k) * (D / 16) + cg));
-#pragma unroll
+#pragma unroll 1
     for (int vq = 0; vq < 2; ++vq) {
       uint32_t x[4], tl[4], th[4];
 #pragma unroll
@@ -2805,7 +2808,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
       }
     }
   }
-#pragma unroll 2
+#pragma unroll 1
   for (int it = tid; it < c.n8 * LPT; it += kThreads) {        // token-major bytes
     const int i8 = it / LPT, c8 = it % LPT;
     const uint2 w = *(const uint2*)(base + r.r8 + (uint32_t)i8 * D + 8u * (uint32_t)c8);
@@ -2817,7 +2820,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant(QaqDequantArgs a) {
 #pragma unroll
     for (int k = 0; k < 8; ++k)
       l[k] = *(const uint32_t*)(base + r.r1b + (uint32_t)u * (2 * D) + 4u * (uint32_t)((n0 + k) * (D / 32) + (cg >> 1))) >> (4 * (cg & 1));
-#pragma unroll
+#pragma unroll 1
     for (int vq = 0; vq < 4; ++vq) {
       uint32_t x[4], tl[4], th[4];
 #pragma unroll
