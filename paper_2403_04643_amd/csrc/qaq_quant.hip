@@ -98,42 +98,29 @@ __device__ void tile_load(const QaqView& v, int side, int b, int h, int tile, in
 }
 
 // ---------------------------------------------------------------------------------
-// Tile build (append / requantize).  Codes travel through LDS as one byte per
-// (position, channel); both directions between that staging form and the stored code
-// planes work on whole 32-bit words: one AND and one shift move four codes, and the
-// token-transposed value planes go through 4x4 byte transposes in registers.
+// Tile build (append / requantize): a tile side is written as a whole.  Codes travel through LDS as one byte per
+// (position, channel), a token's code in the upper bits of its byte; both directions between that staging form and the
+// stored code planes work on whole 32-bit words: shifts and masks take four codes along, and the token-transposed value
+// planes go through 4x4 byte transposes in registers.
 // ---------------------------------------------------------------------------------
 template <int D, int MAXO = QAQ_MAX_NO2>   // MAXO: outlier entries held per token (2 in the common one-per-end build)
 struct BuildLds {
   static constexpr int SROW = D / 4 + 1;   // dwords per staged row; the odd stride spreads rows over the banks
-  uint32_t stage[QAQ_TT * SROW];           // byte d of row pos = code of channel d
+  uint32_t stage[(QAQ_TT + 1) * SROW];     // byte d of row pos = code of channel d (the last row: nobody's)
   uint32_t mm[QAQ_TT];                     // fp16 min | fp16 max << 16, by position
   uint8_t oidx[QAQ_TT][MAXO];              // outlier channels, by position
   uint16_t oval[QAQ_TT][MAXO];             // outlier fp16 values
-  uint8_t bits_old[QAQ_TT];
-  uint8_t bits_new[QAQ_TT];
-  uint8_t shf[QAQ_TT];                     // by position: low bits a staged code still has to drop (narrowing);
-                                           // bit 7: the token keeps its slot and its width (what is stored for it stays valid)
-  uint8_t kept[QAQ_TT];                    // by slot: a token stays here
-  alignas(16) uint16_t pos_of_slot[QAQ_TT];   // (a tile that held nothing: byte offset of the staged row)
-  uint16_t slot_of_pos[QAQ_TT];
-  uint16_t freeslot[QAQ_TT];               // per class, in slot order: the slots nobody keeps
-  uint16_t pos_old[QAQ_TT];                // position of the token that held a slot before
-  uint8_t need[QAQ_TT];                    // by position: 1 = the stored code of this cached token is read again
-                                           // (it moves), 2 = it is re-encoded from the unquantized copy, 0 = neither
-  uint32_t mask2[16];                      // value side, per unit of 16 slots of the 2-bit field region: slots whose
-                                           // fields are written (bit i = slot 16u+i)
-  uint32_t mask4[32];                      // ... per half-unit of 8 slots of the 4-bit region
-  uint32_t mask1b[16];                     // ... per unit of 16 slots of the 1-bit tokens' region
+  uint8_t bits_old[QAQ_TT];                // widths, by position
+  uint8_t order[QAQ_TT];                   // positions to encode; later the position of the token that holds a slot
+  alignas(16) uint16_t row_of_slot[QAQ_TT];      // byte offset of the staged row of the token that holds a slot
+  alignas(16) uint16_t row_of_old[QAQ_TT];       // ... that held it before
   int wave_cnt[QAQ_NCLASS][4];
-  int wave_need[QAQ_NCLASS][4];
-  int wave_free[QAQ_NCLASS][4];
+  int wave_enc[4];
   float wave_bound[4];
   float wave_bound2[4];
   int wave_ocnt[4];                        // variable-length side store: entries of the new tokens per wavefront
   int wave_wide[4];                        // widenings asked for, per wavefront
 };
-constexpr int kKeptFlag = 0x80;
 
 __device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set bits of `mask` below this lane
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -497,275 +484,6 @@ struct TokenEncoder {
   }
 };
 
-// Keys: stored code planes of one tile side -> staged bytes (old widths, nothing dropped yet), for
-// the cached tokens whose codes are read again (L.need == 1); whole words / units that hold
-// none of them are not touched.
-template <int D, int MAXO, bool HAS1>
-__device__ void unpack_k(const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
-  constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
-  const int n32 = c.n32();
-  const QaqKRegions r = qaq_k_regions(c, D);
-  for (int it = tid; it < n32 * NQ; it += kThreads) {
-    const int s = it / NQ, q = it % NQ;
-    const int pos = L.pos_old[s];
-    if (L.need[pos] != 1) continue;
-    const bool three = s < c.n3;
-    const uint32_t w2 = *(const uint32_t*)(base + r.r2 + 4u * (uint32_t)it);
-    uint32_t w1 = 0;
-    if (three) w1 = *(const uint32_t*)(base + r.r1 + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1)) >> (4 * (q & 1));
-    uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      uint32_t code = (w2 >> (2 * v)) & 0x03030303u;
-      if (three) code = (code << 1) | ((w1 >> v) & 0x01010101u);
-      row[v] = code;
-    }
-  }
-  for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
-    const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
-    const int pos = L.pos_old[n32 + i4];
-    if (L.need[pos] != 1) continue;
-    const uint32_t w = *(const uint32_t*)(base + r.r4 + 4u * (uint32_t)it);
-    uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
-    row[0] = w & 0x0f0f0f0fu;
-    row[1] = (w >> 4) & 0x0f0f0f0fu;
-  }
-  for (int it = tid; it < c.n8 * (D / 4); it += kThreads) {
-    const int i8 = it / (D / 4), jj = it % (D / 4), q = jj >> 2, v = jj & 3;
-    const int pos = L.pos_old[n32 + c.n4 + i8];
-    if (L.need[pos] != 1) continue;
-    const uint32_t w = *(const uint32_t*)(base + r.r8 + 4u * (uint32_t)it);
-    L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + v] = w ^ 0x80808080u;
-  }
-  for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
-    const int i1 = it / (D / 32), jj = it % (D / 32);
-    const int pos = L.pos_old[c.first1() + i1];
-    if (L.need[pos] != 1) continue;
-    const uint32_t w = *(const uint32_t*)(base + r.r1b + 4u * (uint32_t)it);
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int q = 2 * jj + hh;
-      uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) row[v] = (w >> (4 * hh + v)) & 0x01010101u;
-    }
-  }
-}
-
-// Value side: codes of the cached tokens that move, token by token.  The list holds their
-// positions (L.freeslot) and the slots they had (L.kept, reused); a work item is (token, four
-// channels), and every code is read with the per-element accessor of the layout -- a tile in
-// a decode step moves a handful of tokens, far fewer than its units hold.
-template <int D, int MAXO, bool HAS1>
-__device__ void unpack_moved_v(const uint8_t* base, const QaqCounts& c, int n_moved, BuildLds<D, MAXO>& L, int tid) {
-  constexpr int SROW = BuildLds<D, MAXO>::SROW;
-  const QaqVRegions r = qaq_v_regions(c, D);
-  for (int e = tid; e < n_moved * (D / 4); e += kThreads) {
-    const int m = e / (D / 4), c4 = e % (D / 4);
-    const int pos = L.freeslot[m], slot = L.kept[m];
-    uint32_t w = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w |= load_code<D, HAS1>(1, base, c, r.r2, r.r1, r.r4, r.r8, r.r1b, slot, 4 * c4 + k) << (8 * k);
-    L.stage[pos * SROW + c4] = w;
-  }
-}
-
-// Keys: staged bytes -> stored code planes of one tile side, in the new slot order; codes that
-// narrow drop their low bits here (the coarser grid's segments contain the finer one's).
-// c0 = the class counts the tile had before: a
-// word whose tokens all keep slot and width, in a region that has not moved, is left alone.
-template <int D, int MAXO, bool HAS1>
-__device__ void pack_k(uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
-  constexpr int SROW = BuildLds<D, MAXO>::SROW, NQ = D / 16, KS = D / 64;
-  const int n32 = c.n32();
-  const bool same32 = c0.n32() == n32;
-  const QaqKRegions r = qaq_k_regions(c, D), r0 = qaq_k_regions(c0, D);
-  const bool same1 = r.r1 == r0.r1;
-  const bool same4 = same32 && r.r4 == r0.r4;
-  const bool same8 = same4 && c0.n4 == c.n4 && r.r8 == r0.r8;
-  for (int it = tid; it < n32 * NQ; it += kThreads) {
-    const int s = it / NQ, q = it % NQ;
-    const int pos = L.pos_of_slot[s];
-    const int f = L.shf[pos];
-    if (f & kKeptFlag) continue;
-    const int sh = (f & 7) + (s < c.n3 ? 1 : 0);
-    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-    uint32_t w = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x03030303u) << (2 * v);
-    *(uint32_t*)(base + r.r2 + 4u * (uint32_t)it) = w;
-  }
-  for (int it = tid; it < c.n3 * (D / 32); it += kThreads) {
-    const int s = it / (D / 32), jj = it % (D / 32);
-    const int pos = L.pos_of_slot[s];
-    const int f = L.shf[pos];
-    if (same1 && (f & kKeptFlag)) continue;
-    const int sh = f & 7;
-    uint32_t w = 0;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int q = 2 * jj + hh;
-      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
-    }
-    *(uint32_t*)(base + r.r1 + 4u * (uint32_t)it) = w;
-  }
-  for (int it = tid; it < c.n4 * (D / 8); it += kThreads) {
-    const int i4 = it / (D / 8), jj = it % (D / 8), q = jj >> 1, dw = jj & 1;
-    const int pos = L.pos_of_slot[n32 + i4];
-    const int f = L.shf[pos];
-    if (same4 && (f & kKeptFlag)) continue;
-    const int sh = f & 7;
-    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS) + 2 * dw];
-    *(uint32_t*)(base + r.r4 + 4u * (uint32_t)it) = ((row[0] >> sh) & 0x0f0f0f0fu) | (((row[1] >> sh) & 0x0f0f0f0fu) << 4);
-  }
-  for (int it = tid; it < c.n8 * NQ; it += kThreads) {        // one slice (16 bytes) per item
-    const int i8 = it / NQ, q = it % NQ;
-    const int pos = L.pos_of_slot[n32 + c.n4 + i8];
-    if (same8 && (L.shf[pos] & kKeptFlag)) continue;
-    const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-    *(uint4*)(base + r.r8 + 16u * (uint32_t)it) =
-        make_uint4(row[0] ^ 0x80808080u, row[1] ^ 0x80808080u, row[2] ^ 0x80808080u, row[3] ^ 0x80808080u);
-  }
-  const bool same1b = same8 && c0.n8 == c.n8;           // then r1b has not moved either
-  for (int it = tid; HAS1 && it < c.n1 * (D / 32); it += kThreads) {
-    const int i1 = it / (D / 32), jj = it % (D / 32);
-    const int pos = L.pos_of_slot[c.first1() + i1];
-    const int f = L.shf[pos];
-    if (same1b && (f & kKeptFlag)) continue;
-    const int sh = f & 7;
-    uint32_t w = 0;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const int q = 2 * jj + hh;
-      const uint32_t* row = &L.stage[pos * SROW + 16 * (q % KS) + 4 * (q / KS)];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) w |= ((row[v] >> sh) & 0x01010101u) << (4 * hh + v);
-    }
-    *(uint32_t*)(base + r.r1b + 4u * (uint32_t)it) = w;
-  }
-}
-
-// ---------------------------------------------------------------------------------
-// Tile build: append new tokens and / or move cached tokens to other widths, then
-// write the tile side back in class order.
-// Value side of a rebuild: only the fields of the slots in L.mask2 / L.mask4 are written,
-// into the words as they are stored (read-modify-write; a word of a unit that did not exist,
-// or whose region has moved, starts from zero -- then the masks hold all its slots).  Fields
-// of slots past the end of a region are left as they are: no reader looks at them.
-template <int D, int MAXO, bool HAS1>
-__device__ void pack_masked_v(uint8_t* base, const QaqCounts& c, const QaqCounts& c0, const BuildLds<D, MAXO>& L, int tid) {
-  constexpr int SROW = BuildLds<D, MAXO>::SROW;
-  const int n32 = c.n32(), n32o = c0.n32();
-  const QaqVRegions r = qaq_v_regions(c, D), r0 = qaq_v_regions(c0, D);
-  const bool same1 = r.r1 == r0.r1;
-  const bool same4 = n32 == n32o && r.r4 == r0.r4;
-  const bool same8 = same4 && c0.n4 == c.n4 && r.r8 == r0.r8;
-  const int units2_old = (n32o + 15) / 16;
-  const int units1_old = same1 ? (c0.n3 + 15) / 16 : 0;
-  const int half4_old = same4 ? (c0.n4 + 7) / 8 : 0;
-  for (int it = tid; it < ((n32 + 15) / 16) * (D / 4); it += kThreads) {
-    const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-    uint32_t m = L.mask2[u];
-    if (!m) continue;
-    uint32_t* wp = (uint32_t*)(base + r.r2 + (uint32_t)u * (4 * D)) + (4 * (c4 & 3)) * (D / 16) + cg;
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = u < units2_old ? wp[k * (D / 16)] : 0u;
-    while (m) {
-      const int i = __ffs(m) - 1;
-      m &= m - 1;
-      const int sl = 16 * u + i;
-      const int pos = L.pos_of_slot[sl];
-      const uint32_t w = (L.stage[pos * SROW + c4] >> ((L.shf[pos] & 7) + (sl < c.n3 ? 1 : 0))) & 0x03030303u;
-      const int bp = 8 * (i & 3) + 2 * (i >> 2);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(3u << bp)) | (((w >> (8 * k)) & 3u) << bp);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wp[k * (D / 16)] = o[k];
-  }
-  for (int it = tid; it < ((c.n3 + 15) / 16) * (D / 8); it += kThreads) {
-    const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
-    const int in3 = c.n3 - 16 * u;                       // slots of this unit inside the 3-bit class
-    uint32_t m = L.mask2[u] & (in3 >= 16 ? 0xffffu : (1u << in3) - 1u);
-    if (!m) continue;
-    uint32_t* wp = (uint32_t*)(base + r.r1 + (uint32_t)u * (2 * D)) + (4 * n4) * (D / 32) + cgp;
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = u < units1_old ? wp[k * (D / 32)] : 0u;
-    while (m) {
-      const int i = __ffs(m) - 1;
-      m &= m - 1;
-      const int pos = L.pos_of_slot[16 * u + i];
-      const int sh = L.shf[pos] & 7;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const uint32_t w = (L.stage[pos * SROW + 4 * (2 * cgp + hh) + n4] >> sh) & 0x01010101u;
-        const int bp = 8 * (i & 3) + 4 * hh + (i >> 2);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(1u << bp)) | (((w >> (8 * k)) & 1u) << bp);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wp[k * (D / 32)] = o[k];
-  }
-  for (int it = tid; it < ((c.n4 + 7) / 8) * (D / 4); it += kThreads) {
-    const int hu = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-    uint32_t m = L.mask4[hu];
-    if (!m) continue;
-    uint32_t* wp = (uint32_t*)(base + r.r4 + (uint32_t)hu * (4 * D)) + (4 * (c4 & 3)) * (D / 16) + cg;
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = hu < half4_old ? wp[k * (D / 16)] : 0u;
-    while (m) {
-      const int i = __ffs(m) - 1;
-      m &= m - 1;
-      const int pos = L.pos_of_slot[n32 + 8 * hu + i];
-      const uint32_t w = (L.stage[pos * SROW + c4] >> (L.shf[pos] & 7)) & 0x0f0f0f0fu;
-      const int bp = 8 * (i & 3) + 4 * (i >> 2);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(15u << bp)) | (((w >> (8 * k)) & 15u) << bp);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wp[k * (D / 16)] = o[k];
-  }
-  for (int it = tid; it < c.n8 * (D / 16); it += kThreads) {    // 16 bytes per item
-    const int i8 = it / (D / 16), dq = 4 * (it % (D / 16));
-    const int pos = L.pos_of_slot[n32 + c.n4 + i8];
-    if (same8 && (L.shf[pos] & kKeptFlag)) continue;
-    const uint32_t* row = &L.stage[pos * SROW + dq];
-    *(uint4*)(base + r.r8 + 16u * (uint32_t)it) = make_uint4(row[0], row[1], row[2], row[3]);
-  }
-  const bool same1b = same8 && c0.n8 == c.n8;
-  const int units1b_old = same1b ? (c0.n1 + 15) / 16 : 0;
-  for (int it = tid; HAS1 && it < ((c.n1 + 15) / 16) * (D / 8); it += kThreads) {
-    const int u = it / (D / 8), rest = it % (D / 8), cgp = rest >> 2, n4 = rest & 3;
-    uint32_t m = L.mask1b[u];
-    if (!m) continue;
-    uint32_t* wp = (uint32_t*)(base + r.r1b + (uint32_t)u * (2 * D)) + (4 * n4) * (D / 32) + cgp;
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = u < units1b_old ? wp[k * (D / 32)] : 0u;
-    while (m) {
-      const int i = __ffs(m) - 1;
-      m &= m - 1;
-      const int pos = L.pos_of_slot[c.first1() + 16 * u + i];
-      const int sh = L.shf[pos] & 7;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const uint32_t w = (L.stage[pos * SROW + 4 * (2 * cgp + hh) + n4] >> sh) & 0x01010101u;
-        const int bp = 8 * (i & 3) + 4 * hh + (i >> 2);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = (o[k] & ~(1u << bp)) | (((w >> (8 * k)) & 1u) << bp);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) wp[k * (D / 32)] = o[k];
-  }
-}
-
 // ---------------------------------------------------------------------------------
 // Widenings asked for in a tile side: every wavefront leaves its count in LDS (`per_wave`,
 // four entries); after the next barrier add_widenings, called by one thread, adds them to the
@@ -781,7 +499,7 @@ __device__ __forceinline__ void add_widenings(const QaqView& v, size_t tile_side
   if (n) v.refused[tile_side * 2 + (served ? 1 : 0)] += (unsigned int)n;
 }
 
-// What the general and the fresh build have in common, for one position's thread.
+// What both forms of the build have in common, for one position's thread.
 // Width by the rules of Section 4.1: the narrowest that satisfies lhs <= threshold * 2^B, else the widest
 __device__ __forceinline__ int rule_width(const QaqRuleArgs& ru, float lhs, float thr) {
   int w = ru.bit_set[ru.nbits - 1];
@@ -888,7 +606,7 @@ __device__ __forceinline__ void pack_fresh(int side, uint8_t* base, const QaqCou
   constexpr int NQ = D / 16, KS = D / 64;
   const int n32 = c.n32();
   const uint8_t* const staged = (const uint8_t*)L.stage;
-  auto row_of = [&](int slot) { return (const uint32_t*)(staged + L.pos_of_slot[slot]); };
+  auto row_of = [&](int slot) { return (const uint32_t*)(staged + L.row_of_slot[slot]); };
   if (side == 0) {
     const QaqKRegions r = qaq_k_regions(c, D);
     auto slice = [&](const uint32_t* row, int q) { return row + (16 * (q % KS) + 4 * (q / KS)); };
@@ -929,7 +647,7 @@ __device__ __forceinline__ void pack_fresh(int side, uint8_t* base, const QaqCou
   const QaqVRegions r = qaq_v_regions(c, D);
   for (int it = tid; it < ((n32 + 15) / 16) * (D / 4); it += kThreads) {
     const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
-    const uint4* offs = (const uint4*)&L.pos_of_slot[16 * u];
+    const uint4* offs = (const uint4*)&L.row_of_slot[16 * u];
     const uint4 oa = offs[0], ob = offs[1];
     const uint32_t off[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
     uint32_t w[16], m[4], o[4];
@@ -987,9 +705,155 @@ __device__ __forceinline__ void pack_fresh(int side, uint8_t* base, const QaqCou
   if (HAS1) low_units(r.r1b, c.first1(), c.n1, std::integral_constant<int, 0>{});
 }
 
+// ---- what a fresh tile side and one that is written anew as a whole have in common ----
+// Slots by class, in position order inside a class (thread t: position t, its class or -1).  Afterwards, behind a barrier,
+// row_of_slot holds the staged rows' byte offsets and `order` the positions, by slot; slots past the last token: row 0.
+template <int D, int MAXO, bool HAS1>
+__device__ __forceinline__ void sort_slots(int cls, QaqCounts& cn, BuildLds<D, MAXO>& L, int tid) {
+  constexpr int NC = HAS1 ? QAQ_NCLASS : 4, ROW = 4 * BuildLds<D, MAXO>::SROW;
+  const int lane = tid & 63, wave = tid >> 6;
+  int rank = 0;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const unsigned long long bal = __ballot(cls == k);
+    if (lane == 0) L.wave_cnt[k][wave] = __popcll(bal);
+    rank = cls == k ? lanes_below(bal) : rank;
+  }
+  L.row_of_slot[tid] = 0;
+  __syncthreads();
+  int m[QAQ_NCLASS];
+  m[QC1] = 0;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { const int x = __builtin_amdgcn_readfirstlane(L.wave_cnt[k][w]); before += w < wave ? x : 0; all += x; }
+    m[k] = all;
+    rank += cls == k ? before : 0;
+  }
+  cn.n3 = m[QC3]; cn.n2 = m[QC2]; cn.n4 = m[QC4]; cn.n8 = m[QC8]; cn.n1 = m[QC1];
+  if (cls >= 0) {
+    const int sl = cn.start(cls) + rank;
+    L.row_of_slot[sl] = (uint16_t)(tid * ROW);
+    L.order[sl] = (uint8_t)tid;
+  }
+}
+// Metadata in slot order, the tile's summary, the code planes (positions n_before .. n - 1 are new)
+template <int D, bool ONE, bool HAS1>
+__device__ __forceinline__ void put_sorted(const QaqView& v, int side, int bh, int tile, int n_before, int n, const QaqCounts& cn, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, int tid) {
+  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2;
+  const bool csr = !ONE && v.csr;
+  const int b = bh / v.Hkv, h = bh % v.Hkv;
+  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
+  if (tid < n) {
+    const int p = L.order[tid];
+    v.mm[side][gi0 + tid] = L.mm[p];
+    v.perm[side][gi0 + tid] = (uint8_t)p;
+    if (ONE) {
+      *(uint16_t*)(v.oidx[side] + (gi0 + tid) * 2) = *(const uint16_t*)L.oidx[p];
+      *(uint32_t*)(v.oval[side] + (gi0 + tid) * 2) = *(const uint32_t*)L.oval[p];
+    } else {
+      for (int k = 0; k < v.no2 && !csr; ++k) {
+        v.oidx[side][(gi0 + tid) * v.no2 + k] = L.oidx[p][k];
+        v.oval[side][(gi0 + tid) * v.no2 + k] = L.oval[p][k];
+      }
+    }
+  }
+  if (csr && n > n_before) put_new_runs<D, MAXO>(v, side, gi0, n_before, n, L, tid);
+  if (tid == 0) put_tile_summary(v, side, qaq_bh(v, b, h) * v.NT + tile, cn, L.wave_bound, L.wave_bound2);
+  pack_fresh<D, MAXO, HAS1>(side, qaq_tile_codes(v, side, b, h, tile), cn, L, tid);
+}
+
+// All stored codes of a tile side -> staged bytes, a code in the upper bits of its byte (what is below it is left to
+// chance: a token's width never grows here).  
+template <int D, int MAXO, bool HAS1>
+__device__ __forceinline__ void unpack_all(int side, const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
+  constexpr int NQ = D / 16, KS = D / 64;
+  const int n32 = c.n32();
+  uint8_t* const staged = (uint8_t*)L.stage;
+  constexpr uint32_t LOW = 0x20202020u;
+  if (side == 0) {
+    const QaqKRegions r = qaq_k_regions(c, D);
+    auto slice = [&](int slot, int q) { return (uint32_t*)(staged + L.row_of_old[slot]) + (16 * (q % KS) + 4 * (q / KS)); };
+#pragma unroll 2
+    for (int it = tid; it < n32 * NQ; it += kThreads) {
+      const int s = it / NQ, q = it % NQ;
+      const uint32_t w2 = *(const uint32_t*)(base + (r.r2 + 4u * (uint32_t)it));
+      const uint32_t w1 = *(const uint32_t*)(base + (s < c.n3 ? r.r1 + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1) : r.r2)) >> (4 * (q & 1));
+      uint32_t* row = slice(s, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) row[v] = ((w2 << (6 - 2 * v)) & ~LOW) | ((w1 << (5 - v)) & LOW);
+    }
+    for (int it = tid; it < c.n4 * NQ; it += kThreads) {
+      const uint2 w = *(const uint2*)(base + (r.r4 + 8u * (uint32_t)it));
+      uint32_t* row = slice(n32 + it / NQ, it % NQ);
+      row[0] = w.x << 4; row[1] = w.x; row[2] = w.y << 4; row[3] = w.y;
+    }
+    for (int it = tid; it < c.n8 * NQ; it += kThreads) {
+      const uint4 w = *(const uint4*)(base + (r.r8 + 16u * (uint32_t)it));
+      uint32_t* row = slice(n32 + c.n4 + it / NQ, it % NQ);
+      row[0] = w.x ^ 0x80808080u; row[1] = w.y ^ 0x80808080u; row[2] = w.z ^ 0x80808080u; row[3] = w.w ^ 0x80808080u;
+    }
+    for (int it = tid; HAS1 && it < c.n1 * NQ; it += kThreads) {
+      const int s = it / NQ, q = it % NQ;
+      const uint32_t w = *(const uint32_t*)(base + (r.r1b + (uint32_t)s * (D / 8) + 4u * (uint32_t)(q >> 1))) >> (4 * (q & 1));
+      uint32_t* row = slice(c.first1() + s, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) row[v] = w << (7 - v);
+    }
+    return;
+  }
+  const QaqVRegions r = qaq_v_regions(c, D);
+  auto words = [&](uint32_t at, int stride, uint32_t (&m)[4]) {      // four channels' words -> per token of a group of four
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = *(const uint32_t*)(base + (at + (uint32_t)(4 * k * stride)));
+    transpose4(w, m);
+  };
+  for (int it = tid; it < ((n32 + 15) / 16) * (D / 4); it += kThreads) {
+    const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2, n0 = 4 * (c4 & 3);
+    const uint4* offs = (const uint4*)&L.row_of_old[16 * u];
+    const uint4 oa = offs[0], ob = offs[1];
+    const uint32_t off[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
+    uint32_t m[4], l[4] = {0u, 0u, 0u, 0u};
+    words(r.r2 + (uint32_t)u * (4 * D) + 4u * (uint32_t)(n0 * (D / 16) + cg), D / 16, m);
+    if (16 * u < c.n3) {
+      words(r.r1 + (uint32_t)u * (2 * D) + 4u * (uint32_t)(n0 * (D / 32) + (cg >> 1)), D / 32, l);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) l[j] >>= 4 * (cg & 1);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {            // token 4 v + j of the unit
+      const int j = i & 3, v = i >> 2;
+      if (16 * u + i < n32) *(uint32_t*)(staged + ((off[i >> 1] >> (16 * (i & 1))) & 0xffffu) + 4 * c4) = ((m[j] << (6 - 2 * v)) & ~LOW) | ((l[j] << (5 - v)) & LOW);
+    }
+  }
+  for (int it = tid; it < ((c.n4 + 7) / 8) * (D / 4); it += kThreads) {
+    const int hu = it / (D / 4), c4 = it % (D / 4);
+    uint32_t m[4];
+    words(r.r4 + (uint32_t)hu * (4 * D) + 4u * (uint32_t)(4 * (c4 & 3) * (D / 16) + (c4 >> 2)), D / 16, m);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (8 * hu + i < c.n4) *(uint32_t*)(staged + L.row_of_old[n32 + 8 * hu + i] + 4 * c4) = i < 4 ? m[i & 3] << 4 : m[i & 3];
+  }
+  for (int it = tid; it < c.n8 * (D / 16); it += kThreads) {
+    const uint4 w = *(const uint4*)(base + (r.r8 + 16u * (uint32_t)it));
+    uint32_t* row = (uint32_t*)(staged + L.row_of_old[n32 + c.n4 + it / (D / 16)]) + 4 * (it % (D / 16));
+    row[0] = w.x; row[1] = w.y; row[2] = w.z; row[3] = w.w;
+  }
+  for (int it = tid; HAS1 && it < ((c.n1 + 15) / 16) * (D / 4); it += kThreads) {
+    const int u = it / (D / 4), c4 = it % (D / 4), cg = c4 >> 2;
+    uint32_t m[4];
+    words(r.r1b + (uint32_t)u * (2 * D) + 4u * (uint32_t)(4 * (c4 & 3) * (D / 32) + (cg >> 1)), D / 32, m);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (16 * u + i < c.n1) *(uint32_t*)(staged + L.row_of_old[c.first1() + 16 * u + i] + 4 * c4) = (m[i & 3] >> (4 * (cg & 1))) << (7 - (i >> 2));
+  }
+}
+
 template <int D, bool ONE, bool HAS1>
 __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, const int bh, const int tile, const int side, const int tid) {
-  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2, NC = HAS1 ? QAQ_NCLASS : 4, ROW = 4 * BuildLds<D, MAXO>::SROW;
+  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2, ROW = 4 * BuildLds<D, MAXO>::SROW;
   typedef TokenEncoder<D, ONE> Enc;
   const QaqView& v = a.v;
   const QaqRuleArgs& ru = a.rule;
@@ -998,7 +862,7 @@ __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ON
   const int b = bh / v.Hkv, h = bh % v.Hkv, t0 = tile * QAQ_TT;
   const int len_before = qaq_seq_len(v, b, a.len_before), n_new0 = t0 - len_before;      // (position 0 is new token n_new0)
   const int n = min(qaq_seq_len(v, b, a.len_after) - t0, QAQ_TT);
-  const size_t tile_id = qaq_bh(v, b, h) * v.NT + tile, gi0 = qaq_slot_index(v, b, h, tile, 0);
+  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
 
   // encode: a quad of lanes per token, 64 tokens per pass, the next pass's rows requested before the current one's are used
   const uint8_t* const rows = (const uint8_t*)a.newx[side] + ((long long)bh * a.n_new + n_new0) * (2 * D);
@@ -1047,7 +911,6 @@ __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ON
 #pragma unroll
     for (int i = 0; i < Enc::NCH; ++i) cur[i] = nxt[i];
   }
-  L.pos_of_slot[tid] = 0;        // (slots past the last token: any staged row)
   __syncthreads();
 
   // widths, the tile's bounds, classes (thread t: position t)
@@ -1075,64 +938,26 @@ __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ON
       if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
     }
   }
-  // slots: by class, in position order inside a class
-  int rank = 0;
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const unsigned long long bal = __ballot(cls == k);
-    if (lane == 0) L.wave_cnt[k][wave] = __popcll(bal);
-    rank = cls == k ? lanes_below(bal) : rank;
-  }
-  __syncthreads();
   QaqCounts cn;
-  {
-    int m[QAQ_NCLASS];
-    m[QC1] = 0;
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      int before = 0, all = 0;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) { const int x = __builtin_amdgcn_readfirstlane(L.wave_cnt[k][w]); before += w < wave ? x : 0; all += x; }
-      m[k] = all;
-      rank += cls == k ? before : 0;
-    }
-    cn.n3 = m[QC3]; cn.n2 = m[QC2]; cn.n4 = m[QC4]; cn.n8 = m[QC8]; cn.n1 = m[QC1];
-  }
-  if (cls >= 0) {
-    const int sl = cn.start(cls) + rank;
-    L.pos_of_slot[sl] = (uint16_t)(tid * ROW);
-    L.kept[sl] = (uint8_t)tid;
-  }
+  sort_slots<D, MAXO, HAS1>(cls, cn, L, tid);
   __syncthreads();
-  if (tid < n) {                // metadata, in slot order
-    const int p = L.kept[tid];
-    v.mm[side][gi0 + tid] = L.mm[p];
-    v.perm[side][gi0 + tid] = (uint8_t)p;
-    if (ONE) {
-      *(uint16_t*)(v.oidx[side] + (gi0 + tid) * 2) = *(const uint16_t*)L.oidx[p];
-      *(uint32_t*)(v.oval[side] + (gi0 + tid) * 2) = *(const uint32_t*)L.oval[p];
-    } else {
-      for (int k = 0; k < v.no2 && !csr; ++k) {
-        v.oidx[side][(gi0 + tid) * v.no2 + k] = L.oidx[p][k];
-        v.oval[side][(gi0 + tid) * v.no2 + k] = L.oval[p][k];
-      }
-    }
-  }
-  if (csr) put_new_runs<D, MAXO>(v, side, gi0, 0, n, L, tid);
-  if (tid == 0) put_tile_summary(v, side, tile_id, cn, L.wave_bound, L.wave_bound2);
-  pack_fresh<D, MAXO, HAS1>(side, qaq_tile_codes(v, side, b, h, tile), cn, L, tid);
+  put_sorted<D, ONE, HAS1>(v, side, bh, tile, 0, n, cn, L, tid);
 }
 
 // HAS1: the width set contains 1 (five classes); without it the fifth class costs nothing.
-// One tile side (unit bh, tile, side) of a build; tid: the thread (an argument: see k_build_listed).
+// One tile side (unit bh, tile, side) that holds tokens: appends to it, moves its tokens to other widths.  tid: the thread
+// (an argument: see k_build_listed).
+//
+// A side with nothing to do is left after its widths are known.  Any other is read into LDS and written anew in the manner
+// of a fresh one, with the tokens that are new or widen encoded in between.  Moving only the tokens that change (the
+// decode-step kernel's way, with few registers) was not worth its bookkeeping here: 8 x 32 heads x 4000 tokens, 0.5 % of the
+// tokens changed 93 -> 77 us, 5 % 154 -> 109, half of them 198 -> 113, all 225 -> 128; two outliers per end 157 -> 138 ... 392 -> 223.
 template <int D, bool ONE, bool HAS1>
 __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, const int bh, const int tile, const int side, const int tid) {
-  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2;
-  constexpr int NC = HAS1 ? QAQ_NCLASS : 4;
-  auto bits_at = [](const QaqCounts& c, int s) { return HAS1 ? c.bits_of_slot(s) : c.bits_of_slot4(s); };
-  constexpr int SROW = BuildLds<D, MAXO>::SROW;
-
+  constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2, ROW = 4 * BuildLds<D, MAXO>::SROW;
+  typedef TokenEncoder<D, ONE> Enc;
   const QaqView& v = a.v;
+  const QaqRuleArgs& ru = a.rule;
   const bool csr = !ONE && v.csr;     // (the one-per-end build never has the variable-length side store)
   const int lane = tid & 63, wave = tid >> 6;
   const int b = bh / v.Hkv, h = bh % v.Hkv;
@@ -1140,7 +965,6 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
   const int len_before = qaq_seq_len(v, b, a.len_before), len_after = qaq_seq_len(v, b, a.len_after);   // of this sequence
   const int n_before = min(max(len_before - t0, 0), QAQ_TT);
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
-  const int n_o = v.no2 / 2;
 
   if (a.mode == 1 && a.newbits[side] == nullptr) return;   // requantize: nothing to do for this side
   // an append, where sequences differ in length: the grid starts at the shortest sequence's open
@@ -1150,36 +974,36 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
   // decode-step update, key side: the rule compares a token's range with one threshold per
   // (T, head); the tile keeps, from when it was built, the interval of thresholds for which
   // none of its tokens changes width, so a tile with nothing to do costs one 8-byte load
-  if (a.mode == 2 && side == 0 && n_before == n_after && !a.rule.out_bits[0]) {
-    const float2 keep = ((const float2*)v.kthr)[qaq_bh(v, b, h) * v.NT + tile];
-    const float tau = qaq_tau_k(a.rule, v, b, h);
+  const size_t tile_id = qaq_bh(v, b, h) * v.NT + tile;
+  if (a.mode == 2 && side == 0 && n_before == n_after && !ru.out_bits[0]) {
+    const float2 keep = ((const float2*)v.kthr)[tile_id];
+    const float tau = qaq_tau_k(ru, v, b, h);
     if (tau >= keep.x && tau < keep.y) return;
   }
 
-  // cached tokens: everything whose address is known up front is requested in one go (the
-  // slot-order metadata, and for a requantize the widths that decide whether the tile is
-  // touched at all), so that a rebuild costs two dependent round trips to memory, not three
-  uint8_t* base = qaq_tile_codes(v, side, b, h, tile);
+  // everything whose address is known up front is requested in one go: the slot-order metadata, and what the
+  // widths come from (for a requantize the widths themselves)
+  const uint8_t* const base = qaq_tile_codes(v, side, b, h, tile);
   QaqCounts c_old = qaq_load_counts(v, side, b, h, tile, n_before);
   if (!HAS1) c_old.n1 = 0;
+  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
+  const bool cached = tid < n_before, fresh = tid >= n_before && tid < n_after;
   int pos_old = 0;
   uint32_t mm_old = 0;
   uint8_t oi_old[MAXO];
   uint16_t ov_old[MAXO];
-  if (tid < n_before) {
-    const size_t gi = qaq_slot_index(v, b, h, tile, tid);
-    pos_old = v.perm[side][gi];
-    mm_old = v.mm[side][gi];
+  if (cached) {
+    pos_old = v.perm[side][gi0 + tid];
+    mm_old = v.mm[side][gi0 + tid];
 #pragma unroll
     for (int k = 0; k < MAXO; ++k)
-      if (k < v.no2 && !csr) { oi_old[k] = v.oidx[side][gi * v.no2 + k]; ov_old[k] = v.oval[side][gi * v.no2 + k]; }
+      if (k < v.no2 && !csr) { oi_old[k] = v.oidx[side][(gi0 + tid) * v.no2 + k]; ov_old[k] = v.oval[side][(gi0 + tid) * v.no2 + k]; }
   }
-  // decode-step update: the inputs of the width rules that are indexed by position (this
-  // step's scores, the window rows) are requested now as well; the value side keeps the window
-  // (an append by the rules, mode 3, takes the window as it stands and writes no row)
+  // the inputs of the width rules that are indexed by position (this step's scores, the window rows); the value side
+  // keeps the window (an append by the rules, mode 3, takes the window as it stands and writes no row)
   float pred = 0.0f;
-  if ((a.mode == 2 || (a.mode == 3 && tid >= n_before)) && side == 1 && tid < n_after) {
-    const QaqRuleArgs& ru = a.rule;
+  int oldb = 0, want = a.widest;        // of position tid: width so far, width asked for
+  if (side == 1 && ((a.mode == 2 && tid < n_after) || (a.mode == 3 && fresh))) {
     const int t = t0 + tid;
     const size_t ring_row = (size_t)v.B * v.Hkv * v.Tmax;
     const size_t ri = qaq_bh(v, b, h) * v.Tmax + t;
@@ -1192,38 +1016,38 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
     pred = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t), ru.new_row, ri, s);
     if (a.mode == 2) qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri, s);
   }
+  if (a.mode == 1 && cached) {
+    oldb = v.tags[side][gi0 + tid];
+    want = a.newbits[side][(size_t)bh * a.len_before + t0 + tid];
+  } else if (a.mode == 0 && fresh && a.newbits[side]) {
+    want = a.newbits[side][(size_t)bh * a.n_new + (t0 + tid - len_before)];
+  }
+  const bool served = a.orig[side] != nullptr;
+  bool wider = false, changed = false;
   if (a.mode == 1) {
     // no token of the tile changes: leave it alone
-    bool changed = false, wider = false;
-    if (tid < n_before) {
-      const int oldb = v.tags[side][qaq_slot_index(v, b, h, tile, tid)];
-      const int req = a.newbits[side][(size_t)bh * a.len_before + t0 + tid];
-      if (req < oldb) changed = true;
-      else if (req > oldb) { wider = true; if (a.orig[side]) changed = true; }
-    }
+    wider = cached && want > oldb;
+    changed = cached && (want < oldb || (wider && served));
     note_widenings(L.wave_wide, wider, tid);
     const bool any = __syncthreads_or(changed ? 1 : 0) != 0;
-    if (tid == 0) add_widenings(v, (qaq_bh(v, b, h) * v.NT + tile) * 2 + side, L.wave_wide, a.orig[side] != nullptr);
+    if (tid == 0) add_widenings(v, tile_id * 2 + side, L.wave_wide, served);
     if (!any) return;
   }
 
   // metadata by position
-  if (tid < n_before) {
+  if (cached) {
     L.mm[pos_old] = mm_old;
-    L.pos_of_slot[tid] = (uint16_t)pos_old;
-    L.pos_old[tid] = (uint16_t)pos_old;
-    L.slot_of_pos[pos_old] = (uint16_t)tid;
-    L.bits_old[pos_old] = (uint8_t)bits_at(c_old, tid);
+    L.row_of_old[tid] = (uint16_t)pos_old;       // (the position until it is known which rows are encoded)
+    L.bits_old[pos_old] = (uint8_t)(HAS1 ? c_old.bits_of_slot(tid) : c_old.bits_of_slot4(tid));
 #pragma unroll
     for (int k = 0; k < MAXO; ++k)
       if (k < v.no2 && !csr) { L.oidx[pos_old][k] = oi_old[k]; L.oval[pos_old][k] = ov_old[k]; }
   }
   // variable-length side store: the tile's pool is in position order and a token's entries never
   // move; thread `tid` fetches those of position tid (unused places of its row: channel 255)
-  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0), pool0 = gi0 * (size_t)v.no2;
-  if (csr && tid < n_before) {
-    const size_t pi = qaq_slot_index(v, b, h, tile, tid);
-    const int cnt = v.ocnt[side][pi], st = v.ostart[side][pi];
+  if (csr && cached) {
+    const size_t pool0 = gi0 * (size_t)v.no2;
+    const int cnt = v.ocnt[side][gi0 + tid], st = v.ostart[side][gi0 + tid];
 #pragma unroll
     for (int k = 0; k < MAXO; ++k) {
       const bool have = k < cnt;
@@ -1237,70 +1061,51 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
   // if none of them moves and the new token is not in it
   auto ruled_width = [&](uint32_t m) {
     const float range = h2f((uint16_t)(m >> 16)) - h2f((uint16_t)(m & 0xffffu));
-    return rule_width(a.rule, side == 0 ? range : range * pred, side == 0 ? qaq_tau_k(a.rule, v, b, h) : qaq_c_v(a.rule, v, b));
+    return rule_width(ru, side == 0 ? range : range * pred, side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b));
   };
-  int req_rule = 0;
+  if (cached) oldb = L.bits_old[tid];
   if (a.mode == 2) {
-    bool changed = false, wider = false;
-    if (tid < n_before) {
-      const int oldb = L.bits_old[tid];
-      req_rule = ruled_width(L.mm[tid]);
-      if (a.rule.out_bits[side]) a.rule.out_bits[side][(size_t)bh * a.len_after + t0 + tid] = (uint8_t)req_rule;
-      if (req_rule < oldb) changed = true;
-      else if (req_rule > oldb) { wider = true; if (a.orig[side]) changed = true; }
+    if (cached) {
+      want = ruled_width(L.mm[tid]);
+      if (ru.out_bits[side]) ru.out_bits[side][(size_t)bh * a.len_after + t0 + tid] = (uint8_t)want;
     }
+    wider = cached && want > oldb;
+    changed = cached && (want < oldb || (wider && served));
     note_widenings(L.wave_wide, wider, tid);
-    const bool has_new = len_before >= t0 && len_before < t0 + QAQ_TT;
     const bool any = __syncthreads_or(changed ? 1 : 0) != 0;
-    if (tid == 0) add_widenings(v, (qaq_bh(v, b, h) * v.NT + tile) * 2 + side, L.wave_wide, a.orig[side] != nullptr);
-    if (!any && !has_new) return;
+    if (tid == 0) add_widenings(v, tile_id * 2 + side, L.wave_wide, served);
+    if (!any && n_before == n_after) return;
   }
 
-  // final width of every position; whether it is encoded in this pass (new tokens, and
-  // cached tokens that widen from the unquantized copy)
-  bool enc = false;
-  if (tid < n_after) {
-    int nb, drop = 0;
-    if (tid < n_before) {
-      const int oldb = L.bits_old[tid];
-      nb = oldb;
-      if (a.mode == 1 || a.mode == 2) {       // appends leave the cached tokens at their widths
-        const int req = a.mode == 1 ? (int)a.newbits[side][(size_t)bh * a.len_before + t0 + tid] : req_rule;
-        if (req < oldb) { nb = req; drop = oldb - req; }
-        else if (req > oldb && a.orig[side]) nb = req;
-      }
-      enc = nb > oldb;
-    } else {
-      const int r = t0 + tid - len_before;
-      nb = a.newbits[side] ? a.newbits[side][(size_t)bh * a.n_new + r] : a.widest;
-      L.bits_old[tid] = (uint8_t)nb;
-      enc = true;
-    }
-    L.bits_new[tid] = (uint8_t)nb;
-    L.shf[tid] = (uint8_t)drop;
-  }
-  // The few positions to encode are gathered into a list, so that they fill the encoder's passes
-  // densely; a tile with none (most value-side tiles of a decode step without the unquantized
-  // copies) goes on after one barrier.
+  // width of every position (appends leave the cached tokens at theirs; a new token's by the rules follows from its
+  // range); whether it is encoded: new tokens, and cached ones that widen from the unquantized copy
+  int bits = cached && !changed ? oldb : want;
+  const bool enc = fresh || (changed && wider);
   const unsigned long long enc_bal = __ballot(enc);
-  if (lane == 0) L.wave_need[0][wave] = __popcll(enc_bal);    // (this array's other use comes two barriers later)
+  if (lane == 0) L.wave_enc[wave] = __popcll(enc_bal);
   __syncthreads();
-
-  // encode: a quad of lanes per token, 64 tokens per pass; the rows of the next pass are
-  // requested before the current pass is computed
-  const int n_enc = L.wave_need[0][0] + L.wave_need[0][1] + L.wave_need[0][2] + L.wave_need[0][3];
-  if (n_enc > 0) {                           // uniform: every thread has the same sum
+  // encode: a quad of lanes per token, 64 tokens per pass, the positions gathered into a list so that they fill
+  // the passes densely; the rows of the next pass are requested before the current pass is computed
+  const int n_enc = L.wave_enc[0] + L.wave_enc[1] + L.wave_enc[2] + L.wave_enc[3];
+  {
     int off = 0;
-    for (int w = 0; w < wave; ++w) off += L.wave_need[0][w];
-    if (enc) L.freeslot[off + __popcll(enc_bal & ((1ull << lane) - 1ull))] = (uint16_t)tid;
-    __syncthreads();
-    typedef TokenEncoder<D, ONE> Enc;
+    for (int w = 0; w < wave; ++w) off += L.wave_enc[w];
+    if (enc) L.order[off + lanes_below(enc_bal)] = (uint8_t)tid;
+  }
+  // staged rows by old slot (what is encoded is not staged from its old code); the widths' place now says who is encoded
+  L.bits_old[tid] = enc ? 1 : 0;
+  __syncthreads();
+  {
+    const int p = cached ? (int)L.row_of_old[tid] : QAQ_TT;
+    L.row_of_old[tid] = (uint16_t)((p < QAQ_TT && !L.bits_old[p] ? p : QAQ_TT) * ROW);
+  }
+  if (n_enc > 0) {                           // uniform: every thread has the same sum
     const float thr_lo = csr ? v.othr[(side * v.Hkv + h) * 2] : INFINITY;
     const float thr_hi = csr ? v.othr[(side * v.Hkv + h) * 2 + 1] : -INFINITY;
     constexpr int TPP = kThreads / 4;     // tokens per pass
     const int NP = (n_enc + TPP - 1) / TPP;
     const int c = tid & 3, gt = tid >> 2;
-    auto position = [&](int pass) { return (int)L.freeslot[min(pass * TPP + gt, QAQ_TT - 1)]; };
+    auto position = [&](int pass) { return (int)L.order[min(pass * TPP + gt, QAQ_TT - 1)]; };
     // rows by position of this tile (the new tokens' first row is that of position n_before)
     const uint8_t* const new_rows = (const uint8_t*)a.newx[side] + ((long long)bh * a.n_new + (t0 - len_before)) * (2 * D);
     const uint8_t* const old_rows = (const uint8_t*)a.orig[side] + ((long long)bh * a.orig_tokens + t0) * (2 * D);
@@ -1308,19 +1113,19 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
     auto fetch = [&](int pass, uint4 (&raw)[Enc::NCH]) -> int {   // 0 = nothing to do, 1 = fresh, 2 = widen
       if (pass >= NP || pass * TPP + gt >= n_enc) return 0;
       const int p = position(pass);
-      const bool fresh = p >= n_before;
+      const bool is_new = p >= n_before;
       const uint32_t at = (uint32_t)p * (2 * D) + 16u * (uint32_t)c;
-      const uint8_t* src = (fresh ? new_rows : old_rows) + at;
+      const uint8_t* src = (is_new ? new_rows : old_rows) + at;
 #pragma unroll
       for (int i = 0; i < Enc::NCH; ++i) {      // read once: streaming loads
         const u32x4 t = __builtin_nontemporal_load((const u32x4*)(src + 64 * i));
         raw[i] = make_uint4(t.x, t.y, t.z, t.w);
       }
-      if (fresh && put_rows) {             // keep the unquantized token for later widening
+      if (is_new && put_rows) {            // keep the unquantized token for later widening
 #pragma unroll
         for (int i = 0; i < Enc::NCH; ++i) *(uint4*)(put_rows + at + 64 * i) = raw[i];
       }
-      return fresh ? 1 : 2;
+      return is_new ? 1 : 2;
     };
     uint4 cur[Enc::NCH], nxt[Enc::NCH];
     int kind = fetch(0, cur);
@@ -1329,7 +1134,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
       const int kind_next = fetch(pass + 1, nxt);
       if (kind) {                          // whole quads drop out together
         const int p = position(pass);
-        Enc::run(cur, c, kind == 1, L.bits_new[p], n_o, &L.mm[p], L.oidx[p], L.oval[p], &L.stage[p * SROW], thr_lo, thr_hi);
+        Enc::run(cur, c, kind == 1, 8, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
       }
 #pragma unroll
       for (int i = 0; i < Enc::NCH; ++i) cur[i] = nxt[i];
@@ -1338,27 +1143,22 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
     __syncthreads();
   }
 
-  // decode-step update, append by the rules: the width of a new token from the range the
-  // encoder has just found (it was encoded at the widest width; narrowing drops low bits)
-  if ((a.mode == 2 || a.mode == 3) && tid >= n_before && tid < n_after) {
-    const int w = ruled_width(L.mm[tid]);
-    if (a.rule.out_bits[side]) {
-      if (a.mode == 2) a.rule.out_bits[side][(size_t)bh * a.len_after + t0 + tid] = (uint8_t)w;
-      else a.rule.out_bits[side][(size_t)bh * a.n_new + (t0 + tid - len_before)] = (uint8_t)w;
-    }
-    L.shf[tid] = (uint8_t)(a.widest - w);
-    L.bits_new[tid] = (uint8_t)w;
-  }
-
-  if (!ONE && tid >= n_before && tid < n_after) sort_side_store(L.oidx[tid], L.oval[tid], v.no2);
-
-  // the tile's bounds
+  // the width of a new token by the rules, the tile's bounds, classes
+  int cls = -1;
   {
     float bnd = 0.0f, lo = 0.0f, hi = INFINITY;
     if (tid < n_after) {
-      const float mn = h2f((uint16_t)(L.mm[tid] & 0xffffu)), mx = h2f((uint16_t)(L.mm[tid] >> 16));
-      if (side == 1) bnd = value_bound(L.bits_new[tid], mn, mx, L.oidx[tid], L.oval[tid], v.no2);
-      else key_interval(a.rule, L.bits_new[tid], mx - mn, lo, hi);
+      const uint32_t m = L.mm[tid];
+      const float mn = h2f((uint16_t)(m & 0xffffu)), mx = h2f((uint16_t)(m >> 16));
+      if (fresh && a.mode >= 2) {
+        bits = ruled_width(m);
+        if (ru.out_bits[side]) ru.out_bits[side][(a.mode == 2 ? (size_t)bh * a.len_after + t0 : (size_t)bh * a.n_new + (t0 - len_before)) + tid] = (uint8_t)bits;
+      }
+      if (fresh || changed) v.tags[side][gi0 + tid] = (uint8_t)bits;
+      cls = qaq_class_of_bits(bits);
+      if (!ONE && fresh) sort_side_store(L.oidx[tid], L.oval[tid], v.no2);
+      if (side == 1) bnd = value_bound(bits, mn, mx, L.oidx[tid], L.oval[tid], v.no2);
+      else key_interval(ru, bits, mx - mn, lo, hi);
     }
     if (side == 1) {
       bnd = wave_max(bnd);
@@ -1368,147 +1168,11 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
       if (lane == 0) { L.wave_bound[wave] = lo; L.wave_bound2[wave] = hi; }
     }
   }
-
-  // Slots: class by class (3, 2, 4, 8).  A cached token whose class is unchanged and whose
-  // old slot still lies in its class's range stays where it is; the others (new tokens, tokens
-  // that change class, tokens squeezed out by a moved class boundary) take the remaining
-  // slots of their class, in position order: a rebuild moves only as many tokens as it has to
-  // -- what is stored for the tokens that stay is not written again.
-  const int cls = tid < n_after ? qaq_class_of_bits(L.bits_new[tid]) : -1;
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const unsigned long long bal = __ballot(cls == c);
-    if (lane == 0) L.wave_cnt[c][wave] = __popcll(bal);
-  }
-  L.kept[tid] = 0;
-  if (tid < 32) L.mask4[tid] = 0;
-  if (HAS1 && tid < 16) L.mask1b[tid] = 0;
-  __syncthreads();
   QaqCounts cn;
-  {
-    int n[QAQ_NCLASS];
-    n[QC1] = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) n[c] = L.wave_cnt[c][0] + L.wave_cnt[c][1] + L.wave_cnt[c][2] + L.wave_cnt[c][3];
-    cn.n3 = n[QC3]; cn.n2 = n[QC2]; cn.n4 = n[QC4]; cn.n8 = n[QC8]; cn.n1 = n[QC1];
-  }
-  int old_slot = -1;              // cached tokens: the slot held so far
-  {
-    const bool was_cached = tid < n_before;
-    old_slot = was_cached ? (int)L.slot_of_pos[tid] : -1;
-    bool keep = false;
-    if (was_cached && cls == qaq_class_of_bits(L.bits_old[tid])) {
-      const int lo = cn.start(cls);
-      keep = old_slot >= lo && old_slot < lo + cn.count(cls);
-    }
-    if (keep) L.kept[old_slot] = 1;
-    __syncthreads();
-    // ranks: of the tokens that need a slot (by position), of the free slots (by slot)
-    const bool need = cls >= 0 && !keep;
-    const int slot_cls = tid < n_after ? qaq_class_of_bits(bits_at(cn, tid)) : -1;   // class owning slot `tid`
-    const bool is_free = slot_cls >= 0 && !L.kept[tid];
-    int need_rank = 0, free_rank = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const unsigned long long bn = __ballot(need && cls == c);
-      const unsigned long long bf = __ballot(is_free && slot_cls == c);
-      if (lane == 0) { L.wave_need[c][wave] = __popcll(bn); L.wave_free[c][wave] = __popcll(bf); }
-      if (need && cls == c) need_rank = __popcll(bn & ((1ull << lane) - 1ull));
-      if (is_free && slot_cls == c) free_rank = __popcll(bf & ((1ull << lane) - 1ull));
-    }
-    __syncthreads();
-    if (is_free) {
-      int r = cn.start(slot_cls) + free_rank;
-      for (int w = 0; w < wave; ++w) r += L.wave_free[slot_cls][w];
-      L.freeslot[r] = (uint16_t)tid;
-    }
-    __syncthreads();
-    if (cls >= 0) {
-      int sl = old_slot;
-      if (!keep) {
-        int r = cn.start(cls) + need_rank;
-        for (int w = 0; w < wave; ++w) r += L.wave_need[cls][w];
-        sl = L.freeslot[r];
-      }
-      L.slot_of_pos[tid] = (uint16_t)sl;
-      L.pos_of_slot[sl] = (uint16_t)tid;
-      if (keep && L.bits_new[tid] == L.bits_old[tid] && was_cached) L.shf[tid] |= kKeptFlag;
-    }
-    __syncthreads();
-  }
-
-  // Which tokens are written again: those that do not keep slot and width, and those whose
-  // region starts elsewhere than before.  A cached token among them that does not widen has
-  // its stored code read back (the others are left alone); on the value side, where a stored
-  // word holds one channel of up to 16 tokens, the slots to write are gathered per unit and
-  // the tokens to read back into a list.
-  int n_moved = 0;
-  {
-    const int n32 = cn.n32(), n32o = c_old.n32();
-    bool same1, same4, same8;
-    if (side == 0) {
-      const QaqKRegions r = qaq_k_regions(cn, D), r0 = qaq_k_regions(c_old, D);
-      same1 = r.r1 == r0.r1;
-      same4 = n32 == n32o && r.r4 == r0.r4;
-      same8 = same4 && c_old.n4 == cn.n4 && r.r8 == r0.r8;
-    } else {
-      const QaqVRegions r = qaq_v_regions(cn, D), r0 = qaq_v_regions(c_old, D);
-      same1 = r.r1 == r0.r1;
-      same4 = n32 == n32o && r.r4 == r0.r4;
-      same8 = same4 && c_old.n4 == cn.n4 && r.r8 == r0.r8;
-    }
-    const bool same1b = same8 && c_old.n8 == cn.n8;
-    auto written = [&](int pos, int c) {
-      return !(L.shf[pos] & kKeptFlag) || (c == QC3 && !same1) || (c == QC4 && !same4) || (c == QC8 && !same8) ||
-             (HAS1 && c == QC1 && !same1b);
-    };
-    if (side == 1) {
-      // by slot of the new layout
-      const bool wr = tid < n_after && written(L.pos_of_slot[tid], qaq_class_of_bits(bits_at(cn, tid)));
-      const unsigned long long bal = __ballot(wr && tid < n32);
-      if (lane < 4) L.mask2[4 * wave + lane] = (uint32_t)(bal >> (16 * lane)) & 0xffffu;
-      if (wr && tid >= n32 && tid < n32 + cn.n4) atomicOr(&L.mask4[(tid - n32) >> 3], 1u << ((tid - n32) & 7));
-      if (HAS1 && wr && tid >= cn.first1()) atomicOr(&L.mask1b[(tid - cn.first1()) >> 4], 1u << ((tid - cn.first1()) & 15));
-    }
-    // by position
-    int nd = 0;
-    if (tid < n_before) nd = L.bits_new[tid] > L.bits_old[tid] ? 2 : written(tid, cls) ? 1 : 0;
-    if (tid < n_after) L.need[tid] = (uint8_t)nd;
-    if (side == 1) {
-      const unsigned long long bal = __ballot(nd == 1);
-      if (lane == 0) L.wave_cnt[0][wave] = __popcll(bal);
-      __syncthreads();
-      int off = 0;
-      for (int w = 0; w < wave; ++w) off += L.wave_cnt[0][w];
-      if (nd == 1) {
-        const int k = off + __popcll(bal & ((1ull << lane) - 1ull));
-        L.freeslot[k] = (uint16_t)tid;       // position
-        L.kept[k] = (uint8_t)old_slot;       // the slot it had (both arrays are free by now)
-      }
-      n_moved = L.wave_cnt[0][0] + L.wave_cnt[0][1] + L.wave_cnt[0][2] + L.wave_cnt[0][3];
-    }
-    __syncthreads();
-    if (side == 0) unpack_k<D, MAXO, HAS1>(base, c_old, L, tid);
-    else unpack_moved_v<D, MAXO, HAS1>(base, c_old, n_moved, L, tid);
-    __syncthreads();
-  }
-
-  // metadata in slot order, widths by position, class counts
-  if (tid < n_after && !(L.shf[tid] & kKeptFlag)) {
-    const int s = L.slot_of_pos[tid];
-    const size_t gi = qaq_slot_index(v, b, h, tile, s);
-    v.mm[side][gi] = L.mm[tid];
-    v.perm[side][gi] = (uint8_t)tid;
-    for (int k = 0; k < v.no2 && !csr; ++k) {
-      v.oidx[side][gi * v.no2 + k] = L.oidx[tid][k];
-      v.oval[side][gi * v.no2 + k] = L.oval[tid][k];
-    }
-    v.tags[side][qaq_slot_index(v, b, h, tile, tid)] = L.bits_new[tid];
-  }
-  if (csr && n_after > n_before) put_new_runs<D, MAXO>(v, side, gi0, n_before, n_after, L, tid);
-  if (tid == 0) put_tile_summary(v, side, qaq_bh(v, b, h) * v.NT + tile, cn, L.wave_bound, L.wave_bound2);
-  if (side == 1) pack_masked_v<D, MAXO, HAS1>(base, cn, c_old, L, tid);
-  else pack_k<D, MAXO, HAS1>(base, cn, c_old, L, tid);
+  sort_slots<D, MAXO, HAS1>(cls, cn, L, tid);
+  unpack_all<D, MAXO, HAS1>(side, base, c_old, L, tid);
+  __syncthreads();
+  put_sorted<D, ONE, HAS1>(v, side, bh, tile, n_before, n_after, cn, L, tid);
 }
 
 // Grid (units, tiles, 2 sides) -- heads are the fastest grid dimension: with tiles fastest and a
