@@ -105,16 +105,22 @@ float value_threshold(const qaq_cache* c, int T) { return (float)(c->sigma_x / s
 // Share of a tile side's tokens that a decode-step update at the value threshold c_v can be expected to move, by what has
 // changed since the widths were last chosen: tokens came at other widths than the rules', the threshold fell (quality), or --
 // with the 1-bit width, whose borders are where most ranges are -- it rose.  (Other rises move few tokens, and key thresholds
-// half of the sides: not counted.)  The factors are fits to where the decode-step kernel with what it hands over takes as long
-// as the general kernel alone; 8 x 32 heads x 4000 tokens, us, the one | the other, 64 channels (119 tokens staged per side)
-// and 128 (64 staged): 256 tokens of the prompt at the widest width 86 | 108, 222 | 176; 1000: 169 | 116, 352 | 204 (1-bit
-// width).  Threshold x 0.83: 78 | 109, 252 | 184; x 0.75: 141 | 113, 256 | 191 (x 0.71).  1-bit width, threshold x 1.1: 91 | 134,
-// 246 | 196; x 1.2: 185 | 140, 285 | 207.
+// half of the sides: not counted.)  The factors are fits, at the smallest staging, to where the decode-step kernel with what it
+// hands over takes as long as the general kernel alone.  8 x 32 heads x 4000 tokens, us, the one | the other:
+//   one outlier per end     128 channels: threshold x 0.83 80 | 87, x 0.70 99 | 88; 64 tokens at the widest width 97 | 109, 128: 126 | 121;
+//                           with the 1-bit width x 0.90 84 | 90, x 0.83 93 | 92, x 1.2 82 | 83, x 1.5 110 | 83
+//                           64 channels: x 0.70 42 | 60, x 0.50 60 | 61; 256 tokens 67 | 77, 512: 82 | 79; with the 1-bit width x 3 62 | 59
+//   other forms (more       128 channels, two per end: x 0.70 102 | 152, x 0.50 200 | 158; 512 tokens 201 | 235, 1000: 265 | 239
+//   registers, half the     64 channels, two per end: x 0.50 53 | 82; 512 tokens 85 | 114, 1000: 107 | 112
+//   wavefronts)             thresholds, 128 channels: x 0.70 108 | 157, x 0.50 208 | 163; 512 tokens 233 | 253, 1000: 289 | 258
 float expected_moves(const qaq_cache* c, float c_v) {
-  float share = c->len > 0 ? 4.0f * (float)c->unruled / (float)c->len : 0.0f;
+  const bool one = c->dims.no2 == 2 && !c->dims.csr, wide = c->dims.D == 128, has1 = c->view.has1 != 0;
+  const float came = one ? (wide ? 9.0f : 4.1f) : (wide ? 1.4f : 1.9f);
+  const float fell = !one ? 0.34f : !wide ? 0.46f : has1 ? 1.0f : 0.8f, rose = !has1 ? 0.0f : wide ? 0.95f : 0.31f;
+  float share = c->len > 0 ? came * (float)c->unruled / (float)c->len : 0.0f;
   if (c->ruled_c_v > 0.0f && c_v > 0.0f) {
     const float octaves = std::log2(c_v / c->ruled_c_v);
-    share = std::fmax(share, octaves < 0.0f ? -1.18f * octaves : c->view.has1 ? 2.0f * octaves : 0.0f);
+    share = std::fmax(share, octaves < 0.0f ? -fell * octaves : rose * octaves);
   }
   return share;
 }

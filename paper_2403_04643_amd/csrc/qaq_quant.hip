@@ -1194,10 +1194,10 @@ __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
 // steps may be replayed from its start); a workgroup that starts after that had no entry anyway.
 //
 // Bound by the workgroups in flight, i.e. by registers: left to itself the compiler keeps everything that
-// follows from the thread or from the kernel's arguments in registers across the loop (142-247 of them, and
-// 127-185 scalars spilled).  So each round takes the thread's index and the arguments as if they were new: 81-199
-// registers, no scratch.  With the grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands every side over
-// takes 430 us where it took 633 (128 channels; 64 channels 432 -> 280, with the 1-bit width 482 -> 303).
+// follows from the thread or from the kernel's arguments in registers across the loop (142-247 of them when that was tried).
+// So each round takes the thread's index and the arguments as if they were new: 80-184 registers, no scratch.  With the
+// grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands half of the sides over takes 145-159 us (274-306 when
+// the general build moved token by token; 64 channels 115-120, 202-216 then).
 template <int D, bool ONE>
 constexpr int listed_per_cu() { return D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4); }      // workgroups a compute unit takes
 template <int D, bool ONE, bool HAS1>
@@ -2610,8 +2610,7 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float movi
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.max_moved == QAQ_TT) return e;
   // The tile sides it handed over (their number is only known on the device): as many workgroups as a compute unit holds
-  // at the kernel's registers and LDS.  An empty list costs the same with 512 and with 1536 of them (4.6 us, the launch);
-  // handed-over sides take 2/3 (128 channels) and half (64) of the time they take with two per compute unit.
+  // at the kernel's registers and LDS.  An empty list costs the same with 512 and with 1536 of them (4.6 us, the launch).
   const long long most = (long long)listed_per_cu<D, ONE>() * cus;
   hipLaunchKernelGGL((k_build_listed<D, ONE, HAS1>), dim3((unsigned)(sides < most ? sides : most)), dim3(kThreads), 0, s, a);
   return hipGetLastError();
