@@ -153,27 +153,7 @@ __device__ __forceinline__ uint32_t quad_umin(uint32_t x) {
   uint32_t y = dpp_u<0xB1>(x); x = x < y ? x : y;
   y = dpp_u<0x4E>(x); return x < y ? x : y;
 }
-__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
-// Integer image of a float that orders like the float (unsigned compare), maps +0 and -0
-// to the same number, and has its low 13 bits clear when the float is an fp16 value: the
-// channel number can ride in the low 7 bits, so that "largest value, lowest channel" is a
-// single unsigned maximum of key + (127 - channel), and "smallest value, lowest channel"
-// a single unsigned minimum of key + channel.
-__device__ __forceinline__ uint32_t order_key(float x) {
-  const uint32_t b = __float_as_uint(x);
-  const uint32_t mag = b & 0x7fffffffu;
-  return (int32_t)b < 0 ? 0x80000000u - mag : 0x80000000u + mag;
-}
-__device__ __forceinline__ float key_value(uint32_t key) {
-  key &= ~0x7fu;
-  return key >= 0x80000000u ? __uint_as_float(key - 0x80000000u) : __uint_as_float((0x80000000u - key) | 0x80000000u);
-}
-// The same order on the fp16 bit patterns themselves, two at a time: per 16-bit half,
+// Integers that order like the fp16 numbers (both zeros the same): on the bit patterns, two at a time: per 16-bit half,
 // 0x8000 + magnitude for a positive number, 0x8000 - magnitude for a negative one (both zeros
 // give 0x8000).  Shifted into the upper half of a word such a key leaves 16 low bits for the
 // channel number.
@@ -399,6 +379,121 @@ struct TokenEncoder {
     mx = h2f((uint16_t)signed_key_bits(A2.x)); mn = h2f((uint16_t)signed_key_bits(-A2.y));
   }
 
+  // Any number of outliers: the largest, then the smallest of the rest, each found over the quad (keys as in ends_by_keys;
+  // kx, kn: of the elements that are left, a taken one at the far end).  The loops over words stay short of registers: 32
+  // keys for each end made this form take 177 of them, two wavefronts per SIMD.
+  __device__ static __forceinline__ void outliers_one_by_one(const uint4 (&raw)[NCH], int c, us2 one, int n_o, float thr_lo, float thr_hi,
+                                                             uint8_t* oidx_row, uint16_t* oval_row, float& mn, float& mx) {
+    constexpr int W = 4 * NCH;
+    ss2 kx[W], kn[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) kx[j] = kn[j] = signed_keys_pair(word_of(raw, j));
+    auto largest = [&]() -> int {
+      ss2 m = kx[0];
+#pragma unroll
+      for (int j = 1; j < W; ++j) m = pk_max(m, kx[j]);
+      m = pk_max(m, m.yx);
+      m = pk_max(m, __builtin_bit_cast(ss2, dpp_u<0xB1>(__builtin_bit_cast(uint32_t, m))));
+      return pk_max(m, __builtin_bit_cast(ss2, dpp_u<0x4E>(__builtin_bit_cast(uint32_t, m)))).x;
+    };
+    auto smallest = [&]() -> int {
+      ss2 m = kn[0];
+#pragma unroll
+      for (int j = 1; j < W; ++j) m = pk_min(m, kn[j]);
+      m = pk_min(m, m.yx);
+      m = pk_min(m, __builtin_bit_cast(ss2, dpp_u<0xB1>(__builtin_bit_cast(uint32_t, m))));
+      return pk_min(m, __builtin_bit_cast(ss2, dpp_u<0x4E>(__builtin_bit_cast(uint32_t, m)))).x;
+    };
+    int n_rec = 0;
+#pragma unroll 1
+    for (int end = 0; end < 2; ++end) {
+      bool alive = true;                   // the same for the four lanes of a quad
+#pragma unroll 1
+      for (int k = 0; k < n_o; ++k) {
+        const int M = end == 0 ? largest() : smallest();
+        const float val = h2f((uint16_t)signed_key_bits(M));
+        alive = alive && (end == 0 ? val > thr_hi : val < thr_lo);
+        if (__ballot(alive) == 0ull) break;
+        const uint32_t pair = __builtin_amdgcn_perm(0u, (uint32_t)M, 0x01000100u);
+        const uint32_t ch = first_channel([&](int j) { return __builtin_bit_cast(uint32_t, end == 0 ? kx[j] : kn[j]); }, c, pair, one);
+        const bool mine = alive && ((ch >> 3) & 3u) == (uint32_t)c;
+        const uint32_t at = (ch >> 5) * 4u + ((ch >> 1) & 3u);
+        const uint32_t half = mine ? (ch & 1u ? 0xffff0000u : 0xffffu) : 0u;
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+          const uint32_t m = at == (uint32_t)j ? half : 0u;
+          kx[j] = __builtin_bit_cast(ss2, (__builtin_bit_cast(uint32_t, kx[j]) & ~m) | (0x80008000u & m));
+          kn[j] = __builtin_bit_cast(ss2, (__builtin_bit_cast(uint32_t, kn[j]) & ~m) | (0x7fff7fffu & m));
+        }
+        if (mine) { oidx_row[n_rec] = (uint8_t)ch; oval_row[n_rec] = outlier_bits(raw, c, (int)ch, val); }
+        n_rec += alive ? 1 : 0;
+      }
+    }
+    if (c == 0)
+      for (int k = n_rec; k < 2 * n_o; ++k) { oidx_row[k] = 0xffu; oval_row[k] = 0; }
+    mx = h2f((uint16_t)signed_key_bits(largest())); mn = h2f((uint16_t)signed_key_bits(smallest()));
+  }
+
+  // Outliers by thresholds, where no token of the wavefront has more of them at an end than are kept and no value is not a
+  // number (else nothing is done and the result is false): every value outside is one, in any order, the rest is [min, max].
+  __device__ static __forceinline__ bool passing_thresholds(const uint4 (&raw)[NCH], int c, us2 one, int n_o, float thr_lo, float thr_hi,
+                                                            uint8_t* oidx_row, uint16_t* oval_row, float& mn, float& mx) {
+    constexpr int W = 4 * NCH;
+    // the thresholds as keys: of the largest fp16 number not above thr_hi, the smallest not below thr_lo
+    const uint32_t hb = f2h(thr_hi), lb = f2h(thr_lo);
+    const int key_hi = (int)signed_keys_pair(hb).x - (h2f((uint16_t)hb) > thr_hi ? 1 : 0), key_lo = (int)signed_keys_pair(lb).x + (h2f((uint16_t)lb) < thr_lo ? 1 : 0);
+    const ss2 hi = {(short)key_hi, (short)key_hi}, lo = {(short)key_lo, (short)key_lo};
+    uint32_t any = raw[0].x, hits = 0u;        // (hits, values outside: per word a bit for each half, the first word's in bit W - 1)
+    ss2 most = {-0x8000, -0x8000}, least = {0x7fff, 0x7fff};
+    uint32_t n_top = 0u;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const ss2 k = signed_keys_pair(word_of(raw, j));
+      if (j & 1) any = pk_hmaximum(any, word_of(raw, j), word_of(raw, j - 1));
+      // one where the clamped value differs from the value
+      const uint32_t over = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, __builtin_bit_cast(uint32_t, pk_max(k, hi)) ^ __builtin_bit_cast(uint32_t, hi)), one));
+      const uint32_t under = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(us2, __builtin_bit_cast(uint32_t, pk_min(k, lo)) ^ __builtin_bit_cast(uint32_t, lo)), one));
+      const uint32_t out = over | under;
+      n_top += over;
+      asm("v_lshl_or_b32 %0, %1, 1, %2" : "=v"(hits) : "v"(hits), "v"(out));
+      const ss2 mask = (ss2)0 - __builtin_bit_cast(ss2, out);
+      const uint32_t m = __builtin_bit_cast(uint32_t, mask), kw = __builtin_bit_cast(uint32_t, k);
+      most = pk_max(most, __builtin_bit_cast(ss2, (kw & ~m) | (0x80008000u & m)));
+      least = pk_min(least, __builtin_bit_cast(ss2, (kw & ~m) | (0x7fff7fffu & m)));
+    }
+    const int top = (int)((n_top & 0xffffu) + (n_top >> 16)), all = __popc(hits);
+    auto quad_sum = [](int x) { x += (int)dpp_u<0xB1>((uint32_t)x); return x + (int)dpp_u<0x4E>((uint32_t)x); };
+    const int counts = quad_sum(top | (all << 16)), q_top = counts & 0xffff, q_all = counts >> 16;
+    any = pk_hmaximum(any, halves_swapped(any), any);
+    const bool nan = (any & 0x7fffu) > 0x7c00u;
+    if (__ballot(nan || q_top > n_o || q_all - q_top > n_o) != 0ull) return false;
+    most = pk_max(most, most.yx); least = pk_min(least, least.yx);
+#pragma unroll
+    for (int step = 0; step < 2; ++step) {
+      const uint32_t a = __builtin_bit_cast(uint32_t, most), b = __builtin_bit_cast(uint32_t, least);
+      most = pk_max(most, __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(a) : dpp_u<0xB1>(a)));
+      least = pk_min(least, __builtin_bit_cast(ss2, step ? dpp_u<0x4E>(b) : dpp_u<0xB1>(b)));
+    }
+    mx = h2f((uint16_t)signed_key_bits(most.x)); mn = h2f((uint16_t)signed_key_bits(least.x));
+    // the row: unused places first, then every lane's entries behind those of the lanes before it
+    if (c == 0)
+      for (int k = q_all; k < 2 * n_o; ++k) { oidx_row[k] = 0xffu; oval_row[k] = 0; }
+    const int x1 = (int)dpp_u<0xB1>((uint32_t)all), x2 = (int)dpp_u<0x4E>((uint32_t)all), x3 = (int)dpp_u<0x1B>((uint32_t)all);     // of lanes c^1, c^2, c^3
+    int at = (c & 1 ? x1 : 0) + (c & 2 ? x2 + x3 : 0);
+    while (hits) {
+      const int bit = 31 - __builtin_clz(hits);
+      hits &= ~(1u << bit);
+      const int hf = bit >> 4, w = W - 1 - (bit & 15);
+      uint32_t x = 0u;
+#pragma unroll
+      for (int j = 0; j < W; ++j) x = w == j ? word_of(raw, j) : x;
+      oidx_row[at] = (uint8_t)(32 * (w >> 2) + 8 * c + 2 * (w & 3) + hf);
+      oval_row[at] = (uint16_t)(x >> (16 * hf));
+      ++at;
+    }
+    return true;
+  }
+
   // thr_lo, thr_hi: an outlier must lie below thr_lo resp. above thr_hi (+inf, -inf: the count
   // rule, every candidate passes); a side stops at its first candidate that does not, and the
   // rows of the side store are filled from the front, the rest marked unused (channel 255)
@@ -411,44 +506,11 @@ struct TokenEncoder {
       if constexpr (ONE) {
         ends_of_token(raw, c, oidx_row, oval_row, mn, mx, finite);
       } else {
-        uint32_t kx[EPL], kn[EPL];
-#pragma unroll
-        for (int i = 0; i < NCH; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const uint32_t k = order_key(h2f((uint16_t)half_bits(raw, i, e)));
-            kx[8 * i + e] = k + (uint32_t)(127 - channel(c, i, e));
-            kn[8 * i + e] = k + (uint32_t)channel(c, i, e);
-          }
-        int n_rec = 0;
-        bool alive = true;
-        for (int k = 0; k < 2 * n_o; ++k) {
-          const bool top = k < n_o;
-          if (k == n_o) alive = true;
-          uint32_t m = top ? 0u : 0xffffffffu;
-#pragma unroll
-          for (int j = 0; j < EPL; ++j) m = top ? (m > kx[j] ? m : kx[j]) : (m < kn[j] ? m : kn[j]);
-          const uint32_t M = top ? quad_umax(m) : quad_umin(m);
-          const int ch = top ? 127 - (int)(M & 127u) : (int)(M & 127u);
-          const float val = key_value(M);
-          alive = alive && (top ? val > thr_hi : val < thr_lo);      // the same for the four lanes of the quad
-          if (alive) {
-#pragma unroll
-            for (int j = 0; j < EPL; ++j) {
-              const bool dead = top ? kx[j] == M : kn[j] == M;
-              if (dead) { kx[j] = 0u; kn[j] = 0xffffffffu; }
-            }
-            if (((ch >> 3) & 3) == c) { oidx_row[n_rec] = (uint8_t)ch; oval_row[n_rec] = outlier_bits(raw, c, ch, val); }
-            ++n_rec;
-          }
-        }
-        if (c == 0)
-          for (int k = n_rec; k < 2 * n_o; ++k) { oidx_row[k] = 0xffu; oval_row[k] = 0; }
-        uint32_t m1 = 0u, m0 = 0xffffffffu;
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) { m1 = m1 > kx[j] ? m1 : kx[j]; m0 = m0 < kn[j] ? m0 : kn[j]; }
-        const uint32_t key_mx = quad_umax(m1), key_mn = quad_umin(m0);
-        mx = key_value(key_mx); mn = key_value(key_mn);
+        uint32_t ones = 0x10001u;
+        asm("" : "+s"(ones));              // (see ends_of_token)
+        const us2 one = __builtin_bit_cast(us2, ones);
+        if (thr_lo == INFINITY || !passing_thresholds(raw, c, one, n_o, thr_lo, thr_hi, oidx_row, oval_row, mn, mx))
+          outliers_one_by_one(raw, c, one, n_o, thr_lo, thr_hi, oidx_row, oval_row, mn, mx);
       }
       if (c == 0) *mm_pos = (uint32_t)f2h(mn) | ((uint32_t)f2h(mx) << 16);
     } else {
@@ -1199,7 +1261,7 @@ __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
 // grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands half of the sides over takes 145-159 us (274-306 when
 // the general build moved token by token; 64 channels 115-120, 202-216 then).
 template <int D, bool ONE>
-constexpr int listed_per_cu() { return D == 128 ? (ONE ? 4 : 2) : (ONE ? 5 : 4); }      // workgroups a compute unit takes
+constexpr int listed_per_cu() { return D == 128 ? (ONE ? 4 : 3) : (ONE ? 5 : 4); }      // workgroups a compute unit takes
 template <int D, bool ONE, bool HAS1>
 __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_listed(QaqBuildArgs a) {
   __shared__ BuildLds<D, ONE ? 2 : QAQ_MAX_NO2> L;
