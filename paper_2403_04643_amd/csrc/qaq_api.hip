@@ -110,13 +110,13 @@ float value_threshold(const qaq_cache* c, int T) { return (float)(c->sigma_x / s
 //   one outlier per end     128 channels: threshold x 0.83 80 | 87, x 0.70 99 | 88; 64 tokens at the widest width 97 | 109, 128: 126 | 121;
 //                           with the 1-bit width x 0.90 84 | 90, x 0.83 93 | 92, x 1.2 82 | 83, x 1.5 110 | 83
 //                           64 channels: x 0.70 42 | 60, x 0.50 60 | 61; 256 tokens 67 | 77, 512: 82 | 79; with the 1-bit width x 3 62 | 59
-//   other forms (more       128 channels, two per end: x 0.70 102 | 152, x 0.50 200 | 158; 512 tokens 201 | 235, 1000: 265 | 239
-//   registers, half the     64 channels, two per end: x 0.50 53 | 82; 512 tokens 85 | 114, 1000: 107 | 112
-//   wavefronts)             thresholds, 128 channels: x 0.70 108 | 157, x 0.50 208 | 163; 512 tokens 233 | 253, 1000: 289 | 258
+//   other forms (more       128 channels, two per end: x 0.70 92 | 114, x 0.50 173 | 120; 256 tokens 101 | 169, 512: 178 | 179
+//   registers, fewer        64 channels, two per end: x 0.50 55 | 84; 512 tokens 85 | 115, 1000: 112 | 112
+//   wavefronts)             thresholds, 128 channels: x 0.70 99 | 120, x 0.50 179 | 124; 256 tokens 160 | 183, 512: 193 | 195
 float expected_moves(const qaq_cache* c, float c_v) {
   const bool one = c->dims.no2 == 2 && !c->dims.csr, wide = c->dims.D == 128, has1 = c->view.has1 != 0;
-  const float came = one ? (wide ? 9.0f : 4.1f) : (wide ? 1.4f : 1.9f);
-  const float fell = !one ? 0.34f : !wide ? 0.46f : has1 ? 1.0f : 0.8f, rose = !has1 ? 0.0f : wide ? 0.95f : 0.31f;
+  const float came = one ? (wide ? 9.0f : 4.1f) : (wide ? 2.0f : 1.9f);
+  const float fell = !one ? (wide ? 0.38f : 0.33f) : !wide ? 0.46f : has1 ? 1.0f : 0.8f, rose = !has1 ? 0.0f : wide ? 0.95f : 0.31f;
   float share = c->len > 0 ? came * (float)c->unruled / (float)c->len : 0.0f;
   if (c->ruled_c_v > 0.0f && c_v > 0.0f) {
     const float octaves = std::log2(c_v / c->ruled_c_v);
