@@ -649,7 +649,7 @@ __device__ __forceinline__ void put_tile_summary(const QaqView& v, int side, siz
 //
 // Bound by vector instructions (the search and the codes, see TokenEncoder), then by the fp16 rows it reads.  Vector instructions
 // per wavefront 3240 -> 2600 by the encoder, -> 2020 by this form (through the general path before): 2 x 32 heads x 12001
-// tokens 167 -> 140 -> 113 us = 4.1 TB/s, 16 x 8 heads x 8192 216 -> 152, 8 x 32 heads x 4096 at eight bits, in three chunks,
+// tokens 167 -> 140 -> 109 us = 4.2 TB/s, 16 x 8 heads x 8192 216 -> 143, 8 x 32 heads x 4096 at eight bits, in three chunks,
 // 229 -> 197 -> 187.
 // ---------------------------------------------------------------------------------
 
