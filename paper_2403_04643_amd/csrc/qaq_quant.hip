@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ON
 // A side with nothing to do is left after its widths are known.  Any other is read into LDS and written anew in the manner
 // of a fresh one, with the tokens that are new or widen encoded in between.  Moving only the tokens that change (the
 // decode-step kernel's way, with few registers) was not worth its bookkeeping here: 8 x 32 heads x 4000 tokens, 0.5 % of the
-// tokens changed 93 -> 77 us, 5 % 154 -> 109, half of them 198 -> 113, all 225 -> 128; two outliers per end 157 -> 138 ... 392 -> 223.
+// tokens changed 93 -> 74 us, 5 % 154 -> 102, half of them 198 -> 106, all 225 -> 122; two outliers per end 157 -> 95 ... 392 -> 161.
 template <int D, bool ONE, bool HAS1>
 __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ONE ? 2 : QAQ_MAX_NO2>& L, const int bh, const int tile, const int side, const int tid) {
   constexpr int MAXO = ONE ? 2 : QAQ_MAX_NO2, ROW = 4 * BuildLds<D, MAXO>::SROW;
