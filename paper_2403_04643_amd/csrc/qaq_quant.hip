@@ -1232,7 +1232,9 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
   }
   QaqCounts cn;
   sort_slots<D, MAXO, HAS1>(cls, cn, L, tid);
-  unpack_all<D, MAXO, HAS1>(side, base, c_old, L, tid);
+  // (with every token of the side encoded there is nothing to keep: 8 x 32 heads x 4000 tokens all widened 214 us with the old
+  // codes read all the same, 176 without; 198 when only moved tokens were handled)
+  if (n_enc < n_after) unpack_all<D, MAXO, HAS1>(side, base, c_old, L, tid);
   __syncthreads();
   put_sorted<D, ONE, HAS1>(v, side, bh, tile, n_before, n_after, cn, L, tid);
 }

@@ -78,3 +78,20 @@ def test_values_that_are_not_numbers(head_dim):
         a, b, c = (o[key].view(np.uint16) if key == "minmax" else o[key] for o in out)
         np.testing.assert_array_equal(a, b, err_msg=key)
         np.testing.assert_array_equal(a, c, err_msg=key)
+
+
+@pytest.mark.parametrize("head_dim,n_o", [(128, 1), (64, 1), (128, 2)])
+def test_sides_of_which_every_token_widens(head_dim, n_o):
+    """Nothing of such a tile side's old codes is kept; of its neighbours, one token's are, or those of the tokens that
+    were at the widest width already."""
+    sh = W.shape(2, batch=1, n_q_heads=2, n_kv_heads=2, head_dim=head_dim, context=3 * 256 + 90)
+    rng = np.random.default_rng(43)
+    K, V = W.make_kv(2, sh)
+    narrow = rng.choice(np.array([2, 3, 4], np.uint8), size=K.shape[:3])
+    narrow[:, :, 2 * 256 + 5 : 3 * 256 : 7] = 8            # the third tile: some need not widen
+    wide = np.full_like(narrow, 8)
+    wide[:, :, 256 + 100] = narrow[:, :, 256 + 100]        # the second tile: one stays
+    oc, gc = make_pair(sh, 0.02, n_outlier_per_side=n_o)
+    oc.append(K, V, narrow, narrow); gc.quantize_append(dev(K), dev(V), dev(narrow), dev(narrow))
+    oc.requantize(wide, wide, K, V); gc.requantize(dev(wide), dev(wide), dev(K), dev(V))
+    compare_canonical(oc, gc, "widened")
