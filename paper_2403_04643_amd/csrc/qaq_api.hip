@@ -105,18 +105,30 @@ float value_threshold(const qaq_cache* c, int T) { return (float)(c->sigma_x / s
 // Share of a tile side's tokens that a decode-step update at the value threshold c_v can be expected to move, by what has
 // changed since the widths were last chosen: tokens came at other widths than the rules', the threshold fell (quality), or --
 // with the 1-bit width, whose borders are where most ranges are -- it rose.  (Other rises move few tokens, and key thresholds
-// half of the sides: not counted.)  The factors are fits, at the smallest staging, to where the decode-step kernel with what it
-// hands over takes as long as the general kernel alone.  8 x 32 heads x 4000 tokens, us, the one | the other:
-//   one outlier per end     128 channels: threshold x 0.83 80 | 87, x 0.70 99 | 88; 64 tokens at the widest width 97 | 109, 128: 126 | 121;
-//                           with the 1-bit width x 0.90 84 | 90, x 0.83 93 | 92, x 1.2 82 | 83, x 1.5 110 | 83
-//                           64 channels: x 0.70 42 | 60, x 0.50 60 | 61; 256 tokens 67 | 77, 512: 82 | 79; with the 1-bit width x 3 62 | 59
-//   other forms (more       128 channels, two per end: x 0.70 92 | 114, x 0.50 173 | 120; 256 tokens 101 | 169, 512: 178 | 179
-//   registers, fewer        64 channels, two per end: x 0.50 55 | 84; 512 tokens 85 | 115, 1000: 112 | 112
-//   wavefronts)             thresholds, 128 channels: x 0.70 99 | 120, x 0.50 179 | 124; 256 tokens 160 | 183, 512: 193 | 195
+// half of the sides: not counted.)
+//
+// How many tokens a threshold passes as it moves depends on how the scores are spread, which the host does not see, so the
+// factors are a compromise between four laws of scores: a prompt's own (close together), the same with spiked keys and values,
+// ~ rank^-1.1 (spread out), the sixth power of a uniform number.  The decode-step kernel with what it hands over | the general
+// kernel alone, us, 8 x 32 heads x 4000 tokens, the smallest staging (64 tokens of 128 channels, 120 of 64); "to" marks the line:
+//                                                         prompt    spiked    rank      power
+//   threshold fallen  128 channels              x 0.90     91 |  72   34 |  71  28 |  70   87 |  76   to the decode-step kernel
+//                                               x 0.83    141 |  80   40 |  72  30 |  73  138 |  80   to the general kernel
+//                     two outliers per end      x 0.83    165 | 118   68 | 112  37 | 113  162 | 121   to the general kernel
+//                     outliers by thresholds    x 0.83    168 | 108   86 | 116  34 | 103  163 | 109   to the general kernel
+//                     64 channels               x 0.77     90 |  57   30 |  53  30 |  55   61 |  59   to the decode-step kernel
+//                                               x 0.70    122 |  60   30 |  53  31 |  55  116 |  60   to the general kernel
+//   risen, 1-bit width          128 channels    x 1.20     68 |  70   39 |  76  32 |  76  110 |  77   to the general kernel
+//                                64 channels    x 2.00     48 |  51   35 |  58  35 |  57  103 |  57   to the decode-step kernel
+//   tokens at the widest width  128 channels      200      88 |  94   63 |  98  83 |  97   98 | 104   to the decode-step kernel
+//   behind the others                             256     123 |  94   89 |  98 121 |  98  132 | 104   to the general kernel
+//                     two outliers per end        256     152 | 136  137 | 141 152 | 138  166 | 143   to the general kernel
+//                                64 channels      384      65 |  66   72 |  66  61 |  65   69 |  68   to the decode-step kernel
+// With more staging, 4 x 32 heads x 4000 tokens of 128 channels (138 tokens): x 0.83 61 | 46 (prompt), 24 | 42 (rank); x 0.70
+// 99 | 52, 25 | 43: both still to the decode-step kernel; 16 x 8 heads x 8100 tokens, 384 of them at the widest width 75 | 94
+// (to the decode-step kernel), 512 121 | 94 (to the general one).
 float expected_moves(const qaq_cache* c, float c_v) {
-  const bool one = c->dims.no2 == 2 && !c->dims.csr, wide = c->dims.D == 128, has1 = c->view.has1 != 0;
-  const float came = one ? (wide ? 9.0f : 4.1f) : (wide ? 2.0f : 1.9f);
-  const float fell = !one ? (wide ? 0.38f : 0.33f) : !wide ? 0.46f : has1 ? 1.0f : 0.8f, rose = !has1 ? 0.0f : wide ? 0.95f : 0.31f;
+  const float came = 4.0f, fell = 1.18f, rose = c->view.has1 ? (c->dims.D == 128 ? 0.95f : 0.31f) : 0.0f;
   float share = c->len > 0 ? came * (float)c->unruled / (float)c->len : 0.0f;
   if (c->ruled_c_v > 0.0f && c_v > 0.0f) {
     const float octaves = std::log2(c_v / c->ruled_c_v);

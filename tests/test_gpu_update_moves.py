@@ -114,6 +114,35 @@ def test_who_does_a_step(B, Hkv, D, T, bit_set, n_o, thresholds, staged):
         assert 0 < handed[1] < everything and 0 < handed[2] < everything
 
 
+@pytest.mark.parametrize("D,factor,behind,general", [
+    (64, 0.7, 0, True), (64, 0.9, 0, False), (128, 0.8, 0, True), (128, 0.95, 0, False),      # the bound on the output's error falls
+    (128, 1.0, 128, False), (128, 1.0, 300, True), (64, 1.0, 300, False), (64, 1.0, 600, True),   # tokens at the widest width behind the others
+])
+def test_when_the_general_kernel_takes_a_whole_step(D, factor, behind, general):
+    """At the smallest staging (sixteen value sides per compute unit): the side of the line on which the kernel that takes
+    the step is the faster one for scores as a prompt has them."""
+    B, Hkv, T = 8, 32, 3900
+    print(f"whole step: D={D} factor={factor} behind={behind}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(D + behind)
+    cap = T + behind + 2
+    k = torch.randn((B, Hkv, cap, D), device="cuda", generator=gen).half()
+    cache = qaq.Cache(qaq.make_config(B, Hkv, Hkv, D, cap, [1.0] * Hkv, sigma_s_max=2e-4, sigma_x_max=1e-2))
+    cache.quantize_append(*[k[:, :, :T].contiguous()] * 2)
+    for step in range(2):
+        n = cache.length()
+        if step and behind:
+            cache.quantize_append(*[k[:, :, n:n + behind].contiguous()] * 2)
+        if step:
+            cache.set_sigmas(2e-4, 1e-2 * factor)
+        n = cache.length()
+        s = torch.rand((B, Hkv, n + 1), device="cuda", generator=gen).pow_(6)
+        cache.decode_update((s / s.sum(-1, keepdim=True)).contiguous(), *[k[:, :, n].contiguous()] * 2)
+    handed = cache.stats().update_handovers
+    everything = 2 * B * Hkv * ((cache.length() + 255) // 256)
+    assert (handed == everything) == general, (handed, everything)
+
+
 @pytest.mark.parametrize("B,Hkv,D,T,bit_set,n_o,thresholds", [
     (8, 32, 128, 1290, (2, 3, 4, 8), 1, False),
     (8, 32, 128, 1290, (2, 3, 4, 8), 4, True),
