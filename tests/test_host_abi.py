@@ -193,14 +193,23 @@ def test_decode_path_kernels_do_not_spill():
 @pytest.mark.parametrize("key,max_vgpr,max_scratch", [
     ("k_attn_tileILi128ELi8E", 128, 48),      # several outliers per end, or outliers by thresholds: a few words spilled, and no more
     ("k_attn_tileILi64ELi8E", 128, 0),
-    ("k_build_listedILi128ELb1E", 128, 0),    # four, two, five and four workgroups per compute unit, as the launch counts on
-    ("k_build_listedILi128ELb0E", 256, 0),
+    ("k_build_listedILi128ELb1E", 128, 0),    # four, three, five and four workgroups per compute unit, as the launch counts on
+    ("k_build_listedILi128ELb0E", 168, 0),
     ("k_build_listedILi64ELb1E", 96, 0),
     ("k_build_listedILi64ELb0E", 128, 0),
+    ("k_buildILi128ELb1E", 128, 0),           # four, three, seven and four wavefronts per SIMD
+    ("k_buildILi128ELb0E", 168, 0),
+    ("k_buildILi64ELb1E", 72, 0),
+    ("k_buildILi64ELb0E", 128, 0),
     ("k_attn_gqaILi128ELi2E", 168, 8),        # three workgroups per compute unit; two words, none of them inside the tile loop
     ("k_attn_gqaILi128ELi0E", 168, 0),
     ("k_attn_gqaILi64E", 168, 0),
-    ("k_dequantILi128ELi2E", 128, 0),
+    ("k_dequantILi128ELi2E", 64, 0),          # eight wavefronts per SIMD
+    ("k_dequantILi128ELi0E", 64, 0),
+    ("k_dequantILi64ELi2E", 64, 0),
+    ("k_dequantILi64ELi0E", 64, 0),
+    ("k_dequantILi128ELi8E", 72, 0),          # seven
+    ("k_dequantILi64ELi8E", 72, 0),
     ("k_prefill_softmaxILi64E", 256, 0),      # 64 logits per thread
 ])
 def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
