@@ -15,12 +15,8 @@ struct TileLds {
   uint32_t mm[QAQ_TT];                 // fp16 min | fp16 max << 16, by position
   uint8_t oidx[QAQ_TT][QAQ_MAX_NO2];   // outlier channels, by position
   uint16_t oval[QAQ_TT][QAQ_MAX_NO2];  // outlier fp16 values
-  uint8_t bits_old[QAQ_TT];
-  uint8_t bits_new[QAQ_TT];
+  uint8_t bits[QAQ_TT];
   uint16_t slot_of_pos[QAQ_TT];
-  uint16_t pos_of_slot[QAQ_TT];
-  int wave_cnt[4][4];
-  int flag;
 };
 
 __device__ __forceinline__ float h2f(uint16_t b) { return __half2float(__ushort_as_half(b)); }
@@ -31,11 +27,11 @@ __device__ __forceinline__ uint32_t rd_field(const uint8_t* base, QaqFieldPos p,
 }
 
 // Code of (slot, channel d) as stored for this tile side.
-template <int D, bool HAS1 = true>
+template <int D>
 __device__ __forceinline__ uint32_t load_code(int side, const uint8_t* base, const QaqCounts& c, uint32_t r2,
                                               uint32_t r1, uint32_t r4, uint32_t r8, uint32_t r1b, int slot, int d) {
   const int n32 = c.n32();
-  if (HAS1 && slot >= c.first1()) {
+  if (slot >= c.first1()) {
     const int i1 = slot - c.first1();
     return side == 0 ? rd_field(base, qaq_k_field(r1b, 1, i1, d, D), 1u) : rd_field(base, qaq_v_field(r1b, 1, i1, d, D), 1u);
   }
@@ -73,7 +69,7 @@ __device__ void tile_load(const QaqView& v, int side, int b, int h, int tile, in
     const int pos = v.perm[side][gi];
     L.mm[pos] = v.mm[side][gi];
     L.slot_of_pos[pos] = (uint16_t)s;
-    L.bits_old[pos] = (uint8_t)c.bits_of_slot(s);
+    L.bits[pos] = (uint8_t)c.bits_of_slot(s);
     for (int k = 0; k < v.no2 && !v.csr; ++k) {
       L.oidx[pos][k] = v.oidx[side][gi * v.no2 + k];
       L.oval[pos][k] = v.oval[side][gi * v.no2 + k];
@@ -126,7 +122,6 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {     // set
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // rows of four bytes <-> columns of four bytes: t[k] byte j = w[j] byte k
 __device__ __forceinline__ void transpose4(const uint32_t (&w)[4], uint32_t (&t)[4]) {
   const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);   // w0.b0 w1.b0 w0.b1 w1.b1
@@ -226,7 +221,7 @@ __device__ __forceinline__ float key16_value(uint32_t key) {
 // chunks c, c+4, c+8, ... (a quad reads 64 contiguous bytes per load).  Outliers
 // (Section 4.2): the n_o largest, then the n_o smallest of the rest, ties to the lower
 // channel; [min,max] over what remains; then the midpoint quantizer of Section 4.1:
-// code = clamp(floor((x-min)*2^B/range)).
+// code = clamp(floor((x-min)*2^B/range)), always at eight bits: a narrower code is its upper bits.
 //
 // Bound by vector instructions: a bulk build spends four fifths of its on the search and the codes.  So the search works
 // on pairs of fp16 values and looks for the channels afterwards (228 instructions for a quad's lane with 32 elements; 282 on
@@ -497,7 +492,7 @@ struct TokenEncoder {
   // thr_lo, thr_hi: an outlier must lie below thr_lo resp. above thr_hi (+inf, -inf: the count
   // rule, every candidate passes); a side stops at its first candidate that does not, and the
   // rows of the side store are filled from the front, the rest marked unused (channel 255)
-  __device__ static __forceinline__ void run(const uint4 (&raw)[NCH], int c, bool fresh, int bits, int n_o, uint32_t* mm_pos,
+  __device__ static __forceinline__ void run(const uint4 (&raw)[NCH], int c, bool fresh, int n_o, uint32_t* mm_pos,
                                              uint8_t* oidx_row, uint16_t* oval_row, uint32_t* stage_row,
                                              float thr_lo = INFINITY, float thr_hi = -INFINITY) {
     float mn, mx;
@@ -519,12 +514,9 @@ struct TokenEncoder {
       mx = h2f((uint16_t)(m >> 16));
     }
     const float range = mx - mn;
-    const float levels = (float)(1 << bits);
-    const float inv = range > 0.0f ? levels / range : 0.0f;   // an empty range gives code 0 everywhere
-    const float top_code = levels - 1.0f;
-    // (eight bits, the widest width, at which new tokens are encoded: the byte conversion's own clamp is the quantizer's,
-    // but for a NaN, whose code is the top one)
-    const bool clamps = __ballot(bits < 8 || !finite) != 0ull;
+    const float inv = range > 0.0f ? 256.0f / range : 0.0f;   // an empty range gives code 0 everywhere
+    // (the byte conversion's own clamp is the quantizer's at eight bits, but for a NaN, whose code is the top one)
+    const bool clamps = __ballot(!finite) != 0ull;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       float x[8];
@@ -536,7 +528,7 @@ struct TokenEncoder {
       }
       if (clamps) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = vminf(x[e], top_code);
+        for (int e = 0; e < 8; ++e) x[e] = vminf(x[e], 255.0f);
       }
       uint32_t w0, w1;
       floor_bytes(x, w0, w1);
@@ -827,7 +819,7 @@ __device__ __forceinline__ void put_sorted(const QaqView& v, int side, int bh, i
 }
 
 // All stored codes of a tile side -> staged bytes, a code in the upper bits of its byte (what is below it is left to
-// chance: a token's width never grows here).  
+// chance: a token's width never grows here).
 template <int D, int MAXO, bool HAS1>
 __device__ __forceinline__ void unpack_all(int side, const uint8_t* base, const QaqCounts& c, BuildLds<D, MAXO>& L, int tid) {
   constexpr int NQ = D / 16, KS = D / 64;
@@ -947,7 +939,7 @@ __device__ __forceinline__ void fresh_tile(const QaqBuildArgs& a, BuildLds<D, ON
   };
   auto encode = [&](int pass, const uint4 (&raw)[Enc::NCH]) {
     const int p = pass * TPP + gt;
-    if (p < n) Enc::run(raw, c, true, 8, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
+    if (p < n) Enc::run(raw, c, true, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
   };
   uint4 cur[Enc::NCH], nxt[Enc::NCH];
   fetch(0, cur);
@@ -1196,7 +1188,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
       const int kind_next = fetch(pass + 1, nxt);
       if (kind) {                          // whole quads drop out together
         const int p = position(pass);
-        Enc::run(cur, c, kind == 1, 8, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
+        Enc::run(cur, c, kind == 1, v.no2 / 2, &L.mm[p], L.oidx[p], L.oval[p], (uint32_t*)((uint8_t*)L.stage + p * ROW), thr_lo, thr_hi);
       }
 #pragma unroll
       for (int i = 0; i < Enc::NCH; ++i) cur[i] = nxt[i];
@@ -1259,7 +1251,8 @@ __global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
 //
 // Bound by the workgroups in flight, i.e. by registers: left to itself the compiler keeps everything that
 // follows from the thread or from the kernel's arguments in registers across the loop (142-247 of them when that was tried).
-// So each round takes the thread's index and the arguments as if they were new: 80-184 registers, no scratch.  With the
+// So each round takes the thread's index and the arguments as if they were new: 80 | 108 registers at 64 channels, 119 | 168 at
+// 128 (one outlier per end | other forms, which keep up to 21 scalars in lanes of vector registers), no scratch.  With the
 // grid of launch_update, a step of 8 x 32 heads x 4000 tokens that hands half of the sides over takes 145-159 us (274-306 when
 // the general build moved token by token; 64 channels 115-120, 202-216 then).
 template <int D, bool ONE>
@@ -2307,7 +2300,7 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
   tile_load<D>(v, a.side, b, h, tile, n_tok, L);
   if (tid < n_tok) {
     const size_t o = (size_t)bh * a.len + t0 + tid;
-    if (a.bits) a.bits[o] = L.bits_old[tid];
+    if (a.bits) a.bits[o] = L.bits[tid];
     if (a.minmax) { a.minmax[2 * o] = (uint16_t)(L.mm[tid] & 0xffffu); a.minmax[2 * o + 1] = (uint16_t)(L.mm[tid] >> 16); }
     for (int k = 0; k < v.no2; ++k) {
       if (a.oidx) a.oidx[o * v.no2 + k] = L.oidx[tid][k];
@@ -2317,7 +2310,7 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
   if (a.codes) {
     for (int e = tid; e < n_tok * D; e += kThreads) {
       const int pos = e / D, k = e % D;
-      const int bits = L.bits_old[pos];
+      const int bits = L.bits[pos];
       uint32_t byte = 0;
       if (k < D * bits / 8) {
         for (int j = 0; j < 8; ++j) {
@@ -2338,8 +2331,8 @@ __global__ __launch_bounds__(kThreads) void k_export(QaqExportArgs a) {
 // belongs to the token alone.  Values: an item is (unit of 16 tokens, eight channels) -- eight words, each
 // one channel of the 16 tokens, turned into rows by 4x4 byte transposes; the D/8 lanes of a unit read its
 // 4 D bytes between them.
-// The stores want wavefronts in flight more than long ones: loops are not unrolled, so that 64 registers (80 where a token has
-// more than two outliers) let 32 of them live on a compute unit; unrolled they took 104 and half as many did.
+// The stores want wavefronts in flight more than long ones: loops are not unrolled, so that 64 registers (72 where a token has
+// more than two outliers) let 32 (28) of them live on a compute unit; unrolled they took 104 and half as many did.
 // 8 sequences x 32 heads x 4096 tokens x 128 channels, all 8-bit (805 MB): 1232 us code by code through an LDS staging
 // tile, 209 us (3.8 TB/s; a 4 GiB copy: 4.85) with whole words at 16 wavefronts, 175 (4.6) at 32; widths of mean 2.5 / 2.1
 // (615 MB) 203 -> 101; 64 channels, mean 4 / 3, 112 -> 68; three outliers per end 250 -> 174.
@@ -2657,11 +2650,12 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float movi
   QaqBuildArgs a = a_in;
   const long long sides = (long long)a.v.B * a.v.Hkv * ntiles * 2;
   // LDS for moved tokens: what is left of a compute unit's 160 KB when all value sides are resident at once (the key
-  // sides, few of which have work, take the places that become free), from a sixteenth -- 64 tokens of 128 channels, 119
+  // sides, few of which have work, take the places that become free), from a sixteenth -- 64 tokens of 128 channels, 120
   // of 64 -- up to a whole tile, which leaves nothing for the general kernel to do (a batch of six with unequal prompts,
   // 72 heads in all: 20.4 + 13.8 us with staging for 60 tokens and the second launch, 17.4 us without)
   constexpr int lds = 160 * 1024, grain = 1280;       // (LDS is handed out 1280 bytes at a time)
   constexpr int least = (lds / kUpdResident / grain * grain - (int)sizeof(UpdLds<D>)) / UpdLds<D>::PER_TOKEN;
+  static_assert(least == (D == 128 ? 64 : 120), "the figures above and those at expected_moves");
   static_assert(least * UpdLds<D>::PER_TOKEN >= 2 * QAQ_TT * 4, "the space also holds two words per position before any code is staged");
   const int cus = qaq_compute_units();
   const long long resident = (sides / 2 + cus - 1) / cus;
