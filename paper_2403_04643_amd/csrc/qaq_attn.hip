@@ -136,6 +136,18 @@ struct DigitExchange {
   }
 };
 
+// A weight as a whole number.  (Halves to even: the values' codes and minima cancel to a hundredth in an output, and with
+// halves upwards -- v_cvt_rpi_i32_f32, one instruction less -- the error of an output was 2 to 3 times as large.)
+__device__ __forceinline__ uint32_t round_weight(float x) { return (uint32_t)rintf(x); }
+// A matrix operand out of a table [slot][16 rows]: the 16 lanes of a group read 16 slots' rows, 16 bytes each, in two halves
+// of eight slots -- lane n bytes 8*n .. of each half -- and the transposing read leaves row n's bytes of the slots, in order, with lane n.
+__device__ __forceinline__ v4i weight_operand(const int8_t* p) {
+  typedef int v2i __attribute__((ext_vector_type(2)));
+  typedef __attribute__((address_space(3))) v2i* lds_v2i;
+  const v2i a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)p), b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(p + 128));
+  return v4i{a[0], a[1], b[0], b[1]};
+}
+
 // B operand (16 byte-spread codes of one slice).  "Scaled" variants leave the factors
 // 1, 4, 16, 1 (2-bit) resp. 1, 2, 4, 8 (1-bit) on the four element groups.
 template <int BF>
@@ -422,21 +434,34 @@ struct ValRegs {
   uint32_t v8;   // 8-bit values (token-major rows): this lane's four channels of row lane / (D/16), so
                  // that the first 64 / (D/16) such tokens of a tile -- a tile of a cache the rules shaped rarely
                  // has more -- cost no load inside the tile loop
+  // In two steps, the first without what depends on the class counts, so that the first tile of a part is on its way while its
+  // counts are: the 2-bit field units start the tile side.  (With a width set that has 1 the region may be short: as far as it reaches.)
   template <bool H1, bool PRE8 = false>
-  __device__ __forceinline__ void load(const QaqView& v, int len, int b, int h, int tile, const QaqCounts& cv, int tid, int wave, int nn, int g) {
-    c = cv;
+  __device__ __forceinline__ void load_first(const QaqView& v, int len, int b, int h, int tile, int tid, int wave, int nn, int g) {
     const int n_tok = min(len - tile * QAQ_TT, QAQ_TT);
-    const uint8_t* base = qaq_tile_codes(v, 1, b, h, tile);
-    const gbytes_t ubase = uniform_ptr(base);
+    const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 1, b, h, tile));
     const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
     const uint32_t slot = (uint32_t)min(tid, n_tok - 1);
     mm = gload32(uniform_ptr(v.mm[1] + gi0), 4u * slot);
     pos = gload32(uniform_ptr(v.perm[1] + gi0), slot & ~3u);
     o.load(v, 1, gi0, slot, v.no2);
-    const uint32_t voff = (uint32_t)g * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave;
+    if (!H1) {
+      const uint32_t voff = (uint32_t)g * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave;
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk)
-      if (!H1 || blk * 64 < c.n32()) gload_dwords<CGW>(ubase + voff + (uint32_t)blk * (16u * D), vw2[blk]);   // (blocks past the region are not used)
+      for (int blk = 0; blk < 4; ++blk) gload_dwords<CGW>(ubase + voff + (uint32_t)blk * (16u * D), vw2[blk]);   // (blocks past the region are not used)
+    }
+  }
+  template <bool H1, bool PRE8 = false>
+  __device__ __forceinline__ void load_rest(const QaqView& v, int b, int h, int tile, const QaqCounts& cv, int tid, int wave, int nn, int g) {
+    c = cv;
+    const uint8_t* base = qaq_tile_codes(v, 1, b, h, tile);
+    const gbytes_t ubase = uniform_ptr(base);
+    if (H1) {
+      const uint32_t voff = (uint32_t)g * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk)
+        if (blk * 64 < c.n32()) gload_dwords<CGW>(ubase + voff + (uint32_t)blk * (16u * D), vw2[blk]);
+    }
     const QaqVRegions rV = qaq_v_regions(c, D);
     if (PRE8 && CGW == 2) {
       const int nhu = (c.n4 + 7) >> 3;
@@ -459,46 +484,10 @@ struct ValRegs {
           vw1[3 - blk] = *(const uint32_t*)(base + rV.r1b + (uint32_t)min(blk * 4 + g, nu1b - 1) * (2u * D) + (uint32_t)nn * (NCG * 2) + 4u * ((CGW * wave) >> 1));
     }
   }
-  // the first tile of a part in two steps, as for the keys: the 2-bit field units start the tile side
-  template <bool H1>
-  __device__ __forceinline__ void load_head(const QaqView& v, int len, int b, int h, int tile, int tid, int wave, int nn, int g) {
-    const int n_tok = min(len - tile * QAQ_TT, QAQ_TT);
-    const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 1, b, h, tile));
-    const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
-    const uint32_t slot = (uint32_t)min(tid, n_tok - 1);
-    mm = gload32(uniform_ptr(v.mm[1] + gi0), 4u * slot);
-    pos = gload32(uniform_ptr(v.perm[1] + gi0), slot & ~3u);
-    o.load(v, 1, gi0, slot, v.no2);
-    if (!H1) {
-      const uint32_t voff = (uint32_t)g * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave;
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk) gload_dwords<CGW>(ubase + voff + (uint32_t)blk * (16u * D), vw2[blk]);
-    }
-  }
-  template <bool H1>
-  __device__ __forceinline__ void load_tail(const QaqView& v, int b, int h, int tile, const QaqCounts& cv, int wave, int nn, int g) {
-    c = cv;
-    const uint8_t* base = qaq_tile_codes(v, 1, b, h, tile);
-    if (H1) {
-      const gbytes_t ubase = uniform_ptr(base);
-      const uint32_t voff = (uint32_t)g * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave;
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk)
-        if (blk * 64 < c.n32()) gload_dwords<CGW>(ubase + voff + (uint32_t)blk * (16u * D), vw2[blk]);
-    }
-    const QaqVRegions rV = qaq_v_regions(c, D);
-    const int nu1 = (c.n3 + 15) >> 4;
-#pragma unroll
-    for (int blk = 0; blk < 4; ++blk)
-      if (blk * 4 < nu1)
-        vw1[blk] = *(const uint32_t*)(base + rV.r1 + (uint32_t)min(blk * 4 + g, nu1 - 1) * (2u * D) + (uint32_t)nn * (NCG * 2) + 4u * ((CGW * wave) >> 1));
-    if (H1) {
-      const int nb3 = (nu1 + 3) >> 2, nu1b = (c.n1 + 15) >> 4;
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk)
-        if (blk * 4 < nu1b && 3 - blk >= nb3)
-          vw1[3 - blk] = *(const uint32_t*)(base + rV.r1b + (uint32_t)min(blk * 4 + g, nu1b - 1) * (2u * D) + (uint32_t)nn * (NCG * 2) + 4u * ((CGW * wave) >> 1));
-    }
+  template <bool H1, bool PRE8 = false>
+  __device__ __forceinline__ void load(const QaqView& v, int len, int b, int h, int tile, const QaqCounts& cv, int tid, int wave, int nn, int g) {
+    load_first<H1, PRE8>(v, len, b, h, tile, tid, wave, nn, g);
+    load_rest<H1, PRE8>(v, b, h, tile, cv, tid, wave, nn, g);
   }
 };
 
@@ -518,6 +507,19 @@ __device__ __forceinline__ void die_neighbours(int lin, int total, int share, in
     const int r = lin - whole;
     member = r % share; item = whole / share + r / share;
   }
+}
+
+// The tiles of part `chunk` of a head with `ntile` of them: runs of ntile / nparts, the last ntile % nparts of them one longer.
+// (The quotient of the longest sequence comes from the host: a division is a hundred cycles of every workgroup's way to its
+// first load, and with a 64-bit product in it several hundred.)
+__device__ __forceinline__ void part_tiles(const QaqAttnArgs& a, int ntile, int chunk, int& begin, int& end) {
+  int run = a.run, shorter = a.shorter;
+  if (a.v.ragged) {
+    run = ntile / a.nparts;
+    shorter = a.nparts - (ntile - run * a.nparts);
+  }
+  begin = chunk * run + max(chunk - shorter, 0);
+  end = begin + run + (chunk >= shorter ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -576,8 +578,8 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   const int b = bq / v.Hq, hq = bq % v.Hq, h = hq / a.G;
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
   const int ntile = (len + QAQ_TT - 1) / QAQ_TT;
-  const int tile_begin = (int)((long long)chunk * ntile / a.nparts);
-  const int tile_end = (int)((long long)(chunk + 1) * ntile / a.nparts);
+  int tile_begin, tile_end;
+  part_tiles(a, ntile, chunk, tile_begin, tile_end);
   if (!P && tile_begin >= tile_end) {
     // a sequence shorter than the longest can leave a part without tiles: a partial that the merge ignores
     float* part = a.partial + ((size_t)bq * a.part_stride + chunk) * (D + 4);
@@ -609,7 +611,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   KeyRegs<D, NO2> kr;
   ValRegs<D, NO2> vr;
   kr.load_head(v, len, b, h, tile_begin, ktid);
-  vr.template load_head<H1>(v, len, b, h, tile_begin, tid, wave, nn, g);
+  vr.template load_first<H1>(v, len, b, h, tile_begin, tid, wave, nn, g);
   const float qv = tid < D ? __half2float(q_raw) : 0.0f;
   if (new_here) {
     const float qk = wave_sum(tid < D ? __half2float(q_raw) * __half2float(kn_raw) : 0.0f);
@@ -641,7 +643,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
     return r;
   };
   kr.template load_tail<H1>(v, b, h, tile_begin, counts_of(tile_begin, 0), ktid);
-  vr.template load_tail<H1>(v, b, h, tile_begin, counts_of(tile_begin, 1), wave, nn, g);
+  vr.template load_rest<H1>(v, b, h, tile_begin, counts_of(tile_begin, 1), tid, wave, nn, g);
   const float qmax = KS == 1 ? S.red[0] : fmaxf(S.red[0], S.red[1]);
   const float sumq = KS == 1 ? S.red[4] : S.red[4] + S.red[5];
   int qexp = 0;
@@ -1092,6 +1094,12 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 // head and raw logits; k_attn_combine merges them.  Width sets without 1, the fixed-length
 // side store with one outlier per end or none; G a multiple of 4 (a KV head with 8 query
 // heads is scanned twice, by two workgroups that run side by side).
+//
+// Bound: vector instructions (60 % of the issue slots at three wavefronts per SIMD, the most its registers allow) and, in
+// front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
+// group of keys and one head's weights after the other, behind branches; 166 in straight sequences for all four, with what a
+// weight has in common for the heads computed once; 161 with every fourth group of slots per wavefront and the weight digits
+// through the transposing LDS read; 157 with the first tile on its way before its class counts are there.
 // ---------------------------------------------------------------------------------------
 constexpr int kHG = 4;
 
@@ -1106,10 +1114,13 @@ struct GqaLds {
   alignas(16) int8_t ql[3][kHG][4][D + 16];
   alignas(16) uint16_t cnt[QAQ_MAX_NTC][8];
   float vb[QAQ_MAX_NTC];
-  float logit[kHG][QAQ_TT + 8];                // raw logits by position; at the very end: outlier corrections by channel
-  alignas(16) int8_t wl2[kHG][4][QAQ_TT + 16];  // weight digits [head][digit][slot of the 2-bit field region]
-  alignas(16) int8_t wl1[kHG][4][QAQ_TT + 16];
-  alignas(16) int8_t wl4[kHG][4][QAQ_TT + 16];
+  float logit[kHG][QAQ_TT + 8];                // raw logits by position, minus infinity behind them; at the very end: outlier corrections by channel
+  // Weight digits [slot of the region][4 * head + digit]: one 16-byte store per slot; the matrix operand, which wants a row's
+  // sixteen consecutive slots in a lane, comes out of the transposing LDS read.
+  alignas(16) int8_t wl2[QAQ_TT][4 * kHG];     // ... of the 2-bit field region
+  alignas(16) int8_t wl1[QAQ_TT][4 * kHG];     // ... of the 1-bit field region
+  alignas(16) int8_t wl4[QAQ_TT][4 * kHG];     // ... of the 4-bit region
+  alignas(16) int8_t zero[16][4 * kHG];        // ... of slots that no region has
   float w8[kHG][QAQ_TT];                       // fp32 weights of the 8-bit slots
   float xw[4][kHG][D / 4];                     // per wavefront: 8-bit-class outputs of its own channels
   alignas(16) int8_t k8[4][1024 / D][D + 16];  // per wavefront: its first 1024 / D 8-bit keys of the tile
@@ -1125,6 +1136,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   constexpr int KS = D / 64;
   constexpr int NCG = D / 16;
   constexpr int CGW = NCG / 4;
+  qaq_request_arguments<0, sizeof(QaqAttnArgs)>();
   __shared__ GqaLds<D> S;
   const QaqView& v = a.v;
   // (a wavefront constant, so that what depends on the wavefront's slots is decided by scalar branches: 184.3 -> 177.6 us for
@@ -1142,8 +1154,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   const int bq0 = b * v.Hq + h * a.G + kHG * hg;           // first of the four query heads
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
   const int ntile = (len + QAQ_TT - 1) / QAQ_TT;
-  const int tile_begin = (int)((long long)chunk * ntile / a.nparts);
-  const int tile_end = (int)((long long)(chunk + 1) * ntile / a.nparts);
+  int tile_begin, tile_end;
+  part_tiles(a, ntile, chunk, tile_begin, tile_end);
   if (tile_begin >= tile_end) {
     // a sequence shorter than the longest can leave a part without tiles: partials that the merge ignores
     for (int e = tid; e < kHG * (D + 2); e += kThreads) {
@@ -1156,13 +1168,106 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   const float inv_sqrt_d = 1.0f / sqrtf((float)D);
   const v4i zero4 = {0, 0, 0, 0};
 
+  // (as in k_attn_tile: no load of the prologue sits behind a branch, and what the first tile's class counts are not needed
+  // for is on its way while they are)
+  __half q_raw[kHG];
+#pragma unroll
+  for (int j = 0; j < kHG; ++j) q_raw[j] = a.q[(size_t)(bq0 + j) * D + min(tid, D - 1)];
+  const int my_tile = tile_begin + min(tid, tile_end - tile_begin - 1);
+  const uint4 cnt_raw = *(const uint4*)(v.counts + ((qaq_bh(v, b, h) * v.NT + my_tile) * 2) * 4);
+  const float vb_raw = v.vbound[qaq_bh(v, b, h) * v.NT + my_tile];
+  asm volatile("" ::: "memory");
+
+  // ---- what is loaded ahead for the key side.  Of a tile's sixteen groups of 16 slots a wavefront takes every fourth
+  // (slots are sorted by width: four neighbouring groups each, one wavefront had all the 3-bit keys and another all the rare
+  // wide ones, which the other three waited for).  Lane (n, g) holds, for each of its wavefront's four groups, the
+  // slices g*KS .. g*KS+KS-1 of slot 64*tg + 16*wave + n; the metadata of a slot is held once, by lane 16*tg + n, and handed
+  // to the other three lanes that work on the token (one per head) when its group is processed --------------------
+  // An 8-bit key's record is 128 bytes where a 2-bit one's is 32: a wavefront's first 1024 / D of them come with the tile
+  // as well, 16 bytes per lane, and go through LDS when they are used (fetched there, at the end of a chain that
+  // everything else waits for, they and an LDS atomic loop over the query made two layers at 16 x 64 heads on 8, 8192 tokens
+  // 193.7 instead of 186.3 us).
+  constexpr int LPR8 = D / 16, ROWS8 = 64 / LPR8;
+  uint32_t ka[4][KS], kb[4][KS], k8[4], kmm, kpos, koi, kov;
+  QaqCounts cKn;
+  int n_tok_n = 0;
+  const int w0 = 16 * wave;                    // the wavefront's first slot
+  // first slot of the wavefront at or behind slot x
+  auto first_own = [&](int x) { const int a = (x & ~15) + ((w0 - (x & ~15)) & 48); return max(a, x); };
+  auto counts_of = [&](int t, int side) {
+    const uint2 c = *(const uint2*)&S.cnt[t - tile_begin][4 * side];
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(c.x), hi = __builtin_amdgcn_readfirstlane(c.y);
+    QaqCounts r;
+    r.n3 = lo & 0xffffu; r.n2 = lo >> 16; r.n4 = hi & 0xffffu; r.n8 = hi >> 16; r.n1 = 0;
+    return r;
+  };
+
+  // (in two steps, the second with what depends on the class counts: the first tile's first step does not wait for them)
+  auto load_keys_first = [&](int tile) {
+    int l = lane;
+    asm volatile("" : "+v"(l));        // (nothing that follows from it is worth a register across the loop)
+    n_tok_n = min(len - tile * QAQ_TT, QAQ_TT);
+    const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
+    const int so = min(64 * (l >> 4) + w0 + (l & 15), n_tok_n - 1);
+    kmm = gload32(uniform_ptr(v.mm[0] + gi0), 4u * (uint32_t)so);
+    kpos = gload32(uniform_ptr(v.perm[0] + gi0), (uint32_t)so & ~3u);
+    if (NO2 == 2) {
+      koi = gload32(uniform_ptr(v.oidx[0] + gi0 * 2), (2u * (uint32_t)so) & ~3u);
+      kov = gload32(uniform_ptr(v.oval[0] + gi0 * 2), 4u * (uint32_t)so);
+    }
+  };
+  auto load_keys_rest = [&](int tile) {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int g = l >> 4, ks0 = w0 + (l & 15);      // the lane's first slot
+    const uint32_t lane_a = (uint32_t)ks0 * (uint32_t)(D / 4) + (uint32_t)g * (4u * KS);
+    const uint32_t lane_b = (uint32_t)ks0 * (uint32_t)(D / 8) + 4u * (uint32_t)((g * KS) >> 1);
+    cKn = counts_of(tile, 0);
+    const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 0, b, h, tile));
+    const QaqKRegions rK = qaq_k_regions(cKn, D);
+    const int n32 = cKn.n32();
+    if (cKn.n8 > 0) {                              // uniform over the workgroup
+      const int first8 = n32 + cKn.n4, s8 = first_own(first8);
+      const uint32_t row = (uint32_t)min(s8 - first8 + lane / LPR8, cKn.n8 - 1);
+      gload_dwords<4>(ubase + (rK.r8 + row * (uint32_t)D + 16u * (uint32_t)(lane % LPR8)), k8);
+    }
+    // Addresses.  A wavefront none of whose slots hold a 4-bit token: record s of the 2-bit fields, and of the low bits
+    // if its group has a 3-bit token at all -- a lane constant, the tile's region and a distance per group (slots of other classes and
+    // past the tile's tokens are fed what lies there, inside the tile side's place of 256 records and more; nobody uses their results).
+    uint32_t off_a[4], off_b[4];
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) {
+      off_a[tg] = lane_a + (uint32_t)(64 * tg * (D / 4));
+      off_b[tg] = w0 + 64 * tg < cKn.n3 ? lane_b + (rK.r1 + (uint32_t)(64 * tg * (D / 8))) : 0u;
+    }
+    if (cKn.n4 > 0 && first_own(n32) < n32 + cKn.n4) {        // (scalar)
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        const int s = ks0 + 64 * tg;
+        const bool is3 = s < cKn.n3, is4 = s >= n32 && s < n32 + cKn.n4;
+        const uint32_t rec4 = rK.r4 + (uint32_t)(s - n32) * (uint32_t)(D / 2) + (uint32_t)g * (8u * KS);
+        off_a[tg] = is4 ? rec4 : off_a[tg];
+        // the low bits of a 3-bit token: the word that holds the lane's slices (KS = 2: both halves of
+        // word g; KS = 1: one half of word g / 2); a 4-bit token: the second half of its slices
+        off_b[tg] = is4 ? rec4 + 4u * KS : is3 ? off_b[tg] : 0u;
+      }
+    }
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) {
+      gload_dwords<KS>(ubase + off_a[tg], ka[tg]);
+      gload_dwords<KS>(ubase + off_b[tg], kb[tg]);
+    }
+  };
+  ValRegs<D, NO2> vr;
+  load_keys_first(tile_begin);
+  vr.template load_first<false, true>(v, len, b, h, tile_begin, tid, wave, nn, g);
+  if (tid < tile_end - tile_begin) {
+    *(uint4*)&S.cnt[tid][0] = cnt_raw;
+    S.vb[tid] = vb_raw;
+  }
   float qv[kHG];
 #pragma unroll
-  for (int j = 0; j < kHG; ++j) qv[j] = tid < D ? __half2float(a.q[(size_t)(bq0 + j) * D + tid]) : 0.0f;
-  if (tid < tile_end - tile_begin) {
-    *(uint4*)&S.cnt[tid][0] = *(const uint4*)(v.counts + ((qaq_bh(v, b, h) * v.NT + tile_begin + tid) * 2) * 4);
-    S.vb[tid] = v.vbound[qaq_bh(v, b, h) * v.NT + tile_begin + tid];
-  }
+  for (int j = 0; j < kHG; ++j) qv[j] = tid < D ? __half2float(q_raw[j]) : 0.0f;
   if (wave < KS) {
 #pragma unroll
     for (int j = 0; j < kHG; ++j) {
@@ -1172,67 +1277,15 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
       S.qf[j][tid] = qv[j];
     }
   }
-  for (int e = tid; e < 3 * kHG * (D + 16); e += kThreads) S.ql[e / (kHG * (D + 16))][(e / (D + 16)) % kHG][3][e % (D + 16)] = 0;
-  for (int e = tid; e < kHG * D * 4; e += kThreads) (&S.xc[0][0][0])[e] = 0;
+  constexpr int ZROW = (D + 16) / 4;
+  for (int e = tid; e < 3 * kHG * ZROW; e += kThreads) ((uint32_t*)&S.ql[0][e / ZROW][3][0])[e % ZROW] = 0u;
+  for (int e = tid; e < kHG * D; e += kThreads) *(int4*)&S.xc[0][e][0] = make_int4(0, 0, 0, 0);
+  if (tid < 64) ((uint32_t*)&S.zero[0][0])[tid] = 0u;
+  if (tid < kHG) S.logit[tid][QAQ_TT] = -INFINITY;
   lds_barrier();
 
-  auto counts_of = [&](int t, int side) {
-    const uint2 c = *(const uint2*)&S.cnt[t - tile_begin][4 * side];
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(c.x), hi = __builtin_amdgcn_readfirstlane(c.y);
-    QaqCounts r;
-    r.n3 = lo & 0xffffu; r.n2 = lo >> 16; r.n4 = hi & 0xffffu; r.n8 = hi >> 16; r.n1 = 0;
-    return r;
-  };
-
-  // ---- what is loaded ahead for the key side: lane (n, g) holds, for each of its wavefront's four
-  // groups of 16 slots, the slices g*KS .. g*KS+KS-1 of slot 16*tg + n; the metadata of a slot is
-  // held once, by lane 16*tg + n (slot = lane index), and handed to the other three lanes that work
-  // on the token (one per head) when its group is processed ----------------------------------------
-  // An 8-bit key's record is 128 bytes where a 2-bit one's is 32: a wavefront's first 1024 / D of them come with the tile
-  // as well, 16 bytes per lane, and go through LDS when they are used (fetched there, at the end of a chain that
-  // everything else waits for, they and an LDS atomic loop over the query made two layers at 16 x 64 heads on 8, 8192 tokens
-  // 193.7 instead of 186.3 us).
-  constexpr int LPR8 = D / 16, ROWS8 = 64 / LPR8;
-  uint32_t ka[4][KS], kb[4][KS], k8[4], kmm, kpos, koi, kov;
-  QaqCounts cKn;
-  int n_tok_n = 0;
-  auto load_keys = [&](int tile) {
-    cKn = counts_of(tile, 0);
-    n_tok_n = min(len - tile * QAQ_TT, QAQ_TT);
-    const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 0, b, h, tile));
-    const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
-    const QaqKRegions rK = qaq_k_regions(cKn, D);
-    const int n32 = cKn.n32();
-    {
-      const int so = min(64 * wave + lane, n_tok_n - 1);
-      kmm = gload32(uniform_ptr(v.mm[0] + gi0), 4u * (uint32_t)so);
-      kpos = gload32(uniform_ptr(v.perm[0] + gi0), (uint32_t)so & ~3u);
-      if (NO2 == 2) {
-        koi = gload32(uniform_ptr(v.oidx[0] + gi0 * 2), (2u * (uint32_t)so) & ~3u);
-        kov = gload32(uniform_ptr(v.oval[0] + gi0 * 2), 4u * (uint32_t)so);
-      }
-    }
-    if (cKn.n8 > 0) {                              // uniform over the workgroup
-      const int first8 = n32 + cKn.n4, s8 = max(first8, 64 * wave);
-      const uint32_t row = (uint32_t)min(s8 - first8 + lane / LPR8, cKn.n8 - 1);
-      gload_dwords<4>(ubase + (rK.r8 + row * (uint32_t)D + 16u * (uint32_t)(lane % LPR8)), k8);
-    }
-#pragma unroll
-    for (int tg = 0; tg < 4; ++tg) {
-      const int s = min(64 * wave + 16 * tg + nn, n_tok_n - 1);
-      const bool is3 = s < cKn.n3, is23 = s < n32, is4 = !is23 && s < n32 + cKn.n4;
-      const uint32_t rec4 = rK.r4 + (uint32_t)(s - n32) * (uint32_t)(D / 2) + (uint32_t)g * (8u * KS);
-      const uint32_t off_a = is23 ? (uint32_t)s * (uint32_t)(D / 4) + (uint32_t)g * (4u * KS) : is4 ? rec4 : 0u;
-      // the low bits of a 3-bit token: the word that holds the lane's slices (KS = 2: both halves of
-      // word g; KS = 1: one half of word g / 2); a 4-bit token: the second half of its slices
-      const uint32_t off_b = is3 ? rK.r1 + (uint32_t)s * (uint32_t)(D / 8) + 4u * (uint32_t)((g * KS) >> 1) : is4 ? rec4 + 4u * KS : 0u;
-      gload_dwords<KS>(ubase + off_a, ka[tg]);
-      gload_dwords<KS>(ubase + off_b, kb[tg]);
-    }
-  };
-  ValRegs<D, NO2> vr;
-  load_keys(tile_begin);
-  vr.template load<false, true>(v, len, b, h, tile_begin, counts_of(tile_begin, 1), tid, wave, nn, g);
+  load_keys_rest(tile_begin);
+  vr.template load_rest<false, true>(v, b, h, tile_begin, counts_of(tile_begin, 1), tid, wave, nn, g);
 
   // ---- query digits: 22-bit fixed point per head, three signed base-256 digits, one table per
   // spreading format ---------------------------------------------------------------------------------
@@ -1267,14 +1320,11 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   const int8_t* abase0 = &S.ql[0][arow_h][arow_d][16 * g * KS];
   const int8_t* abase1 = abase0 + sizeof(S.ql[0]);
   const int8_t* abase2 = abase0 + 2 * sizeof(S.ql[0]);
-  const int8_t* wb2 = &S.wl2[arow_h][arow_d][16 * g];
-  const int8_t* wb1 = wb2 + sizeof(S.wl2);       // the three tables have one shape and follow one another
-  const int8_t* wb4 = wb2 + 2 * sizeof(S.wl2);
-  static_assert(offsetof(GqaLds<D>, wl1) - offsetof(GqaLds<D>, wl2) == sizeof(S.wl2) &&
-                offsetof(GqaLds<D>, wl4) - offsetof(GqaLds<D>, wl2) == 2 * sizeof(S.wl2), "weight digit tables are contiguous");
+  const int8_t* wb2 = &S.wl2[16 * g][8 * nn];        // (eight slots' rows are 128 consecutive bytes, eight of them per lane: see lds_transposed)
+  const int8_t* wb1 = &S.wl1[16 * g][8 * nn];
+  const int8_t* wb4 = &S.wl4[16 * g][8 * nn];
   auto real_of = [&](const v4i& c) { return (((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) * qscale_g; };
 
-  const DigitExchange exchange(lane);
   float m_run[kHG], l_run[kHG], bias_run[kHG];
 #pragma unroll
   for (int j = 0; j < kHG; ++j) { m_run[j] = -INFINITY; l_run[j] = 0.0f; bias_run[j] = 0.0f; }
@@ -1301,10 +1351,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
     // What depends on the token only is worked out once, by the lane that holds the slot's metadata
     // (slot = lane index), not by each of the four lanes that work on the token: min, scale, the two
     // outlier corrections, and (one word) the outlier channels and the position.
+    int ks0 = w0 + nn;
+    asm volatile("" : "+v"(ks0));
     float t_mn, t_scale, t_c0 = 0.0f, t_c1 = 0.0f;
     uint32_t t_idx;
     {
-      const int so = 64 * wave + lane;
+      const int so = 64 * g + ks0;
       const float mx = h2f((uint16_t)(kmm >> 16));
       t_mn = h2f((uint16_t)(kmm & 0xffffu));
       t_scale = ldexpf(mx - t_mn, -cK.bits_of_slot4(min(so, n_tok - 1)));
@@ -1318,83 +1370,125 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
         t_idx |= (koi >> (16 * (so & 1))) & 0xffffu;
       }
     }
-    // 8-bit keys among this wavefront's slots: from slot s8w on, n8w of them
-    const int s8w = max(first8K, 64 * wave), n8w = cK.n8 > 0 ? min(n_tok, 64 * wave + 64) - s8w : 0;
+    // 8-bit keys among this wavefront's slots: from slot s8w on, n8w of them in its group
+    const int s8w = first_own(first8K), n8w = cK.n8 > 0 ? min(n_tok, (s8w & ~15) + 16) - s8w : 0;
     if (n8w > 0) *(uint4*)&S.k8[wave][lane / LPR8][16 * (lane % LPR8)] = make_uint4(k8[0], k8[1], k8[2], k8[3]);
     // (LDS operations of one wavefront complete in order: no barrier between the write and the reads)
-    float vmax = -INFINITY;
+    // The common classes for all four groups at once, without a branch between them: four independent chains of matrix
+    // instructions, exchanges and look-ups in flight where one group after the other waited for its own, step by step.  A
+    // 3-bit token's digit sums are 2 * (top plane's) + (low plane's), exact in 32 bits and in a float.
+    float dotq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (w0 < n32K) {
+      v4i c[4];
+      {
+        v4i q[KS];
 #pragma unroll
-    for (int tg = 0; tg < 4; ++tg) {
-      const int s0 = 64 * wave + 16 * tg;           // uniform
-      if (s0 >= n_tok) continue;
-      const int s = s0 + nn;
-      float dotq = 0.0f;
-      if (s0 < n32K) {
-        v4i c = zero4;
+        for (int ks = 0; ks < KS; ++ks) q[ks] = *(const v4i*)(abase0 + 16 * ks);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) c = mma(*(const v4i*)(abase0 + 16 * ks), spread<2>(&ka[tg][ks], 0), c);
-        dotq = real_of(c);
-        if (s0 < cK.n3) {
-          v4i c1 = zero4;
+        for (int tg = 0; tg < 4; ++tg) {
+          c[tg] = mma(q[0], spread<2>(&ka[tg][0], 0), zero4);
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) c1 = mma(*(const v4i*)(abase1 + 16 * ks), spread<1>(&kb[tg][0], (g * KS + ks) & 1), c1);
-          const float low = real_of(c1);
-          dotq = s < cK.n3 ? 2.0f * dotq + low : dotq;
+          for (int ks = 1; ks < KS; ++ks) c[tg] = mma(q[ks], spread<2>(&ka[tg][ks], 0), c[tg]);
         }
       }
-      if (s0 + 16 > n32K && s0 < first8K) {
-        uint32_t k4[2 * KS];
+      if (w0 < cK.n3) {
+        v4i q[KS];
 #pragma unroll
-        for (int i = 0; i < KS; ++i) { k4[i] = ka[tg][i]; k4[KS + i] = kb[tg][i]; }
-        v4i c = zero4;
+        for (int ks = 0; ks < KS; ++ks) q[ks] = *(const v4i*)(abase1 + 16 * ks);
+        auto low_planes = [&](int t0) {              // two groups
+          v4i l[2];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) c = mma(*(const v4i*)(abase2 + 16 * ks), spread<4>(&k4[2 * ks], 0), c);
-        const float d4 = real_of(c);
-        if (s >= n32K) dotq = d4;
-      }
-      if (cK.n8 > 0 && s0 + 16 > first8K) {
-        // 8-bit keys: stored as code - 128, so the product gets 128 * (sum of the head's query integers)
-        // back, rebuilt from the digits; more of them than came with the tile are fetched here
-        uint32_t w8r[4 * KS];
-        if (n8w <= ROWS8) {
-          const int8_t* row = &S.k8[wave][min(max(s - s8w, 0), ROWS8 - 1)][g * (16 * KS)];
+          for (int t = 0; t < 2; ++t) {
+            l[t] = mma(q[0], spread<1>(&kb[t0 + t][0], (g * KS) & 1), zero4);
 #pragma unroll
-          for (int i = 0; i < KS; ++i) {
-            const uint4 t = *(const uint4*)(row + 16 * i);
-            w8r[4 * i] = t.x; w8r[4 * i + 1] = t.y; w8r[4 * i + 2] = t.z; w8r[4 * i + 3] = t.w;
+            for (int ks = 1; ks < KS; ++ks) l[t] = mma(q[ks], spread<1>(&kb[t0 + t][0], (g * KS + ks) & 1), l[t]);
           }
-        } else {
-          const int i8 = min(max(s - first8K, 0), max(cK.n8 - 1, 0));
-          gload_dwords<4 * KS>(baseK + (rK.r8 + (uint32_t)i8 * D + (uint32_t)g * (16u * KS)), w8r);
-        }
-        const int sq = KS == 1 ? S.sq[0][g] : S.sq[0][g] + S.sq[1][g];
-        v4i c = zero4;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) c = mma(*(const v4i*)(abase2 + 16 * ks), spread<8>(&w8r[4 * ks], 0), c);
-        if (s >= first8K) dotq = ((((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) + 128.0f * (float)sq) * qscale_g;
+          for (int t = 0; t < 2; ++t) {
+            const bool is3 = ks0 + 64 * (t0 + t) < cK.n3;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) c[t0 + t][i] = is3 ? 2 * c[t0 + t][i] + l[t][i] : c[t0 + t][i];
+          }
+        };
+        low_planes(0);
+        if (w0 + 128 < cK.n3) low_planes(2);
       }
-      // metadata of slot s from the lane that holds it (every lane takes part in the exchange)
-      const int src = 4 * (16 * tg + nn);
-      const float mn = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_mn)));
-      const float scale = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_scale)));
-      const uint32_t idx = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)t_idx);
-      float c0 = 0.0f, c1 = 0.0f;
-      if (NO2 == 2) {
-        c0 = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_c0)));
-        c1 = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_c1)));
-      }
-      if (s < n_tok) {
-        float val = mn * sumq_g + scale * (dotq + 0.5f * sumq_g);
-        if (NO2 == 2) {
-          val += S.qf[g][idx & 0xffu] * c0;
-          val += S.qf[g][(idx >> 8) & 0xffu] * c1;
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) dotq[tg] = real_of(c[tg]);
+    }
+    if (w0 + 192 + 16 > n32K) {                  // the rarer classes, group by group
+      v4i q[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) q[ks] = *(const v4i*)(abase2 + 16 * ks);
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        const int s0 = w0 + 64 * tg, s = s0 + nn;
+        if (s0 + 16 > n32K && s0 < first8K) {
+          uint32_t k4[2 * KS];
+#pragma unroll
+          for (int i = 0; i < KS; ++i) { k4[i] = ka[tg][i]; k4[KS + i] = kb[tg][i]; }
+          v4i c = zero4;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) c = mma(q[ks], spread<4>(&k4[2 * ks], 0), c);
+          const float d4 = real_of(c);
+          if (s >= n32K) dotq[tg] = d4;
         }
-        const float lg = val * inv_sqrt_d;
-        S.logit[g][idx >> 16] = lg;
-        vmax = vmaxf(vmax, lg);
+        if (cK.n8 > 0 && s0 + 16 > first8K && s0 < n_tok) {
+          // 8-bit keys: stored as code - 128, so the product gets 128 * (sum of the head's query integers)
+          // back, rebuilt from the digits; more of them than came with the tile are fetched here
+          uint32_t w8r[4 * KS];
+          if (s8w >= s0 && n8w <= ROWS8) {
+            const int8_t* row = &S.k8[wave][min(max(s - s8w, 0), ROWS8 - 1)][g * (16 * KS)];
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+              const uint4 t = *(const uint4*)(row + 16 * i);
+              w8r[4 * i] = t.x; w8r[4 * i + 1] = t.y; w8r[4 * i + 2] = t.z; w8r[4 * i + 3] = t.w;
+            }
+          } else {
+            const int i8 = min(max(s - first8K, 0), max(cK.n8 - 1, 0));
+            gload_dwords<4 * KS>(baseK + (rK.r8 + (uint32_t)i8 * D + (uint32_t)g * (16u * KS)), w8r);
+          }
+          const int sq = KS == 1 ? S.sq[0][g] : S.sq[0][g] + S.sq[1][g];
+          v4i c = zero4;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) c = mma(q[ks], spread<8>(&w8r[4 * ks], 0), c);
+          if (s >= first8K) dotq[tg] = ((((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) + 128.0f * (float)sq) * qscale_g;
+        }
       }
     }
-    if (tile + 1 < tile_end) load_keys(tile + 1);
+    // metadata of slot s from the lane that holds it (every lane takes part in the exchange)
+    float vmax = -INFINITY;
+    {
+      float mn[4], scale[4], c0[4], c1[4];
+      uint32_t idx[4];
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        const int src = 4 * (16 * tg + nn);
+        idx[tg] = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)t_idx);
+        mn[tg] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_mn)));
+        scale[tg] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_scale)));
+        if (NO2 == 2) {
+          c0[tg] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_c0)));
+          c1[tg] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(t_c1)));
+        }
+      }
+      float q0[4], q1[4];
+      if (NO2 == 2) {
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) { q0[tg] = S.qf[g][idx[tg] & 0xffu]; q1[tg] = S.qf[g][(idx[tg] >> 8) & 0xffu]; }
+      }
+#pragma unroll
+      for (int tg = 0; tg < 4; ++tg) {
+        float val = mn[tg] * sumq_g + scale[tg] * (dotq[tg] + 0.5f * sumq_g);
+        if (NO2 == 2) { val += q0[tg] * c0[tg]; val += q1[tg] * c1[tg]; }
+        if (ks0 + 64 * tg < n_tok) {
+          const float lg = val * inv_sqrt_d;
+          S.logit[g][idx[tg] >> 16] = lg;
+          vmax = vmaxf(vmax, lg);
+        }
+      }
+    }
+    if (tile + 1 < tile_end) { load_keys_first(tile + 1); load_keys_rest(tile + 1); }
 
     // maximum of the lane's head over its row of 16 lanes, then over the wavefronts
     asm volatile(QAQ_DPP_STEP("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
@@ -1422,17 +1516,16 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
     int wexp = 0;
     if (smax > 0.0f) (void)frexpf(smax, &wexp);
     const float wscale = smax > 0.0f ? ldexpf(1.0f, wexp - 28) : 0.0f;
-    if (a.scores && tid < n_tok) {
+    float raw[kHG];                                // the raw logits of position `tid`
 #pragma unroll
-      for (int j = 0; j < kHG; ++j) a.scores[(size_t)(bq0 + j) * a.score_stride + tile * QAQ_TT + tid] = S.logit[j][tid];
-    }
+    for (int j = 0; j < kHG; ++j) raw[j] = S.logit[j][tid];
 
     // ---- values: the four heads' weights of slot `tid`, as digits ---------------------------------------
     {
       const int s = tid;
       const bool live = s < n_tok;
       const uint32_t slot = (uint32_t)min(tid, n_tok - 1);
-      const int posv = (int)((vr.pos >> (8u * (slot & 3u))) & 0xffu);
+      const int posv = live ? (int)((vr.pos >> (8u * (slot & 3u))) & 0xffu) : QAQ_TT;      // (a slot that is not there: weight zero)
       const float mn = h2f((uint16_t)(vr.mm & 0xffffu)), mx = h2f((uint16_t)(vr.mm >> 16));
       const float range = mx - mn;
       const float scale = ldexpf(range, -cV.bits_of_slot4(s));
@@ -1448,69 +1541,94 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
           och[j] = vr.o.idx(j, slot);
         }
       }
+      // Everything of a weight that does not depend on the head once per slot, powers of two included (exact: nothing that
+      // rounds to more than zero leaves the normal range); zero where the slot is not in a table's region.  The four heads then
+      // go through one straight sequence, so that their look-ups, exponentials and exchanges overlap.
       const bool fx = live && smax > 0.0f;
       const int vg = (s & 15) >> 2;
       const int i4 = (s - n32V) & (QAQ_TT - 1);
+      const float f2 = fx && s < n32V ? ldexpf(scale, 28 - wexp - shift2(vg) + (s < cV.n3 ? 1 : 0)) : 0.0f;
+      const float f0 = mn + hs;                      // what a weight adds besides its codes
+#pragma unroll
+      for (int k = 0; k < 2; ++k) corr[k] = ldexpf(corr[k], 25 - wexp);
+      float pt[kHG];
+#pragma unroll
+      for (int j = 0; j < kHG; ++j) pt[j] = S.logit[j][posv];
+      if (a.scores && live) {
+#pragma unroll
+        for (int j = 0; j < kHG; ++j) a.scores[(size_t)(bq0 + j) * a.score_stride + tile * QAQ_TT + tid] = raw[j];
+      }
 #pragma unroll
       for (int j = 0; j < kHG; ++j) {
-        float pt = 0.0f, w = 0.0f;
-        if (live) {
-          pt = __expf(S.logit[j][posv] - M[j]);
-          w = pt * scale;
-          if (NO2 == 2) {
+        pt[j] = __expf(pt[j] - M[j]);
+        l_run[j] = l_run[j] * keep[j] + pt[j];
+        bias_run[j] = bias_run[j] * keep[j] + pt[j] * f0;
+      }
+      if (NO2 == 2 && live) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
-              atomicAdd(&S.xc[j][och[k]][lane & 3], (int)rintf(ldexpf(pt * corr[k], 25 - wexp)));
-          }
-          if (s >= first8V) S.w8[j][s - first8V] = w;
-        }
-        l_run[j] = l_run[j] * keep[j] + pt;
-        bias_run[j] = bias_run[j] * keep[j] + (pt * mn + 0.5f * w);
-        const uint32_t W2 = (fx && s < n32V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift2(vg) + (s < cV.n3 ? 1 : 0))) : 0u;
-        *(uint32_t*)&S.wl2[j][s & 3][s & ~3] = exchange(weight_digits(W2));
-        // (the value phase reads these two tables in blocks of 64 slots, as far as the class reaches:
-        // slots of later blocks need no digits, not even zeros)
-        if (s < ((cV.n3 + 63) & ~63)) {
-          const uint32_t W1 = (fx && s < cV.n3) ? (uint32_t)rintf(ldexpf(w, 28 - wexp - shift1(vg))) : 0u;
-          *(uint32_t*)&S.wl1[j][s & 3][s & ~3] = exchange(weight_digits(W1));
-        }
-        if (i4 < ((cV.n4 + 63) & ~63)) {
-          put_digits(S.wl4[j], i4, weight_digits((fx && s >= n32V && s < first8V) ? (uint32_t)rintf(ldexpf(w, 28 - wexp)) : 0u));
-        }
+        for (int j = 0; j < kHG; ++j)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) atomicAdd(&S.xc[j][och[k]][lane & 3], (int)rintf(pt[j] * corr[k]));
+      }
+      // (whole weights, rounded to nearest, of the four heads, as digits)
+      auto put_weights = [&](int8_t (&row)[4 * kHG], float f) {
+        uint4 w;
+        w.x = weight_digits(round_weight(pt[0] * f)); w.y = weight_digits(round_weight(pt[1] * f));
+        w.z = weight_digits(round_weight(pt[2] * f)); w.w = weight_digits(round_weight(pt[3] * f));
+        *(uint4*)&row[0] = w;
+      };
+      put_weights(S.wl2[s], f2);
+      // (the value phase reads these two tables in blocks of 64 slots, as far as the class reaches:
+      // slots of later blocks need no digits, not even zeros)
+      if (64 * wave < cV.n3) put_weights(S.wl1[s], fx && s < cV.n3 ? ldexpf(scale, 28 - wexp - shift1(vg)) : 0.0f);
+      if (cV.n4 > 0 && i4 < ((cV.n4 + 63) & ~63)) put_weights(S.wl4[i4], fx && s >= n32V && s < first8V ? ldexpf(scale, 28 - wexp) : 0.0f);
+      if (live && s >= first8V) {
+#pragma unroll
+        for (int j = 0; j < kHG; ++j) S.w8[j][s - first8V] = pt[j] * scale;
       }
     }
     lds_barrier();
     // outlier corrections of this tile: (head, channel) pairs sum their copies and clear them
-    if (NO2 == 2) {
-#pragma unroll
-      for (int r = 0; r < NCR; ++r) {
-        const int item = tid + kThreads * r;
-        if (item < kHG * D) {
-          const int j = item / D;
-          int4* c4 = (int4*)&S.xc[0][0][0] + item;
-          const int4 x = *c4;
-          *c4 = make_int4(0, 0, 0, 0);
-          const float kp = j == 0 ? keep[0] : j == 1 ? keep[1] : j == 2 ? keep[2] : keep[3];
-          c_run[r] = c_run[r] * kp + ((float)(x.x + x.y) + (float)(x.z + x.w)) * ldexpf(wscale, 3);
-        }
-      }
-    }
-
     // ---- values: integer contractions, rows = 4 heads x 4 weight digits ----------------------------------
+    // (all weights of the 2-bit fields and the first block of the low planes are asked for together; the digits of slots
+    // past a region are zero, and a block of low planes that is not there reads a row of zeros)
     v4i cv[CGW];
 #pragma unroll
     for (int j = 0; j < CGW; ++j) cv[j] = zero4;
+    if (n32V > 0) {
+      v4i wa[4];
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
-      if (blk * 64 < n32V) {
-        const v4i wa = *(const v4i*)(wb2 + 64 * blk);
+      for (int blk = 0; blk < 4; ++blk) wa[blk] = weight_operand(wb2 + 64 * blk * 4 * kHG);
+      const v4i wl0 = weight_operand(wb1);
 #pragma unroll
-        for (int j = 0; j < CGW; ++j) cv[j] = mma(wa, spread<2>(&vr.vw2[blk][j], 0), cv[j]);
+      for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+        for (int j = 0; j < CGW; ++j) cv[j] = mma(wa[blk], spread<2>(&vr.vw2[blk][j], 0), cv[j]);
+      if (cV.n3 > 0) {
+#pragma unroll
+        for (int j = 0; j < CGW; ++j) cv[j] = mma(wl0, spread<1>(&vr.vw1[0], (CGW * wave + j) & 1), cv[j]);
+        if (cV.n3 > 64) {
+          const int8_t* const none = &S.zero[0][8 * nn];
+          v4i wl[3];
+#pragma unroll
+          for (int blk = 1; blk < 4; ++blk) wl[blk - 1] = weight_operand(blk * 64 < cV.n3 ? wb1 + 64 * blk * 4 * kHG : none);
+#pragma unroll
+          for (int blk = 1; blk < 4; ++blk)
+#pragma unroll
+            for (int j = 0; j < CGW; ++j) cv[j] = mma(wl[blk - 1], spread<1>(&vr.vw1[blk], (CGW * wave + j) & 1), cv[j]);
+        }
       }
-      if (blk * 64 < cV.n3) {
-        const v4i wa = *(const v4i*)(wb1 + 64 * blk);
+    }
+    // outlier corrections of this tile: (head, channel) pairs sum their copies and clear them
+    static_assert(kHG * D % kThreads == 0, "(head, channel) pairs per thread");
+    if (NO2 == 2) {
 #pragma unroll
-        for (int j = 0; j < CGW; ++j) cv[j] = mma(wa, spread<1>(&vr.vw1[blk], (CGW * wave + j) & 1), cv[j]);
+      for (int r = 0; r < NCR; ++r) {
+        const int item = tid + kThreads * r, j = item / D;
+        const int4 x = *((int4*)&S.xc[0][0][0] + item);
+        *((int4*)&S.xc[0][0][0] + item) = make_int4(0, 0, 0, 0);
+        const float kp = j == 0 ? keep[0] : j == 1 ? keep[1] : j == 2 ? keep[2] : keep[3];
+        c_run[r] = c_run[r] * kp + ((float)(x.x + x.y) + (float)(x.z + x.w)) * ldexpf(wscale, 3);
       }
     }
     // 4-bit values.  Up to 16 of them in a tile (the usual case where the rules chose the widths):
@@ -1524,7 +1642,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
         const uint32_t d10 = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (nn + 16), (int)vr.v4p);
         const uint32_t d01 = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (nn + 32), (int)vr.v4p);
         const uint32_t d11 = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (nn + 48), (int)vr.v4p);
-        const v4i wa = *(const v4i*)wb4;
+        const v4i wa = weight_operand(wb4);
         const uint32_t p0[2] = {d00, d01}, p1[2] = {d10, d11};
         cv[0] = mma(wa, spread<4>(p0, 0), cv[0]);
         cv[1] = mma(wa, spread<4>(p1, 0), cv[1]);
@@ -1536,7 +1654,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
       uint32_t w0[CGW], w1d[CGW];
       gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w0);
       gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u + 1, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w1d);
-      const v4i wa = *(const v4i*)(wb4 + 64 * blk);
+      const v4i wa = weight_operand(wb4 + 64 * blk * 4 * kHG);
 #pragma unroll
       for (int j = 0; j < CGW; ++j) {
         const uint32_t pr[2] = {w0[j], w1d[j]};
@@ -1561,13 +1679,22 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
         if (r0 > 0) dw = gload32(baseV, rV.r8 + (uint32_t)min(r0 + lane / LPT8, cV.n8 - 1) * D + (D / 4) * wave + 4 * (lane % LPT8));
         S.v8[wave][lane] = dw;        // row lane / LPT8, bytes 4 * (lane % LPT8) .. +3: a row is D/4 consecutive bytes
         // (LDS operations of one wavefront complete in order: no barrier between the write and the reads)
-        const int nr = min(cV.n8 - r0, TPW);
+        // four rows at a time, their look-ups in flight together; a row that is not there gets weight zero
+        static_assert(TPW % 4 == 0, "rows of a batch");
 #pragma unroll
-        for (int r = 0; r < TPW; ++r) {
-          if (r < nr && c8 < D / 4) {
-            const float x = (float)rows[r * (D / 4) + c8];
-            acc0 += S.w8[h0][r0 + r] * x;
-            acc1 += S.w8[h0 + 1][r0 + r] * x;
+        for (int q = 0; q < TPW; q += 4) {
+          if (r0 + q >= cV.n8) break;
+          float x[4], u0[4], u1[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i8 = min(r0 + q + r, QAQ_TT - 1);
+            x[r] = (float)rows[(q + r) * (D / 4) + (c8 & (D / 4 - 1))];
+            u0[r] = S.w8[h0][i8]; u1[r] = S.w8[h0 + 1][i8];
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            acc0 += (r0 + q + r < cV.n8 ? u0[r] : 0.0f) * x[r];
+            acc1 += (r0 + q + r < cV.n8 ? u1[r] : 0.0f) * x[r];
           }
         }
       }
@@ -1788,6 +1915,8 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   const int least = (ntile + QAQ_MAX_NTC - 1) / QAQ_MAX_NTC;    // a part holds at most QAQ_MAX_NTC tiles
   if (a.nparts < least) a.nparts = least;
   a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
+  a.run = a.nparts > 0 ? ntile / a.nparts : 0;
+  a.shorter = a.nparts - (ntile - a.run * a.nparts);
   // Fused form (no second kernel) when the parts of a head fit one workgroup; their raw logits stay
   // in its LDS next to the parts' working blocks if they fit, else they wait in the score buffer.
   // (its parts run in lockstep and every one needs a tile: where the sequences differ in length, the

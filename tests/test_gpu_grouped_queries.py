@@ -1,0 +1,45 @@
+"""Grouped-query attention (four query heads per pass over the codes) where its kernel divides a tile: a wavefront takes every
+fourth group of 16 key slots, eight 8-bit keys and values per wavefront and sixteen 4-bit values come with the tile, weight
+tables reach as far as blocks of 64 slots do."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2403_04643_amd import qaq  # noqa: E402
+
+# K^ and V^ reach the reference rounded to fp16 (2^-11 of each value; logits of a few units, so at most about 1e-3 of a
+# weight, and as much of the output); the library's own sums are off by 1e-5
+TOL = 5e-3
+
+
+@pytest.mark.parametrize("counts", [       # 3, 2, 4, 8 bits in the second tile
+    (0, 1, 0, 0), (1, 0, 0, 0), (0, 0, 1, 0), (0, 0, 0, 1), (15, 1, 0, 0), (16, 0, 0, 1), (17, 14, 1, 1),
+    (64, 150, 12, 9), (65, 127, 16, 8), (63, 160, 17, 16), (129, 100, 18, 9), (128, 0, 64, 64), (0, 191, 65, 0),
+    (0, 240, 0, 16), (0, 247, 0, 9), (200, 0, 30, 26), (256, 0, 0, 0), (0, 256, 0, 0), (0, 0, 256, 0), (0, 0, 0, 256), (3, 250, 2, 1)])
+@pytest.mark.parametrize("D,n_o", [(128, 1), (64, 1), (128, 0)])
+def test_class_borders(counts, D, n_o):
+    n = sum(counts)
+    B, Hkv, G, T = 1, 3, 4, 256 + n
+    print(f"class borders: {counts} D={D} n_o={n_o}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * counts[0] + counts[1] + D + n_o)
+    k, v = (torch.randn((B, Hkv, T, D), device="cuda", generator=gen).half() for _ in range(2))
+    q = torch.randn((B, Hkv * G, D), device="cuda", generator=gen).half()
+    c = qaq.Cache(qaq.make_config(B, Hkv * G, Hkv, D, T, [1.0] * Hkv, n_outlier_per_side=n_o))
+
+    def widths(cn):
+        w = torch.tensor(sum(([b] * m for b, m in zip((3, 2, 4, 8), cn)), []), dtype=torch.uint8, device="cuda")
+        return torch.stack([w[torch.randperm(len(w), device="cuda", generator=gen)] for _ in range(B * Hkv)]).view(B, Hkv, -1)
+
+    first = (256 - n + counts[0],) + counts[1:]
+    c.quantize_append(k, v, *(torch.cat([widths(first), widths(counts)], dim=2).contiguous() for _ in range(2)))
+    x, s = c.decode_attention(q, want_scores=True)
+    kd, vd = (t.double() for t in c.dequantize())
+    ref_s = ((q.double().view(B, Hkv, G, 1, D) * kd[:, :, None]).sum(-1) * D ** -0.5).softmax(-1)
+    ref_x = (ref_s[..., None] * vd[:, :, None]).sum(-2).view(B, Hkv * G, D)
+    ref_s = ref_s.view(B, Hkv * G, T)
+    err_s = ((s - ref_s).abs().amax(-1) / ref_s.amax(-1)).max().item()
+    err_x = ((x - ref_x).abs().amax(-1) / ref_x.abs().amax(-1)).max().item()
+    print(f"  worst errors: scores {err_s:.1e}, output {err_x:.1e}", flush=True)
+    assert err_s < TOL and err_x < TOL
