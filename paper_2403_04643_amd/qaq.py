@@ -143,8 +143,10 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> int:
+    # (the raw handle of torch.cuda.current_stream(): the object around it takes 2.6 us to make, a quarter of what a call
+    # costs the host -- 24 steps of a small model waited for it)
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class HostBuffer:
