@@ -212,6 +212,7 @@ struct TileLds {
                                         // 16-byte reads of their copies start in different banks.
   float red[16];
   float part[D + 4];                    // fused form: this part's partial (output, then max, sum)
+  float qstat[2];                       // scale of the query's fixed point, sum of the query
   float newv[D];                        // fused form, first part: the new token's value row (fetched in the prologue)
 };
 
@@ -371,8 +372,9 @@ struct KeyRegs {
   // The first tile of a part, in two steps, so that its bytes are on their way while the class counts
   // are: `head` asks for what can be addressed without the counts -- the slot's metadata and the 2-bit
   // field record of slot `tid`, which is where the record of a 2- or 3-bit token is -- and `tail`, once
-  // the counts are known, for the rest (and for the first word group again where the tile has 4-bit
-  // tokens, whose records are elsewhere: rare, and uniform over the workgroup).
+  // the counts are known, for the rest, the records of wider tokens into registers of their own (`wide`: a load into
+  // registers that an earlier load is still on its way to is held back until that one has arrived); `settle` puts them in
+  // place in front of the tile loop.
   __device__ __forceinline__ void load_head(const QaqView& v, int len, int b, int h, int tile, int tid) {
     n_tok = min(len - tile * QAQ_TT, QAQ_TT);
     const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
@@ -382,8 +384,15 @@ struct KeyRegs {
     o.load(v, 0, gi0, slot, v.no2);
     gload_dwords<HALF>(uniform_ptr(qaq_tile_codes(v, 0, b, h, tile)) + (uint32_t)tid * (uint32_t)KRec<D, 2>::REC, ka);
   }
+  __device__ __forceinline__ bool is_wide(int tid) const { return tid >= c.n32() && tid < n_tok - c.n1; }
+  __device__ __forceinline__ void settle(const uint32_t (&wide)[HALF], int tid) {
+    const bool w = is_wide(tid);
+    if (__ballot(w) == 0ull) return;
+#pragma unroll
+    for (int i = 0; i < HALF; ++i) ka[i] = w ? wide[i] : ka[i];
+  }
   template <bool H1>
-  __device__ __forceinline__ void load_tail(const QaqView& v, int b, int h, int tile, const QaqCounts& ck, int tid) {
+  __device__ __forceinline__ void load_tail(const QaqView& v, int b, int h, int tile, const QaqCounts& ck, int tid, uint32_t (&wide_words)[HALF]) {
     c = ck;
     const QaqKRegions rK = qaq_k_regions(c, D);
     const int n32 = c.n32();
@@ -399,12 +408,7 @@ struct KeyRegs {
       off_b0 = rK.r1b + (uint32_t)min(tid - c.first1(), c.n1 - 1) * (uint32_t)KRec<D, 1>::REC;
     const uint32_t off_b1 = wide ? rec4 + 4u * HALF + 2u * HALF : 0u;
     const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 0, b, h, tile));
-    if (c.n4 + c.n8 > 0) {     // (into other registers first: a load into registers that an earlier load is still on its way to is held back until that one has arrived)
-      uint32_t t[HALF];
-      gload_dwords<HALF>(ubase + off_a, t);
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) ka[i] = t[i];
-    }
+    if (__ballot(wide) != 0ull) gload_dwords<HALF>(ubase + off_a, wide_words);
     uint32_t b0[HALF / 2], b1[HALF / 2];
     gload_dwords<HALF / 2>(ubase + off_b0, b0);
     gload_dwords<HALF / 2>(ubase + off_b1, b1);
@@ -509,6 +513,25 @@ __device__ __forceinline__ void die_neighbours(int lin, int total, int share, in
   }
 }
 
+// The class counts of one tile, both sides.  By a vector load, the same address in every lane: a wait for scalar loads is a
+// wait for all of them, and the arguments that the other loads' addresses come from are scalar loads.
+struct TileCounts {
+  uint32_t w[4];
+  __device__ __forceinline__ TileCounts(const QaqView& v, size_t tile_id) {
+    uint32_t none = 0u;
+    asm volatile("" : "+v"(none));
+    gload_dwords<4>(uniform_ptr(v.counts + tile_id * 8) + none, w);
+  }
+  template <bool H1>
+  __device__ __forceinline__ QaqCounts of(int side, int n_tok) const {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(w[2 * side]), hi = __builtin_amdgcn_readfirstlane(w[2 * side + 1]);
+    QaqCounts r;
+    r.n3 = lo & 0xffffu; r.n2 = lo >> 16; r.n4 = hi & 0xffffu; r.n8 = hi >> 16;
+    r.n1 = H1 ? n_tok - (r.n3 + r.n2 + r.n4 + r.n8) : 0;
+    return r;
+  }
+};
+
 // The tiles of part `chunk` of a head with `ntile` of them: runs of ntile / nparts, the last ntile % nparts of them one longer.
 // (The quotient of the longest sequence comes from the host: a division is a hundred cycles of every workgroup's way to its
 // first load, and with a 64-bit product in it several hundred.)
@@ -591,10 +614,17 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   const int no2 = v.no2;
   const v4i zero4 = {0, 0, 0, 0};
 
+  // The prologue, 5.9 of a call's 25 us inside the kernel at 8 x 32 heads x 4096 tokens: one barrier, behind which every table is
+  // ready; the whole first tile is asked for in front of it.  (With the rest of that tile and the query's digits behind a
+  // barrier of their own, records of wide tokens loaded over registers in flight and every part making the digits, four such
+  // calls took 119.5 instead of 117.9 us, a call of 12 x 2 heads x 1900 tokens 24.2 instead of 23.3.)
   // (no load of the prologue sits behind a branch: the compiler places its waits by counting the loads
   // issued after the one it waits for, and where that number depends on a branch it waits for all of them
   // -- here for the first tile's codes, before the barrier that everything else is behind)
-  const __half q_raw = a.q[(size_t)bq * D + min(tid, D - 1)];
+  // the first tile's class counts: the rest of that tile is asked for as soon as they are there, not behind a barrier that
+  // waits for the first loads of every wavefront
+  const TileCounts first_counts(v, qaq_bh(v, b, h) * v.NT + tile_begin);
+  const __half q_raw = a.q[(size_t)bq * D + min(tid, D - 1)], q_last = a.q[(size_t)bq * D + (D - 64) + lane];
   // class counts of all tiles of the chunk -> LDS (one 16-byte load per tile), so that the
   // tile loop needs no dependent global load to place its 1-bit regions
   const int my_tile = tile_begin + min(tid, tile_end - tile_begin - 1);
@@ -610,9 +640,44 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
   // the first tile: what its class counts are not needed for is requested at once
   KeyRegs<D, NO2> kr;
   ValRegs<D, NO2> vr;
+  uint32_t wide_words[KeyRegs<D, NO2>::HALF];
   kr.load_head(v, len, b, h, tile_begin, ktid);
   vr.template load_first<H1>(v, len, b, h, tile_begin, tid, wave, nn, g);
-  const float qv = tid < D ? __half2float(q_raw) : 0.0f;
+  __builtin_amdgcn_sched_barrier(0);      // (nothing that waits for one of them in between)
+  const int n_tok0 = min(len - tile_begin * QAQ_TT, QAQ_TT);
+  kr.template load_tail<H1>(v, b, h, tile_begin, first_counts.of<H1>(0, n_tok0), ktid, wide_words);
+  vr.template load_rest<H1>(v, b, h, tile_begin, first_counts.of<H1>(1, n_tok0), tid, wave, nn, g);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- query: fixed point, signed base-256 digits, one table per spreading format; by one wavefront, for all parts ----------
+  TileLds<D>& SQ = S_all[0];
+  if (wave == 0 && (!P || chunk == 0)) {
+    float qx[KS];
+    qx[0] = __half2float(q_raw);
+    if (KS == 2) qx[KS - 1] = __half2float(q_last);
+    const float qmax = wave_max(KS == 1 ? fabsf(qx[0]) : fmaxf(fabsf(qx[0]), fabsf(qx[KS - 1])));
+    const float sumq = KS == 1 ? wave_sum(qx[0]) : wave_sum(qx[0]) + wave_sum(qx[KS - 1]);
+    int qexp = 0;
+    if (qmax > 0.0f) (void)frexpf(qmax, &qexp);
+    const float qscale = qmax > 0.0f ? ldexpf(1.0f, qexp - 22) : 0.0f;
+    if (lane == 0) { SQ.qstat[0] = qscale; SQ.qstat[1] = sumq; }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      SQ.qf[64 * ks + lane] = qx[ks];
+      // channel 64*ks + lane sits at position 16*(g'*KS + ks) + i of a record
+      const int i = lane & 15, vgr = i >> 2;
+      const int pos = 16 * ((lane >> 4) * KS + ks) + i;
+#pragma unroll
+      for (int f = 0; f < 3; ++f) {
+        const int sh = f == 0 ? shift2(vgr) : f == 1 ? shift1(vgr) : 0;
+        const int x = qmax > 0.0f ? (int)rintf(ldexpf(qx[ks], 22 - qexp - sh)) : 0;
+        const uint32_t dg = digits_packed(x);
+        SQ.ql[f][0][pos] = (int8_t)dg; SQ.ql[f][1][pos] = (int8_t)(dg >> 8); SQ.ql[f][2][pos] = (int8_t)(dg >> 16);
+      }
+    }
+  }
+  S.zrow[tid] = 0;
+  for (int e = tid; e < D * 4; e += kThreads) ((int4*)&S.xc[0][0])[e] = make_int4(0, 0, 0, 0);
   if (new_here) {
     const float qk = wave_sum(tid < D ? __half2float(q_raw) * __half2float(kn_raw) : 0.0f);
     if (lane == 0) S.red[12 + wave] = qk;
@@ -622,18 +687,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
     *(uint4*)&S.cnt[tid][0] = cnt_raw;
     S.vb[tid] = vb_raw;
   }
-
-  // ---- query: fixed point, signed base-256 digits, one table per spreading format ------------
-  if (wave < KS) {          // the wavefronts that hold the D query channels
-    const float am = wave_max(fabsf(qv));
-    const float sm = wave_sum(qv);
-    if (lane == 0) { S.red[wave] = am; S.red[4 + wave] = sm; }
-    S.qf[tid] = qv;
-  }
-  S.zrow[tid] = 0;
-  for (int e = tid; e < D * 16; e += kThreads) (&S.xc[0][0])[e] = 0;
   lds_barrier();
-  // the rest of the first tile is requested before the query digits are made
   auto counts_of = [&](int t, int side) {
     const uint2 c = *(const uint2*)&S.cnt[t - tile_begin][4 * side];
     const uint32_t lo = __builtin_amdgcn_readfirstlane(c.x), hi = __builtin_amdgcn_readfirstlane(c.y);
@@ -642,31 +696,12 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
     r.n1 = H1 ? min(len - t * QAQ_TT, QAQ_TT) - (r.n3 + r.n2 + r.n4 + r.n8) : 0;      // the 1-bit class is the rest of the tile
     return r;
   };
-  kr.template load_tail<H1>(v, b, h, tile_begin, counts_of(tile_begin, 0), ktid);
-  vr.template load_rest<H1>(v, b, h, tile_begin, counts_of(tile_begin, 1), tid, wave, nn, g);
-  const float qmax = KS == 1 ? S.red[0] : fmaxf(S.red[0], S.red[1]);
-  const float sumq = KS == 1 ? S.red[4] : S.red[4] + S.red[5];
-  int qexp = 0;
-  if (qmax > 0.0f) (void)frexpf(qmax, &qexp);
-  const float qscale = qmax > 0.0f ? ldexpf(1.0f, qexp - 22) : 0.0f;
-  if (wave < KS) {
-    // channel tid sits at position 16*(g'*KS + ks) + i of a record
-    const int i = tid & 15, vgr = i >> 2;
-    const int pos = 16 * (((tid & 63) >> 4) * KS + (tid >> 6)) + i;
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-      const int sh = f == 0 ? shift2(vgr) : f == 1 ? shift1(vgr) : 0;
-      const int x = qmax > 0.0f ? (int)rintf(ldexpf(qv, 22 - qexp - sh)) : 0;
-      const uint32_t dg = digits_packed(x);
-      S.ql[f][0][pos] = (int8_t)dg; S.ql[f][1][pos] = (int8_t)(dg >> 8); S.ql[f][2][pos] = (int8_t)(dg >> 16);
-    }
-  }
-  lds_barrier();
+  const float qscale = SQ.qstat[0], sumq = SQ.qstat[1];
   // A rows: row r = 4*tg + L is switched on in lane group tg only
   const bool arow = (g == (nn >> 2)) && ((nn & 3) < 3);
-  const int8_t* abase0 = arow ? &S.ql[0][nn & 3][0] : &S.zrow[0];
-  const int8_t* abase1 = arow ? &S.ql[1][nn & 3][0] : &S.zrow[0];
-  const int8_t* abase2 = arow ? &S.ql[2][nn & 3][0] : &S.zrow[0];
+  const int8_t* abase0 = arow ? &SQ.ql[0][nn & 3][0] : &S.zrow[0];
+  const int8_t* abase1 = arow ? &SQ.ql[1][nn & 3][0] : &S.zrow[0];
+  const int8_t* abase2 = arow ? &SQ.ql[2][nn & 3][0] : &S.zrow[0];
   const int8_t* wb2 = nn < 4 ? &S.wl2[nn][16 * g] : &S.zrow[0];
   const int8_t* wb1 = nn < 4 ? &S.wl1[nn][16 * g] : &S.zrow[0];
   const int8_t* wb4 = nn < 4 ? &S.wl4[nn][16 * g] : &S.zrow[0];
@@ -686,7 +721,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       if (j < NO2 && j < no2 && o.used(j)) {
         const float ov = o.val(j);
         const bool top = ov >= mx;
-        val += S.qf[o.idx(j, slot)] * ((ov - (top ? mx : mn)) + (top ? hs : -hs));
+        val += SQ.qf[o.idx(j, slot)] * ((ov - (top ? mx : mn)) + (top ? hs : -hs));
       }
     }
     return val * inv_sqrt_d;
@@ -703,6 +738,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 #pragma unroll
   for (int j = 0; j < CGW; ++j) xrun[j] = 0.0f;
 
+  kr.settle(wide_words, ktid);
   const int n_iter = P ? a.ntc : tile_end - tile_begin;
   for (int it = 0; it < n_iter; ++it) {
     const int tile = tile_begin + it;
@@ -753,7 +789,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
         // with the rest of the tile), fp32 products with the query in a fixed order
         const int j = 8 * (lane & 15) < D ? lane & 15 : 0, sl = j >> 1;   // a record has D bytes: D/8 lanes of the group carry it
         const int ch0 = 64 * (sl % KS) + 16 * (sl / KS) + 8 * (j & 1);   // channel of the lane's first byte
-        const float4 q0 = *(const float4*)&S.qf[ch0], q1 = *(const float4*)&S.qf[ch0 + 4];
+        const float4 q0 = *(const float4*)&SQ.qf[ch0], q1 = *(const float4*)&SQ.qf[ch0 + 4];
         const uint32_t c0 = kr.k8[0] ^ 0x80808080u, c1 = kr.k8[1] ^ 0x80808080u;   // stored as code - 128
         float d = (float)(c0 & 255u) * q0.x;
         d += (float)((c0 >> 8) & 255u) * q0.y;
@@ -773,7 +809,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
         // 8-bit key bytes are stored as code - 128: the dot product gets 128 * (sum of the
         // unscaled query integers) back, rebuilt here from their digits (this class is rare)
         int sq = 0;
-        for (int d = lane; d < D; d += 64) sq += (int)S.ql[2][0][d] + 256 * (int)S.ql[2][1][d] + 65536 * (int)S.ql[2][2][d];
+        for (int d = lane; d < D; d += 64) sq += (int)SQ.ql[2][0][d] + 256 * (int)SQ.ql[2][1][d] + 65536 * (int)SQ.ql[2][2][d];
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o);
         // The first half of a lane's record came with the tile (where a narrower token has its code
@@ -1099,7 +1135,8 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 // front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
 // group of keys and one head's weights after the other, behind branches; 166 in straight sequences for all four, with what a
 // weight has in common for the heads computed once; 161 with every fourth group of slots per wavefront and the weight digits
-// through the transposing LDS read; 157 with the first tile on its way before its class counts are there.
+// through the transposing LDS read; 157 with the first tile on its way before its class counts are there; 155.7 with the rest of
+// it not behind a barrier, and a head's query digits per wavefront.
 // ---------------------------------------------------------------------------------------
 constexpr int kHG = 4;
 
@@ -1128,7 +1165,8 @@ struct GqaLds {
   alignas(16) int xc[kHG][D][4];               // outlier corrections of one tile, fixed point, four copies per channel
   alignas(16) float red[4][kHG];               // per wavefront and head
   alignas(16) float red2[4][kHG];
-  int sq[2][kHG];                              // per wavefront of channels and head: sum of the unscaled query integers (8-bit keys are stored as code - 128)
+  int sq[kHG];                                 // per head: sum of the unscaled query integers (8-bit keys are stored as code - 128)
+  float qstat[kHG][2];                         // per head: scale of the query's fixed point, sum of the query
 };
 
 template <int D, int NO2>
@@ -1170,9 +1208,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
 
   // (as in k_attn_tile: no load of the prologue sits behind a branch, and what the first tile's class counts are not needed
   // for is on its way while they are)
-  __half q_raw[kHG];
+  const TileCounts first_counts(v, qaq_bh(v, b, h) * v.NT + tile_begin);
+  __half q_raw[KS];                 // the query of head `wave`
 #pragma unroll
-  for (int j = 0; j < kHG; ++j) q_raw[j] = a.q[(size_t)(bq0 + j) * D + min(tid, D - 1)];
+  for (int ks = 0; ks < KS; ++ks) q_raw[ks] = a.q[(size_t)(bq0 + wave) * D + 64 * ks + lane];
   const int my_tile = tile_begin + min(tid, tile_end - tile_begin - 1);
   const uint4 cnt_raw = *(const uint4*)(v.counts + ((qaq_bh(v, b, h) * v.NT + my_tile) * 2) * 4);
   const float vb_raw = v.vbound[qaq_bh(v, b, h) * v.NT + my_tile];
@@ -1216,13 +1255,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
       kov = gload32(uniform_ptr(v.oval[0] + gi0 * 2), 4u * (uint32_t)so);
     }
   };
-  auto load_keys_rest = [&](int tile) {
+  auto load_keys_rest = [&](int tile, const QaqCounts& ck) {
     int l = lane;
     asm volatile("" : "+v"(l));
     const int g = l >> 4, ks0 = w0 + (l & 15);      // the lane's first slot
     const uint32_t lane_a = (uint32_t)ks0 * (uint32_t)(D / 4) + (uint32_t)g * (4u * KS);
     const uint32_t lane_b = (uint32_t)ks0 * (uint32_t)(D / 8) + 4u * (uint32_t)((g * KS) >> 1);
-    cKn = counts_of(tile, 0);
+    cKn = ck;
     const gbytes_t ubase = uniform_ptr(qaq_tile_codes(v, 0, b, h, tile));
     const QaqKRegions rK = qaq_k_regions(cKn, D);
     const int n32 = cKn.n32();
@@ -1261,60 +1300,49 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   ValRegs<D, NO2> vr;
   load_keys_first(tile_begin);
   vr.template load_first<false, true>(v, len, b, h, tile_begin, tid, wave, nn, g);
+  __builtin_amdgcn_sched_barrier(0);      // (nothing that waits for one of them in between)
+  load_keys_rest(tile_begin, first_counts.of<false>(0, 0));
+  vr.template load_rest<false, true>(v, b, h, tile_begin, first_counts.of<false>(1, 0), tid, wave, nn, g);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- query digits: 22-bit fixed point per head, three signed base-256 digits, one table per spreading format; a head
+  // per wavefront --------------------------------------------------------------------------------------------------
+  {
+    float qx[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qx[ks] = __half2float(q_raw[ks]);
+    const float qmax = wave_max(KS == 1 ? fabsf(qx[0]) : fmaxf(fabsf(qx[0]), fabsf(qx[KS - 1])));
+    const float sumq = KS == 1 ? wave_sum(qx[0]) : wave_sum(qx[0]) + wave_sum(qx[KS - 1]);
+    int qexp = 0;
+    if (qmax > 0.0f) (void)frexpf(qmax, &qexp);
+    int sum = 0;                                   // (an atomic on one address becomes a loop over the lanes)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      S.qf[wave][64 * ks + lane] = qx[ks];
+      const int i = lane & 15, vgr = i >> 2;
+      const int pos = 16 * ((lane >> 4) * KS + ks) + i;
+#pragma unroll
+      for (int f = 0; f < 3; ++f) {
+        const int sh = f == 0 ? shift2(vgr) : f == 1 ? shift1(vgr) : 0;
+        const int x = qmax > 0.0f ? (int)rintf(ldexpf(qx[ks], 22 - qexp - sh)) : 0;
+        const uint32_t dg = digits_packed(x);
+        S.ql[f][wave][0][pos] = (int8_t)dg; S.ql[f][wave][1][pos] = (int8_t)(dg >> 8); S.ql[f][wave][2][pos] = (int8_t)(dg >> 16);
+        S.ql[f][wave][3][pos] = 0;
+        if (f == 2) sum += x;
+      }
+    }
+    sum = wave_isum(sum);
+    if (lane == 0) { S.qstat[wave][0] = qmax > 0.0f ? ldexpf(1.0f, qexp - 22) : 0.0f; S.qstat[wave][1] = sumq; S.sq[wave] = sum; }
+  }
+  for (int e = tid; e < kHG * D; e += kThreads) *(int4*)&S.xc[0][e][0] = make_int4(0, 0, 0, 0);
+  if (tid < 64) ((uint32_t*)&S.zero[0][0])[tid] = 0u;
+  if (tid < kHG) S.logit[tid][QAQ_TT] = -INFINITY;
   if (tid < tile_end - tile_begin) {
     *(uint4*)&S.cnt[tid][0] = cnt_raw;
     S.vb[tid] = vb_raw;
   }
-  float qv[kHG];
-#pragma unroll
-  for (int j = 0; j < kHG; ++j) qv[j] = tid < D ? __half2float(q_raw[j]) : 0.0f;
-  if (wave < KS) {
-#pragma unroll
-    for (int j = 0; j < kHG; ++j) {
-      const float am = wave_max(fabsf(qv[j]));
-      const float sm = wave_sum(qv[j]);
-      if (lane == 0) { S.red[wave][j] = am; S.red2[wave][j] = sm; }
-      S.qf[j][tid] = qv[j];
-    }
-  }
-  constexpr int ZROW = (D + 16) / 4;
-  for (int e = tid; e < 3 * kHG * ZROW; e += kThreads) ((uint32_t*)&S.ql[0][e / ZROW][3][0])[e % ZROW] = 0u;
-  for (int e = tid; e < kHG * D; e += kThreads) *(int4*)&S.xc[0][e][0] = make_int4(0, 0, 0, 0);
-  if (tid < 64) ((uint32_t*)&S.zero[0][0])[tid] = 0u;
-  if (tid < kHG) S.logit[tid][QAQ_TT] = -INFINITY;
   lds_barrier();
-
-  load_keys_rest(tile_begin);
-  vr.template load_rest<false, true>(v, b, h, tile_begin, counts_of(tile_begin, 1), tid, wave, nn, g);
-
-  // ---- query digits: 22-bit fixed point per head, three signed base-256 digits, one table per
-  // spreading format ---------------------------------------------------------------------------------
-  float qscale_g = 0.0f, sumq_g = 0.0f;        // of the lane's own head g
-#pragma unroll
-  for (int j = 0; j < kHG; ++j) {
-    const float qmax = KS == 1 ? S.red[0][j] : fmaxf(S.red[0][j], S.red[1][j]);
-    const float sumq = KS == 1 ? S.red2[0][j] : S.red2[0][j] + S.red2[1][j];
-    int qexp = 0;
-    if (qmax > 0.0f) (void)frexpf(qmax, &qexp);
-    const float qscale = qmax > 0.0f ? ldexpf(1.0f, qexp - 22) : 0.0f;
-    if (j == g) { qscale_g = qscale; sumq_g = sumq; }
-    if (wave < KS) {
-      const int i = tid & 15, vgr = i >> 2;
-      const int pos = 16 * (((tid & 63) >> 4) * KS + (tid >> 6)) + i;
-#pragma unroll
-      for (int f = 0; f < 3; ++f) {
-        const int sh = f == 0 ? shift2(vgr) : f == 1 ? shift1(vgr) : 0;
-        const int x = qmax > 0.0f ? (int)rintf(ldexpf(qv[j], 22 - qexp - sh)) : 0;
-        const uint32_t dg = digits_packed(x);
-        S.ql[f][j][0][pos] = (int8_t)dg; S.ql[f][j][1][pos] = (int8_t)(dg >> 8); S.ql[f][j][2][pos] = (int8_t)(dg >> 16);
-        if (f == 2) {                              // (an atomic on one address becomes a loop over the lanes)
-          const int sum = wave_isum(x);
-          if (lane == 0) S.sq[wave][j] = sum;
-        }
-      }
-    }
-  }
-  lds_barrier();
+  const float qscale_g = S.qstat[g][0], sumq_g = S.qstat[g][1];        // of the lane's own head
   // A rows: row r = 4 * head + digit; the lane's k-range is slices g*KS ..
   const int arow_h = nn >> 2, arow_d = nn & 3;
   const int8_t* abase0 = &S.ql[0][arow_h][arow_d][16 * g * KS];
@@ -1448,11 +1476,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
             const int i8 = min(max(s - first8K, 0), max(cK.n8 - 1, 0));
             gload_dwords<4 * KS>(baseK + (rK.r8 + (uint32_t)i8 * D + (uint32_t)g * (16u * KS)), w8r);
           }
-          const int sq = KS == 1 ? S.sq[0][g] : S.sq[0][g] + S.sq[1][g];
-          v4i c = zero4;
+            v4i c = zero4;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) c = mma(q[ks], spread<8>(&w8r[4 * ks], 0), c);
-          if (s >= first8K) dotq[tg] = ((((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) + 128.0f * (float)sq) * qscale_g;
+          if (s >= first8K) dotq[tg] = ((((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) + 128.0f * (float)S.sq[g]) * qscale_g;
         }
       }
     }
@@ -1488,7 +1515,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
         }
       }
     }
-    if (tile + 1 < tile_end) { load_keys_first(tile + 1); load_keys_rest(tile + 1); }
+    if (tile + 1 < tile_end) { load_keys_first(tile + 1); load_keys_rest(tile + 1, counts_of(tile + 1, 0)); }
 
     // maximum of the lane's head over its row of 16 lanes, then over the wavefronts
     asm volatile(QAQ_DPP_STEP("v_max_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
