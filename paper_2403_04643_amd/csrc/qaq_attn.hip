@@ -1655,7 +1655,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
         const int4 x = *((int4*)&S.xc[0][0][0] + item);
         *((int4*)&S.xc[0][0][0] + item) = make_int4(0, 0, 0, 0);
         const float kp = j == 0 ? keep[0] : j == 1 ? keep[1] : j == 2 ? keep[2] : keep[3];
-        c_run[r] = c_run[r] * kp + ((float)(x.x + x.y) + (float)(x.z + x.w)) * ldexpf(wscale, 3);
+        // (a copy takes at most 64 corrections below 2^25 in magnitude: 32 bits, and a pair of copies would not fit)
+        c_run[r] = c_run[r] * kp + (((float)x.x + (float)x.y) + ((float)x.z + (float)x.w)) * ldexpf(wscale, 3);
       }
     }
     // 4-bit values.  Up to 16 of them in a tile (the usual case where the rules chose the widths):

@@ -43,3 +43,22 @@ def test_class_borders(counts, D, n_o):
     err_x = ((x - ref_x).abs().amax(-1) / ref_x.abs().amax(-1)).max().item()
     print(f"  worst errors: scores {err_s:.1e}, output {err_x:.1e}", flush=True)
     assert err_s < TOL and err_x < TOL
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("G", [4, 1])
+@pytest.mark.parametrize("value", [1.99, -1.99, 1.0])
+def test_one_channel_carries_everything(D, G, value):
+    """The largest sums an outlier correction can have: equal weights (a query of zeros) over full tiles of tokens whose one
+    channel that is not zero has a value just below a power of two."""
+    Hkv, T = 2, 512
+    c = qaq.Cache(qaq.make_config(1, Hkv * G, Hkv, D, T, [1.0] * Hkv, n_outlier_per_side=1))
+    v = torch.zeros((1, Hkv, T, D), dtype=torch.float16, device="cuda")
+    v[..., 7] = value
+    k = torch.randn((1, Hkv, T, D), device="cuda", generator=torch.Generator(device="cuda").manual_seed(D + G)).half()
+    two = torch.full((1, Hkv, T), 2, dtype=torch.uint8, device="cuda")
+    c.quantize_append(k, v, two, two)
+    x, _ = c.decode_attention(torch.zeros((1, Hkv * G, D), dtype=torch.float16, device="cuda"))
+    want = v[:, :, :1].float().expand(1, Hkv, G, D).reshape(1, Hkv * G, D)
+    # every correction is off by at most half a unit of 2^-25 of the bound, the sums by a few roundings of 32 bits
+    assert (x - want).abs().max().item() < 4e-6
