@@ -696,7 +696,9 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
     r.n1 = H1 ? min(len - t * QAQ_TT, QAQ_TT) - (r.n3 + r.n2 + r.n4 + r.n8) : 0;      // the 1-bit class is the rest of the tile
     return r;
   };
-  const float qscale = SQ.qstat[0], sumq = SQ.qstat[1];
+  // (the same in every lane: scalar registers, two less of those the forms for several outliers spill)
+  const float qscale = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(SQ.qstat[0]))),
+              sumq = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(SQ.qstat[1])));
   // A rows: row r = 4*tg + L is switched on in lane group tg only
   const bool arow = (g == (nn >> 2)) && ((nn & 3) < 3);
   const int8_t* abase0 = arow ? &SQ.ql[0][nn & 3][0] : &S.zrow[0];
