@@ -486,7 +486,13 @@ int qaq_decode_update(qaq_cache* c, const float* dev_scores, const void* dev_k_n
   for (int i = 0; i < QAQ_MAX_WINDOW; ++i) r.row_len[i] = i < c->dims.window ? c->row_len[i] : 0;
   r.row_len[r.new_row] = a.len_after;               // the row this call writes (kept by the cache only if the launch succeeds)
   r.nbits = c->cfg.n_bits;
-  for (int i = 0; i < 5; ++i) r.bit_set[i] = c->cfg.bit_set[i < r.nbits ? i : r.nbits - 1];
+  for (int i = 0; i < 5; ++i) {
+    r.bit_set[i] = c->cfg.bit_set[i < r.nbits ? i : r.nbits - 1];
+    r.width_class[i] = r.bit_set[i] | (qaq_class_of_bits(r.bit_set[i]) << 4);
+  }
+  r.rows_full = a.len_after;
+  for (int i = 0; i < c->dims.window; ++i)
+    if (i != r.new_row && r.row_len[i] < r.rows_full) r.rows_full = r.row_len[i];
   threshold_tables(c, a.len_after, r.tau_k, r.c_v);
   r.out_bits[0] = dev_k_bits; r.out_bits[1] = dev_v_bits;
   a.todo = c->view.todo;

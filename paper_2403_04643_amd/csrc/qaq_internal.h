@@ -284,8 +284,10 @@ struct QaqRuleArgs {
   int score_stride;
   int new_row;             // ring row that receives `scores` (ignored if null)
   int row_len[QAQ_MAX_WINDOW];  // tokens covered by each ring row, 0 = unused
+  int rows_full;           // decode-step update: tokens that every row of the window other than new_row covers (0: a row is unused)
   int nbits;
   int bit_set[5];
+  int width_class[5];      // decode-step update: of each of them, width | class << 4
   uint8_t* out_bits[2];    // [B,Hkv,len] or null
   float c_v[QAQ_MAX_RAGGED_BATCH]; // value-rule threshold; per sequence in a cache with different lengths, else entry 0
   float tau_k[QAQ_MAX_THR];        // key-rule threshold per KV head; per (sequence, KV head) in such a cache
@@ -303,6 +305,7 @@ struct QaqBuildArgs {
   const __half* orig[2];       // requantize: [B,Hkv,orig_tokens,D] or null
   __half* orig_put[2];         // same buffers when the appended tokens are to be written into them, else null
   int orig_tokens;             // token extent of the unquantized copies (>= len)
+  int open_first;              // decode-step update: the sides of the tile that receives the token are dispatched first (set by the launcher)
   int max_moved;               // decode-step update: tokens of a tile side the kernel has staging memory for (set by the launcher)
   // decode-step update: tile sides the fast kernel leaves to the general one, (unit * NT + tile) * 2 + side
   uint32_t* todo;

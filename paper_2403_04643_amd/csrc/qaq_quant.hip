@@ -1301,6 +1301,9 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 // 42.1 -> 33.4 us, 16 x 8 heads x 8192 with 8 query heads each 39.3 -> 32.0, 8 heads x 512 tokens 11.9 -> 11.4; with
 // outliers by thresholds (the general kernel until then) 3 x 16 heads x 2500 34 -> 15.9.  Of that the slots were 10 us,
 // 580 scalar instructions per wavefront for masks class by class; as compares per lane and one list of free slots: 33.4 -> 30.
+// Vector and scalar instructions fill two thirds of the issue slots each.  With indices in 32 bits, the window's rows without
+// a look at their ends where all cover the tile, one load of scores where a KV head has one query head and class counts in pairs a
+// wavefront has 15 % fewer scalar ones, compute units are busy 5 % less, and 24 steps of a small model take 436 instead of 453 us.
 // ---------------------------------------------------------------------------------
 constexpr int kMaxCopy = 8192;
 constexpr int kUpdThreads = 128;
@@ -1322,7 +1325,7 @@ struct UpdLds {
   uint32_t new_oi[2], new_ov[4];           // ... outlier channels, outlier values
   uint32_t new_mm;
   int new_no;                              // ... outliers (variable-length side store)
-  int w_cls[2][QAQ_NCLASS];                // per wavefront
+  int w_cls[2][QAQ_NCLASS];                // per wavefront, two counts per word (not all words are used)
   int w_any[2], w_wide[2], w_moved[2];
   int free0;                               // free slots among the first wavefront's
   int first_free[QAQ_NCLASS];              // per class: free slots before its first slot (256 added: to be counted on from free0)
@@ -1410,6 +1413,68 @@ __device__ __forceinline__ void predicted2(const QaqView& v, const int (&lim)[QA
   for (int j = 0; j < 4; ++j) __builtin_memcpy(&g[j], (const uint8_t*)(row0 + (size_t)min(j, G - 1) * stride) + (uint32_t)(4 * p0), sizeof(Two));
   if (v.ring_half) predicted2_t<uint16_t>(v, lim, skip, ri0, p0, g, s, m);
   else predicted2_t<uint32_t>(v, lim, skip, ri0, p0, g, s, m);
+}
+
+// The same for a tile that every row of the window covers -- all but the last one, once the window is full --: no row has
+// an end to look at, and with one query head per KV head the row of scores is one load.  ring: the ring at the tile's first
+// position.  A row that the window has not, or that this step's row replaces, is another one that counts.
+template <int W, int GB, typename RAW>
+__device__ __forceinline__ void predicted_full_w(const QaqView& v, int skip, const RAW* ring, size_t ring_row, int p0,
+                                                 const float* row0, int G, size_t stride, float (&s)[2], float (&m)[2]) {
+  struct R2 { RAW x[2]; } raw[W > 1 ? W - 1 : 1];
+  const int other = skip == 0 ? 1 : 0;
+#pragma unroll
+  for (int r = 1; r < W; ++r) {                              // the rows behind `skip`, round the ring
+    int at = skip + r;
+    at -= at >= v.window ? v.window : 0;
+    if (W == 3 || W == 8) at = r < v.window ? at : other;    // (these take windows of two, and of six and seven rows)
+    __builtin_memcpy(&raw[r - 1], (const uint8_t*)(ring + (size_t)at * ring_row) + (uint32_t)(p0 * (int)sizeof(RAW)), sizeof(R2));
+  }
+  Two g[GB];
+  s[0] = s[1] = 0.0f;                                        // probabilities: >= 0
+#pragma unroll 1
+  for (int g0 = GB; g0 < G; g0 += GB) {                      // query heads beyond the first GB
+#pragma unroll
+    for (int j = 0; j < GB; ++j) __builtin_memcpy(&g[j], (const uint8_t*)(row0 + (size_t)min(g0 + j, G - 1) * stride) + (uint32_t)(4 * p0), sizeof(Two));
+#pragma unroll
+    for (int j = 0; j < GB; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) s[e] = vmaxf(s[e], g[j].x[e]);
+  }
+#pragma unroll
+  for (int j = 0; j < GB; ++j) __builtin_memcpy(&g[j], (const uint8_t*)(row0 + (size_t)min(j, G - 1) * stride) + (uint32_t)(4 * p0), sizeof(Two));
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+#pragma unroll
+    for (int j = 0; j < GB; ++j) s[e] = vmaxf(s[e], g[j].x[e]);
+    s[e] = qaq_ring_value(v, s[e]);
+    m[e] = s[e];
+#pragma unroll
+    for (int r = 1; r < W; ++r) {
+      const RAW x = raw[r - 1].x[e];
+      m[e] = vmaxf(m[e], sizeof(RAW) == 4 ? __uint_as_float((uint32_t)x) : v.ring_half == 1 ? h2f((uint16_t)x) : __uint_as_float((uint32_t)x << 16));
+    }
+  }
+}
+template <int GB, typename RAW>
+__device__ __forceinline__ void predicted_full_t(const QaqView& v, int skip, size_t ri0, size_t ring_row, int p0,
+                                                 const float* row0, int G, size_t stride, float (&s)[2], float (&m)[2]) {
+  const RAW* ring = (const RAW*)v.ring + ri0;
+  if (v.window == 1) predicted_full_w<1, GB, RAW>(v, skip, ring, ring_row, p0, row0, G, stride, s, m);
+  else if (v.window <= 3) predicted_full_w<3, GB, RAW>(v, skip, ring, ring_row, p0, row0, G, stride, s, m);
+  else if (v.window == 4) predicted_full_w<4, GB, RAW>(v, skip, ring, ring_row, p0, row0, G, stride, s, m);
+  else if (v.window == 5) predicted_full_w<5, GB, RAW>(v, skip, ring, ring_row, p0, row0, G, stride, s, m);
+  else predicted_full_w<8, GB, RAW>(v, skip, ring, ring_row, p0, row0, G, stride, s, m);
+}
+__device__ __forceinline__ void predicted_full(const QaqView& v, int skip, size_t ri0, size_t ring_row, int p0,
+                                               const float* row0, int G, size_t stride, float (&s)[2], float (&m)[2]) {
+  if (v.ring_half) {
+    if (G == 1) predicted_full_t<1, uint16_t>(v, skip, ri0, ring_row, p0, row0, 1, stride, s, m);
+    else predicted_full_t<4, uint16_t>(v, skip, ri0, ring_row, p0, row0, G, stride, s, m);
+  } else {
+    if (G == 1) predicted_full_t<1, uint32_t>(v, skip, ri0, ring_row, p0, row0, 1, stride, s, m);
+    else predicted_full_t<4, uint32_t>(v, skip, ri0, ring_row, p0, row0, G, stride, s, m);
+  }
 }
 
 // class of a slot (the classes are numbered in slot order), width of a class: no branches
@@ -1508,33 +1573,42 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   const QaqView& v = a.v;
   const QaqRuleArgs& ru = a.rule;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), tok0 = 64 * J * wave + lane;
-  const int bh = blockIdx.x, b = bh / v.Hkv, h = bh % v.Hkv;
-  // value sides first: nearly every one of them has work (a token's predicted score moves every
-  // step), most key sides leave after one load and fill in behind
-  const int tile = blockIdx.y, side = 1 - (int)blockIdx.z;
+  // (indices in 32 bits: a tile takes tens of kilobytes of the arena.  The KV head and the sequence only where they are asked for)
+  const int bh = blockIdx.x;
+  // Value sides first: nearly every one of them has work (a token's predicted score moves every step), most key sides leave after
+  // one load and fill in behind.  Where not all sides are in flight at once, the tile that receives the token (of the
+  // longest sequence) before all others: its sides have the longest way to go, and the key side was started last, 18-23 us
+  // after the first ones at 8 x 32 heads x 4096 tokens, and waited for.
+  int tile = blockIdx.y, side = 1 - (int)blockIdx.z;
+  if (a.open_first) {
+    const int n = (int)gridDim.y, open = a.len_before / QAQ_TT, at = tile + n * (int)blockIdx.z;      // 0 .. 2 n - 1
+    const int r = at - 2, t = r < n - 1 ? r : r - (n - 1);
+    side = at < 2 ? 1 - at : r < n - 1 ? 1 : 0;
+    tile = at < 2 ? open : t + (t >= open ? 1 : 0);
+  }
   const int t0 = tile * QAQ_TT;
-  const int shorter = v.ragged ? v.shortfall[b] : 0;      // than the longest sequence
+  const int shorter = v.ragged ? v.shortfall[bh / v.Hkv] : 0;      // than the longest sequence
   const int len_before = max(a.len_before - shorter, 0), len_after = max(a.len_after - shorter, 0);   // of this sequence
   const int n_before = min(max(len_before - t0, 0), QAQ_TT);
   const int n_after = min(max(len_after - t0, 0), QAQ_TT);
-  if (bh == 0 && tile == 0 && side == 0 && tid == 0) a.todo_count[1] = 0u;      // (k_build_listed, if it has entries, leaves their number)
+  if (bh == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid == 0) a.todo_count[1] = 0u;      // (k_build_listed, if it has entries, leaves their number)
   if (n_after == 0) return;
   const bool csr = !ONE && v.csr;
   const int no2 = ONE ? 2 : v.no2;
   const bool has_new = n_after > n_before;           // the appended token is position n_before of this tile
-  const size_t tile_id = qaq_bh(v, b, h) * v.NT + tile;
+  const uint32_t tile_id = (uint32_t)bh * (uint32_t)v.NT + (uint32_t)tile;
   // keys: the tile recorded, when it was built, the interval of thresholds for which none of its
   // tokens changes width (one 8-byte load decides)
   if (side == 0 && !has_new && !ru.out_bits[0]) {
     const float2 keep = ((const float2*)v.kthr)[tile_id];
-    const float tau = qaq_tau_k(ru, v, b, h);
+    const float tau = ru.tau_k[v.ragged ? bh : bh % v.Hkv];
     if (tau >= keep.x && tau < keep.y) return;
   }
 
   // ---- everything whose address is known up front ------------------------------------------------
-  uint8_t* base = qaq_tile_codes(v, side, b, h, tile);
-  const uint2 counts_raw = *(const uint2*)(v.counts + (tile_id * 2 + side) * 4);
-  const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
+  uint8_t* base = v.codes[side] + (size_t)tile_id * v.cap[side];
+  const uint2 counts_raw = *(const uint2*)(v.counts + ((size_t)tile_id * 2 + side) * 4);
+  const size_t gi0 = (size_t)tile_id * QAQ_TT;      // (units follow one another in whole tiles)
   // token tok0 + 64*j: the cached token in that old slot, or (== n_before) the appended one
   uint32_t mm[J], oi[J], ov[J];      // (oi, ov: ONE; else the side store is read again for the tokens that move)
   uint32_t oext[J];                  // value side, not ONE: largest | smallest outlier << 16
@@ -1573,13 +1647,25 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     }
   }
   if (side == 1) {      // the window (Section 4.2), this step's row stored: two positions per lane
-    const size_t ring_row = (size_t)v.B * v.Hkv * v.Tmax;
-    const size_t ri0 = qaq_bh(v, b, h) * v.Tmax + t0;
-    const float* row0 = ru.scores + ((size_t)b * v.Hq + h * ru.G) * ru.score_stride + t0;
-    int lim[QAQ_MAX_WINDOW];
+    const size_t ring_row = (size_t)((uint32_t)gridDim.x * (uint32_t)v.NT) * QAQ_TT;
+    const size_t ri0 = gi0;
+    const float* row0 = ru.scores + (size_t)(uint32_t)(bh * ru.G) * ru.score_stride + t0;
+    if (t0 + QAQ_TT <= ru.rows_full - shorter) {
+      float s[2], m[2];
+      predicted_full(v, ru.new_row, ri0, ring_row, 2 * tid, row0, ru.G, ru.score_stride, s, m);
+      if (v.ring_half == 0) {
+        __builtin_memcpy((uint8_t*)((float*)v.ring + (size_t)ru.new_row * ring_row + ri0) + (uint32_t)(8 * tid), s, 8);
+      } else {
+        uint16_t hs[2];
 #pragma unroll
-    for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] = max(ru.row_len[r] - shorter, 0) - t0;
-    if (len_after >= 2) {
+        for (int e = 0; e < 2; ++e) hs[e] = v.ring_half == 1 ? f2h(s[e]) : qaq_bf16_bits(s[e]);
+        __builtin_memcpy((uint8_t*)((uint16_t*)v.ring + (size_t)ru.new_row * ring_row + ri0) + (uint32_t)(4 * tid), hs, 4);
+      }
+      pred[2 * tid] = m[0]; pred[2 * tid + 1] = m[1];
+    } else if (len_after >= 2) {
+      int lim[QAQ_MAX_WINDOW];
+#pragma unroll
+      for (int r = 0; r < QAQ_MAX_WINDOW; ++r) lim[r] = max(ru.row_len[r] - shorter, 0) - t0;
       // (the lane that the tile's end falls into reads one position further down: the one before it is
       // another lane's as well, and gets the same value from both)
       // (lane offsets are unsigned: in a tile with one token everything counts from the position before it)
@@ -1609,7 +1695,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       float s = 0.0f;
       for (int g = 0; g < ru.G; ++g) s = fmaxf(s, row0[(size_t)g * ru.score_stride]);
       s = qaq_ring_value(v, s);
-      pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, b, t0), ru.new_row, ri0, s);
+      pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, bh / v.Hkv, t0), ru.new_row, ri0, s);
       qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri0, s);
     }
     if (csr) {
@@ -1659,8 +1745,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     const int ch0 = 2 * lane, ch1 = 2 * lane + 1;
     const uint32_t k0 = kk << 16, k1 = kk & 0xffff0000u;
     bool in0 = act, in1 = act;
-    const float thr_lo = csr ? v.othr[(side * v.Hkv + h) * 2] : INFINITY;
-    const float thr_hi = csr ? v.othr[(side * v.Hkv + h) * 2 + 1] : -INFINITY;
+    float thr_lo = INFINITY, thr_hi = -INFINITY;
+    if (csr) {
+      const float* t = v.othr + (side * v.Hkv + bh % v.Hkv) * 2;
+      thr_lo = t[0]; thr_hi = t[1];
+    }
     // the largest values, lowest channel first; then the smallest of the rest, lowest channel first; the
     // one in lane k is the k-th found
     uint32_t my_ch = 0xffu, my_val = 0u;
@@ -1724,11 +1813,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   }
 
   // ---- widths by the rules of Section 4.1 -----------------------------------------------------------
-  const float thr = side == 0 ? qaq_tau_k(ru, v, b, h) : qaq_c_v(ru, v, b);
+  const float thr = side == 0 ? ru.tau_k[v.ragged ? bh : bh % v.Hkv] : ru.c_v[v.ragged ? bh / v.Hkv : 0];
   float thr_b[NC];             // (entries past the last width repeat it)
   int wc[NC];                  // width | class << 4
 #pragma unroll
-  for (int i = 0; i < NC; ++i) { thr_b[i] = ldexpf(thr, ru.bit_set[i]); wc[i] = ru.bit_set[i] | (qaq_class_of_bits(ru.bit_set[i]) << 4); }
+  for (int i = 0; i < NC; ++i) { thr_b[i] = ldexpf(thr, ru.bit_set[i]); wc[i] = ru.width_class[i]; }
   const bool served = a.orig[side] != nullptr;
   int cls[J];                  // class after this step, -1: no token
   unsigned long long same_cls[J];   // cached tokens that stay in their class
@@ -1788,10 +1877,13 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   else { lo = wave_max(lo); hi = wave_min(hi); }
   if (lane == 0) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
+    for (int c = 0; c < (NC + 1) / 2; ++c) {             // two counts per word
       int n = 0;
 #pragma unroll
-      for (int j = 0; j < J; ++j) n += __popcll(bal_cls[c][j]);
+      for (int j = 0; j < J; ++j) {
+        n += __popcll(bal_cls[2 * c][j]);
+        if (2 * c + 1 < NC) n += __popcll(bal_cls[2 * c + 1 < NC ? 2 * c + 1 : 0][j]) << 16;
+      }
       L.w_cls[wave][c] = n;
     }
     L.w_any[wave] = any != 0ull; L.w_wide[wave] = n_wide;
@@ -1800,13 +1892,16 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   __syncthreads();
   const int all_wide = L.w_wide[0] + L.w_wide[1];
   if (!(L.w_any[0] | L.w_any[1])) {          // nothing moves and nothing is appended
-    if (tid == 0 && all_wide) v.refused[(tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
+    if (tid == 0 && all_wide) v.refused[((size_t)tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
     return;
   }
-  auto both = [](const int (&x)[2][QAQ_NCLASS], int c) { return __builtin_amdgcn_readfirstlane(x[0][c] + x[1][c]); };
+  auto both = [&](int c) { return __builtin_amdgcn_readfirstlane(L.w_cls[0][c] + L.w_cls[1][c]); };
   QaqCounts cn;
-  cn.n3 = both(L.w_cls, QC3); cn.n2 = both(L.w_cls, QC2); cn.n4 = both(L.w_cls, QC4); cn.n8 = both(L.w_cls, QC8);
-  cn.n1 = HAS1 ? both(L.w_cls, QC1) : 0;
+  {
+    const int n01 = both(0), n23 = both(1);
+    cn.n3 = n01 & 0xffff; cn.n2 = n01 >> 16; cn.n4 = n23 & 0xffff; cn.n8 = n23 >> 16;
+    cn.n1 = HAS1 ? both(2) : 0;
+  }
 
   // ---- regions.  A token's codes sit at an index inside its class's region (2- and 3-bit tokens: the
   // slot; the others: the slot less the class's first one).  The 2-bit fields start the tile side; another
@@ -2178,11 +2273,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     }
   }
   if (tid == 0) {
-    uint16_t* cp = v.counts + ((tile_id * 2 + side) * 4);
+    uint16_t* cp = v.counts + (((size_t)tile_id * 2 + side) * 4);
     cp[QC3] = (uint16_t)cn.n3; cp[QC2] = (uint16_t)cn.n2; cp[QC4] = (uint16_t)cn.n4; cp[QC8] = (uint16_t)cn.n8;
     if (side == 1) v.vbound[tile_id] = fmaxf(L.w_bnd[0], L.w_bnd[1]);
     else ((float2*)v.kthr)[tile_id] = make_float2(fmaxf(L.w_lo[0], L.w_lo[1]), fminf(L.w_hi[0], L.w_hi[1]));
-    if (all_wide) v.refused[(tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
+    if (all_wide) v.refused[((size_t)tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
   }
 
   // ---- codes of the moved tokens -> their new places ----------------------------------------------------
@@ -2661,6 +2756,7 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float movi
   const long long resident = (sides / 2 + cus - 1) / cus;
   const int room = lds / (int)(resident < kUpdResident ? resident : kUpdResident) / grain * grain - (int)sizeof(UpdLds<D>);
   a.max_moved = room / UpdLds<D>::PER_TOKEN;
+  a.open_first = sides > (long long)kUpdResident * cus;
   if (a.max_moved > QAQ_TT) a.max_moved = QAQ_TT;
   *whole = a.max_moved < QAQ_TT && moving * QAQ_TT >= (float)a.max_moved;
   if (*whole) return qaq_launch_build(a_in, ntiles, s);
