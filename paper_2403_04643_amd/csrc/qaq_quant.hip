@@ -271,6 +271,45 @@ struct TokenEncoder {
     return (j & 3) == 0 ? raw[j >> 2].x : (j & 3) == 1 ? raw[j >> 2].y : (j & 3) == 2 ? raw[j >> 2].z : raw[j >> 2].w;
   }
 
+  // The same where `pair` is the extreme of the whole token and ext[i] that of chunk i in each half (SMALLEST: which extreme):
+  // by halving, since the extreme of the first half of what is left tells whether it is there.  47 instructions an end at
+  // 128 channels where the sweep over all words takes 60.
+  template <bool SMALLEST>
+  __device__ static __forceinline__ uint32_t channel_of_end(const uint4 (&raw)[NCH], const uint32_t (&ext)[NCH], int c, uint32_t pair) {
+    auto further = [](uint32_t a, uint32_t b) { return SMALLEST ? pk_hmin(a, b) : pk_hmax(a, b); };
+    auto has = [&](uint32_t m) {
+      const uint32_t x = m ^ pair;
+      const us2 z = __builtin_elementwise_min(__builtin_bit_cast(us2, x), __builtin_bit_cast(us2, halves_swapped(x)));
+      return z.x == 0;
+    };
+    uint32_t w[8], e = 0u, first = ext[0];
+    if constexpr (NCH == 4) {
+      const bool in = has(further(ext[0], ext[1]));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) w[j] = in ? word_of(raw, j) : word_of(raw, 8 + j);
+      first = in ? ext[0] : ext[2];
+      e = in ? 0u : 16u;
+    } else {
+      static_assert(NCH == 2, "chunks per lane");
+#pragma unroll
+      for (int j = 0; j < 8; ++j) w[j] = word_of(raw, j);
+    }
+    bool in = has(first);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = in ? w[j] : w[4 + j];
+    e += in ? 0u : 8u;
+    in = has(further(w[0], w[1]));
+    w[0] = in ? w[0] : w[2]; w[1] = in ? w[1] : w[3];
+    e += in ? 0u : 4u;
+    in = has(w[0]);
+    w[0] = (in ? w[0] : w[1]) ^ pair;
+    e += in ? 0u : 2u;
+    const bool low = (w[0] & 0xffffu) == 0u, high = w[0] < 0x10000u;
+    e += low ? 0u : 1u;
+    const uint32_t ch = ((e & ~7u) << 2) + (uint32_t)(8 * c) + (e & 7u);
+    return quad_umin(low || high ? ch : 0xffu);
+  }
+
   // One outlier per end: the largest and the smallest value of a token and the runners-up.  The two largest and the two
   // smallest come from four words at a time, sorted as pairs (ten instructions for eight elements) and merged into the
   // running ones; then over the halves of the words and the lanes of the quad (there the largest and minus the smallest
@@ -281,12 +320,14 @@ struct TokenEncoder {
     asm("" : "+s"(ones));              // (known to be ones, the minimum with them becomes two compares and two selects)
     const us2 one = __builtin_bit_cast(us2, ones);
     uint32_t A1 = 0u, A2 = 0u, B1 = 0u, B2 = 0u, any = 0u;      // (any: the largest, or a NaN if there is one)
+    uint32_t hi[NCH], lo[NCH];                                  // of each chunk
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const uint32_t x = raw[i].x, y = raw[i].y, z = raw[i].z, w = raw[i].w;
       const uint32_t h0 = pk_hmax(x, y), l0 = pk_hmin(x, y), h1 = pk_hmax(z, w), l1 = pk_hmin(z, w);
       const uint32_t s3 = pk_hmax(h0, h1), s0 = pk_hmin(l0, l1), m0 = pk_hmin(h0, h1), m1 = pk_hmax(l0, l1);
       const uint32_t s2 = pk_hmax(m0, m1), s1 = pk_hmin(m0, m1);
+      hi[i] = s3; lo[i] = s0;
       if (i == 0) { A1 = s3; A2 = s2; B1 = s0; B2 = s1; any = pk_hmaximum(x, y, z); any = pk_hmaximum(any, w, w); }
       else {
         A2 = pk_hmax(pk_hmin(A1, s3), pk_hmax(A2, s2)); A1 = pk_hmax(A1, s3);
@@ -312,9 +353,8 @@ struct TokenEncoder {
     uint32_t ch_top, ch_bot, v_top, v_bot;
     if (__ballot(most.x >= 0x7bffu) == 0ull) {
       const uint32_t top_pair = __builtin_amdgcn_perm(0u, e1, 0x01000100u), bot_pair = __builtin_amdgcn_perm(0u, e1, 0x03020302u) ^ 0x80008000u;
-      auto word = [&](int j) { return word_of(raw, j); };
-      ch_top = first_channel(word, c, top_pair, one);
-      ch_bot = first_channel(word, c, bot_pair, one);
+      ch_top = channel_of_end<false>(raw, hi, c, top_pair);
+      ch_bot = channel_of_end<true>(raw, lo, c, bot_pair);
       // the smallest of the rest is the overall smallest unless that is the top element itself: all values are equal
       // then, and it is the second of them
       if (top_pair == bot_pair) ch_bot = 1u;
@@ -1235,7 +1275,7 @@ __device__ __forceinline__ void build_tile(const QaqBuildArgs& a, BuildLds<D, ON
 // tile count that is a multiple of eight, every die would see the same two tile indices of every
 // head, which ran 30 % slower.
 template <int D, bool ONE, bool HAS1>
-__global__ __launch_bounds__(kThreads) void k_build(QaqBuildArgs a) {
+__global__ __launch_bounds__(kThreads, (D == 64 && ONE ? 7 : 1)) void k_build(QaqBuildArgs a) {      // (the narrow form at 75 registers without a bound: six wavefronts per SIMD)
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, c_v)>();
   __shared__ BuildLds<D, ONE ? 2 : QAQ_MAX_NO2> L;
   const int tile = a.tile0 + (int)blockIdx.y, t0 = tile * QAQ_TT, b = (int)blockIdx.x / a.v.Hkv;
