@@ -1130,8 +1130,9 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 // digit sums for it; on the value side the rows are summed over 64 slots and lane (n, g)
 // receives head g's digit sums for channel n.  Parts write partials (max, sum, X) per query
 // head and raw logits; k_attn_combine merges them.  Width sets without 1, the fixed-length
-// side store with one outlier per end or none; G a multiple of 4 (a KV head with 8 query
-// heads is scanned twice, by two workgroups that run side by side).
+// side store with one outlier per end or none; G > 2, in passes of four heads and one of
+// what is left (a KV head with 5 to 8 query heads is scanned twice, by two workgroups that
+// run side by side), where the cache is large enough (the rule and its figures: qaq_launch_attention).
 //
 // Bound: vector instructions (60 % of the issue slots at three wavefronts per SIMD, the most its registers allow) and, in
 // front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
@@ -1171,7 +1172,8 @@ struct GqaLds {
   float qstat[kHG][2];                         // per head: scale of the query's fixed point, sum of the query
 };
 
-template <int D, int NO2>
+// WHOLE: G is a multiple of four.
+template <int D, int NO2, bool WHOLE>
 __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   constexpr int KS = D / 64;
   constexpr int NCG = D / 16;
@@ -1183,7 +1185,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   // two layers at 16 x 64 heads on 8, 8192 tokens; in k_attn_tile the same costs registers it has not: 120.0 -> 128.0 us)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nn = lane & 15, g = lane >> 4;
-  const int NG = a.G / kHG;
+  const int NG = WHOLE ? a.G / kHG : (a.G + kHG - 1) / kHG;
   int chunk = blockIdx.x, bh = (int)blockIdx.y / NG, hg = (int)blockIdx.y - bh * NG;
   if (a.neighbours) {
     int item;
@@ -1192,13 +1194,17 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   }
   const int b = bh / v.Hkv, h = bh % v.Hkv;
   const int bq0 = b * v.Hq + h * a.G + kHG * hg;           // first of the four query heads
+  // ... of which a last group may have fewer: what is left of the four repeats its last one and is not written (a form of its
+  // own, because looking whether a head is there costs the full groups 1.5 %: three layers at 16 x 64 heads on 8, 8192 tokens
+  // 215.6 and 218.9 us)
+  const int heads = WHOLE ? kHG : min(kHG, a.G - kHG * hg);
   const int len = qaq_seq_len(v, b, a.len);          // cached tokens of this sequence
   const int ntile = (len + QAQ_TT - 1) / QAQ_TT;
   int tile_begin, tile_end;
   part_tiles(a, ntile, chunk, tile_begin, tile_end);
   if (tile_begin >= tile_end) {
     // a sequence shorter than the longest can leave a part without tiles: partials that the merge ignores
-    for (int e = tid; e < kHG * (D + 2); e += kThreads) {
+    for (int e = tid; e < heads * (D + 2); e += kThreads) {
       float* part = a.partial + ((size_t)(bq0 + e / (D + 2)) * a.part_stride + chunk) * (D + 4);
       const int c = e % (D + 2);
       part[c] = c == D ? -INFINITY : 0.0f;
@@ -1213,7 +1219,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   const TileCounts first_counts(v, qaq_bh(v, b, h) * v.NT + tile_begin);
   __half q_raw[KS];                 // the query of head `wave`
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) q_raw[ks] = a.q[(size_t)(bq0 + wave) * D + 64 * ks + lane];
+  for (int ks = 0; ks < KS; ++ks) q_raw[ks] = a.q[(size_t)(bq0 + (WHOLE ? wave : min(wave, heads - 1))) * D + 64 * ks + lane];
   const int my_tile = tile_begin + min(tid, tile_end - tile_begin - 1);
   const uint4 cnt_raw = *(const uint4*)(v.counts + ((qaq_bh(v, b, h) * v.NT + my_tile) * 2) * 4);
   const float vb_raw = v.vbound[qaq_bh(v, b, h) * v.NT + my_tile];
@@ -1585,7 +1591,9 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
       for (int j = 0; j < kHG; ++j) pt[j] = S.logit[j][posv];
       if (a.scores && live) {
 #pragma unroll
-        for (int j = 0; j < kHG; ++j) a.scores[(size_t)(bq0 + j) * a.score_stride + tile * QAQ_TT + tid] = raw[j];
+        for (int j = 0; j < kHG; ++j) {
+          if (WHOLE || j < heads) a.scores[(size_t)(bq0 + j) * a.score_stride + tile * QAQ_TT + tid] = raw[j];
+        }
       }
 #pragma unroll
       for (int j = 0; j < kHG; ++j) {
@@ -1758,7 +1766,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
     if (item < kHG * D) S.logit[item / D][item % D] = c_run[r];
   }
   lds_barrier();
-  {
+  if (WHOLE || g < heads) {
     const float lsum = (S.red[0][g] + S.red[1][g]) + (S.red[2][g] + S.red[3][g]);
     const float bias = (S.red2[0][g] + S.red2[1][g]) + (S.red2[2][g] + S.red2[3][g]);
     float* part = a.partial + ((size_t)(bq0 + g) * a.part_stride + chunk) * (D + 4);
@@ -1896,6 +1904,12 @@ void launch_tile(const QaqAttnArgs& a, int fused_parts, int BQ, size_t lds, hipS
   }
 }
 
+template <int D, int NO2>
+void launch_gqa(const QaqAttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (a.G % kHG == 0) hipExtLaunchKernelGGL((k_attn_gqa<D, NO2, true>), grid, dim3(kThreads), 0, s, e0, e1, 0, a);
+  else hipExtLaunchKernelGGL((k_attn_gqa<D, NO2, false>), grid, dim3(kThreads), 0, s, e0, e1, 0, a);
+}
+
 // Scratch for callers that must not allocate (qaq_decode_attention_static): the partial results
 // of the two-kernel form.  One copy per GPU the library runs on, held until the process ends;
 // host code reaches it only through the address hipGetSymbolAddress returns for the current
@@ -1936,25 +1950,43 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // workgroups per compute unit), so that no second, partly filled round of workgroups trails
   // the first; every part gets floor or ceil of ntile/nparts tiles
   const int n_cu = qaq_compute_units();
-  // grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form
-  const bool gqa = a.G >= kHG && a.G % kHG == 0 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0);
-  const int units = gqa ? BQ / kHG : BQ;
-  const int slots = (gqa ? 3 : 4) * n_cu;
-  const int per_head = slots / units > 0 ? slots / units : 1;
-  a.nparts = ntile < per_head ? ntile : per_head;
   const int least = (ntile + QAQ_MAX_NTC - 1) / QAQ_MAX_NTC;    // a part holds at most QAQ_MAX_NTC tiles
-  if (a.nparts < least) a.nparts = least;
+  auto split = [&](int slots, int units) {
+    const int per_head = slots / units > 0 ? slots / units : 1;
+    a.nparts = ntile < per_head ? ntile : per_head;
+    if (a.nparts < least) a.nparts = least;
+  };
+  split(4 * n_cu, BQ);
   a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
-  a.run = a.nparts > 0 ? ntile / a.nparts : 0;
-  a.shorter = a.nparts - (ntile - a.run * a.nparts);
   // Fused form (no second kernel) when the parts of a head fit one workgroup; their raw logits stay
   // in its LDS next to the parts' working blocks if they fit, else they wait in the score buffer.
   // (its parts run in lockstep and every one needs a tile: where the sequences differ in length, the
   // shortest must have as many tiles as a head has parts)
   const int ntile_shortest = (a.len_shortest + QAQ_TT - 1) / QAQ_TT;
   a.lds_logits = a.nparts * a.ntc <= kFusedMaxTiles || !a.scores;
-  const bool fused = !gqa && ntile > 0 && a.nparts <= 4 && (!a.v.ragged || ntile_shortest >= a.nparts) &&
-                     (a.lds_logits || a.nparts == 4);
+  bool fused = ntile > 0 && a.nparts <= 4 && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
+  // Grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form, or a scan per query
+  // head.  A pass of four takes about as long as 1.3 scans of one head, however many of the four are there, so what is won is
+  // 10 scans less 13 per pass, times the tiles; what it costs is a launch where the scans would need no second kernel, and a
+  // tile's longer way through one workgroup where the cache does not fill the chip.  Per call of three, in us, scans | passes (x: tenths
+  // of a scan won per CU): one kernel -- 1 x 8 x 8 heads per KV head, 1000 tokens 9.0 | 11.2 (x 6), 16 x 8 x 8, 250 9.5 | 11.5 (27),
+  // 16 x 16 x 3, 500 11.8 | 13.5 (34), 8 x 8 x 4, 1500 12.6 | 13.3 (41), 16 x 8 x 5, 1000 18.5 | 17.7 (48), 16 x 8 x 3, 2000 22.3 | 19.7
+  // (68), 16 x 8 x 5, 2000 33.4 | 25.2 (96); two -- 1 x 4 x 4, 2000, 64 channels 11.3 | 11.4 (4), 2 x 4 x 4, 3000 11.1 | 11.4 (10),
+  // 1 x 8 x 5, 5000 12.7 | 12.9 (15), 1 x 8 x 4, 5000 12.1 | 11.3 (17), 2 x 4 x 8, 3000 12.1 | 11.5 (20), 4 x 8 x 3, 4000 17.4 | 13.4 (41),
+  // 16 x 8 x 3, 8192 75 | 51, 16 x 8 x 7, 8192 197 | 84.  Two heads per KV head stay with scans (8 x 8 x 2, 4096 17.4 | 18.2; 16 x 8 x 2,
+  // 8192 43.1 | 41.5).  (Groups that are not full keep to as many parts as the static scratch has room for, as scans always do.)
+  const int units = a.v.B * a.v.Hkv * ((a.G + kHG - 1) / kHG);
+  const int most = (int)(kStaticScratchBytes / ((size_t)BQ * (a.v.D + 4) * sizeof(float)));      // parts whose partial results fit the static scratch
+  const bool gqa = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) &&
+                   (10ll * BQ - 13ll * units) * ntile >= (fused ? 43ll : 16ll) * n_cu && (a.G % kHG == 0 || (most > 0 && most >= least));
+  if (gqa) {
+    fused = false;
+    split(3 * n_cu, units);
+    if (a.G % kHG != 0 && a.nparts > most) a.nparts = most;
+    a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
+  }
+  a.run = a.nparts > 0 ? ntile / a.nparts : 0;
+  a.shorter = a.nparts - (ntile - a.run * a.nparts);
   // Which workgroups share a die (die_neighbours), where several read the same codes: nothing to do if the parts are a
   // multiple of eight (4 x 16 heads on 8, 8192 tokens, 16 parts: 21.7 us with the re-ordering, 21.4 without), and not where
   // a part is one tile and the grid small, the codes too few for it to matter (1 x 28 on 4 x 7000: 16.6 and 16.1; the other
@@ -1973,14 +2005,14 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
     a.part_stride = a.nparts > 0 ? a.nparts : 1;
   }
   if (ntile > 0 && gqa) {
-    const dim3 grid(a.nparts, units), block(kThreads);
+    const dim3 grid(a.nparts, units);
     hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
     if (a.v.D == 128) {
-      if (a.v.no2 == 2) hipExtLaunchKernelGGL((k_attn_gqa<128, 2>), grid, block, 0, s, e0, e1, 0, a);
-      else hipExtLaunchKernelGGL((k_attn_gqa<128, 0>), grid, block, 0, s, e0, e1, 0, a);
+      if (a.v.no2 == 2) launch_gqa<128, 2>(a, grid, s, e0, e1);
+      else launch_gqa<128, 0>(a, grid, s, e0, e1);
     } else {
-      if (a.v.no2 == 2) hipExtLaunchKernelGGL((k_attn_gqa<64, 2>), grid, block, 0, s, e0, e1, 0, a);
-      else hipExtLaunchKernelGGL((k_attn_gqa<64, 0>), grid, block, 0, s, e0, e1, 0, a);
+      if (a.v.no2 == 2) launch_gqa<64, 2>(a, grid, s, e0, e1);
+      else launch_gqa<64, 0>(a, grid, s, e0, e1);
     }
   } else if (ntile > 0) {
     const int fp = fused ? (a.lds_logits ? a.nparts : 5) : 0;

@@ -62,3 +62,62 @@ def test_one_channel_carries_everything(D, G, value):
     want = v[:, :, :1].float().expand(1, Hkv, G, D).reshape(1, Hkv * G, D)
     # every correction is off by at most half a unit of 2^-25 of the bound, the sums by a few roundings of 32 bits
     assert (x - want).abs().max().item() < 4e-6
+
+
+def stored(c, side):
+    """Per sequence its stored tokens in 64 bits (behind the end of a shorter one the export writes nothing: no index there is
+    one).  A code is where the fp16 reconstruction lies (2^-11 of a value at most half a segment, 2^-9 of the range: the
+    token's largest value is below twice its range)."""
+    e, xs = c.export_canonical(side), c.dequantize()[side]
+    out = []
+    for b, m in enumerate(c.lengths()):
+        mn, mx = (t[..., None] for t in e["minmax"][b, :, :m].double().unbind(-1))
+        seg = (mx - mn) * torch.exp2(-e["bits"][b, :, :m].double())[..., None]
+        x = mn + (((xs[b, :, :m].double() - mn) / seg - 0.5).round() + 0.5) * seg
+        out.append(x.scatter_(-1, e["oidx"][b, :, :m].long(), e["oval"][b, :, :m].double()))
+    return out
+
+
+@pytest.mark.parametrize("counts", [       # 3, 2, 4, 8 bits in the last tile
+    (0, 1, 0, 0), (17, 14, 1, 1), (65, 127, 16, 8), (63, 160, 17, 16), (128, 0, 64, 64), (0, 0, 0, 256), (3, 250, 2, 1)])
+@pytest.mark.parametrize("B,Hkv,G,D,n_o,tiles", [
+    (48, 8, 3, 128, 1, 2), (48, 8, 3, 64, 0, 2), (32, 8, 5, 128, 1, 2), (32, 8, 5, 128, 0, 2), (24, 8, 7, 64, 1, 2), (24, 8, 6, 128, 1, 2),
+    (32, 8, 4, 128, 1, 2), (32, 8, 4, 128, 0, 2), (16, 8, 8, 64, 1, 2), (4, 8, 5, 128, 1, 16), (2, 8, 3, 64, 1, 33)])
+def test_groups_that_are_not_full(counts, B, Hkv, G, D, n_o, tiles):
+    """Caches large enough for four heads per pass, the last pass of a group with one, two, three and four heads; the longer ones
+    with sequences too short for every part to have a tile.  Scores: the query's 22 bits leave at most 128 * 2^-23 * 4 * 8 /
+    sqrt(128) in a logit, twice that in a score; 32-bit sums add a few 1e-6."""
+    n = sum(counts)
+    T, Hq = 256 * (tiles - 1) + n, Hkv * G
+    short = [0] * B if tiles == 2 else [(T - 300) * (b % 2) for b in range(B)]
+    print(f"groups: {counts} B={B} Hkv={Hkv} G={G} D={D} n_o={n_o} T={T}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * counts[0] + counts[1] + D + G)
+    k, v = (torch.randn((B, Hkv, T, D), device="cuda", generator=gen).clamp_(-4, 4).half() for _ in range(2))
+    q = torch.randn((B, Hq, D), device="cuda", generator=gen).clamp_(-4, 4).half()
+    c = qaq.Cache(qaq.make_config(B, Hq, Hkv, D, T, [1.0] * Hkv, n_outlier_per_side=n_o))
+    if any(short):
+        c.set_shortfall(short)
+    last = torch.tensor(sum(([w] * m for w, m in zip((3, 2, 4, 8), counts)), []), dtype=torch.uint8, device="cuda")
+    bits = []
+    for _ in range(2):
+        w = torch.tensor((2, 2, 2, 3, 3, 4, 8), dtype=torch.uint8, device="cuda")[torch.randint(7, (B, Hkv, T), device="cuda", generator=gen)]
+        w[:, :, T - n:] = last[torch.rand((B, Hkv, n), device="cuda", generator=gen).argsort(dim=-1)]
+        bits.append(w.contiguous())
+    c.quantize_append(k, v, *bits)
+    c.profile_begin(1)
+    s = torch.zeros((B, Hq, T), device="cuda")
+    x, _ = c.decode_attention(q, scores_out=s)
+    assert c.profile_read()[1][0] > 0.0          # a merge kernel: not the form with one head per scan, which has none at these sizes
+    out = torch.full((B, Hq, D), float("nan"), device="cuda")
+    if G % 4 != 0:                               # (full groups may exceed the static scratch)
+        c.decode_attention_static(q, None, None, out)
+        assert torch.equal(out, x)
+    kd, vd = stored(c, 0), stored(c, 1)
+    for b in range(B):
+        m = T - short[b]
+        p = (torch.matmul(q[b].double().view(Hkv, G, D), kd[b].transpose(-1, -2).contiguous()) * D ** -0.5).softmax(-1)
+        ref = torch.matmul(p, vd[b])
+        got = s[b, :, :m].double().view(Hkv, G, m)
+        assert ((got - p).abs().amax(-1) / p.amax(-1)).max().item() < 2e-4
+        assert ((x[b].double().view(Hkv, G, D) - ref).abs().amax(-1) / ref.abs().amax(-1)).max().item() < 4e-4
