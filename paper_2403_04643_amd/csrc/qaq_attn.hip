@@ -1958,13 +1958,12 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   };
   split(4 * n_cu, BQ);
   // Between one and four thirds of a head per CU that is three parts a head, and a fused workgroup of three leaves no room for
-  // another on its CU: a second, nearly empty round of them.  Up to eight tiles two parts, all in flight at once; beyond, three
-  // in the two-kernel form, which the chip holds at once as well.  Two calls, in us, three fused | two fused | three apart: 10 x 32 heads
-  // x 700 tokens 30.4 | 25.6 | 27.8, 1000 41.7 | 28.4 | 34.8, 2000 62.7 | 50.1 | 50.0, 3200 93.3 | 76.7 | 72.6; 64 channels, 9 x 32 x 600
-  // 26.5 | 22.2 | 24.4, 3500 87.1 | 67.2 | 59.9.  (Two fused parts a head, 342 to 512 heads, are as good or better than two
-  // apart: 12 x 32 x 2700 69.9 and 72.9, 15 x 32 x 2100 52.5 and 59.6.)
+  // another on its CU: a second, nearly empty round of them.  The two-kernel form has all of them in flight at once.  Two
+  // calls, in us, fused | apart: 10 x 32 heads x 700 tokens 30.4 | 27.8, 1000 41.7 | 34.8, 2000 62.7 | 50.0, 3200 93.3 | 72.6;
+  // 64 channels, 9 x 32 x 600 26.5 | 24.4, 3500 87.1 | 59.9.  (Two fused parts are faster still up to eight tiles -- 25.6, 28.4,
+  // 50.1 -- but the error against 64 bits grows with the tiles of a part, 1.75e-6 -> 2.1e-6 at 1000 tokens.  Where two parts
+  // are what the chip holds, 342 to 512 heads, they stay fused: 12 x 32 x 2700 69.9 and 72.9, 15 x 32 x 2100 52.5 and 59.6.)
   const bool second_round = a.nparts == 3 && BQ > n_cu;
-  if (second_round && ntile <= 8) a.nparts = 2;
   a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
   // Fused form (no second kernel) when the parts of a head fit one workgroup; their raw logits stay
   // in its LDS next to the parts' working blocks if they fit, else they wait in the score buffer.
@@ -1972,7 +1971,7 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // shortest must have as many tiles as a head has parts)
   const int ntile_shortest = (a.len_shortest + QAQ_TT - 1) / QAQ_TT;
   a.lds_logits = a.nparts * a.ntc <= kFusedMaxTiles || !a.scores;
-  bool fused = ntile > 0 && a.nparts <= 4 && !(second_round && a.nparts == 3) && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
+  bool fused = ntile > 0 && a.nparts <= 4 && !second_round && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
   // Grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form, or a scan per query
   // head.  A pass of four takes about as long as 1.3 scans of one head, however many of the four are there, so what is won is
   // 10 scans less 13 per pass, times the tiles; what it costs is a launch where the scans would need no second kernel, and a

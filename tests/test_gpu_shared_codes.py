@@ -47,5 +47,5 @@ def test_every_head_and_part_once(B, Hkv, G, D, T, kw):
 @pytest.mark.parametrize("B,Hkv,G,D,T", [
     (9, 29, 1, 64, 513), (10, 32, 1, 128, 700), (31, 11, 1, 64, 1024), (5, 29, 2, 128, 2048), (10, 32, 1, 64, 2049), (19, 17, 1, 128, 2400)])
 def test_a_little_more_heads_than_the_chip_has_units(B, Hkv, G, D, T):
-    """257 to 341 heads: three parts a head would not be in flight at once in one kernel; two of up to eight tiles, three beyond."""
+    """257 to 341 heads: three parts a head are not in flight at once in one kernel, but are in two."""
     test_every_head_and_part_once(B, Hkv, G, D, T, {})
