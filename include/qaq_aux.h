@@ -39,6 +39,19 @@ int qaq_debug_field(int32_t side, int32_t D, int32_t n3, int32_t n2, int32_t n4,
                     uint32_t* region_end);
 uint32_t qaq_debug_tile_capacity(int32_t side, int32_t D);
 
+/* Host-only helper for tests (no device access): how an attention call on a cache of this
+ * configuration goes on a GPU of `compute_units`, with `tokens` cached tokens in the longest
+ * sequence, `shortest` in the shortest and with or without a score buffer. */
+typedef struct {
+  int32_t heads_per_scan;  /* 4: a pass over a KV head's codes serves up to four query heads; 1: one */
+  int32_t kernels;         /* 2: the scan leaves partial results to a merge kernel; 1: it does not; 0: no cached tokens */
+  int32_t parts;           /* parts that a head's tiles are split into */
+  int32_t tiles;           /* tiles of the longest part */
+  uint64_t static_bytes;   /* of the library's device array that qaq_decode_attention_static needs */
+} qaq_attention_route_t;
+int qaq_debug_attention_route(const qaq_config* cfg, int32_t tokens, int32_t shortest, int32_t with_scores,
+                              int32_t compute_units, qaq_attention_route_t* out);
+
 #ifdef __cplusplus
 }
 #endif

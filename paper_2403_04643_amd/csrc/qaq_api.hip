@@ -774,4 +774,28 @@ int qaq_debug_field(int32_t side, int32_t D, int32_t n3, int32_t n2, int32_t n4,
 
 uint32_t qaq_debug_tile_capacity(int32_t side, int32_t D) { return side == 0 ? qaq_k_cap(D) : qaq_v_cap(D); }
 
+int qaq_debug_attention_route(const qaq_config* cfg, int32_t tokens, int32_t shortest, int32_t with_scores,
+                              int32_t compute_units, qaq_attention_route_t* out) {
+  QaqDims d;
+  if (!valid_config(cfg, &d)) return QAQ_ERR_INVALID_ARG;
+  if (!out || tokens < 0 || tokens > d.Tmax || shortest < 0 || shortest > tokens || compute_units < 1) return fail(QAQ_ERR_INVALID_ARG, "bad route query");
+  QaqAttnArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.v.B = d.B; a.v.Hq = d.Hq; a.v.Hkv = d.Hkv; a.v.D = d.D; a.v.NT = d.NT; a.v.no2 = d.no2;
+  a.v.has1 = cfg->bit_set[0] == 1;
+  a.v.csr = d.csr;
+  a.v.ragged = shortest < tokens;
+  a.len = tokens;
+  a.len_shortest = shortest;
+  a.G = d.Hq / d.Hkv;
+  a.scores = with_scores ? (float*)out : nullptr;      // (whether there is one is all that is asked)
+  const QaqAttnRoute r = qaq_route_attention(a, compute_units);
+  out->heads_per_scan = r.grouped ? 4 : 1;
+  out->kernels = tokens > 0 ? (r.fused ? 1 : 2) : 0;
+  out->parts = a.nparts;
+  out->tiles = a.ntc;
+  out->static_bytes = r.static_bytes;
+  return QAQ_OK;
+}
+
 }  // extern "C"

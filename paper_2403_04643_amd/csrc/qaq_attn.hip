@@ -1938,18 +1938,14 @@ hipError_t static_scratch_ptr(void** out) {
 
 size_t qaq_static_scratch_bytes() { return kStaticScratchBytes; }
 
-hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent_t* ev, int* kernels,
-                                bool static_scratch, bool* too_big) {
-  QaqAttnArgs a = a_in;
-  a.partial = a.v.partial;
-  a.part_stride = a.v.NT;
-  if (too_big) *too_big = false;
+// How a call goes: which kernels, into how many parts the tiles of a head are split (into `a`).  Looks at a.v's sizes, a.len,
+// a.len_shortest, a.G and whether there is a score buffer.
+QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   const int ntile = (a.len + QAQ_TT - 1) / QAQ_TT;
   const int BQ = a.v.B * a.v.Hq;
   // parts per (sequence, query head): as many as keep the whole grid resident at once (four
   // workgroups per compute unit), so that no second, partly filled round of workgroups trails
   // the first; every part gets floor or ceil of ntile/nparts tiles
-  const int n_cu = qaq_compute_units();
   const int least = (ntile + QAQ_MAX_NTC - 1) / QAQ_MAX_NTC;    // a part holds at most QAQ_MAX_NTC tiles
   auto split = [&](int slots, int units) {
     const int per_head = slots / units > 0 ? slots / units : 1;
@@ -1971,7 +1967,8 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // shortest must have as many tiles as a head has parts)
   const int ntile_shortest = (a.len_shortest + QAQ_TT - 1) / QAQ_TT;
   a.lds_logits = a.nparts * a.ntc <= kFusedMaxTiles || !a.scores;
-  bool fused = ntile > 0 && a.nparts <= 4 && !second_round && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
+  QaqAttnRoute r;
+  r.fused = ntile > 0 && a.nparts <= 4 && !second_round && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
   // Grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form, or a scan per query
   // head.  A pass of four takes about as long as 1.3 scans of one head, however many of the four are there, so what is won is
   // 10 scans less 13 per pass, times the tiles; what it costs is a launch where the scans would need no second kernel, and a
@@ -1984,10 +1981,10 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // 8192 43.1 | 41.5).  (Groups that are not full keep to as many parts as the static scratch has room for, as scans always do.)
   const int units = a.v.B * a.v.Hkv * ((a.G + kHG - 1) / kHG);
   const int most = (int)(kStaticScratchBytes / ((size_t)BQ * (a.v.D + 4) * sizeof(float)));      // parts whose partial results fit the static scratch
-  const bool gqa = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) &&
-                   (10ll * BQ - 13ll * units) * ntile >= (fused ? 43ll : 16ll) * n_cu && (a.G % kHG == 0 || (most > 0 && most >= least));
-  if (gqa) {
-    fused = false;
+  r.grouped = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) &&
+              (10ll * BQ - 13ll * units) * ntile >= (r.fused ? 43ll : 16ll) * n_cu && (a.G % kHG == 0 || (most > 0 && most >= least));
+  if (r.grouped) {
+    r.fused = false;
     split(3 * n_cu, units);
     if (a.G % kHG != 0 && a.nparts > most) a.nparts = most;
     a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
@@ -1998,10 +1995,23 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
   // multiple of eight (4 x 16 heads on 8, 8192 tokens, 16 parts: 21.7 us with the re-ordering, 21.4 without), and not where
   // a part is one tile and the grid small, the codes too few for it to matter (1 x 28 on 4 x 7000: 16.6 and 16.1; the other
   // way, 5 parts of 16 tiles at 8 x 24 on 4: 32.0 and 34.1; 20 parts of 20 at 4 x 32 on 4 in k_attn_gqa: 21.1 and 21.4).
-  a.neighbours = !fused && a.G > (gqa ? kHG : 1) && (a.nparts & 7) != 0 && (a.ntc > 1 || (gqa && a.nparts * units >= 2 * n_cu));
-  if (kernels) *kernels = ntile > 0 ? (fused ? 1 : 2) : 0;
-  if (static_scratch && !fused) {
-    if ((size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float) > kStaticScratchBytes) {
+  a.neighbours = !r.fused && a.G > (r.grouped ? kHG : 1) && (a.nparts & 7) != 0 && (a.ntc > 1 || (r.grouped && a.nparts * units >= 2 * n_cu));
+  r.static_bytes = r.fused ? 0 : (size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float);
+  return r;
+}
+
+hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent_t* ev, int* kernels,
+                                bool static_scratch, bool* too_big) {
+  QaqAttnArgs a = a_in;
+  a.partial = a.v.partial;
+  a.part_stride = a.v.NT;
+  if (too_big) *too_big = false;
+  const QaqAttnRoute r = qaq_route_attention(a, qaq_compute_units());
+  const int ntile = (a.len + QAQ_TT - 1) / QAQ_TT;
+  const int BQ = a.v.B * a.v.Hq;
+  if (kernels) *kernels = ntile > 0 ? (r.fused ? 1 : 2) : 0;
+  if (static_scratch && r.static_bytes > 0) {
+    if (r.static_bytes > kStaticScratchBytes) {
       if (too_big) *too_big = true;
       return hipSuccess;
     }
@@ -2011,8 +2021,8 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
     a.partial = (float*)p;
     a.part_stride = a.nparts > 0 ? a.nparts : 1;
   }
-  if (ntile > 0 && gqa) {
-    const dim3 grid(a.nparts, units);
+  if (ntile > 0 && r.grouped) {
+    const dim3 grid(a.nparts, a.v.B * a.v.Hkv * ((a.G + kHG - 1) / kHG));
     hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
     if (a.v.D == 128) {
       if (a.v.no2 == 2) launch_gqa<128, 2>(a, grid, s, e0, e1);
@@ -2022,12 +2032,12 @@ hipError_t qaq_launch_attention(const QaqAttnArgs& a_in, hipStream_t s, hipEvent
       else launch_gqa<64, 0>(a, grid, s, e0, e1);
     }
   } else if (ntile > 0) {
-    const int fp = fused ? (a.lds_logits ? a.nparts : 5) : 0;
-    const size_t lds = fused && a.scores && a.lds_logits ? (size_t)a.nparts * a.ntc * QAQ_TT * sizeof(float) : 0;
+    const int fp = r.fused ? (a.lds_logits ? a.nparts : 5) : 0;
+    const size_t lds = r.fused && a.scores && a.lds_logits ? (size_t)a.nparts * a.ntc * QAQ_TT * sizeof(float) : 0;
     if (a.v.D == 128) launch_tile<128>(a, fp, BQ, lds, s, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
     else launch_tile<64>(a, fp, BQ, lds, s, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
   }
-  if (fused) return hipGetLastError();
+  if (r.fused) return hipGetLastError();
   // scores per block: every block repeats the head's merge (partial maxima and sums, the new token's
   // logit) before it normalises its share, so longer shares where there are blocks enough
   const int ept = (long long)BQ * a.len >= 16ll * kThreads * 1024 ? 16 : 4;

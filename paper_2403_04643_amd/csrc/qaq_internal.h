@@ -347,6 +347,12 @@ struct QaqAttnArgs {
   int neighbours;         // two-kernel form: workgroups that read the same codes get indices eight apart (set by the launcher)
 };
 
+struct QaqAttnRoute {
+  bool grouped;           // four query heads of a KV head per scan of its codes (k_attn_gqa)
+  bool fused;             // no merge kernel: the parts of a head are one workgroup
+  size_t static_bytes;    // of the library's device array that the partial results take in a call that must not use the arena
+};
+
 struct QaqPrefillArgs {
   QaqView v;
   int T, n_rows, G;
@@ -387,6 +393,7 @@ hipError_t qaq_launch_select(const QaqSelectArgs& a, hipStream_t s);
 // array instead of the cache's arena; *too_big is set (and nothing launched) if they do not fit it
 hipError_t qaq_launch_attention(const QaqAttnArgs& a, hipStream_t s, hipEvent_t* ev, int* kernels,
                                 bool static_scratch = false, bool* too_big = nullptr);
+QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu);      // also sets nparts, ntc, run, shorter, lds_logits and neighbours
 size_t qaq_static_scratch_bytes();
 hipError_t qaq_launch_prefill_window(const QaqPrefillArgs& a, hipStream_t s);
 hipError_t qaq_launch_export(const QaqExportArgs& a, hipStream_t s);

@@ -40,6 +40,11 @@ class Stats(C.Structure):
     ]
 
 
+class AttentionRoute(C.Structure):
+    _fields_ = [("heads_per_scan", C.c_int32), ("kernels", C.c_int32), ("parts", C.c_int32), ("tiles", C.c_int32),
+                ("static_bytes", C.c_uint64)]
+
+
 # name -> (restype, argtypes); the names are those declared in include/qaq.h
 _vp, _i32, _u8p, _f32p = C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p
 SIGNATURES = {
@@ -74,6 +79,7 @@ SIGNATURES = {
     "qaq_last_error": (C.c_char_p, []),
     "qaq_debug_field": (C.c_int, [_i32] * 10 + [C.POINTER(C.c_uint32), C.POINTER(C.c_int32), C.POINTER(C.c_uint32)]),
     "qaq_debug_tile_capacity": (C.c_uint32, [_i32, _i32]),
+    "qaq_debug_attention_route": (C.c_int, [C.POINTER(Config), _i32, _i32, _i32, _i32, C.POINTER(AttentionRoute)]),
 }
 
 _lib = None
@@ -391,3 +397,10 @@ def debug_field(side, D, counts, bf, idx, d):
     n3, n2, n4, n8, n1 = counts
     _check(lib.qaq_debug_field(side, D, n3, n2, n4, n8, n1, bf, idx, d, C.byref(off), C.byref(sh), C.byref(end)))
     return off.value, sh.value, end.value
+
+
+def attention_route(cfg, tokens, shortest=None, with_scores=True, compute_units=256) -> AttentionRoute:
+    """Host-only query: how an attention call on a cache of this configuration goes."""
+    r = AttentionRoute()
+    _check(load().qaq_debug_attention_route(C.byref(cfg), tokens, tokens if shortest is None else shortest, int(with_scores), compute_units, C.byref(r)))
+    return r

@@ -107,6 +107,29 @@ def test_layout_is_a_bijection(side, D):
             assert pad <= 8 * (15 * D)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_route_covers_every_tile(D):
+    """However a call goes: parts that hold all tiles, none of them more than a workgroup's tables, and no more parts than the
+    cache's arena has places for."""
+    for B, Hkv, G in ((1, 1, 1), (1, 8, 1), (10, 32, 1), (16, 32, 1), (40, 32, 1), (16, 8, 2), (1, 8, 3), (16, 8, 3), (48, 8, 3),
+                      (1, 8, 4), (8, 8, 4), (16, 8, 5), (16, 8, 7), (16, 8, 8), (16, 8, 9), (64, 32, 4)):
+        for n_o, bit_set in ((-1, (2, 3, 4, 8)), (0, (2, 3, 4, 8)), (3, (2, 3, 4, 8)), (-1, (1, 2, 3, 4, 8))):
+            cfg = qaq.make_config(B, Hkv * G, Hkv, D, 65536, [1.0] * Hkv, bit_set=bit_set, n_outlier_per_side=n_o)
+            for T in (1, 256, 257, 700, 1500, 4096, 33000, 65536):
+                for shortest in (T, (T + 1) // 2, 0):
+                    r = qaq.attention_route(cfg, T, shortest)
+                    tiles = (T + 255) // 256
+                    assert 1 <= r.parts <= tiles and r.parts * r.tiles >= tiles and r.parts * (r.tiles - 1) < tiles and r.tiles <= 64
+                    assert r.heads_per_scan == 1 or (G > 2 and n_o < 1 and bit_set[0] == 2)
+                    assert r.kernels == 1 or r.kernels == 2
+                    if r.kernels == 1:      # the parts are one workgroup and every one has a tile, and nothing is left to merge
+                        assert r.heads_per_scan == 1 and r.parts <= 4 and (shortest == T or (shortest + 255) // 256 >= r.parts) and r.static_bytes == 0
+    empty = qaq.attention_route(cfg, 0)
+    assert empty.kernels == 0
+    with pytest.raises(qaq.QaqError):
+        qaq.attention_route(cfg, 65537)
+
+
 # ---- code objects in the built library: the kernels on the decode path keep their working set in registers ----
 
 def _gfx950_code_objects(path):
