@@ -256,18 +256,25 @@ int qaq_decode_attention(qaq_cache* c, const void* dev_q, const void* dev_k_new,
 
 /* For callers that cannot allocate device memory or hand over a workspace at the moment of the
  * call (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * qaq_decode_attention with the same arguments, results and errors, except that where a
- * head's tiles are scanned by more than four workgroups (long contexts with few heads: the
- * scan kernel is then followed by a merge kernel) the partial results (max, sum, output per
- * part, fp32) go to a file-scope device array of the library instead of the cache's arena.
+ * qaq_decode_attention with the same arguments, results and errors, except that the partial
+ * results (max, sum, output per part, fp32) of a scan that a merge kernel follows go to a
+ * file-scope device array of the library instead of the cache's arena where
+ *   - a head's tiles are scanned by more than four workgroups (long contexts with few heads),
+ *   - or by fewer of them and cannot be merged in one: sequences of which the shortest has
+ *     fewer tiles than a head has workgroups; more than 30 tiles a head with scores asked for
+ *     and fewer than four workgroups a head,
+ *   - or Hq / Hkv is a multiple of four and the cache large enough that four query heads share
+ *     a scan.
  * That array has qaq_static_scratch_limit() bytes (1 MiB; every GPU the library runs on
  * holds one copy until the process ends) and needs B*Hq*parts*(D+4)*4 of them.  The library
- * cuts a call into at most four parts per compute unit (1024 on MI355X: 528 KiB at D = 128)
- * unless a part would then hold more than 64 tiles of 256 tokens; QAQ_ERR_CAPACITY, nothing
- * launched, if such a shape needs more than the array has.  The call itself allocates nothing and calls no allocating routine.  All calls on
- * one GPU share the array (nothing in it has to start at zero: every entry a call reads it
- * has written before), so two such calls that overlap on one GPU -- different streams,
- * different caches -- race; order them. */
+ * cuts a call into at most four parts per compute unit (1024 on MI355X: 528 KiB at D = 128),
+ * or three per compute unit where four heads share a scan (768, of four heads each: up to
+ * 1584 KiB), unless a part would then hold more than 64 tiles of 256 tokens; QAQ_ERR_CAPACITY,
+ * nothing launched, if such a shape needs more than the array has.  The call itself allocates
+ * nothing and calls no allocating routine.  All calls on one GPU that use the array share it
+ * (nothing in it has to start at zero: every entry a call reads it has written before), so two
+ * such calls that overlap on one GPU -- different streams, different caches -- race; order
+ * them.  Other calls do not touch it. */
 int qaq_decode_attention_static(qaq_cache* c, const void* dev_q, const void* dev_k_new,
                                 const void* dev_v_new, void* dev_out, int32_t out_is_fp32,
                                 float* dev_scores_out, void* stream);

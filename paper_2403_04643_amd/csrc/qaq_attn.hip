@@ -1967,8 +1967,9 @@ QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   // shortest must have as many tiles as a head has parts)
   const int ntile_shortest = (a.len_shortest + QAQ_TT - 1) / QAQ_TT;
   a.lds_logits = a.nparts * a.ntc <= kFusedMaxTiles || !a.scores;
+  const bool one_workgroup = ntile > 0 && a.nparts <= 4 && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
   QaqAttnRoute r;
-  r.fused = ntile > 0 && a.nparts <= 4 && !second_round && (!a.v.ragged || ntile_shortest >= a.nparts) && (a.lds_logits || a.nparts == 4);
+  r.fused = one_workgroup && !second_round;
   // Grouped queries: four query heads of a KV head per pass (k_attn_gqa), where the cache has that form, or a scan per query
   // head.  A pass of four takes about as long as 1.3 scans of one head, however many of the four are there, so what is won is
   // 10 scans less 13 per pass, times the tiles; what it costs is a launch where the scans would need no second kernel, and a
@@ -1996,7 +1997,10 @@ QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   // a part is one tile and the grid small, the codes too few for it to matter (1 x 28 on 4 x 7000: 16.6 and 16.1; the other
   // way, 5 parts of 16 tiles at 8 x 24 on 4: 32.0 and 34.1; 20 parts of 20 at 4 x 32 on 4 in k_attn_gqa: 21.1 and 21.4).
   a.neighbours = !r.fused && a.G > (r.grouped ? kHG : 1) && (a.nparts & 7) != 0 && (a.ntc > 1 || (r.grouped && a.nparts * units >= 2 * n_cu));
-  r.static_bytes = r.fused ? 0 : (size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float);
+  // Calls on two caches may overlap as long as neither uses the library's array: what a scan per head does in one workgroup
+  // stays off it, in whatever form, and has its partial results in the cache's own arena.  (Passes of full groups have always
+  // been on it.)
+  r.static_bytes = r.fused || (one_workgroup && !(r.grouped && a.G % kHG == 0)) ? 0 : (size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float);
   return r;
 }
 

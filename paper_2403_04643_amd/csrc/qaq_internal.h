@@ -390,7 +390,7 @@ hipError_t qaq_launch_select(const QaqSelectArgs& a, hipStream_t s);
 // ([0], [1]) and of the merge kernel ([2], [3], two-kernel form only); *kernels = dispatches
 // made (0 for an empty cache without timing, 1 fused, 2 tile + merge)
 // static_scratch: the partial results of the two-kernel form go to the library's file-scope device
-// array instead of the cache's arena; *too_big is set (and nothing launched) if they do not fit it
+// array instead of the cache's arena where the route says so; *too_big is set (and nothing launched) if they do not fit it
 hipError_t qaq_launch_attention(const QaqAttnArgs& a, hipStream_t s, hipEvent_t* ev, int* kernels,
                                 bool static_scratch = false, bool* too_big = nullptr);
 QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu);      // also sets nparts, ntc, run, shorter, lds_logits and neighbours

@@ -130,6 +130,26 @@ def test_attention_route_covers_every_tile(D):
         qaq.attention_route(cfg, 65537)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_static_calls_that_keep_off_the_shared_array(D):
+    """Two qaq_decode_attention_static calls on two caches may overlap where neither uses the library's array: all calls whose
+    heads are at most four workgroups each, except where the passes of four query heads fill their four."""
+    seen = set()
+    for B, Hkv, G in ((1, 1, 1), (9, 32, 1), (10, 32, 1), (341, 1, 1), (10, 16, 2), (16, 8, 2), (16, 8, 3), (48, 8, 3), (16, 8, 5), (8, 8, 7),
+                      (16, 8, 7), (16, 8, 9), (14, 8, 11), (40, 32, 1), (1, 8, 5)):
+        for T in (100, 700, 1300, 2000, 4096, 8192):
+            cfg = qaq.make_config(B, Hkv * G, Hkv, D, T, [1.0] * Hkv)
+            tiles = (T + 255) // 256
+            a_head = min(tiles, max(1, 4 * 256 // (B * Hkv * G)))
+            for scores in (False, True):
+                r = qaq.attention_route(cfg, T, with_scores=scores)
+                alone = a_head <= 4 and (a_head == 4 or a_head * -(-tiles // a_head) <= 32 or not scores)      # (raw logits in LDS)
+                assert (r.static_bytes == 0) == alone, (B, Hkv, G, T, scores)
+                assert r.static_bytes <= qaq.load().qaq_static_scratch_limit()
+                seen.add((alone, r.kernels, r.heads_per_scan))
+    assert {(True, 1, 1), (True, 2, 1), (True, 2, 4), (False, 2, 1), (False, 2, 4)} <= seen
+
+
 # ---- code objects in the built library: the kernels on the decode path keep their working set in registers ----
 
 def _gfx950_code_objects(path):

@@ -63,3 +63,26 @@ def test_static_scratch_entry_point_matches_the_arena_one():
     out16 = torch.zeros((small.batch, small.n_q_heads, small.head_dim), dtype=torch.float16, device="cuda")
     gc.decode_attention_static(q, None, None, out16)
     np.testing.assert_array_equal(out16.cpu().numpy(), X16.cpu().numpy())
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,T", [(10, 32, 1, 128, 700), (9, 32, 1, 64, 1500), (16, 8, 3, 128, 2000), (1, 8, 1, 128, 2000), (8, 8, 1, 64, 300)])
+def test_static_calls_of_four_workgroups_a_head_keep_to_their_cache(B, Hkv, G, D, T):
+    """Partial results of heads that at most four workgroups scan are in the cache's own arena (which the call writes nothing
+    else in), so that calls on two caches may overlap; those of more are in the library's array."""
+    import torch
+    print(f"no-alloc entry point: {B} x {Hkv} x {G} heads, {T} tokens of {D}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B + T)
+    cfg = qaq.make_config(B, Hkv * G, Hkv, D, T, [1.0] * Hkv)
+    gc = qaq.Cache(cfg)
+    k, v = (torch.randn((B, Hkv, T, D), device="cuda", generator=gen).half() for _ in range(2))
+    two = torch.full((B, Hkv, T), 2, dtype=torch.uint8, device="cuda")
+    gc.quantize_append(k, v, two, two)
+    q0, q1 = (torch.randn((B, Hkv * G, D), device="cuda", generator=gen).half() for _ in range(2))
+    gc.decode_attention(q0)
+    before = gc.arena.clone()
+    out = torch.zeros((B, Hkv * G, D), device="cuda")
+    gc.decode_attention_static(q1, None, None, out)
+    route = qaq.attention_route(cfg, T, with_scores=False, compute_units=torch.cuda.get_device_properties(0).multi_processor_count)
+    assert torch.equal(before, gc.arena) == (route.kernels == 1 or route.static_bytes > 0)
+    assert torch.equal(out, gc.decode_attention(q1)[0])
