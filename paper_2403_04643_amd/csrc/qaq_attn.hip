@@ -1132,7 +1132,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 // head and raw logits; k_attn_combine merges them.  Width sets without 1, the fixed-length
 // side store with one outlier per end or none; G > 2, in passes of four heads and one of
 // what is left (a KV head with 5 to 8 query heads is scanned twice, by two workgroups that
-// run side by side), where the cache is large enough (the rule and its figures: qaq_launch_attention).
+// run side by side), where the cache is large enough (the rule and its figures: qaq_route_attention).
 //
 // Bound: vector instructions (60 % of the issue slots at three wavefronts per SIMD, the most its registers allow) and, in
 // front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
@@ -1974,20 +1974,25 @@ QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   // head.  A pass of four takes about as long as 1.3 scans of one head, however many of the four are there, so what is won is
   // 10 scans less 13 per pass, times the tiles; what it costs is a launch where the scans would need no second kernel, and a
   // tile's longer way through one workgroup where the cache does not fill the chip.  Per call of three, in us, scans | passes (x: tenths
-  // of a scan won per CU): one kernel -- 1 x 8 x 8 heads per KV head, 1000 tokens 9.0 | 11.2 (x 6), 16 x 8 x 8, 250 9.5 | 11.5 (27),
-  // 16 x 16 x 3, 500 11.8 | 13.5 (34), 8 x 8 x 4, 1500 12.6 | 13.3 (41), 16 x 8 x 5, 1000 18.5 | 17.7 (48), 16 x 8 x 3, 2000 22.3 | 19.7
-  // (68), 16 x 8 x 5, 2000 33.4 | 25.2 (96); two -- 1 x 4 x 4, 2000, 64 channels 11.3 | 11.4 (4), 2 x 4 x 4, 3000 11.1 | 11.4 (10),
-  // 1 x 8 x 5, 5000 12.7 | 12.9 (15), 1 x 8 x 4, 5000 12.1 | 11.3 (17), 2 x 4 x 8, 3000 12.1 | 11.5 (20), 4 x 8 x 3, 4000 17.4 | 13.4 (41),
-  // 16 x 8 x 3, 8192 75 | 51, 16 x 8 x 7, 8192 197 | 84.  Two heads per KV head stay with scans (8 x 8 x 2, 4096 17.4 | 18.2; 16 x 8 x 2,
-  // 8192 43.1 | 41.5).  (Groups that are not full keep to as many parts as the static scratch has room for, as scans always do.)
+  // of a scan won per CU): one kernel -- 16 x 16 x 3 heads per KV head, 500 tokens 11.8 | 13.5 (x 34), 16 x 8 x 5, 1000 18.5 | 17.7 (48),
+  // 16 x 8 x 3, 2000 22.3 | 19.7 (68), 16 x 8 x 5, 2000 33.4 | 25.2 (96); two -- 1 x 4 x 4, 2000, 64 channels 11.3 | 11.4 (4), 2 x 4 x 4,
+  // 3000 11.1 | 11.4 (10), 1 x 8 x 5, 5000 12.7 | 12.9 (15), 1 x 8 x 4, 5000 12.1 | 11.3 (17), 2 x 4 x 8, 3000 12.1 | 11.5 (20), 4 x 8 x 3,
+  // 4000 17.4 | 13.4 (41), 16 x 8 x 3, 8192 75 | 51, 16 x 8 x 7, 8192 197 | 84.  Two heads per KV head stay with scans (8 x 8 x 2, 4096
+  // 17.4 | 18.2; 16 x 8 x 2, 8192 43.1 | 41.5).  (Groups that are not full keep to as many parts as the static scratch has room for.)
+  // Full groups of four go to scans in one kernel only where every part is one tile and all are in flight at once
+  // (1 x 8 x 8, 1000 9.0 | 11.2, 16 x 8 x 8, 250 9.5 | 11.5).  Parts of two tiles, where passes have parts of one, are hardly
+  // faster (8 x 8 x 4, 1500 12.6 | 13.3 without 8-bit tokens, 16.1 | 14.8 with 4 % of them; 12 x 16 x 4, 500 15.4 | 14.6), and their sums carry
+  // more roundings (error against 64 bits 1.7e-6 and 1.9e-6 for 1.3e-6).
   const int units = a.v.B * a.v.Hkv * ((a.G + kHG - 1) / kHG);
   const int most = (int)(kStaticScratchBytes / ((size_t)BQ * (a.v.D + 4) * sizeof(float)));      // parts whose partial results fit the static scratch
-  r.grouped = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) &&
-              (10ll * BQ - 13ll * units) * ntile >= (r.fused ? 43ll : 16ll) * n_cu && (a.G % kHG == 0 || (most > 0 && most >= least));
+  const bool full = a.G % kHG == 0, at_once = a.ntc == 1 && BQ * a.nparts <= 4 * n_cu;
+  const long long won = (10ll * BQ - 13ll * units) * ntile;
+  r.grouped = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) && ntile > 0 &&
+              (r.fused ? (full ? !at_once : won >= 43ll * n_cu) : won >= 16ll * n_cu) && (full || (most > 0 && most >= least));
   if (r.grouped) {
     r.fused = false;
     split(3 * n_cu, units);
-    if (a.G % kHG != 0 && a.nparts > most) a.nparts = most;
+    if (!full && a.nparts > most) a.nparts = most;
     a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
   }
   a.run = a.nparts > 0 ? ntile / a.nparts : 0;
@@ -2000,7 +2005,7 @@ QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   // Calls on two caches may overlap as long as neither uses the library's array: what a scan per head does in one workgroup
   // stays off it, in whatever form, and has its partial results in the cache's own arena.  (Passes of full groups have always
   // been on it.)
-  r.static_bytes = r.fused || (one_workgroup && !(r.grouped && a.G % kHG == 0)) ? 0 : (size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float);
+  r.static_bytes = r.fused || (one_workgroup && !(r.grouped && full)) ? 0 : (size_t)BQ * (size_t)(a.nparts > 0 ? a.nparts : 1) * (a.v.D + 4) * sizeof(float);
   return r;
 }
 

@@ -130,6 +130,24 @@ def test_attention_route_covers_every_tile(D):
         qaq.attention_route(cfg, 65537)
 
 
+@pytest.mark.parametrize("G", [4, 8, 12])
+def test_full_groups_have_parts_as_short_as_in_passes_of_four(G):
+    """The rounding error of an output grows with the tiles of a part, so a call that could go in passes of four query heads --
+    three workgroups per compute unit -- has no longer parts where it goes in a scan per head."""
+    routes = set()
+    for B in list(range(1, 20)) + [24, 32, 48, 64]:
+        for Hkv in (1, 2, 8, 16, 32):
+            cfg = qaq.make_config(B, Hkv * G, Hkv, 128, 16384, [1.0] * Hkv)
+            for T in (1, 250, 256, 257, 500, 700, 1000, 1025, 1500, 2000, 3000, 5000, 16384):
+                tiles = (T + 255) // 256
+                parts = min(tiles, max(1, 3 * 256 // (B * Hkv * G // 4)))
+                for shortest in (T, T // 2 + 1):
+                    r = qaq.attention_route(cfg, T, shortest)
+                    assert r.tiles <= -(-tiles // parts), (B, Hkv, T, shortest)
+                    routes.add((r.heads_per_scan, r.kernels))
+    assert routes == {(1, 1), (1, 2), (4, 2)}
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_static_calls_that_keep_off_the_shared_array(D):
     """Two qaq_decode_attention_static calls on two caches may overlap where neither uses the library's array: all calls whose
