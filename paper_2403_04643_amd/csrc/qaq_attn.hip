@@ -1161,7 +1161,7 @@ struct GqaLds {
   alignas(16) int8_t wl1[QAQ_TT][4 * kHG];     // ... of the 1-bit field region
   alignas(16) int8_t wl4[QAQ_TT][4 * kHG];     // ... of the 4-bit region
   alignas(16) int8_t zero[16][4 * kHG];        // ... of slots that no region has
-  float w8[kHG][QAQ_TT];                       // fp32 weights of the 8-bit slots
+  alignas(16) float w8[kHG][QAQ_TT];           // fp32 weights of the 8-bit slots
   float xw[4][kHG][D / 4];                     // per wavefront: 8-bit-class outputs of its own channels
   alignas(16) int8_t k8[4][1024 / D][D + 16];  // per wavefront: its first 1024 / D 8-bit keys of the tile
   alignas(16) uint32_t v8[4][64];              // per wavefront: 64 / (D/16) rows of 8-bit values, its D/4 channels of each
@@ -1702,38 +1702,51 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
     if (cV.n8 > 0) {
       // 8-bit values: token-major bytes, fp32 multiply-add; this wavefront's D/4 channels.  Rows go
       // through the wavefront's own LDS block, 64 / (D/16) at a time (the first batch came with the
-      // tile, further ones -- rare -- are fetched here), so that a lane can own a channel and sum
+      // tile, further ones -- rare -- are fetched here, three batches ahead of the sums: each waited for, all tokens
+      // at 8 bits took 129 us a call at 16 x 8 x 3 heads x 4096 tokens, where a scan per head takes 102; now 92, and a
+      // quarter of them 55 -> 46), so that a lane can own a channel and sum
       // over the rows by itself: lane (c, half) = channel c of heads 2*half and 2*half + 1.  (No
       // reduction across lanes: a chain of cross-lane exchanges per head cost more than all the
       // arithmetic of this class.)  Needs D/4 <= 32 channels per wavefront, i.e. D <= 128.
       constexpr int LPT8 = D / 16;
-      constexpr int TPW = 64 / LPT8;
+      constexpr int TPW = 64 / LPT8, AHEAD = 3;
       static_assert(D / 4 <= 32, "a wavefront's channels must fit half its lanes");
       const int c8 = lane & 31, h0 = 2 * (lane >> 5);
       const uint8_t* rows = (const uint8_t*)&S.v8[wave][0];
       float acc0 = 0.0f, acc1 = 0.0f;
-      for (int r0 = 0; r0 < cV.n8; r0 += TPW) {
-        uint32_t dw = vr.v8;
-        if (r0 > 0) dw = gload32(baseV, rV.r8 + (uint32_t)min(r0 + lane / LPT8, cV.n8 - 1) * D + (D / 4) * wave + 4 * (lane % LPT8));
-        S.v8[wave][lane] = dw;        // row lane / LPT8, bytes 4 * (lane % LPT8) .. +3: a row is D/4 consecutive bytes
+      // (four rows at a time, their look-ups in flight together; a row that is not there gets weight zero)
+      static_assert(TPW % 4 == 0, "rows of a batch");
+      auto sum8 = [&](int r0, uint32_t words) {
+        S.v8[wave][lane] = words;     // row lane / LPT8, bytes 4 * (lane % LPT8) .. +3: a row is D/4 consecutive bytes
         // (LDS operations of one wavefront complete in order: no barrier between the write and the reads)
-        // four rows at a time, their look-ups in flight together; a row that is not there gets weight zero
-        static_assert(TPW % 4 == 0, "rows of a batch");
 #pragma unroll
         for (int q = 0; q < TPW; q += 4) {
           if (r0 + q >= cV.n8) break;
-          float x[4], u0[4], u1[4];
+          const float4 u0 = *(const float4*)&S.w8[h0][r0 + q], u1 = *(const float4*)&S.w8[h0 + 1][r0 + q];      // (of the tile's 256 in any case)
+          float x[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = (float)rows[(q + r) * (D / 4) + (c8 & (D / 4 - 1))];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int i8 = min(r0 + q + r, QAQ_TT - 1);
-            x[r] = (float)rows[(q + r) * (D / 4) + (c8 & (D / 4 - 1))];
-            u0[r] = S.w8[h0][i8]; u1[r] = S.w8[h0 + 1][i8];
+            const float w0 = r == 0 ? u0.x : r == 1 ? u0.y : r == 2 ? u0.z : u0.w, w1 = r == 0 ? u1.x : r == 1 ? u1.y : r == 2 ? u1.z : u1.w;
+            acc0 += (r0 + q + r < cV.n8 ? w0 : 0.0f) * x[r];
+            acc1 += (r0 + q + r < cV.n8 ? w1 : 0.0f) * x[r];
           }
+        }
+      };
+      sum8(0, vr.v8);
+      if (cV.n8 > TPW) {
+        auto batch8 = [&](int r0) { return gload32(baseV, rV.r8 + (uint32_t)min(r0 + lane / LPT8, cV.n8 - 1) * D + (D / 4) * wave + 4 * (lane % LPT8)); };
+        uint32_t ahead[AHEAD];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            acc0 += (r0 + q + r < cV.n8 ? u0[r] : 0.0f) * x[r];
-            acc1 += (r0 + q + r < cV.n8 ? u1[r] : 0.0f) * x[r];
-          }
+        for (int i = 0; i < AHEAD; ++i) ahead[i] = batch8((1 + i) * TPW);
+#pragma unroll 1
+        for (int r0 = TPW; r0 < cV.n8; r0 += TPW) {
+          const uint32_t words = ahead[0];
+#pragma unroll
+          for (int i = 0; i + 1 < AHEAD; ++i) ahead[i] = ahead[i + 1];
+          ahead[AHEAD - 1] = batch8(r0 + AHEAD * TPW);
+          sum8(r0, words);
         }
       }
       if (c8 < D / 4) { S.xw[wave][h0][c8] = acc0; S.xw[wave][h0 + 1][c8] = acc1; }
