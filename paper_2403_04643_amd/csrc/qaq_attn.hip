@@ -1990,23 +1990,38 @@ QaqAttnRoute qaq_route_attention(QaqAttnArgs& a, int n_cu) {
   // of a scan won per CU): one kernel -- 16 x 16 x 3 heads per KV head, 500 tokens 11.8 | 13.5 (x 34), 16 x 8 x 5, 1000 18.5 | 17.7 (48),
   // 16 x 8 x 3, 2000 22.3 | 19.7 (68), 16 x 8 x 5, 2000 33.4 | 25.2 (96); two -- 1 x 4 x 4, 2000, 64 channels 11.3 | 11.4 (4), 2 x 4 x 4,
   // 3000 11.1 | 11.4 (10), 1 x 8 x 5, 5000 12.7 | 12.9 (15), 1 x 8 x 4, 5000 12.1 | 11.3 (17), 2 x 4 x 8, 3000 12.1 | 11.5 (20), 4 x 8 x 3,
-  // 4000 17.4 | 13.4 (41), 16 x 8 x 3, 8192 75 | 51, 16 x 8 x 7, 8192 197 | 84.  Two heads per KV head stay with scans (8 x 8 x 2, 4096
-  // 17.4 | 18.2; 16 x 8 x 2, 8192 43.1 | 41.5).  (Groups that are not full keep to as many parts as the static scratch has room for.)
+  // 4000 17.4 | 13.4 (41).  Two heads per KV head stay with scans (8 x 8 x 2, 4096 17.4 | 18.2; 16 x 8 x 2, 8192 43.1 | 41.5).
+  // Large calls go in rounds -- tiles of a part, times how often the parts fill the chip -- and a round of passes takes 1.4 of scans:
+  // against one kernel of scans passes also have to be that much fewer (rounds of scans, passes): 3, 2 -- 24 x 8 x 5, 600 17.9 | 19.6,
+  // 23 x 4 x 11, 627 23.2 | 20.9, with widths of 2 and 3 bits only up to 1.16 times the scans' time; 2, 2 1.1 and 1.2 times; 4, 4 1.07; on
+  // the other side 3, 1 -- 32 x 8 x 3, 700 20.2 | 16 (0.74 to 0.93 times), 4, 2 -- 14 x 8 x 9, 979 28.2 | 22.9 (0.77 to 1.0), 6, 4 --
+  // 19 x 32 x 5, 356 40.6 | 33.2 (0.79 to 0.89).
   // Full groups of four go to scans in one kernel only where every part is one tile and all are in flight at once
   // (1 x 8 x 8, 1000 9.0 | 11.2, 16 x 8 x 8, 250 9.5 | 11.5).  Parts of two tiles, where passes have parts of one, are hardly
   // faster (8 x 8 x 4, 1500 12.6 | 13.3 without 8-bit tokens, 16.1 | 14.8 with 4 % of them; 12 x 16 x 4, 500 15.4 | 14.6), and their sums carry
   // more roundings (error against 64 bits 1.7e-6 and 1.9e-6 for 1.3e-6).
+  // Groups that are not full have as many parts as the chip holds where the partial results are in the cache's arena in any case
+  // (kept to what the static scratch holds, 14 x 8 x 9, 979 took 30.1 us, 24 x 4 x 7, 1785 31.3 and now 24.1, 22 x 16 x 3, 1030 36.7 and 29.5),
+  // as even as they come (47 x 1 x 11, 1286, six tiles in four parts 25.7 us, in three 23.2); on the array, as many as it has room for.
   const int units = a.v.B * a.v.Hkv * ((a.G + kHG - 1) / kHG);
   const int most = (int)(kStaticScratchBytes / ((size_t)BQ * (a.v.D + 4) * sizeof(float)));      // parts whose partial results fit the static scratch
-  const bool full = a.G % kHG == 0, at_once = a.ntc == 1 && BQ * a.nparts <= 4 * n_cu;
-  const long long won = (10ll * BQ - 13ll * units) * ntile;
-  r.grouped = a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) && ntile > 0 &&
-              (r.fused ? (full ? !at_once : won >= 43ll * n_cu) : won >= 16ll * n_cu) && (full || (most > 0 && most >= least));
-  if (r.grouped) {
-    r.fused = false;
+  const bool full = a.G % kHG == 0, on_array = full || !one_workgroup;
+  r.grouped = false;
+  if (a.G > 2 && !a.v.has1 && !a.v.csr && (a.v.no2 == 2 || a.v.no2 == 0) && ntile > 0 && (full || !on_array || most >= least)) {
+    const QaqAttnRoute scans = r;
+    const int scan_parts = a.nparts, scan_tiles = a.ntc;
     split(3 * n_cu, units);
-    if (!full && a.nparts > most) a.nparts = most;
-    a.ntc = a.nparts > 0 ? (ntile + a.nparts - 1) / a.nparts : 0;
+    if (!full && a.nparts > most) {
+      const int longest = (ntile + a.nparts - 1) / a.nparts, even = (ntile + longest - 1) / longest;
+      a.nparts = on_array || even < most ? most : even;
+    }
+    a.ntc = (ntile + a.nparts - 1) / a.nparts;
+    auto rounds = [](int tiles, int groups, int places) { return tiles * ((groups + places - 1) / places); };
+    const int scan_rounds = rounds(scan_tiles, BQ * scan_parts, 4 * n_cu), pass_rounds = rounds(a.ntc, units * a.nparts, 3 * n_cu);
+    const long long won = (10ll * BQ - 13ll * units) * ntile;
+    r.grouped = !scans.fused ? won >= 16ll * n_cu : full ? scan_rounds > 1 : won >= 43ll * n_cu && 10 * scan_rounds > 14 * pass_rounds + 2;
+    if (r.grouped) r.fused = false;
+    else { a.nparts = scan_parts; a.ntc = scan_tiles; }
   }
   a.run = a.nparts > 0 ? ntile / a.nparts : 0;
   a.shorter = a.nparts - (ntile - a.run * a.nparts);

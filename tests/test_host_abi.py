@@ -148,6 +148,16 @@ def test_full_groups_have_parts_as_short_as_in_passes_of_four(G):
     assert routes == {(1, 1), (1, 2), (4, 2)}
 
 
+@pytest.mark.parametrize("B,Hkv,G,T,passes,parts", [
+    (24, 8, 5, 600, False, 1), (12, 8, 5, 616, False, 2), (16, 16, 3, 500, False, 1),       # where a scan per head is faster
+    (32, 8, 3, 700, True, 3), (14, 8, 9, 979, True, 2), (24, 4, 7, 1785, True, 4), (22, 16, 3, 1030, True, 2), (16, 8, 7, 8192, True, 3),
+    (16, 8, 3, 8192, True, 6), (21, 8, 3, 1476, False, 2), (47, 1, 11, 1286, True, 3), (19, 32, 5, 356, True, 1), (4, 8, 5, 7032, True, 12)])
+def test_groups_that_are_not_full_have_the_parts_the_chip_holds(B, Hkv, G, T, passes, parts):
+    """... and go in passes of four only where those are the faster ones."""
+    r = qaq.attention_route(qaq.make_config(B, Hkv * G, Hkv, 128, T, [1.0] * Hkv), T)
+    assert (r.heads_per_scan == 4, r.parts) == (passes, parts)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_static_calls_that_keep_off_the_shared_array(D):
     """Two qaq_decode_attention_static calls on two caches may overlap where neither uses the library's array: all calls whose
