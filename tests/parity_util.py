@@ -72,3 +72,10 @@ def attention_errors(X_gpu, S_gpu, X_ref, S_ref):
     if S_gpu is not None:
         es = np.abs(S_gpu.astype(np.float64) - S_ref).max(-1) / S_ref.max(-1)
     return ex, es
+
+
+def attention_route(gc, with_scores=True):
+    """How an attention call on this cache goes on this GPU (heads_per_scan 4: passes of four query heads)."""
+    import torch
+    lens = gc.lengths()
+    return qaq.attention_route(gc.cfg, max(lens), min(lens), with_scores, torch.cuda.get_device_properties(0).multi_processor_count)

@@ -201,8 +201,8 @@ def test_full_size_prompt_encoding():
 
 @pytest.mark.parametrize("batch,parts", [(16, 2), (10, 3)])
 def test_attention_with_two_and_three_parts_per_head(batch, parts):
-    """Head counts at which a head's tiles are split into two resp. three parts that share a
-    workgroup (512 resp. 320 query heads, five tiles each): sampled units against the oracle."""
+    """Head counts at which a head's tiles are split into two parts that share a workgroup resp. three
+    with a workgroup each (512 resp. 320 query heads, five tiles each): sampled units against the oracle."""
     sh = W.shape(3, batch=batch, n_q_heads=32, n_kv_heads=32, head_dim=64, context=1100)
     _log(f"parts per head {parts}: {sh}")
     K, V = W.make_kv(3, sh)

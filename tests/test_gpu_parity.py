@@ -7,7 +7,7 @@ import pytest
 
 from oracle import qaq_oracle as O
 from paper_2403_04643_amd import workloads as W
-from tests.parity_util import F16, F32, attention_errors, compare_canonical, dev, make_pair
+from tests.parity_util import F16, F32, attention_errors, attention_route, compare_canonical, dev, make_pair
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
@@ -239,15 +239,18 @@ def test_decode_attention_matches_oracle(cfgno, shape_kw, p_bits):
 
 
 @pytest.mark.parametrize("shape_kw,p_bits,kw", [
-    (dict(batch=2, n_q_heads=8, n_kv_heads=2, head_dim=64, context=700), (0.4, 0.3, 0.2, 0.1), dict()),          # G = 4, D = 64
-    (dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=128, context=1500), (0.5, 0.45, 0.04, 0.01), dict()),    # G = 8: two passes per KV head
+    (dict(batch=4, n_q_heads=32, n_kv_heads=8, head_dim=128, context=1300), (0.4, 0.3, 0.2, 0.1), dict()),       # passes of four, G = 4
+    (dict(batch=2, n_q_heads=64, n_kv_heads=8, head_dim=64, context=1290), (0.5, 0.45, 0.04, 0.01), dict()),     # ... G = 8: two of them per KV head
+    (dict(batch=4, n_q_heads=24, n_kv_heads=8, head_dim=128, context=1900), (0.3, 0.3, 0.2, 0.2), dict(n_outlier_per_side=0)),     # ... of three
+    (dict(batch=2, n_q_heads=8, n_kv_heads=2, head_dim=64, context=700), (0.4, 0.3, 0.2, 0.1), dict()),          # scans: G = 4, D = 64
+    (dict(batch=1, n_q_heads=16, n_kv_heads=2, head_dim=128, context=1500), (0.5, 0.45, 0.04, 0.01), dict()),    # G = 8
     (dict(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=128, context=520), (0.3, 0.3, 0.2, 0.2), dict(n_outlier_per_side=0)),
     (dict(batch=1, n_q_heads=12, n_kv_heads=1, head_dim=128, context=300), (0.0, 0.0, 0.0, 1.0), dict()),        # G = 12, every token at 8 bits
     (dict(batch=3, n_q_heads=4, n_kv_heads=1, head_dim=64, context=17), (0.0, 0.0, 1.0, 0.0), dict()),
 ])
 def test_grouped_query_attention_matches_oracle(shape_kw, p_bits, kw):
-    """Query heads that share a KV head, four at a time in one pass over its codes: outputs and
-    scores of every query head against the oracle, with and without the new token, and the
+    """Query heads that share a KV head, four at a time in one pass over its codes (the larger
+    shapes) or with a scan for each: outputs and scores of every query head against the oracle, with and without the new token, and the
     same call twice (the sums over outlier corrections are order-independent)."""
     sh = W.shape(5, **shape_kw)
     _log(f"grouped queries shape={sh} p={p_bits} {kw}")
@@ -256,6 +259,7 @@ def test_grouped_query_attention_matches_oracle(shape_kw, p_bits, kw):
     bk, bv = _rand_bits(rng, K.shape[:3], p_bits), _rand_bits(rng, K.shape[:3], p_bits)
     oc, gc = make_pair(sh, 0.01, **kw)
     oc.append(K, V, bk, bv); gc.quantize_append(dev(K), dev(V), dev(bk), dev(bv))
+    assert attention_route(gc).heads_per_scan == (4 if sh.n_kv_heads == 8 else 1)
     qs = W.make_queries(5, sh, n=2)
     qs[1] = (qs[1].astype(F32) * 6.0).astype(F16)          # sharper scores for the second call
     kn, vn = W.make_new_token(5, sh)

@@ -10,7 +10,7 @@ import pytest
 from oracle import qaq_oracle as O
 from paper_2403_04643_amd import qaq
 from paper_2403_04643_amd import workloads as W
-from tests.parity_util import F16, F32, attention_errors, dev, make_oracle, make_pair
+from tests.parity_util import F16, F32, attention_errors, attention_route, dev, make_oracle, make_pair
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
@@ -68,12 +68,13 @@ def compare_all(ocs, gc, what):
 
 
 @pytest.mark.parametrize("n_q_heads,n_kv_heads,lens", [(8, 4, [766, 300, 511]), (8, 2, [766, 300, 511]),
-                                                        (8, 4, [1000, 780, 1021])])
+                                                        (8, 4, [1000, 780, 1021]), (36, 9, [1534, 700, 1279])])
 def test_decode_steps_with_sequences_of_different_lengths(n_q_heads, n_kv_heads, lens):
     """Append prompts of different lengths (padded to the longest), then decode steps that take
-    sequences across a tile border at different steps; the grouped-query attention kernel serves the
-    second shape; in the third every sequence has as many tiles as a head has parts, so the
-    attention call is one kernel until the longest sequence grows a fifth tile.  Attention output
+    sequences across a tile border at different steps; the second shape has several query heads per
+    KV head and the last is large enough for passes of four; in the third every sequence has as many
+    tiles as a head has parts, so the attention call is one kernel until the longest sequence grows a
+    fifth tile.  Attention output
     and scores, the selected widths and the cache contents of every sequence against its own
     oracle cache, at every step."""
     import torch
@@ -92,6 +93,7 @@ def test_decode_steps_with_sequences_of_different_lengths(n_q_heads, n_kv_heads,
         n = lens[b]
         oc.append(K[b:b + 1, :, :n], V[b:b + 1, :, :n], bk0[b:b + 1, :, :n], bv0[b:b + 1, :, :n])
     assert gc.length() == Tmax and gc.lengths() == lens
+    assert attention_route(gc).heads_per_scan == (4 if n_kv_heads == 9 else 1)
     compare_all(ocs, gc, "after the first append")
     _log("first append matches")
 

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from paper_2403_04643_amd import qaq, workloads as W
-from tests.parity_util import F32, dev
+from tests.parity_util import F32, attention_route, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -41,9 +41,11 @@ def test_static_scratch_entry_point_matches_the_arena_one():
     big = W.shape(3, batch=1, n_q_heads=8, n_kv_heads=4, head_dim=128, context=5000)     # 20 tiles, 20 parts per head
     small = W.shape(3, batch=1, n_q_heads=4, n_kv_heads=4, head_dim=64, context=1700)    # 7 tiles, 7 parts per head
     # grouped queries: four query heads per pass over a KV head's codes, also a form with partial results
-    grouped = W.shape(3, batch=2, n_q_heads=8, n_kv_heads=2, head_dim=128, context=1300)
+    grouped = W.shape(3, batch=4, n_q_heads=32, n_kv_heads=8, head_dim=128, context=1300)
     shapes = (big, small, grouped)
     cases = [_cache(big, 1), _cache(small, 2), _cache(grouped, 3)]
+    routes = [attention_route(c[0]) for c in cases]
+    assert [r.heads_per_scan for r in routes] == [1, 1, 4] and all(r.static_bytes > 0 for r in routes)
     ref = []
     for (gc, q, kn, vn), sh in zip(cases, shapes):
         X, S = gc.decode_attention(q, kn, vn, want_scores=True)
@@ -83,6 +85,6 @@ def test_static_calls_of_four_workgroups_a_head_keep_to_their_cache(B, Hkv, G, D
     before = gc.arena.clone()
     out = torch.zeros((B, Hkv * G, D), device="cuda")
     gc.decode_attention_static(q1, None, None, out)
-    route = qaq.attention_route(cfg, T, with_scores=False, compute_units=torch.cuda.get_device_properties(0).multi_processor_count)
+    route = attention_route(gc, with_scores=False)
     assert torch.equal(before, gc.arena) == (route.kernels == 1 or route.static_bytes > 0)
     assert torch.equal(out, gc.decode_attention(q1)[0])
