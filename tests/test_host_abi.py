@@ -107,6 +107,18 @@ def test_layout_is_a_bijection(side, D):
             assert pad <= 8 * (15 * D)
 
 
+def test_stream_lookup_keeps_torchs_checks(monkeypatch):
+    """The current stream's handle is asked for past the object around it, but not past what torch refuses (a process forked
+    after the GPU's first use), and by the public way where the private one is not there."""
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    with pytest.raises(RuntimeError, match="fork"):
+        qaq._stream()
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
+    assert qaq._stream() == 7
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_attention_route_covers_every_tile(D):
     """However a call goes: parts that hold all tiles, none of them more than a workgroup's tables, and no more parts than the
