@@ -5,10 +5,11 @@
 // into parts of consecutive tiles; a part is 256 threads that compute logits, a softmax with
 // a running max and sum over their tiles and the unnormalised output, with the next tile's
 // loads in flight while the current tile is computed.  Where a head has at most four parts
-// they are the 256-thread groups of one workgroup, which merges them in LDS, adds the
-// unquantized new token and writes output and normalised scores itself (one kernel per
-// call).  Otherwise every part is a workgroup of its own, writes a partial (max, sum, X), and
-// k_attn_combine merges the parts, adds the new token and normalises the scores.
+// they are, with few exceptions (qaq_route_attention), the 256-thread groups of one workgroup,
+// which merges them in LDS, adds the unquantized new token and writes output and normalised
+// scores itself (one kernel per call).  Otherwise every part is a workgroup of its own, writes a
+// partial (max, sum, X), and k_attn_combine merges the parts, adds the new token and normalises
+// the scores.
 //
 // Arithmetic.  With per-token scale_t = range_t / 2^B and codes c_td,
 //   q.K^_t  = min_t * sum(q) + scale_t * (sum_d q_d c_td + sum(q)/2) + outlier terms
@@ -1134,8 +1135,8 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
 // what is left (a KV head with 5 to 8 query heads is scanned twice, by two workgroups that
 // run side by side), where the cache is large enough (the rule and its figures: qaq_route_attention).
 //
-// Bound: vector instructions (60 % of the issue slots at three wavefronts per SIMD, the most its registers allow) and, in
-// front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
+// Bound: vector instructions (64 % of the issue slots at three wavefronts per SIMD, the most its registers allow; 6950 per
+// wavefront, 650 a tile) and, in front of the two barriers of a tile, the slowest wavefront.  Two layers at 16 x 64 heads on 8, 8192 tokens: 177 us with one
 // group of keys and one head's weights after the other, behind branches; 166 in straight sequences for all four, with what a
 // weight has in common for the heads computed once; 161 with every fourth group of slots per wavefront and the weight digits
 // through the transposing LDS read; 157 with the first tile on its way before its class counts are there; 155.7 with the rest of
@@ -1356,7 +1357,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
   const int8_t* abase0 = &S.ql[0][arow_h][arow_d][16 * g * KS];
   const int8_t* abase1 = abase0 + sizeof(S.ql[0]);
   const int8_t* abase2 = abase0 + 2 * sizeof(S.ql[0]);
-  const int8_t* wb2 = &S.wl2[16 * g][8 * nn];        // (eight slots' rows are 128 consecutive bytes, eight of them per lane: see lds_transposed)
+  const int8_t* wb2 = &S.wl2[16 * g][8 * nn];        // (eight slots' rows are 128 consecutive bytes, eight of them per lane: see weight_operand)
   const int8_t* wb1 = &S.wl1[16 * g][8 * nn];
   const int8_t* wb4 = &S.wl4[16 * g][8 * nn];
   auto real_of = [&](const v4i& c) { return (((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) * qscale_g; };
@@ -1484,7 +1485,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
             const int i8 = min(max(s - first8K, 0), max(cK.n8 - 1, 0));
             gload_dwords<4 * KS>(baseK + (rK.r8 + (uint32_t)i8 * D + (uint32_t)g * (16u * KS)), w8r);
           }
-            v4i c = zero4;
+          v4i c = zero4;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) c = mma(q[ks], spread<8>(&w8r[4 * ks], 0), c);
           if (s >= first8K) dotq[tg] = ((((float)c[2] * 65536.0f + (float)c[1] * 256.0f) + (float)c[0]) + 128.0f * (float)S.sq[g]) * qscale_g;
@@ -1625,7 +1626,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_attn_gqa(QaqAttnArgs a) {
       }
     }
     lds_barrier();
-    // outlier corrections of this tile: (head, channel) pairs sum their copies and clear them
     // ---- values: integer contractions, rows = 4 heads x 4 weight digits ----------------------------------
     // (all weights of the 2-bit fields and the first block of the low planes are asked for together; the digits of slots
     // past a region are zero, and a block of low planes that is not there reads a row of zeros)

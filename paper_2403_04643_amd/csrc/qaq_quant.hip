@@ -224,8 +224,8 @@ __device__ __forceinline__ float key16_value(uint32_t key) {
 // code = clamp(floor((x-min)*2^B/range)), always at eight bits: a narrower code is its upper bits.
 //
 // Bound by vector instructions: a bulk build spends four fifths of its on the search and the codes.  So the search works
-// on pairs of fp16 values and looks for the channels afterwards (228 instructions for a quad's lane with 32 elements; 282 on
-// integer keys, 395 with the channel in the low bits of 32-bit keys), and a code takes three instructions, not six.  Figures:
+// on pairs of fp16 values and looks for the channels afterwards (193 instructions for a quad's lane with 32 elements; 228 with a
+// sweep over all words for each channel, 282 on integer keys, 395 with the channel in the low bits of 32-bit keys), and a code takes three instructions, not six.  Figures:
 // see fresh_tile.
 // ---------------------------------------------------------------------------------
 template <int D, bool ONE>   // ONE: exactly one outlier per end (the common case) has its own, shorter search
@@ -1343,7 +1343,7 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 // 580 scalar instructions per wavefront for masks class by class; as compares per lane and one list of free slots: 33.4 -> 30.
 // Vector and scalar instructions fill two thirds of the issue slots each.  With indices in 32 bits, the window's rows without
 // a look at their ends where all cover the tile, one load of scores where a KV head has one query head and class counts in pairs a
-// wavefront has 15 % fewer scalar ones, compute units are busy 5 % less, and 24 steps of a small model take 436 instead of 453 us.
+// wavefront has 15 % fewer scalar ones (517 -> 438), compute units are busy 7 % less, and 24 steps of a small model take 436 instead of 453 us.
 // ---------------------------------------------------------------------------------
 constexpr int kMaxCopy = 8192;
 constexpr int kUpdThreads = 128;

@@ -284,7 +284,7 @@ def test_decode_path_kernels_do_not_spill():
     ("k_buildILi128ELb0E", 168, 0),
     ("k_buildILi64ELb1E", 72, 0),
     ("k_buildILi64ELb0E", 128, 0),
-    ("k_attn_gqaILi128ELi2E", 168, 8),        # three workgroups per compute unit; two words, none of them inside the tile loop
+    ("k_attn_gqaILi128ELi2E", 168, 0),        # three workgroups per compute unit
     ("k_attn_gqaILi128ELi0E", 168, 0),
     ("k_attn_gqaILi64E", 168, 0),
     ("k_dequantILi128ELi2E", 64, 0),          # eight wavefronts per SIMD
