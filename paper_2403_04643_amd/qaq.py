@@ -150,13 +150,13 @@ def _ptr(t) -> Optional[int]:
 
 def _stream() -> int:
     # (the raw handle of torch.cuda.current_stream(): the object around it takes 2.6 us to make, a quarter of what a call
-    # costs the host -- 24 steps of a small model waited for it.  torch.cuda.current_device() has torch's checks: a GPU, no fork
-    # since it was first used.)
+    # costs the host -- 24 steps of a small model waited for it.  Asking for the device has torch's checks: a GPU, no fork since
+    # it was first used.)
     import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
         return torch.cuda.current_stream().cuda_stream
-    return raw(torch.cuda.current_device())
 
 
 class HostBuffer:
