@@ -29,6 +29,7 @@
 // most one shift of the dword.
 #include "qaq_internal.h"
 #include <hip/hip_ext.h>
+#include <type_traits>
 
 namespace {
 
@@ -92,6 +93,17 @@ __device__ __forceinline__ void gload_dwords(gbytes_t p, uint32_t (&w)[N]) {
       w[4 * i] = t.x; w[4 * i + 1] = t.y; w[4 * i + 2] = t.z; w[4 * i + 3] = t.w;
     }
   }
+}
+
+__device__ __forceinline__ uint16_t gload16(gbytes_t base, uint32_t off) { return *(const __attribute__((address_space(1))) uint16_t*)(base + off); }
+__device__ __forceinline__ uint8_t gload8(gbytes_t base, uint32_t off) { return *(const __attribute__((address_space(1))) uint8_t*)(base + off); }
+// ... from any byte
+template <int N>
+__device__ __forceinline__ void gload_unaligned(gbytes_t p, uint32_t (&w)[N]) {
+  typedef uint32_t words __attribute__((ext_vector_type(N), aligned(1)));
+  const words t = *(const __attribute__((address_space(1))) words*)p;
+#pragma unroll
+  for (int i = 0; i < N; ++i) w[i] = t[i];
 }
 
 // Workgroup barrier that orders LDS traffic only.  All communication between the threads
@@ -235,12 +247,14 @@ __device__ __forceinline__ v4i k_contract(const uint32_t (&w)[KRec<D, BF>::RDW],
   return c0 + c1;
 }
 
-// Outlier side store of one slot: NO2 entries known at compile time (0 or 2), or up to 8
-// with a run-time count.  Loads only move raw words; unpacking happens where the values
+// Outlier side store of one slot: NO2 entries known at compile time (0 or 2), up to 8 with a run-time
+// count, or (kRuns) up to 8 of the variable-length store.  Loads only move raw words; unpacking happens where the values
 // are used, so that a load issued ahead of time is not waited for at its issue point.
+constexpr int kRuns = 16;
 template <int NO2>
 struct Outl {
-  static constexpr int CAP = NO2 ? NO2 : 1;
+  static constexpr bool RUNS = NO2 == kRuns;
+  static constexpr int CAP = RUNS ? QAQ_MAX_NO2 : NO2 ? NO2 : 1;
   static constexpr int NI = (CAP + 3) / 4, NV = (CAP + 1) / 2;
   uint32_t i2, v2;            // NO2 == 2: word holding the two channel bytes, two fp16 values
   int nmax = CAP;             // NO2 > 2: places any lane of the wavefront uses (uniform)
@@ -262,8 +276,7 @@ struct Outl {
       // to be done to the loaded register until it is used
       i2 = gload32(uniform_ptr(v.oidx[side] + gi0 * 2), (2u * slot) & ~3u);
       v2 = gload32(uniform_ptr(v.oval[side] + gi0 * 2), 4u * slot);
-    } else if constexpr (NO2 > 2) {
-      if (v.csr) return;              // variable-length side store: fetched when the position is known (load_csr)
+    } else if constexpr (NO2 > 2 && !RUNS) {      // (runs: fetched when the position is known)
       const size_t gi = gi0 + slot;
       clear();
       if (no2 == 8) {                 // a row is two aligned words of channels and four of values
@@ -283,20 +296,33 @@ struct Outl {
     }
   }
   // Variable-length side store (outliers by thresholds): the tile's pool is in position order;
-  // `pos` = the token's position inside the tile.  Unused places keep channel 255.
-  __device__ __forceinline__ void load_csr(const QaqView& v, int side, size_t gi0, uint32_t pos, int no2) {
-    if constexpr (NO2 > 2) {
-      const int cnt = v.ocnt[side][gi0 + pos], st = v.ostart[side][gi0 + pos];
+  // `pos` = the token's position inside the tile.  In two steps, each one trip to memory: where the run is, then the eight places
+  // from there on, whether they are the token's or not (the last tile's reach into what follows the pool in the arena); places past
+  // its own get channel 255.  Place by place behind a test whether any lane
+  // has one, after the contractions and in one kernel form with the fixed counts, a call at 8 x 32 heads x 4096 tokens took 56.7 us, now
+  // 40.7 (43.9 in one form with the fixed counts, whose calls with two per end took 38 us there, 37.2 on their own); 16 x 64 heads on 8 x
+  // 2000 63.4 and 50.5, 3 x 16 x 2500 15.0 and 13.3.
+  __device__ __forceinline__ static uint32_t run_of(const QaqView& v, int side, size_t gi0, uint32_t pos) {
+    if constexpr (RUNS) return (uint32_t)gload16(uniform_ptr(v.ostart[side] + gi0), 2u * pos) | ((uint32_t)gload8(uniform_ptr(v.ocnt[side] + gi0), pos) << 16);
+    else return 0u;
+  }
+  __device__ __forceinline__ void load_run(const QaqView& v, int side, size_t gi0, uint32_t run, int no2) {
+    if constexpr (RUNS) {
+      static_assert(NI == 2 && NV == 4, "eight places");
+      const uint32_t st = run & 0xffffu;
+      nmax = (int)(run >> 16);              // (the lane's own count until it is used)
+      gload_unaligned<2>(uniform_ptr(v.oidx[side] + gi0 * no2) + st, ip);
+      gload_unaligned<4>(uniform_ptr(v.oval[side] + gi0 * no2) + 2u * st, vp);
+    }
+  }
+  __device__ __forceinline__ void settle_run() {
+    if constexpr (RUNS) {
+      const int cnt = nmax;
+      ip[0] |= cnt < 4 ? 0xffffffffu << (8 * max(cnt, 0)) : 0u;
+      ip[1] |= cnt < 8 ? 0xffffffffu << (8 * max(cnt - 4, 0)) : 0u;
       nmax = 0;
-      clear();
 #pragma unroll
-      for (int j = 0; j < NO2; ++j) {
-        const bool have = j < cnt && j < no2;
-        if (__ballot(have) != 0ull) {        // uniform: most tokens have one or two, the row has room for eight
-          nmax = j + 1;
-          if (have) put(j, v.oidx[side][gi0 * no2 + st + j], v.oval[side][gi0 * no2 + st + j]);
-        }
-      }
+      for (int j = 0; j < CAP; ++j) nmax += __ballot(cnt > j) != 0ull ? 1 : 0;      // uniform: most tokens have one or two
     }
   }
   // slot: the slot the store was loaded for (selects the half of the channel word)
@@ -764,6 +790,13 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
     // occurs among its 64 slots (one, except where a class boundary falls inside them) and
     // every lane keeps the result of its own class.
     float vmax = -INFINITY;
+    uint32_t run_v = 0u;              // variable-length side store: where the run of the lane's value token is
+    if constexpr (Outl<NO2>::RUNS) {
+      if (on) {
+        const size_t gi0 = qaq_slot_index(v, b, h, tile, 0);
+        kr.o.load_run(v, 0, gi0, Outl<NO2>::run_of(v, 0, gi0, (kr.pos >> (8u * (kslot & 3u))) & 0xffu), no2);
+      }
+    }
     if (on) {
       const int w0 = kwave * 64, w1 = w0 + 64;
       const int first8K = n32K + cK.n4;
@@ -853,14 +886,17 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
         const float d1 = real_of(k_contract<D, 1>(k1, abase1));
         if (ktid >= first1K) dotq = d1;
       }
+      if constexpr (Outl<NO2>::RUNS)
+        run_v = Outl<NO2>::run_of(v, 1, qaq_slot_index(v, b, h, tile, 0), (vr.pos >> (8u * (slot & 3u))) & 0xffu);
       if (ktid < n_tok) {
-        if constexpr (NO2 > 2)
-          if (v.csr) kr.o.load_csr(v, 0, qaq_slot_index(v, b, h, tile, 0), (kr.pos >> (8u * (kslot & 3u))) & 0xffu, no2);
+        if constexpr (Outl<NO2>::RUNS) kr.o.settle_run();
         const float lg = key_logit(kr.mm, kr.o, kslot, H1 ? cK.bits_of_slot(ktid) : cK.bits_of_slot4(ktid), dotq);
         S.logit[(kr.pos >> (8u * (kslot & 3u))) & 0xffu] = lg;
         vmax = lg;
       }
     }
+    if constexpr (Outl<NO2>::RUNS)
+      if (on) vr.o.load_run(v, 1, qaq_slot_index(v, b, h, tile, 0), run_v, no2);
     // the key registers are free: request the next tile's keys
     if (tile + 1 < tile_end) kr.template load<H1>(v, len, b, h, tile + 1, counts_of(tile + 1, 0), ktid);
 
@@ -889,8 +925,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       const bool live = s < n_tok;
       float pt = 0.0f, bias_l = 0.0f, w = 0.0f;
       if (live) {
-        if constexpr (NO2 > 2)
-          if (v.csr) vr.o.load_csr(v, 1, qaq_slot_index(v, b, h, tile, 0), (vr.pos >> (8u * (slot & 3u))) & 0xffu, no2);
+        if constexpr (Outl<NO2>::RUNS) vr.o.settle_run();
         pt = __expf(S.logit[(vr.pos >> (8u * (slot & 3u))) & 0xffu] - M);
         const float mn = h2f((uint16_t)(vr.mm & 0xffffu)), mx = h2f((uint16_t)(vr.mm >> 16));
         const float range = mx - mn;
@@ -1895,15 +1930,17 @@ __global__ __launch_bounds__(kThreads) void k_attn_combine(QaqAttnArgs a) {
 template <int D, int P>
 void launch_tile_p(const QaqAttnArgs& a, dim3 grid, size_t lds, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const dim3 block((P == 5 ? 4 : P ? P : 1) * kThreads);
-  if (a.v.has1) {
-    if (a.v.no2 == 2 && !a.v.csr) hipExtLaunchKernelGGL((k_attn_tile<D, 2, P, true>), grid, block, lds, s, e0, e1, 0, a);
-    else if (a.v.no2 == 0) hipExtLaunchKernelGGL((k_attn_tile<D, 0, P, true>), grid, block, lds, s, e0, e1, 0, a);
-    else hipExtLaunchKernelGGL((k_attn_tile<D, 8, P, true>), grid, block, lds, s, e0, e1, 0, a);
-    return;
-  }
-  if (a.v.no2 == 2 && !a.v.csr) hipExtLaunchKernelGGL((k_attn_tile<D, 2, P, false>), grid, block, lds, s, e0, e1, 0, a);   // (the variable-length side store runs in the general form)
-  else if (a.v.no2 == 0) hipExtLaunchKernelGGL((k_attn_tile<D, 0, P, false>), grid, block, lds, s, e0, e1, 0, a);
-  else hipExtLaunchKernelGGL((k_attn_tile<D, 8, P, false>), grid, block, lds, s, e0, e1, 0, a);
+  auto go = [&](auto no2, auto has1) {
+    hipExtLaunchKernelGGL((k_attn_tile<D, decltype(no2)::value, P, decltype(has1)::value>), grid, block, lds, s, e0, e1, 0, a);
+  };
+  auto form = [&](auto has1) {
+    if (a.v.csr) go(std::integral_constant<int, kRuns>{}, has1);
+    else if (a.v.no2 == 2) go(std::integral_constant<int, 2>{}, has1);
+    else if (a.v.no2 == 0) go(std::integral_constant<int, 0>{}, has1);
+    else go(std::integral_constant<int, QAQ_MAX_NO2>{}, has1);
+  };
+  if (a.v.has1) form(std::true_type{});
+  else form(std::false_type{});
 }
 template <int D>
 void launch_tile(const QaqAttnArgs& a, int fused_parts, int BQ, size_t lds, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

@@ -92,3 +92,20 @@ def test_decode_steps():
         np.testing.assert_array_equal(bk_g.cpu().numpy(), bk_o, err_msg=f"step {s}")
         np.testing.assert_array_equal(bv_g.cpu().numpy(), bv_o, err_msg=f"step {s}")
     compare_canonical(oc, gc, "after decode steps")
+
+
+@pytest.mark.parametrize("head_dim,context,cap,alpha,heads", [
+    (128, 512, 4, 0.9, 2), (128, 1300, 4, 0.9, 2),     # eight per token: every pool full, the last run ends where its pool does; one and two kernels
+    (64, 256, 3, 0.9, 3), (128, 257, 2, 1e-9, 2),      # six per token; none but the population's own extremes
+    (128, 300, 1, 0.3, 3), (64, 70, 4, 0.1, 520)])     # two places; heads enough for one part each
+def test_attention_over_full_and_empty_pools(head_dim, context, cap, alpha, heads):
+    """The attention kernel reads eight places from a run's start, whatever the run's length."""
+    sh = W.shape(2, batch=2, n_q_heads=heads, n_kv_heads=heads if heads < 128 else heads // 8, head_dim=head_dim, context=context)
+    print(f"pools: {sh} cap={cap} alpha={alpha}", flush=True)
+    K, V = W.make_kv(2, sh)
+    oc, gc = make_pair(sh, 0.01, n_outlier_per_side=cap, outlier_thresholds=_thresholds(K, V, alpha))
+    rng = np.random.default_rng(5)
+    bk, bv = (rng.choice(np.array([2, 3, 4, 8], np.uint8), size=K.shape[:3]) for _ in range(2))
+    oc.append(K, V, bk, bv); gc.quantize_append(dev(K), dev(V), dev(bk), dev(bv))
+    kn, vn = W.make_new_token(2, sh, step=0)
+    _check_attention(oc, gc, W.make_queries(2, sh)[0], kn, vn, tag="pools")

@@ -276,6 +276,8 @@ def test_decode_path_kernels_do_not_spill():
 @pytest.mark.parametrize("key,max_vgpr,max_scratch", [
     ("k_attn_tileILi128ELi8E", 128, 48),      # several outliers per end, or outliers by thresholds: a few words spilled, and no more
     ("k_attn_tileILi64ELi8E", 128, 0),
+    ("k_attn_tileILi128ELi16E", 128, 72),     # outliers by thresholds
+    ("k_attn_tileILi64ELi16E", 128, 20),
     ("k_build_listedILi128ELb1E", 128, 0),    # four, three, five and four workgroups per compute unit, as the launch counts on
     ("k_build_listedILi128ELb0E", 168, 0),
     ("k_build_listedILi64ELb1E", 96, 0),
