@@ -1323,7 +1323,8 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 // after the attention).  Same result as build_tile in mode 2, built for what a decode step does to
 // a tile: a few tokens change width, one token is appended to the last tile, everything else stays.
 //
-// Two wavefronts per tile side, two tokens per lane.  What bounds the update is the chain of dependent
+// Two wavefronts per tile side, two tokens per lane (k_update), where the value sides fill the chip; where they do not,
+// four, one token per lane (k_update_few).  What bounds the update is the chain of dependent
 // steps of a tile side -- metadata, widths, codes of the tokens that move, read-modify-write of the words
 // they go to -- and the instructions spent on all 256 tokens of a tile to move the dozen that change.  Half
 // as many wavefronts as tokens / 64 evaluate what is uniform over the tile half as often and leave room for
@@ -1344,33 +1345,45 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 // Vector and scalar instructions fill two thirds of the issue slots each.  With indices in 32 bits, the window's rows without
 // a look at their ends where all cover the tile, one load of scores where a KV head has one query head and class counts in pairs a
 // wavefront has 15 % fewer scalar ones (517 -> 438), compute units are busy 7 % less, and 24 steps of a small model take 436 instead of 453 us.
+// With the taken slots worked out from the old ones (not marked in LDS behind a barrier), 2- and 3-bit slots without a look at the
+// rest, the moved tokens' slots beside the gathering of their codes and every value region from another wavefront on, 8 x 32 heads x
+// 4096 tokens 29.4 -> 27.7 us, 16 x 8 x 8192 29.0 -> 27.8 (kernel trace).
+//
+// Where a compute unit has few tile sides, an instruction that waits for the one before it takes eight cycles and nothing
+// else fills them: a side's way is its instructions and some five trips to memory.  Four wavefronts halve what a lane does for
+// the tile; two of them look at the window, the last one encodes the appended token, whose row is asked for with everything else.
+// Two | four wavefronts, kernel trace: 8 heads x 512 tokens of 64 channels 9.7 | 7.9 us, 6 x 12 heads of 336 to 1901 tokens
+// with the copies in host memory 16.1 | 12.0, outliers by thresholds, 3 x 16 x 2500, 15.4 | 11.3.
 // ---------------------------------------------------------------------------------
 constexpr int kMaxCopy = 8192;
-constexpr int kUpdThreads = 128;
+// Four wavefronts per tile side up to this many value sides per compute unit (28 of the 32 wavefronts it holds, 72 registers each).
+// Eight steps with their prompt, us, two | four: 5 (2 x 32 heads x 4100 tokens) 351.3 | 343.2, 6 (3 x 32 x 4000) 411.8 | 399.9,
+// 7 (4 x 32 x 3500 of 64 channels) 352.9 | 347.6, 8 (4 x 32 x 4000) 454.4 | 455.3, the same with spiked values 467.7 | 470.7.
+constexpr int kUpdFew = 7;
 constexpr int kUpdResident = 16;    // tile sides a compute unit takes: two wavefronts of at most 64 registers each
 
 // Beside this block a tile side has LDS for the codes of `a.max_moved` tokens (dynamic, sized at launch): that many
 // staged rows, then a list word and a [min, max] for each.  Before any code is gathered the space holds, by position,
 // the value side's predicted scores and (variable-length side store) largest | smallest outlier << 16.
-template <int D>
+template <int D, int NW>
 struct UpdLds {
   // keys: byte d of a staged row = channel d; values: byte n*(D/16) + g = channel 16*g + n, the order of a unit's words
   static constexpr int SROW = D / 4 + 1;   // dwords per staged row (odd stride: rows spread over the banks)
   static constexpr int PER_TOKEN = 4 * SROW + 8;
-  uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list; before that 1 = a token keeps the slot
-  uint8_t freeslot[QAQ_TT];                // the slots no token keeps, in order: the first wavefront's from the front, the second's from the back
+  uint8_t m_of_slot[QAQ_TT];               // by new slot: index in the moved list
+  uint8_t freeslot[QAQ_TT];                // the slots no token keeps, in order, those of every 64 slots in 64 places of their own
+  unsigned long long same[QAQ_TT / 64];    // bit by old slot: the cached token there stays in its class
   uint32_t mask2[16], mask4[32], mask1b[16];   // value side: slots to write per unit of 16 (2-bit fields, 1-bit tokens) or half-unit of 8 (4-bit)
   unsigned long long written[QAQ_TT / 64 + 1];   // ... bit by slot
   uint32_t newrow[D / 4];                  // the appended token: its codes at the widest width, byte d = channel d
   uint32_t new_oi[2], new_ov[4];           // ... outlier channels, outlier values
   uint32_t new_mm;
   int new_no;                              // ... outliers (variable-length side store)
-  int w_cls[2][QAQ_NCLASS];                // per wavefront, two counts per word (not all words are used)
-  int w_any[2], w_wide[2], w_moved[2];
-  int free0;                               // free slots among the first wavefront's
-  int first_free[QAQ_NCLASS];              // per class: free slots before its first slot (256 added: to be counted on from free0)
-  float w_bnd[2], w_lo[2], w_hi[2];
-  uint8_t units[2][32];                    // ... units with words to write
+  int w_cls[NW][3];                        // per wavefront: tokens of a class, two counts per word
+  int w_any[NW], w_wide[NW], w_moved[NW];
+  int first_free[QAQ_NCLASS];              // per class: free slots before its first one among its 64 | which 64 << 8
+  float w_bnd[NW], w_lo[NW], w_hi[NW];
+  uint8_t units[NW][32];                   // ... units with words to write
 };
 
 // unsigned wavefront reductions, as wave_max.  (The appended token is a chain of one per outlier and two more, and the side
@@ -1552,13 +1565,14 @@ __device__ __forceinline__ int class_start(const QaqCounts& c, int k) {        /
 // one channel of up to 16 tokens; a word of a unit that did not exist starts from zero).  BF: field
 // width; `masks`: slots to write per unit of 16 (BF 4: of 8) from slot0 on, those from n_slots on left out; `n3`: slots
 // below it hold 3-bit codes (BF 2: their upper bits are wanted).  Each wavefront lists the units with
-// work and takes every other group of them, the words of a batch requested together.
-template <int D, int BF>
-__device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks, int units_old, int n_slots, int slot0, int n3, const uint32_t* stage, UpdLds<D>& L) {
+// work and takes every NW-th group of them from `wave` on (the regions start with different wavefronts: a trip to memory
+// each), the words of a batch requested together.
+template <int D, int BF, int NW>
+__device__ __forceinline__ void put_units(int wave, uint8_t* region, const uint32_t* masks, int units_old, int n_slots, int slot0, int n3, const uint32_t* stage, UpdLds<D, NW>& L) {
   constexpr int LPU = BF == 1 ? D / 8 : D / 4;       // lanes per unit, four consecutive words each
-  constexpr int UPW = 64 / LPU, U = 2, SPU = BF == 4 ? 8 : 16;
+  constexpr int UPW = 64 / LPU, U = NW > 2 && UPW > 2 ? 1 : 2, SPU = BF == 4 ? 8 : 16;
   constexpr uint32_t UB = BF == 1 ? 2 * D : 4 * D;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, own = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   auto mask_of = [&](int u) {
     const int n = min(max(n_slots - SPU * u, 0), SPU);
     return masks[u] & ((1u << n) - 1u);
@@ -1567,16 +1581,16 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
   const unsigned long long work = __ballot(lane < n_units && mask_of(min(lane, 256 / SPU - 1)) != 0u);
   const int nu = __popcll(work);
   if (nu == 0) return;
-  if ((work >> lane) & 1ull) L.units[wave][lanes_below(work)] = (uint8_t)lane;
+  if ((work >> lane) & 1ull) L.units[own][lanes_below(work)] = (uint8_t)lane;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (the wavefront's own list)
   const int sub = lane / LPU, c = lane % LPU;
 #pragma unroll 1
-  for (int i0 = wave * UPW * U; i0 < nu; i0 += 2 * UPW * U) {
+  for (int i0 = wave * UPW * U; i0 < nu; i0 += NW * UPW * U) {
     u32x4 o[U];
     int un[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      un[k] = L.units[wave][min(i0 + k * UPW + sub, nu - 1)];
+      un[k] = L.units[own][min(i0 + k * UPW + sub, nu - 1)];
       o[k] = *(const u32x4*)(region + (uint32_t)(un[k] * (int)UB + 16 * c));
     }
 #pragma unroll
@@ -1588,7 +1602,7 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
         const int i = __ffs(msk) - 1;
         msk &= msk - 1;
         const int sl = slot0 + SPU * un[k] + i;
-        const uint32_t* row = &stage[(int)L.m_of_slot[sl] * UpdLds<D>::SROW];
+        const uint32_t* row = &stage[(int)L.m_of_slot[sl] * UpdLds<D, NW>::SROW];
         if (BF == 1) {
           const uint32_t w0 = row[2 * c], w1 = row[2 * c + 1];      // word e: bytes 2*e and 2*e + 1 of the pair
           const int bp = 8 * (i & 3) + (i >> 2);
@@ -1612,13 +1626,14 @@ __device__ __forceinline__ void put_units(uint8_t* region, const uint32_t* masks
 
 // ONE: one outlier per end in the fixed-length side store; else any count, or the variable-length store.
 // HAS1: the width set contains 1.
-template <int D, bool ONE, bool HAS1>
-__global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
+// NW: wavefronts per tile side, two or four.
+template <int D, bool ONE, bool HAS1, int NW>
+__device__ __forceinline__ void update_side(const QaqBuildArgs& a) {
   // (and the key thresholds of the first 128 heads)
   qaq_request_arguments<0, offsetof(QaqBuildArgs, rule) + offsetof(QaqRuleArgs, tau_k) + 128 * sizeof(float)>();
-  __shared__ UpdLds<D> L;
+  __shared__ UpdLds<D, NW> L;
   extern __shared__ uint32_t stage[];        // [max_moved][SROW], then the moved list
-  constexpr int SROW = UpdLds<D>::SROW, NQ = D / 16, KS = D / 64, J = QAQ_TT / kUpdThreads, NC = HAS1 ? QAQ_NCLASS : 4;
+  constexpr int SROW = UpdLds<D, NW>::SROW, NQ = D / 16, KS = D / 64, NT = 64 * NW, J = QAQ_TT / NT, NC = HAS1 ? QAQ_NCLASS : 4;
   constexpr int NOI = ONE ? 1 : 4;          // words of outlier values per token, pairs of outlier channels
   uint32_t* const mv = stage + a.max_moved * SROW;      // moved list: token | new slot << 8 | position << 16 | old width << 24 | new width << 28
   uint32_t* const mv_mm = mv + a.max_moved;             // ... fp16 min | max << 16
@@ -1663,10 +1678,16 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   uint8_t* base = v.codes[side] + (size_t)tile_id * v.cap[side];
   const uint2 counts_raw = *(const uint2*)(v.counts + ((size_t)tile_id * 2 + side) * 4);
   const size_t gi0 = (size_t)tile_id * QAQ_TT;      // (units follow one another in whole tiles)
+  // the appended token's row, two channels per lane (where there is none, what is read anyway: no load behind a branch.  Two
+  // wavefronts have no register for it until it is used)
+  auto new_row = [&](bool some) { return (some ? (const uint32_t*)(a.newx[side] + (size_t)(uint32_t)(bh * a.n_new) * D) : v.mm[side] + gi0)[min(lane, D / 2 - 1)]; };
+  uint32_t new_w = 0u;
+  if (NW > 2) new_w = new_row(has_new);
   // token tok0 + 64*j: the cached token in that old slot, or (== n_before) the appended one
   uint32_t mm[J], oi[J], ov[J];      // (oi, ov: ONE; else the side store is read again for the tokens that move)
   uint32_t oext[J];                  // value side, not ONE: largest | smallest outlier << 16
   int pos[J];
+  float thr_lo = INFINITY, thr_hi = -INFINITY;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     const uint32_t s = (uint32_t)min(tok0 + 64 * j, max(n_before - 1, 0));
@@ -1679,6 +1700,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       ov[j] = *(const uint32_t*)((const uint8_t*)(v.oval[side] + gi0 * 2) + 4u * s);
     }
   }
+  auto thresholds = [&] {
+    const float* t = v.othr + (side * v.Hkv + bh % v.Hkv) * 2;
+    thr_lo = t[0]; thr_hi = t[1];
+  };
+  if (NW > 2 && csr) thresholds();
   if (!ONE && !csr && side == 1 && no2 > 0) {
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -1700,7 +1726,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       oext[j] = some ? (uint32_t)f2h(hi) | ((uint32_t)f2h(lo) << 16) : 0xffffffffu;
     }
   }
-  if (side == 1) {      // the window (Section 4.2), this step's row stored: two positions per lane
+  if (side == 1 && (NW == 2 || wave < 2)) {      // the window (Section 4.2), this step's row stored: two positions per lane of two wavefronts
     const size_t ring_row = (size_t)((uint32_t)gridDim.x * (uint32_t)v.NT) * QAQ_TT;
     const size_t ri0 = gi0;
     const float* row0 = ru.scores + (size_t)(uint32_t)(bh * ru.G) * ru.score_stride + t0;
@@ -1752,7 +1778,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       pred[0] = qaq_window_max_compact(v, qaq_rows_covering(v, ru.row_len, bh / v.Hkv, t0), ru.new_row, ri0, s);
       qaq_ring_store(v, (size_t)ru.new_row * ring_row + ri0, s);
     }
-    if (csr) {
+  }
+  if (csr && side == 1) {
       // outliers by thresholds: the extremes of every position's run in the tile's pool
       const size_t pool0 = gi0 * (size_t)no2;
       int cnt[J], st[J], most = 0;
@@ -1782,28 +1809,21 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 #pragma unroll
       for (int j = 0; j < J; ++j)
         if (tok0 + 64 * j < n_before) oext_at[tok0 + 64 * j] = cnt[j] > 0 ? (uint32_t)f2h(hi[j]) | ((uint32_t)f2h(lo[j]) << 16) : 0xffffffffu;
-    }
   }
-#pragma unroll
-  for (int j = 0; j < J; ++j) L.m_of_slot[tok0 + 64 * j] = 0u;
 
   // ---- the appended token: outliers, range, codes at the widest width (Section 4.2 "Outliers",
-  // Section 4.1 quantizer), by the second wavefront, two channels per lane ------------------------------
-  if (has_new && wave == 1) {
+  // Section 4.1 quantizer), by the last wavefront, two channels per lane --------------------------------
+  if (has_new && wave == NW - 1) {
     int new_no = 0;              // outliers found (the variable-length store: as many as pass the thresholds)
     const bool act = 2 * lane < D;
-    const uint32_t* src = (const uint32_t*)(a.newx[side] + (size_t)bh * a.n_new * D);
-    const uint32_t w = act ? src[lane] : 0u;
+    if (NW == 2) new_w = new_row(true);
+    const uint32_t w = act ? new_w : 0u;
     if (act && a.orig_put[side]) ((uint32_t*)(a.orig_put[side] + ((size_t)bh * a.orig_tokens + len_before) * D))[lane] = w;
     const uint32_t kk = order_keys_pair(w);
     const int ch0 = 2 * lane, ch1 = 2 * lane + 1;
     const uint32_t k0 = kk << 16, k1 = kk & 0xffff0000u;
     bool in0 = act, in1 = act;
-    float thr_lo = INFINITY, thr_hi = -INFINITY;
-    if (csr) {
-      const float* t = v.othr + (side * v.Hkv + bh % v.Hkv) * 2;
-      thr_lo = t[0]; thr_hi = t[1];
-    }
+    if (NW == 2 && csr) thresholds();
     // the largest values, lowest channel first; then the smallest of the rest, lowest channel first; the
     // one in lane k is the k-th found
     uint32_t my_ch = 0xffu, my_val = 0u;
@@ -1931,6 +1951,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   else { lo = wave_max(lo); hi = wave_min(hi); }
   if (lane == 0) {
 #pragma unroll
+    for (int j = 0; j < J; ++j) L.same[J * wave + j] = same_cls[j];
+#pragma unroll
     for (int c = 0; c < (NC + 1) / 2; ++c) {             // two counts per word
       int n = 0;
 #pragma unroll
@@ -1944,17 +1966,24 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     L.w_bnd[wave] = bnd; L.w_lo[wave] = lo; L.w_hi[wave] = hi;
   }
   __syncthreads();
-  const int all_wide = L.w_wide[0] + L.w_wide[1];
-  if (!(L.w_any[0] | L.w_any[1])) {          // nothing moves and nothing is appended
+  int all_wide = 0, some = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { all_wide += L.w_wide[w]; some |= L.w_any[w]; }
+  if (!some) {          // nothing moves and nothing is appended
     if (tid == 0 && all_wide) v.refused[((size_t)tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
     return;
   }
-  auto both = [&](int c) { return __builtin_amdgcn_readfirstlane(L.w_cls[0][c] + L.w_cls[1][c]); };
+  auto all_waves = [&](int c) {
+    int n = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) n += L.w_cls[w][c];
+    return __builtin_amdgcn_readfirstlane(n);
+  };
   QaqCounts cn;
   {
-    const int n01 = both(0), n23 = both(1);
+    const int n01 = all_waves(0), n23 = all_waves(1);
     cn.n3 = n01 & 0xffff; cn.n2 = n01 >> 16; cn.n4 = n23 & 0xffff; cn.n8 = n23 >> 16;
-    cn.n1 = HAS1 ? both(2) : 0;
+    cn.n1 = HAS1 ? all_waves(2) : 0;
   }
 
   // ---- regions.  A token's codes sit at an index inside its class's region (2- and 3-bit tokens: the
@@ -1996,69 +2025,96 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
 
   // ---- slots: a cached token that stays in its class keeps its index if the region still reaches it; the others --
   // tokens that change class, tokens squeezed out, the appended one -- take the free slots of their class in order.
-  // Which old slots can be kept follows from the class counts alone; free slots are in class order as they are, so
-  // they make one list, and only the tokens that move ask where their class begins in it. -------------------------
+  // Which old slots can be kept follows from the class counts alone, and which of a class's new slots are then taken from
+  // the old slots they were; free slots are in class order as they are, so they make one list, and only the tokens that
+  // move ask where their class begins in it. ------------------------------------------------------------------------
   const int shift4 = n32n - n32o, shift8 = shift4 + cn.n4 - c_old.n4, shift1 = shift8 + cn.n8 - c_old.n8;     // new slot less old slot of a kept token
   auto kept_end = [&](int c, int first, int n_old, int n_new) { return (lost >> c) & 1u ? first : first + min(n_old, n_new); };
   const int f8 = n32o + c_old.n4, f1 = f8 + c_old.n8;
   const int e3 = kept_end(QC3, 0, c_old.n3, cn.n3), s2 = max(cn.n3, c_old.n3), e2 = min(n32o, n32n);
   const int e4 = kept_end(QC4, n32o, c_old.n4, cn.n4), e8 = kept_end(QC8, f8, c_old.n8, cn.n8), e1 = kept_end(QC1, f1, c_old.n1, cn.n1);
-  int my_slot[J];
-  unsigned long long need_bal[J], live_bal[J];
+  // What is left to write of a token, in one register: position, slot (of a token that moves: its place among the wavefront's
+  // that do), width, old width, and whether it moves or its place changes, whether its width does, whether it moves.
+  uint32_t left[J];
+  constexpr uint32_t kMoves = 1u << 20, kRetag = 1u << 21, kNeeds = 1u << 22;
+  unsigned long long need_bal[J];
+  int moved_here = 0;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
-    const int tok = tok0 + 64 * j;
-    bool can = (tok < e3) | ((tok >= s2) & (tok < e2)) | ((tok >= n32o) & (tok < e4)) | ((tok >= f8) & (tok < e8));
-    if (HAS1) can |= (tok >= f1) & (tok < e1);
-    int to = tok + (tok >= n32o ? shift4 : 0);
-    to = tok >= f8 ? tok + shift8 : to;
-    if (HAS1) to = tok >= f1 ? tok + shift1 : to;
-    my_slot[j] = to;
-    const unsigned long long keep_bal = same_cls[j] & __ballot(can);
-    live_bal[j] = __ballot(tok < n_after);
-    need_bal[j] = live_bal[j] & ~keep_bal;
-    if ((keep_bal >> lane) & 1ull) L.m_of_slot[to] = 1u;
+    const int at = J * wave + j, tok = tok0 + 64 * j;      // (tokens 64*at .. +63, and the slots of these numbers)
+    const unsigned long long live_bal = __ballot(tok < n_after);
+    unsigned long long free_bal;
+    int to = tok;
+    const bool narrow = 64 * at + 64 <= e2;
+    if (narrow) {                   // (scalar) 2- and 3-bit tokens before and after: what is kept stays where it is
+      need_bal[j] = free_bal = live_bal & ~(same_cls[j] & __ballot((tok < e3) | (tok >= s2)));
+    } else {
+      bool can = (tok < e3) | ((tok >= s2) & (tok < e2)) | ((tok >= n32o) & (tok < e4)) | ((tok >= f8) & (tok < e8));
+      if (HAS1) can |= (tok >= f1) & (tok < e1);
+      to = tok + (tok >= n32o ? shift4 : 0);
+      to = tok >= f8 ? tok + shift8 : to;
+      if (HAS1) to = tok >= f1 ? tok + shift1 : to;
+      need_bal[j] = live_bal & ~(same_cls[j] & __ballot(can));
+      // the same place as a new slot: its class, and whether the old slot that class would have kept there was kept
+      const int k = class_at<HAS1>(cn, tok);
+      int from = tok - (k == QC4 ? shift4 : k == QC8 ? shift8 : HAS1 && k == QC1 ? shift1 : 0);
+      const int k0 = k == QC3 ? 0 : k == QC2 ? s2 : k == QC4 ? n32o : !HAS1 || k == QC8 ? f8 : f1;
+      const int k1 = k == QC3 ? e3 : k == QC2 ? e2 : k == QC4 ? e4 : !HAS1 || k == QC8 ? e8 : e1;
+      const bool inside = (from >= k0) & (from < k1);
+      from = inside ? from : 0;
+      const bool taken = inside & (((((const uint32_t*)L.same)[from >> 5] >> (from & 31)) & 1u) != 0u);
+      free_bal = __ballot(!taken) & live_bal;
+    }
+    const int below = lanes_below(free_bal);
+    if ((free_bal >> lane) & 1ull) L.freeslot[64 * at + below] = (uint8_t)tok;
+    if (tok == cn.n3) L.first_free[QC2] = below | (at << 8);      // (a class that has no slot is never asked for)
+    if (!narrow && ((tok == n32n) | (tok == n32n + cn.n4) | (HAS1 && tok == cn.first1()))) {
+      const int x = below | (at << 8);
+      if (tok == n32n) L.first_free[QC4] = x;
+      if (tok == n32n + cn.n4) L.first_free[QC8] = x;
+      if (HAS1 && tok == cn.first1()) L.first_free[QC1] = x;
+    }
+    // every free slot is taken by a token that moves: the slots to write
+    if (lane == 0) L.written[at] = free_bal;
+    const bool live = tok < n_after, need = ((need_bal[j] >> lane) & 1ull) != 0ull, is_new = has_new & (tok == n_before);
+    if (need) to = moved_here + lanes_below(need_bal[j]);
+    left[j] = (uint32_t)pos[j] | ((uint32_t)(to & 0xff) << 8) | ((uint32_t)nb[j] << 16) | ((uint32_t)ob[j] << 24) |
+              ((live & ((to != tok) | need)) ? kMoves : 0u) | ((live & ((nb[j] != ob[j]) | is_new)) ? kRetag : 0u) | (need ? kNeeds : 0u);
+    moved_here += __popcll(need_bal[j]);
   }
-  if (lane == 0) L.w_moved[wave] = __popcll(need_bal[0]) + __popcll(need_bal[J - 1]);
-  static_assert(J == 2, "");
+  if (lane == 0) L.w_moved[wave] = moved_here;
+  if (tid == 0) L.written[QAQ_TT / 64] = 0ull;
   __syncthreads();
-  const int moved0 = __builtin_amdgcn_readfirstlane(L.w_moved[0]), n_moved = moved0 + __builtin_amdgcn_readfirstlane(L.w_moved[1]);
+  int n_moved = 0, moved0 = 0;          // tokens that move; ... of the wavefronts before this one
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const int n = __builtin_amdgcn_readfirstlane(L.w_moved[w]);
+    moved0 += w < wave ? n : 0;
+    n_moved += n;
+  }
   if (n_moved > a.max_moved) {
     // nothing of the cache has been written yet (the window row and the width outputs are the same
     // numbers when the general kernel writes them again)
     if (tid == 0) a.todo[atomicAdd(a.todo_count, 1u)] = (uint32_t)(tile_id * 2 + side);
     return;
   }
-  {
-    int m = wave ? moved0 : 0, r = 0;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int slot = tok0 + 64 * j;
-      const unsigned long long free_bal = __ballot(L.m_of_slot[slot] == 0u) & live_bal[j];
-      const int below = r + lanes_below(free_bal);
-      if ((free_bal >> lane) & 1ull) L.freeslot[wave == 0 ? below : QAQ_TT - 1 - below] = (uint8_t)slot;
-      if (slot == cn.n3 || slot == n32n || slot == n32n + cn.n4) {      // (a class that has no slot is never asked for)
-        const int x = below + (wave ? QAQ_TT : 0);
-        if (slot == cn.n3) L.first_free[QC2] = x;
-        if (slot == n32n) L.first_free[QC4] = x;
-        if (slot == n32n + cn.n4) L.first_free[QC8] = x;
-      }
-      if (HAS1 && slot == cn.first1()) L.first_free[QC1] = below + (wave ? QAQ_TT : 0);
-      r += __popcll(free_bal);
-      // every free slot is taken by a token that moves: the slots to write
-      if (lane == 0) L.written[J * wave + j] = free_bal;
-      if ((need_bal[j] >> lane) & 1ull) {
-        const int at = m + lanes_below(need_bal[j]);
-        mv[at] = (uint32_t)slot | ((uint32_t)pos[j] << 16) | ((uint32_t)ob[j] << 24) | ((uint32_t)nb[j] << 28);
-        mv_mm[at] = mm[j];
-      }
-      m += __popcll(need_bal[j]);
+  for (int j = 0; j < J; ++j)
+    if (left[j] & kNeeds) {
+      const int at = moved0 + (int)((left[j] >> 8) & 0xffu);
+      mv[at] = (uint32_t)(tok0 + 64 * j) | ((left[j] & 0xffu) << 16) | (left[j] & 0xf000000u) | ((left[j] << 12) & 0xf0000000u);
+      mv_mm[at] = mm[j];
     }
-    if (tid == 0) { L.written[QAQ_TT / 64] = 0ull; L.free0 = r; }
-  }
   __syncthreads();
+  // (what follows up to the next barrier does not look at the moved tokens' slots)
   if (wave == 0) {            // the moved tokens' slots, a token per lane
-    const int free0 = __builtin_amdgcn_readfirstlane(L.free0);
+    int free_to[3], sum = 0;               // free slots among the first 64, 128, 192
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const uint2 m = *(const uint2*)&L.written[i];
+      sum += __builtin_popcount(__builtin_amdgcn_readfirstlane((int)m.x)) + __builtin_popcount(__builtin_amdgcn_readfirstlane((int)m.y));
+      free_to[i] = sum;
+    }
     int used[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) used[c] = 0;
@@ -2066,8 +2122,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     for (int m0 = 0; m0 < n_moved; m0 += 64) {
       const bool live = m0 + lane < n_moved;
       const int m = min(m0 + lane, n_moved - 1);
-      const uint32_t e = mv[m];
-      const int c = live ? qaq_class_of_bits((int)(e >> 28)) : -1;
+      const int c = live ? qaq_class_of_bits((int)(mv[m] >> 28)) : -1;
       int rank = 0;
 #pragma unroll
       for (int k = 0; k < NC; ++k) {
@@ -2075,12 +2130,17 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
         rank = c == k ? used[k] + lanes_below(bal) : rank;
         used[k] += __popcll(bal);
       }
-      const int x = c > 0 ? L.first_free[c] : 0;
-      const int f = (x & (QAQ_TT - 1)) + (x >= QAQ_TT ? free0 : 0) + rank;
-      const int slot = L.freeslot[f < free0 ? f : QAQ_TT - 1 - (f - free0)];
-      if (live) { mv[m] = e | ((uint32_t)slot << 8); L.m_of_slot[slot] = (uint8_t)m; }
+      const int x = c > 0 ? L.first_free[c] : 0, i = x >> 8;
+      const int f = rank + (x & 255) + (i == 0 ? 0 : i == 1 ? free_to[0] : i == 2 ? free_to[1] : free_to[2]);
+      const int of = f < free_to[0] ? 0 : f < free_to[1] ? 64 - free_to[0] : f < free_to[2] ? 128 - free_to[1] : 192 - free_to[2];
+      if (live) {
+        const int slot = L.freeslot[f + of];
+        ((uint8_t*)&mv[m])[1] = (uint8_t)slot;
+        L.m_of_slot[slot] = (uint8_t)m;
+      }
     }
-  } else if (side == 1) {     // value side: which slots are written, by unit of the region they are in
+  }
+  if (side == 1 && wave == NW - 1) {     // value side: which slots are written, by unit of the region they are in
     auto slots_from = [&](int first) -> uint32_t {       // slots [first, first + 16) of those to write
       const uint32_t* p = (const uint32_t*)L.written + (min(first, QAQ_TT) >> 5);
       return __builtin_amdgcn_alignbit(p[1], p[0], (uint32_t)first & 31u) & 0xffffu;
@@ -2089,26 +2149,6 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     else if (lane < 48) L.mask4[lane - 16] = slots_from(n32n + 8 * (lane - 16)) & 0xffu;
     else if (HAS1) L.mask1b[lane - 48] = slots_from(cn.first1() + 16 * (lane - 48));
   }
-  __syncthreads();
-  {
-    int m = wave ? moved0 : 0;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      if ((need_bal[j] >> lane) & 1ull) my_slot[j] = (int)((mv[m + lanes_below(need_bal[j])] >> 8) & 0xffu);
-      m += __popcll(need_bal[j]);
-    }
-  }
-  // what is left to write of a token, in one register: position, slot, width; whether slot or width changed
-  uint32_t left[J];
-  constexpr uint32_t kMoves = 1u << 20, kRetag = 1u << 21;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int tok = tok0 + 64 * j;
-    const bool live = tok < n_after, need = ((need_bal[j] >> lane) & 1ull) != 0ull, is_new = has_new & (tok == n_before);
-    left[j] = (uint32_t)pos[j] | ((uint32_t)(my_slot[j] & 0xff) << 8) | ((uint32_t)nb[j] << 16) | ((live & ((my_slot[j] != tok) | need)) ? kMoves : 0u) |
-              ((live & ((nb[j] != ob[j]) | is_new)) ? kRetag : 0u);
-  }
-
   // ---- codes of the moved tokens -> LDS, at the new width: sixteen channels per work item --------------------
   // (all loads of an item without a condition, so that they are in flight together: the class selects addresses,
   // shifts and masks.  Four channels per item cost as many instructions per item.)
@@ -2138,7 +2178,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     auto gather = [&](auto side_c) {
       constexpr int SD = decltype(side_c)::value;
 #pragma unroll 1
-      for (int it = tid; it < n_items; it += kUpdThreads) {
+      for (int it = tid < 64 ? tid + NT - 64 : tid - 64; it < n_items; it += NT) {      // (the first wavefront is still at the slots)
         int c = it % LPT;
         asm volatile("" : "+v"(c));        // (nothing that follows from it is worth a register across the loop)
         const int m = it / LPT;
@@ -2249,15 +2289,16 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     else gather(std::integral_constant<int, 1>{});
   }
 
-  // ---- regions that start elsewhere: read as a whole, then written --------------------------------------
+  // ---- regions that start elsewhere: read as a whole, then written.  (Asked for before the moved tokens' codes by four
+  // wavefronts: no difference) ------------------------------------------------------------------------------
   const int n_cp = cp_end[NC - 1];
   if (n_cp > 0) {
-    constexpr int CP = kMaxCopy / (16 * kUpdThreads);
+    constexpr int CP = kMaxCopy / (16 * NT);
     u32x4 x[CP];
     uint32_t dst[CP];
 #pragma unroll
     for (int k = 0; k < CP; ++k) {
-      const int i = min(kUpdThreads * k + tid, n_cp - 1);
+      const int i = min(NT * k + tid, n_cp - 1);
       uint32_t so = 0u, d = 0u;
 #pragma unroll
       for (int c = NC - 1; c >= 0; --c)          // the class whose share holds piece i
@@ -2272,7 +2313,7 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
     __syncthreads();           // old and new places may overlap: everything read before anything is written
 #pragma unroll
     for (int k = 0; k < CP; ++k)
-      if (kUpdThreads * k + tid < n_cp) *(u32x4*)(base + dst[k]) = x[k];
+      if (NT * k + tid < n_cp) *(u32x4*)(base + dst[k]) = x[k];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // ... and written before words of it are read again
   }
   uint32_t oi_mv[J][NOI], ov_mv[J][NOI];
@@ -2291,6 +2332,8 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       }
     }
   }
+#pragma unroll
+  for (int j = 0; j < J; ++j) asm volatile("" :: "v"(oi[j]), "v"(ov[j]));      // (the side store's too)
   __syncthreads();      // every read of the old layout is done
 
   // ---- metadata: tokens whose slot changed (moved ones, and tokens behind a moved class border),
@@ -2299,7 +2342,9 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   for (int j = 0; j < J; ++j) {
     const int p = (int)(left[j] & 0xffu);
     if (left[j] & kMoves) {
-      const size_t gi = gi0 + ((left[j] >> 8) & 0xffu);
+      uint32_t slot = (left[j] >> 8) & 0xffu;
+      if (left[j] & kNeeds) slot = (mv[moved0 + slot] >> 8) & 0xffu;
+      const size_t gi = gi0 + slot;
       v.mm[side][gi] = mm[j];
       v.perm[side][gi] = (uint8_t)p;
       if (ONE) {
@@ -2329,14 +2374,17 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   if (tid == 0) {
     uint16_t* cp = v.counts + (((size_t)tile_id * 2 + side) * 4);
     cp[QC3] = (uint16_t)cn.n3; cp[QC2] = (uint16_t)cn.n2; cp[QC4] = (uint16_t)cn.n4; cp[QC8] = (uint16_t)cn.n8;
-    if (side == 1) v.vbound[tile_id] = fmaxf(L.w_bnd[0], L.w_bnd[1]);
-    else ((float2*)v.kthr)[tile_id] = make_float2(fmaxf(L.w_lo[0], L.w_lo[1]), fminf(L.w_hi[0], L.w_hi[1]));
+    float b = L.w_bnd[0], l = L.w_lo[0], h = L.w_hi[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { b = fmaxf(b, L.w_bnd[w]); l = fmaxf(l, L.w_lo[w]); h = fminf(h, L.w_hi[w]); }
+    if (side == 1) v.vbound[tile_id] = b;
+    else ((float2*)v.kthr)[tile_id] = make_float2(l, h);
     if (all_wide) v.refused[((size_t)tile_id * 2 + side) * 2 + (served ? 1 : 0)] += (unsigned int)all_wide;
   }
 
   // ---- codes of the moved tokens -> their new places ----------------------------------------------------
   if (side == 0) {
-    for (int it = tid; it < n_moved * NQ; it += kUpdThreads) {
+    for (int it = tid; it < n_moved * NQ; it += NT) {
       const int m = it / NQ, q = it % NQ;
       const uint32_t e = mv[m];
       const int sl = (int)((e >> 8) & 0xffu), n_b = (int)(e >> 28);
@@ -2370,12 +2418,13 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
   // value side: the words of the units with slots to write
   // (the slots that are written were marked before the codes were gathered: barriers since)
   auto old_units = [&](int c, int n) { return (lost >> c) & 1u ? 0 : n; };
-  if (n32n > 0) put_units<D, 2>(base + r_new[QC2], L.mask2, (n32o + 15) / 16, n32n, 0, cn.n3, stage, L);
-  if (cn.n3 > 0) put_units<D, 1>(base + r_new[QC3], L.mask2, old_units(QC3, (min(c_old.n3, cn.n3) + 15) / 16), cn.n3, 0, 0, stage, L);
-  if (cn.n4 > 0) put_units<D, 4>(base + r_new[QC4], L.mask4, old_units(QC4, (min(c_old.n4, cn.n4) + 7) / 8), cn.n4, n32n, 0, stage, L);
-  if (HAS1 && cn.n1 > 0) put_units<D, 1>(base + r_new[QC1], L.mask1b, old_units(QC1, (min(c_old.n1, cn.n1) + 15) / 16), cn.n1, cn.first1(), 0, stage, L);
+  auto from = [&](int w) { return (wave + w) & (NW - 1); };
+  if (n32n > 0) put_units<D, 2>(wave, base + r_new[QC2], L.mask2, (n32o + 15) / 16, n32n, 0, cn.n3, stage, L);
+  if (cn.n3 > 0) put_units<D, 1>(from(1), base + r_new[QC3], L.mask2, old_units(QC3, (min(c_old.n3, cn.n3) + 15) / 16), cn.n3, 0, 0, stage, L);
+  if (cn.n4 > 0) put_units<D, 4>(from(2), base + r_new[QC4], L.mask4, old_units(QC4, (min(c_old.n4, cn.n4) + 7) / 8), cn.n4, n32n, 0, stage, L);
+  if (HAS1 && cn.n1 > 0) put_units<D, 1>(from(3), base + r_new[QC1], L.mask1b, old_units(QC1, (min(c_old.n1, cn.n1) + 15) / 16), cn.n1, cn.first1(), 0, stage, L);
   if (cn.n8 > 0)
-    for (int it = tid; it < n_moved * (D / 16); it += kUpdThreads) {        // 8-bit tokens: token-major bytes, 16 per item
+    for (int it = tid; it < n_moved * (D / 16); it += NT) {        // 8-bit tokens: token-major bytes, 16 per item
       const int m = it / (D / 16), dq = 4 * (it % (D / 16));
       const uint32_t e = mv[m];
       if ((e >> 28) != 8u) continue;
@@ -2387,6 +2436,11 @@ __global__ __launch_bounds__(kUpdThreads, 8) void k_update(QaqBuildArgs a) {
       *(uint4*)(base + r_new[QC8] + (uint32_t)(sl - n32n - cn.n4) * D + 4u * (uint32_t)dq) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
+
+template <int D, bool ONE, bool HAS1>
+__global__ __launch_bounds__(128, 8) void k_update(QaqBuildArgs a) { update_side<D, ONE, HAS1, 2>(a); }
+template <int D, bool ONE, bool HAS1>
+__global__ __launch_bounds__(256, 4) void k_update_few(QaqBuildArgs a) { update_side<D, ONE, HAS1, 4>(a); }
 
 // ---------------------------------------------------------------------------------
 // Width selection (Section 4.1 bit rules written as comparisons, Section 4.2 window).
@@ -2803,18 +2857,21 @@ static hipError_t launch_update(const QaqBuildArgs& a_in, int ntiles, float movi
   // of 64 -- up to a whole tile, which leaves nothing for the general kernel to do (a batch of six with unequal prompts,
   // 72 heads in all: 20.4 + 13.8 us with staging for 60 tokens and the second launch, 17.4 us without)
   constexpr int lds = 160 * 1024, grain = 1280;       // (LDS is handed out 1280 bytes at a time)
-  constexpr int least = (lds / kUpdResident / grain * grain - (int)sizeof(UpdLds<D>)) / UpdLds<D>::PER_TOKEN;
+  constexpr int least = (lds / kUpdResident / grain * grain - (int)sizeof(UpdLds<D, 2>)) / UpdLds<D, 2>::PER_TOKEN;
   static_assert(least == (D == 128 ? 64 : 120), "the figures above and those at expected_moves");
-  static_assert(least * UpdLds<D>::PER_TOKEN >= 2 * QAQ_TT * 4, "the space also holds two words per position before any code is staged");
+  static_assert(least * UpdLds<D, 2>::PER_TOKEN >= 2 * QAQ_TT * 4, "the space also holds two words per position before any code is staged");
   const int cus = qaq_compute_units();
   const long long resident = (sides / 2 + cus - 1) / cus;
-  const int room = lds / (int)(resident < kUpdResident ? resident : kUpdResident) / grain * grain - (int)sizeof(UpdLds<D>);
-  a.max_moved = room / UpdLds<D>::PER_TOKEN;
+  const bool few = resident <= kUpdFew;
+  const int room = lds / (int)(resident < kUpdResident ? resident : kUpdResident) / grain * grain - (int)(few ? sizeof(UpdLds<D, 4>) : sizeof(UpdLds<D, 2>));
+  a.max_moved = room / UpdLds<D, 2>::PER_TOKEN;
   a.open_first = sides > (long long)kUpdResident * cus;
   if (a.max_moved > QAQ_TT) a.max_moved = QAQ_TT;
   *whole = a.max_moved < QAQ_TT && moving * QAQ_TT >= (float)a.max_moved;
   if (*whole) return qaq_launch_build(a_in, ntiles, s);
-  hipLaunchKernelGGL((k_update<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(kUpdThreads), (size_t)a.max_moved * UpdLds<D>::PER_TOKEN, s, a);
+  const size_t staging = (size_t)a.max_moved * UpdLds<D, 2>::PER_TOKEN;
+  if (few) hipLaunchKernelGGL((k_update_few<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(256), staging, s, a);
+  else hipLaunchKernelGGL((k_update<D, ONE, HAS1>), dim3(a.v.B * a.v.Hkv, ntiles, 2), dim3(128), staging, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.max_moved == QAQ_TT) return e;
   // The tile sides it handed over (their number is only known on the device): as many workgroups as a compute unit holds

@@ -61,6 +61,14 @@ def test_update_equals_separate_calls_when_many_tokens_move(B, Hkv, G, D, T, ste
     assert len(widths) > 1
 
 
+@pytest.mark.parametrize("B", [7, 14])      # 4 value sides per compute unit, 7 and 14 as the second tile begins: four wavefronts a side, four and two
+@pytest.mark.parametrize("D,bit_set,n_o,thresholds", [
+    (128, (2, 3, 4, 8), 1, False), (128, (1, 2, 3, 4, 8), 1, False), (128, (2, 3, 4, 8), 3, True), (128, (1, 2, 4, 8), 2, False),
+    (64, (2, 3, 4, 8), 0, False), (64, (1, 2, 3, 4, 8), 4, True)])
+def test_both_forms_of_the_update(B, D, bit_set, n_o, thresholds):
+    test_update_equals_separate_calls_when_many_tokens_move(B, 128, 1, D, 254, 5, bit_set, n_o, thresholds, 3, {})
+
+
 @pytest.mark.parametrize("B,Hkv,D,T,bit_set,n_o,thresholds,staged", [
     (8, 32, 128, 3900, (2, 3, 4, 8), 1, False, "some"),        # sixteen sides per compute unit: the smallest staging
     (8, 32, 128, 1290, (1, 2, 3, 4, 8), 1, False, "some"),

@@ -295,6 +295,7 @@ def test_decode_path_kernels_do_not_spill():
     ("k_dequantILi64ELi0E", 64, 0),
     ("k_dequantILi128ELi8E", 72, 0),          # seven
     ("k_dequantILi64ELi8E", 72, 0),
+    ("k_update_fewI", 72, 0),                 # seven
     ("k_prefill_softmaxILi64E", 256, 0),      # 64 logits per thread
 ])
 def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
