@@ -1861,6 +1861,17 @@ __global__ __launch_bounds__(kThreads) void k_attn_combine(QaqAttnArgs a) {
     pm[k] = i < nparts ? part[(size_t)i * (D + 4) + D] : -INFINITY;
     pl[k] = i < nparts ? part[(size_t)i * (D + 4) + D + 1] : 0.0f;
   }
+  // the first block's share of the output: wavefront w takes parts w, w + 4, ..., lanes take channels; the first eight with
+  // everything else (not behind the factors: a call of six sequences' 72 heads x up to 1901 tokens' merge 4.6 -> 4.2 us by the trace,
+  // 32 heads x 32768 6.3 -> 5.8)
+  constexpr int AHEAD = 8;
+  float ahead[AHEAD][D / 64];
+  if (blockIdx.x == 0 && nparts > 0) {
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+#pragma unroll
+      for (int c = 0; c < D / 64; ++c) ahead[k][c] = part[(size_t)min(wave + 4 * k, nparts - 1) * (D + 4) + lane + 64 * c];
+  }
   float qk = 0.0f;
   if (a.k_new && tid < D) qk = __half2float(a.q[(size_t)bq * D + tid]) * __half2float(a.k_new[((size_t)b * v.Hkv + h) * D + tid]);
 
@@ -1893,8 +1904,7 @@ __global__ __launch_bounds__(kThreads) void k_attn_combine(QaqAttnArgs a) {
     }
   }
   if (blockIdx.x == 0) {
-    // output vector: wavefront w takes tiles w, w+4, ..., lanes take channels; several
-    // independent loads in flight per lane, then a fixed-order sum over the wavefronts
+    // output vector: the parts of every wavefront in order, then a fixed-order sum over the wavefronts
     __shared__ float fac[64 * MAXP];
     __shared__ float xacc[4][D];
     if (wave == 0) {
@@ -1905,8 +1915,15 @@ __global__ __launch_bounds__(kThreads) void k_attn_combine(QaqAttnArgs a) {
     float acc[D / 64];
 #pragma unroll
     for (int c = 0; c < D / 64; ++c) acc[c] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k)
+      if (wave + 4 * k < nparts) {
+        const float f = fac[wave + 4 * k];
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c) acc[c] += f * ahead[k][c];
+      }
 #pragma unroll 4
-    for (int i = wave; i < nparts; i += 4) {
+    for (int i = wave + 4 * AHEAD; i < nparts; i += 4) {
       const float f = i < 64 * MAXP ? fac[i] : __expf(part[(size_t)i * (D + 4) + D] - M);
 #pragma unroll
       for (int c = 0; c < D / 64; ++c) acc[c] += f * part[(size_t)i * (D + 4) + lane + 64 * c];
