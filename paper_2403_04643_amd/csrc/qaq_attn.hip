@@ -120,6 +120,28 @@ __device__ __forceinline__ float vmaxf(float a, float b) {
   return r;
 }
 
+// Sums over the 16 lanes of a row, and over the lanes of the wavefront whose numbers are equal modulo N (4 or 8), in every lane:
+// without the trip through LDS that a shuffle is.
+__device__ __forceinline__ float row_sum(float x) {
+  asm volatile(QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_f32_dpp", "row_half_mirror row_mask:0xf bank_mask:0xf")
+               QAQ_DPP_STEP("v_add_f32_dpp", "row_mirror row_mask:0xf bank_mask:0xf")
+               "s_nop 1"
+               : "+v"(x));
+  return x;
+}
+template <int N>
+__device__ __forceinline__ float stride_sum(float x) {
+  static_assert(N == 4 || N == 8, "lanes of a group");
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));             // row_ror:8
+  if (N == 4) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, true));   // row_ror:4
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
 // Signed base-256 digits of an integer (each in [-128, 127]), packed little endian: with 128 added to every byte
 // (carries and all) the bytes are the digits plus 128, and flipping their top bits takes that off again.
 __device__ __forceinline__ uint32_t digits_packed(int x) { return ((uint32_t)x + 0x80808080u) ^ 0x80808080u; }
@@ -462,6 +484,11 @@ struct ValRegs {
   // the rare classes gain):
   uint32_t v4p;  // D = 128: one word of the first two half-units (16 slots) of the 4-bit region: lane
                  // group g holds word g & 1 of half-unit g >> 1 (handed to the lanes that need it when it is used)
+  // D = 64, in k_attn_tile, whose forms there have the registers: the first 64 slots of the 4-bit region and the first row of the
+  // lane's share of the 8-bit values come with the tile too (and sums across lanes without shuffles; two calls at 4 x 32 heads x 3000
+  // tokens 32.1 -> 30.8 us, with spiked values 37.5 -> 34.0, all at 8 bits 52.8 -> 49.9)
+  static constexpr bool WITH48 = CGW == 1 && NO2 <= 2;
+  uint32_t v4w[2];
   uint32_t v8;   // 8-bit values (token-major rows): this lane's four channels of row lane / (D/16), so
                  // that the first 64 / (D/16) such tokens of a tile -- a tile of a cache the rules shaped rarely
                  // has more -- cost no load inside the tile loop
@@ -498,7 +525,12 @@ struct ValRegs {
       const int nhu = (c.n4 + 7) >> 3;
       v4p = gload32(ubase, c.n4 > 0 ? rV.r4 + (uint32_t)min(g >> 1, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * (uint32_t)(CGW * wave + (g & 1)) : 0u);
     }
-    if (PRE8) {
+    if (WITH48 && !PRE8 && c.n4 > 0) {
+      const int nhu = (c.n4 + 7) >> 3;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) v4w[k] = gload32(ubase, rV.r4 + (uint32_t)min(2 * g + k, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * (uint32_t)(CGW * wave));
+    }
+    if (PRE8 || WITH48) {
       const int lane = tid & 63;
       v8 = gload32(ubase, c.n8 > 0 ? rV.r8 + (uint32_t)min(lane / (D / 16), c.n8 - 1) * D + (D / 4) * wave + 4 * (lane % (D / 16)) : 0u);
     }
@@ -836,8 +868,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
         d += (float)((c1 >> 16) & 255u) * q1.z;
         d += (float)(c1 >> 24) * q1.w;
         if (8 * (lane & 15) >= D) d = 0.0f;
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) d += __shfl_xor(d, o);
+        d = row_sum(d);
         const int own = ktid - s8_0;                       // the lane that owns the slot
         const float dd = __shfl(d, 16 * (own & 3));
         if (own >= 0 && own < n8w) dotq = dd;
@@ -1014,8 +1045,12 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       const int nhu = (cV.n4 + 7) >> 3;
       uint32_t w0[CGW], w1d[CGW];
       // a half-unit past the end repeats the last one; its slots carry zero digits
-      gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w0);
-      gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u + 1, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w1d);
+      if (ValRegs<D, NO2>::WITH48 && blk == 0) {
+        w0[0] = vr.v4w[0]; w1d[0] = vr.v4w[1];
+      } else {
+        gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w0);
+        gload_dwords<CGW>(baseV + (rV.r4 + (uint32_t)min(2 * u + 1, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * CGW * wave), w1d);
+      }
       const v4i wa = *(const v4i*)(wb4 + 64 * blk);
 #pragma unroll
       for (int j = 0; j < CGW; ++j) {
@@ -1051,7 +1086,7 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       constexpr int UB = 4;
       const uint32_t lane8 = (D / 4) * wave + 4 * ch4;
       auto row8 = [&](int i8) { return gload32(baseV, rV.r8 + (uint32_t)min(i8, cV.n8 - 1) * D + lane8); };
-      const uint32_t dw0 = row8(sub);
+      const uint32_t dw0 = ValRegs<D, NO2>::WITH48 ? vr.v8 : row8(sub);
       uint32_t cur[UB];
 #pragma unroll
       for (int u = 0; u < UB; ++u) cur[u] = row8(sub + (1 + u) * TPW);
@@ -1077,9 +1112,15 @@ __global__ __launch_bounds__((PP == 5 ? 4 : PP ? PP : 1) * kThreads, 4) void k_a
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
+        // (four calls at 8 x 32 heads x 4096 tokens of 128 channels, one kernel each, 118.1 us by shuffles, 118.9 without; four at 32
+        // heads x 32768, two kernels each, 154.2 and 151.5)
         float t = a8[j];
+        if constexpr (D == 64 || P == 0) {
+          t = stride_sum<LPT8>(t);
+        } else {
 #pragma unroll
-        for (int o = LPT8; o < 64; o <<= 1) t += __shfl_xor(t, o);
+          for (int o = LPT8; o < 64; o <<= 1) t += __shfl_xor(t, o);
+        }
         if (sub == 0) S.xw[wave][4 * ch4 + j] = t;
       }
     }
