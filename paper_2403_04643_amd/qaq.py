@@ -1,4 +1,5 @@
-"""ctypes binding over libqaq.so: argument marshalling only.
+"""ctypes binding over libqaq.so: argument marshalling only.  The two calls of a decode step
+go through _qaq_call.so (csrc/qaq_call.c), which does the same without ctypes.
 
 Every step of the method runs inside the library's HIP kernels; PyTorch is used
 here for device memory (torch tensors own every buffer, including the cache
@@ -83,6 +84,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_call = None
 
 
 class QaqError(RuntimeError):
@@ -93,7 +95,7 @@ class QaqError(RuntimeError):
 
 def load() -> C.CDLL:
     """Load libqaq.so (built by __graft_entry__.build()).  Raises if it is missing."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python __graft_entry__.py`; "
@@ -103,6 +105,13 @@ def load() -> C.CDLL:
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
+        import torch
+        from . import _qaq_call
+        lookups = [getattr(torch._C, name, None) for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream")]
+        if None in lookups:
+            lookups = [None, None]
+        _qaq_call.setup(HostBuffer, torch.float32, *lookups, _stream)
+        _call = _qaq_call
         _lib = lib
     return _lib
 
@@ -208,12 +217,15 @@ class Cache:
         with torch.cuda.device(self.device):
             _check(self.lib.qaq_create(C.byref(cfg), self._base, n, C.byref(h)))
         self.h = h
+        self._handle = h.value
+        self._attention, self._update = (C.cast(getattr(self.lib, name), C.c_void_p).value for name in ("qaq_decode_attention", "qaq_decode_update"))
         self.n_o = self.lib.qaq_outliers_per_side(C.byref(cfg))
 
     def close(self):
         if getattr(self, "h", None):
             self.lib.qaq_destroy(self.h)
             self.h = None
+            self._handle = 0
 
     def __del__(self):
         try:
@@ -283,17 +295,16 @@ class Cache:
         """The part of a decode step after the attention, in one call: scores fp32
         [B, Hq, T+1]; k_new, v_new fp16 [B, Hkv, D]; originals fp16 [B, Hkv, >=T+1, D] or
         None.  Returns (k_bits, v_bits) uint8 [B, Hkv, T+1] if want_bits."""
-        import torch
-        cfg = self.cfg
         src = k_orig if k_orig is not None else v_orig
         n_orig = src.shape[2] if src is not None else 0
         kb = vb = None
         if want_bits:
-            T1 = self.length() + 1
-            kb = torch.empty((cfg.batch, cfg.n_kv_heads, T1), dtype=torch.uint8, device="cuda")
+            import torch
+            kb = torch.empty((self.cfg.batch, self.cfg.n_kv_heads, self.length() + 1), dtype=torch.uint8, device="cuda")
             vb = torch.empty_like(kb)
-        _check(self.lib.qaq_decode_update(self.h, _ptr(scores), _ptr(k_new), _ptr(v_new), _ptr(k_orig), _ptr(v_orig),
-                                          n_orig, _ptr(kb), _ptr(vb), _stream()))
+        rc = _call.update(self._update, self._handle, scores, k_new, v_new, k_orig, v_orig, n_orig, kb, vb)
+        if rc:
+            _check(rc)
         return kb, vb
 
     def prefill_window(self, q_last, k, scores_out=None):
@@ -343,16 +354,18 @@ class Cache:
     def decode_attention(self, q, k_new=None, v_new=None, out=None, scores_out=None, want_scores=False, out_fp32=True):
         """q: fp16 [B, Hq, D]; k_new, v_new: fp16 [B, Hkv, D] or None.
         Returns (X [B, Hq, D], scores [B, Hq, T(+1)] or None)."""
-        import torch
-        cfg = self.cfg
-        if out is None:
-            out = torch.empty((cfg.batch, cfg.n_q_heads, cfg.head_dim),
-                              dtype=torch.float32 if out_fp32 else torch.float16, device=self.device)
-        if scores_out is None and want_scores:
-            scores_out = torch.empty((cfg.batch, cfg.n_q_heads, self.length() + (k_new is not None)),
-                                     dtype=torch.float32, device=self.device)
-        _check(self.lib.qaq_decode_attention(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                             1 if out.dtype == torch.float32 else 0, _ptr(scores_out), _stream()))
+        if out is None or (scores_out is None and want_scores):
+            import torch
+            cfg = self.cfg
+            if out is None:
+                out = torch.empty((cfg.batch, cfg.n_q_heads, cfg.head_dim),
+                                  dtype=torch.float32 if out_fp32 else torch.float16, device=self.device)
+            if scores_out is None and want_scores:
+                scores_out = torch.empty((cfg.batch, cfg.n_q_heads, self.length() + (k_new is not None)),
+                                         dtype=torch.float32, device=self.device)
+        rc = _call.attention(self._attention, self._handle, q, k_new, v_new, out, scores_out)
+        if rc:
+            _check(rc)
         return out, scores_out
 
     def dequantize(self, t0=0, t1=None, want_k=True, want_v=True):

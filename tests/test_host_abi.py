@@ -311,3 +311,58 @@ def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
                 assert k[".private_segment_fixed_size"] <= max_scratch, (name, k[".private_segment_fixed_size"])
                 assert k[".vgpr_count"] <= max_vgpr, (name, k[".vgpr_count"])
     assert found, key
+
+
+def test_the_steps_calls_pass_what_they_are_given():
+    """_qaq_call: addresses of tensors, of page-locked buffers and of nothing, the stream, the output's type and the status, in
+    the order of the C functions; what the binding refuses, refused."""
+    if not os.path.exists(qaq.LIB_PATH):
+        pytest.skip("library not built")
+    torch = pytest.importorskip("torch")
+    import ctypes as C
+    qaq.load()
+    call = qaq._call
+
+    class Tensor:
+        is_cuda, dtype = True, torch.float32
+
+        def __init__(self, at, contiguous=True):
+            self.at, self.contiguous = at, contiguous
+
+        def is_contiguous(self):
+            return self.contiguous
+
+        def data_ptr(self):
+            return self.at
+
+    got = []
+    vp, i32 = C.c_void_p, C.c_int32
+    fn_a = C.CFUNCTYPE(C.c_int, vp, vp, vp, vp, vp, i32, vp, vp)(lambda *a: got.append(a) or -3)
+    fn_u = C.CFUNCTYPE(C.c_int, vp, vp, vp, vp, vp, vp, i32, vp, vp, vp)(lambda *a: got.append(a) or 0)
+    at_a, at_u = (C.cast(f, vp).value for f in (fn_a, fn_u))
+    buf = qaq.HostBuffer.__new__(qaq.HostBuffer)
+    buf.dev_ptr = 0xB0F
+    big = 0x7fff_ffff_fff0
+    try:
+        call.setup(qaq.HostBuffer, torch.float32, lambda: 3, lambda dev: 0x500 + dev, None)
+        assert call.attention(at_a, big, Tensor(1), None, None, Tensor(2), Tensor(big)) == -3
+        assert got.pop() == (big, 1, None, None, 2, 1, big, 0x503)
+        half = Tensor(2)
+        half.dtype = torch.float16
+        call.attention(at_a, big, Tensor(1), Tensor(7), Tensor(8), half, None)
+        assert got.pop() == (big, 1, 7, 8, 2, 0, None, 0x503)
+        call.setup(qaq.HostBuffer, torch.float32, None, None, lambda: 0)      # torch without those lookups
+        assert call.update(at_u, 5, Tensor(1), Tensor(2), Tensor(3), buf, None, 77, None, Tensor(4)) == 0
+        assert got.pop() == (5, 1, 2, 3, 0xB0F, None, 77, None, 4, None)
+        for bad in (Tensor(1, contiguous=False), torch.zeros(2)):
+            with pytest.raises(AssertionError, match="contiguous CUDA tensors"):
+                call.attention(at_a, big, bad, None, None, Tensor(2), None)
+        for bad in (3, "q"):
+            with pytest.raises(AttributeError):
+                call.update(at_u, 5, Tensor(1), Tensor(2), Tensor(3), bad, None, 77, None, None)
+        with pytest.raises(TypeError):
+            call.attention(at_a, big, Tensor(1))
+        assert not got
+    finally:
+        buf.__dict__.clear()
+        call.setup(qaq.HostBuffer, torch.float32, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, qaq._stream)
