@@ -143,6 +143,64 @@ __global__ __launch_bounds__(kThreads) void k_prefill_softmax(QaqPrefillArgs a) 
   }
 }
 
+// The same for rows that are long or few: sixteen wavefronts per row.  Four leave most of the chip idle where rows are few, compute
+// every exponential of a row on four SIMDs, and read again what their registers do not hold of rows of more than 16384 tokens (figures: see
+// the launcher; rows of up to 8192 and 16384 tokens 8 and 16 logits per thread, so that two rows share a compute unit).  The exponentials go through LDS so that
+// their sum keeps the order it has there: thread j adds every 256th from the j-th on, then the four wavefronts' sums.
+constexpr int kWide = 1024, kWideMost = 32;       // threads, most logits of each: rows up to 32768 tokens, 128 KB of LDS
+template <int KEEP>
+__global__ __launch_bounds__(kWide, (KEEP <= 16 ? 8 : 4)) void k_prefill_softmax_wide(QaqPrefillArgs a) {
+  extern __shared__ float e_row[];                // [T]
+  __shared__ float red[kWide / 64];
+  const QaqView& v = a.v;
+  const int tid = threadIdx.x;
+  const int bq = blockIdx.x, b = bq / v.Hq, i = blockIdx.y;
+  const int len = row_length(qaq_seq_len(v, b, a.T), a.n_rows, i);
+  float* row = a.scores + ((size_t)i * v.B * v.Hq + bq) * a.T;
+  float mine[KEEP];
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    const int t = tid + k * kWide;
+    mine[k] = t < len ? row[t] : -INFINITY;
+  }
+  float m = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) m = fmaxf(m, mine[k]);
+  m = wave_max(m);
+  if ((tid & 63) == 0) red[tid >> 6] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWide / 64; ++w) m = fmaxf(m, red[w]);
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    const int t = tid + k * kWide;
+    if (t >= len) break;
+    mine[k] = expf(mine[k] - m);
+    e_row[t] = mine[k];
+  }
+  __syncthreads();                                // (red[] has been read, too)
+  if (tid < kThreads) {
+    float l = 0.0f;
+#pragma unroll 8
+    for (int t = tid; t < len; t += kThreads) l += e_row[t];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o);
+    if ((tid & 63) == 0) red[tid >> 6] = l;
+  }
+  __syncthreads();
+  const float l = (red[0] + red[1]) + (red[2] + red[3]);
+  const bool ring = a.G == 1;
+  const size_t ring0 = (size_t)i * ((size_t)v.B * v.Hkv * v.Tmax) + (size_t)bq * v.Tmax;
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    const int t = tid + k * kWide;
+    if (t >= a.T) break;
+    const float s = t < len ? mine[k] / l : 0.0f;
+    row[t] = s;
+    if (ring && t < len) qaq_ring_store(v, ring0 + t, s);
+  }
+}
+
 // Grouped queries: the window's rows, the maximum of the scores over the G query heads of a KV head (what the kernel
 // before has just written: from the last-level cache).
 __global__ __launch_bounds__(kThreads) void k_prefill_ring(QaqPrefillArgs a) {
@@ -172,7 +230,16 @@ hipError_t qaq_launch_prefill_window(const QaqPrefillArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 rows(v.B * v.Hq, a.n_rows), block(kThreads);
-  if (a.T <= 16 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<16>, rows, block, 0, s, a);
+  // Which form: sixteen wavefronts per row where the rows are few (two per compute unit) or long, four where there are many of
+  // up to 8192 tokens.  Logits and scores of 64 channels, five rows per head, us, four | sixteen: 1 x 8 heads x 2000 tokens 9.2 | 8.7,
+  // 1 x 32 x 3000 11.9 | 10.7, 2 x 50 x 6000 29.5 | 26.9, 8 x 32 x 4000 38.2 | 40.6, 4 x 32 x 8000 40.4 | 40.8, 16 x 64 x 8192
+  // 163.1 | 166.7, x 12000 261 | 233, 2 x 32 x 12001 37.8 | 32.5, 8 x 32 x 9000 110.8 | 99.2, 1 x 32 x 32000 94 | 43.
+  const bool wide = a.T <= kWide * kWideMost && (a.T > 32 * kThreads || (long long)rows.x * rows.y <= 2ll * qaq_compute_units());
+  const size_t row_bytes = (size_t)a.T * sizeof(float);
+  if (wide && a.T <= 8 * kWide) hipLaunchKernelGGL(k_prefill_softmax_wide<8>, rows, dim3(kWide), row_bytes, s, a);
+  else if (wide && a.T <= 16 * kWide) hipLaunchKernelGGL(k_prefill_softmax_wide<16>, rows, dim3(kWide), row_bytes, s, a);
+  else if (wide) hipLaunchKernelGGL(k_prefill_softmax_wide<kWideMost>, rows, dim3(kWide), row_bytes, s, a);
+  else if (a.T <= 16 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<16>, rows, block, 0, s, a);
   else if (a.T <= 32 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<32>, rows, block, 0, s, a);
   else hipLaunchKernelGGL(k_prefill_softmax<64>, rows, block, 0, s, a);
   e = hipGetLastError();

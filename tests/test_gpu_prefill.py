@@ -262,3 +262,36 @@ def test_rows_at_the_borders_of_the_register_forms(D, Hkv, G, T, n, shortfall):
         bk_o, bv_o, _ = oc.prefill(qb, Kb, Vb, score_rows=[got[i][..., : length - n + i + 1] for i in range(n)])
         np.testing.assert_array_equal(bk_g[b:b + 1, :, :length], bk_o)
         np.testing.assert_array_equal(bv_g[b:b + 1, :, :length], bv_o)
+
+
+@pytest.mark.parametrize("T", [300, 4096, 4097, 8192])
+@pytest.mark.parametrize("G", [1, 2])
+def test_a_row_does_not_depend_on_how_many_there_are(G, T):
+    """Few rows take sixteen wavefronts each, many take four: the same scores, to the last bit, and the same widths."""
+    import torch
+    B, Hkv, D, n = 20, 8, 64, 4
+    sh = W.shape(3, batch=1, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
+    _log(f"few and many rows: {sh}")
+    K, V = (dev(x) for x in W.make_kv(3, sh))
+    q = dev(np.ascontiguousarray(W.make_queries(3, sh, n=n, seed_offset=4).transpose(1, 2, 0, 3) * F16(4.0)))
+    got = []
+    for copies in (1, B):
+        cache = qaq.Cache(qaq.make_config(copies, Hkv * G, Hkv, D, T, [1.0] * Hkv, window=n, sigma_s_max=1e-3, sigma_x_max=1e-2))
+        k, v, ql = (x.repeat(copies, 1, 1, 1) for x in (K, V, q))
+        got.append((cache.prefill_window(ql, k), *cache.quantize_append_selected(k, v, want_bits=True)))
+    assert n * Hkv <= 512 < n * Hkv * B
+    (few, kb, vb), (many, kbm, vbm) = got
+    assert torch.equal(few.expand_as(many), many)
+    assert torch.equal(kb.expand_as(kbm), kbm) and torch.equal(vb.expand_as(vbm), vbm)
+
+
+@pytest.mark.parametrize("T", [32767, 32768, 32769])
+def test_the_longest_rows_in_registers(T):
+    """... and the first that sixteen wavefronts do not hold."""
+    sh = W.shape(3, batch=1, n_q_heads=2, n_kv_heads=1, head_dim=64, context=T)
+    _log(f"longest rows: {sh}")
+    K, _ = W.make_kv(3, sh)
+    q_last = np.ascontiguousarray(W.make_queries(3, sh, n=2, seed_offset=4).transpose(1, 2, 0, 3) * F16(4.0))
+    cache = qaq.Cache(qaq.make_config(1, 2, 1, 64, T, [1.0], window=2))
+    rows = cache.prefill_window(dev(q_last), dev(K)).cpu().numpy()
+    _log(f"  worst score error {_check_rows(rows, q_last, K, 2):.2e}")
