@@ -110,7 +110,8 @@ float value_threshold(const qaq_cache* c, int T) { return (float)(c->sigma_x / s
 // How many tokens a threshold passes as it moves depends on how the scores are spread, which the host does not see, so the
 // factors are a compromise between four laws of scores: a prompt's own (close together), the same with spiked keys and values,
 // ~ rank^-1.1 (spread out), the sixth power of a uniform number.  The decode-step kernel with what it hands over | the general
-// kernel alone, us, 8 x 32 heads x 4000 tokens, the smallest staging (64 tokens of 128 channels, 120 of 64); "to" marks the line:
+// kernel alone, us, 8 x 32 heads x 4000 tokens, the smallest staging (64 tokens of 128 channels, 120 of 64); "to" marks the line (taken
+// when the decode-step kernel alone was 2 us slower there):
 //                                                         prompt    spiked    rank      power
 //   threshold fallen  128 channels              x 0.90     91 |  72   34 |  71  28 |  70   87 |  76   to the decode-step kernel
 //                                               x 0.83    141 |  80   40 |  72  30 |  73  138 |  80   to the general kernel
