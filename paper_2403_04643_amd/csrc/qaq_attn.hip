@@ -121,7 +121,7 @@ __device__ __forceinline__ float vmaxf(float a, float b) {
 }
 
 // Sums over the 16 lanes of a row, and over the lanes of the wavefront whose numbers are equal modulo N (4 or 8), in every lane:
-// without the trip through LDS that a shuffle is.
+// neighbours first, as by shuffles, without the trip through LDS that a shuffle is.
 __device__ __forceinline__ float row_sum(float x) {
   asm volatile(QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")
                QAQ_DPP_STEP("v_add_f32_dpp", "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
@@ -134,8 +134,12 @@ __device__ __forceinline__ float row_sum(float x) {
 template <int N>
 __device__ __forceinline__ float stride_sum(float x) {
   static_assert(N == 4 || N == 8, "lanes of a group");
+  if (N == 4) {                                     // the lane four further up or down: row_shl:4 in the even fours, row_shr:4 in the odd ones
+    int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x104, 0xf, 0x5, false);
+    y = __builtin_amdgcn_update_dpp(y, __float_as_int(x), 0x114, 0xf, 0xa, false);
+    x += __int_as_float(y);
+  }
   x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));             // row_ror:8
-  if (N == 4) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, true));   // row_ror:4
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
