@@ -145,11 +145,13 @@ __global__ __launch_bounds__(kThreads) void k_prefill_softmax(QaqPrefillArgs a) 
 
 // The same for rows that are long or few: sixteen wavefronts per row.  Four leave most of the chip idle where rows are few, compute
 // every exponential of a row on four SIMDs, and read again what their registers do not hold of rows of more than 16384 tokens (figures: see
-// the launcher; rows of up to 8192 and 16384 tokens 8 and 16 logits per thread, so that two rows share a compute unit).  The exponentials go through LDS so that
+// the launcher).  Rows of up to 8192, 16384 and 20464 tokens take 8, 16 and 20 logits per thread, so that two rows share a compute
+// unit; longer ones 32, a compute unit each.  The exponentials go through LDS so that
 // their sum keeps the order it has there: thread j adds every 256th from the j-th on, then the four wavefronts' sums.
 constexpr int kWide = 1024, kWideMost = 32;       // threads, most logits of each: rows up to 32768 tokens, 128 KB of LDS
+constexpr int kWideTwo = (160 * 1024 / 2 - 64) / 4;       // longest row of which a compute unit's LDS holds two: 20464 tokens, 20 logits per thread
 template <int KEEP>
-__global__ __launch_bounds__(kWide, (KEEP <= 16 ? 8 : 4)) void k_prefill_softmax_wide(QaqPrefillArgs a) {
+__global__ __launch_bounds__(kWide, (KEEP <= 20 ? 8 : 4)) void k_prefill_softmax_wide(QaqPrefillArgs a) {
   extern __shared__ float e_row[];                // [T]
   __shared__ float red[kWide / 64];
   const QaqView& v = a.v;
@@ -233,11 +235,16 @@ hipError_t qaq_launch_prefill_window(const QaqPrefillArgs& a, hipStream_t s) {
   // Which form: sixteen wavefronts per row where the rows are few (two per compute unit) or long, four where there are many of
   // up to 8192 tokens.  Logits and scores of 64 channels, five rows per head, us, four | sixteen: 1 x 8 heads x 2000 tokens 9.2 | 8.7,
   // 1 x 32 x 3000 11.9 | 10.7, 2 x 50 x 6000 29.5 | 26.9, 8 x 32 x 4000 38.2 | 40.6, 4 x 32 x 8000 40.4 | 40.8, 16 x 64 x 8192
-  // 163.1 | 166.7, x 12000 261 | 233, 2 x 32 x 12001 37.8 | 32.5, 8 x 32 x 9000 110.8 | 99.2, 1 x 32 x 32000 94 | 43.
+  // 163.1 | 166.7, x 12000 261 | 233, 2 x 32 x 12001 37.8 | 32.5, 8 x 32 x 9000 110.8 | 99.2, 1 x 32 x 32000 94 | 43.  Short rows, 128
+  // channels: 1 x 32 x 64 7.4 | 6.7, x 512 8.8 | 8.2, 3 x 32 x 100 8.4 | 7.8, x 500 9.6 | 9.2, 1 x 8 x 1 token and row 5.7 | 4.9.
+  // Past 16384 tokens, 128 channels, four | sixteen with a compute unit per row | sixteen with two rows on one (as far as its LDS holds
+  // two): 16 x 64 heads on 8 x 16385 465 | 482 | 451, x 20464 664 | 561 | 541, 1 x 64 on 8 x 16640, 8 rows 51.0 | 52.6 | 48.1,
+  // 8 x 32 x 17400 336 | 332 | 325, 1 x 32 x 16385 42.4 | 36.2 | 36.1.
   const bool wide = a.T <= kWide * kWideMost && (a.T > 32 * kThreads || (long long)rows.x * rows.y <= 2ll * qaq_compute_units());
   const size_t row_bytes = (size_t)a.T * sizeof(float);
   if (wide && a.T <= 8 * kWide) hipLaunchKernelGGL(k_prefill_softmax_wide<8>, rows, dim3(kWide), row_bytes, s, a);
   else if (wide && a.T <= 16 * kWide) hipLaunchKernelGGL(k_prefill_softmax_wide<16>, rows, dim3(kWide), row_bytes, s, a);
+  else if (wide && a.T <= kWideTwo) hipLaunchKernelGGL(k_prefill_softmax_wide<20>, rows, dim3(kWide), row_bytes, s, a);
   else if (wide) hipLaunchKernelGGL(k_prefill_softmax_wide<kWideMost>, rows, dim3(kWide), row_bytes, s, a);
   else if (a.T <= 16 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<16>, rows, block, 0, s, a);
   else if (a.T <= 32 * kThreads) hipLaunchKernelGGL(k_prefill_softmax<32>, rows, block, 0, s, a);

@@ -235,6 +235,8 @@ def test_score_rows_over_many_shares(D, Hkv, G, T, n, gain):
     (64, 1, 1, 16384, 2, None),
     (64, 1, 1, 16385, 2, None),             # one logit, and a row of them, that no register holds
     (64, 1, 4, 16641, 2, None),
+    (64, 1, 1, 20464, 2, None),             # the longest row of which a compute unit takes two, and the first that has one to itself
+    (64, 1, 2, 20465, 2, (0, 4000)),
     (64, 1, 1, 16900, 2, (0, 600)),         # the shorter sequence's row ends inside the registers
     (64, 1, 2, 8300, 2, (0, 8200)),
 ])

@@ -297,6 +297,7 @@ def test_decode_path_kernels_do_not_spill():
     ("k_dequantILi64ELi8E", 72, 0),
     ("k_update_fewI", 72, 0),                 # seven
     ("k_prefill_softmaxILi64E", 256, 0),      # 64 logits per thread
+    ("k_prefill_softmax_wideILi20E", 64, 0),  # two rows of sixteen wavefronts per compute unit
 ])
 def test_other_kernels_at_their_budget(key, max_vgpr, max_scratch):
     """The same for kernels off the benchmark's shape that sit at the edge of their budget: one register more in each
