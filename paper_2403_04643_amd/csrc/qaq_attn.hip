@@ -490,7 +490,9 @@ struct ValRegs {
                  // group g holds word g & 1 of half-unit g >> 1 (handed to the lanes that need it when it is used)
   // D = 64, in k_attn_tile, whose forms there have the registers: the first 64 slots of the 4-bit region and the first row of the
   // lane's share of the 8-bit values come with the tile too (and sums across lanes without shuffles; two calls at 4 x 32 heads x 3000
-  // tokens 32.1 -> 30.8 us, with spiked values 37.5 -> 34.0, all at 8 bits 52.8 -> 49.9)
+  // tokens 32.1 -> 30.8 us, with spiked values 37.5 -> 34.0, all at 8 bits 52.8 -> 49.9).  Behind a test each, the same in every lane: a
+  // row asked for where there is none, any word of the tile, had cost tiles without such tokens 1 to 3 % (20 x 32 heads x 1000 tokens,
+  // all at 2 bits, one call: 16.3 us without, 16.8 with it, 16.4 behind the test; 8 x 32 x 4096 20.7, 21.0, 20.8)
   static constexpr bool WITH48 = CGW == 1 && NO2 <= 2;
   uint32_t v4w[2];
   uint32_t v8;   // 8-bit values (token-major rows): this lane's four channels of row lane / (D/16), so
@@ -534,7 +536,7 @@ struct ValRegs {
 #pragma unroll
       for (int k = 0; k < 2; ++k) v4w[k] = gload32(ubase, rV.r4 + (uint32_t)min(2 * g + k, nhu - 1) * (4u * D) + (uint32_t)nn * (NCG * 4) + 4u * (uint32_t)(CGW * wave));
     }
-    if (PRE8 || WITH48) {
+    if (PRE8 || (WITH48 && c.n8 > 0)) {
       const int lane = tid & 63;
       v8 = gload32(ubase, c.n8 > 0 ? rV.r8 + (uint32_t)min(lane / (D / 16), c.n8 - 1) * D + (D / 4) * wave + 4 * (lane % (D / 16)) : 0u);
     }
