@@ -95,7 +95,7 @@ class QaqError(RuntimeError):
 
 def load() -> C.CDLL:
     """Load libqaq.so (built by __graft_entry__.build()).  Raises if it is missing."""
-    global _lib, _call
+    global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python __graft_entry__.py`; "
@@ -105,15 +105,26 @@ def load() -> C.CDLL:
             fn = getattr(lib, name)
             fn.restype = res
             fn.argtypes = args
+        _lib = lib
+    return _lib
+
+
+def _load_call():
+    """The two calls of a decode step, for a Cache: what needs no cache needs neither torch nor the extension."""
+    global _call
+    if _call is None:
         import torch
-        from . import _qaq_call
+        try:
+            from . import _qaq_call
+        except ImportError as e:
+            raise RuntimeError(f"the binding's extension _qaq_call is missing from {_HERE}: build it with "
+                               "`python __graft_entry__.py`; there is no fallback path") from e
         lookups = [getattr(torch._C, name, None) for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream")]
         if None in lookups:
             lookups = [None, None]
         _qaq_call.setup(HostBuffer, torch.float32, *lookups, _stream)
         _call = _qaq_call
-        _lib = lib
-    return _lib
+    return _call
 
 
 def _check(rc: int) -> None:
@@ -204,6 +215,7 @@ class Cache:
     def __init__(self, cfg: Config, device="cuda:0"):
         import torch
         self.lib = load()
+        self._call = _load_call()
         self.cfg = cfg
         self.device = torch.device(device)
         n = self.lib.qaq_arena_bytes(C.byref(cfg))
@@ -302,7 +314,7 @@ class Cache:
             import torch
             kb = torch.empty((self.cfg.batch, self.cfg.n_kv_heads, self.length() + 1), dtype=torch.uint8, device="cuda")
             vb = torch.empty_like(kb)
-        rc = _call.update(self._update, self._handle, scores, k_new, v_new, k_orig, v_orig, n_orig, kb, vb)
+        rc = self._call.update(self._update, self._handle, scores, k_new, v_new, k_orig, v_orig, n_orig, kb, vb)
         if rc:
             _check(rc)
         return kb, vb
@@ -363,7 +375,7 @@ class Cache:
             if scores_out is None and want_scores:
                 scores_out = torch.empty((cfg.batch, cfg.n_q_heads, self.length() + (k_new is not None)),
                                          dtype=torch.float32, device=self.device)
-        rc = _call.attention(self._attention, self._handle, q, k_new, v_new, out, scores_out)
+        rc = self._call.attention(self._attention, self._handle, q, k_new, v_new, out, scores_out)
         if rc:
             _check(rc)
         return out, scores_out

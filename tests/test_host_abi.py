@@ -321,8 +321,7 @@ def test_the_steps_calls_pass_what_they_are_given():
         pytest.skip("library not built")
     torch = pytest.importorskip("torch")
     import ctypes as C
-    qaq.load()
-    call = qaq._call
+    call = qaq._load_call()
 
     class Tensor:
         is_cuda, dtype = True, torch.float32
@@ -366,4 +365,30 @@ def test_the_steps_calls_pass_what_they_are_given():
         assert not got
     finally:
         buf.__dict__.clear()
-        call.setup(qaq.HostBuffer, torch.float32, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, qaq._stream)
+        qaq._call = None
+        qaq._load_call()
+
+
+def test_what_needs_no_cache_needs_neither_torch_nor_the_extension():
+    """Sizes, limits and routes by ctypes alone; a cache without the extension says how to build it."""
+    if not os.path.exists(qaq.LIB_PATH):
+        pytest.skip("library not built")
+    import subprocess
+    import sys
+    code = '''
+import ctypes as C, sys
+sys.modules["paper_2403_04643_amd._qaq_call"] = None
+%s
+from paper_2403_04643_amd import qaq
+cfg = qaq.make_config(2, 8, 8, 128, 1000, [0.01] * 8)
+assert qaq.load().qaq_arena_bytes(C.byref(cfg)) > 0 and qaq.attention_route(cfg, 1000).parts > 0
+try:
+    qaq.Cache(cfg)
+except %s as e:
+    assert %r in str(e), e
+else:
+    raise SystemExit("a cache without what it needs")
+'''
+    for block, error, says in (('sys.modules["torch"] = None', "ImportError", "torch"), ("", "RuntimeError", "build it with")):
+        r = subprocess.run([sys.executable, "-c", code % (block, error, says)], cwd=ROOT, capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stderr
