@@ -1,5 +1,5 @@
 """ctypes binding over libqaq.so: argument marshalling only.  The two calls of a decode step
-go through _qaq_call.so (csrc/qaq_call.c), which does the same without ctypes.
+go through the extension _qaq_call (csrc/qaq_call.c), which does the same without ctypes.
 
 Every step of the method runs inside the library's HIP kernels; PyTorch is used
 here for device memory (torch tensors own every buffer, including the cache
@@ -117,7 +117,7 @@ def _load_call():
         try:
             from . import _qaq_call
         except ImportError as e:
-            raise RuntimeError(f"the binding's extension _qaq_call is missing from {_HERE}: build it with "
+            raise RuntimeError(f"the binding's extension _qaq_call is missing from {_HERE}, for this Python: build it with "
                                "`python __graft_entry__.py`; there is no fallback path") from e
         lookups = [getattr(torch._C, name, None) for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream")]
         if None in lookups:

@@ -369,6 +369,15 @@ def test_the_steps_calls_pass_what_they_are_given():
         qaq._load_call()
 
 
+def test_the_extension_is_for_this_python():
+    """It is built against one Python's headers: its name tells the others to leave it alone."""
+    if not os.path.exists(qaq.LIB_PATH):
+        pytest.skip("library not built")
+    pytest.importorskip("torch")
+    import sysconfig
+    assert sysconfig.get_config_var("SOABI") and os.path.basename(qaq._load_call().__file__) == "_qaq_call" + sysconfig.get_config_var("EXT_SUFFIX")
+
+
 def test_what_needs_no_cache_needs_neither_torch_nor_the_extension():
     """Sizes, limits and routes by ctypes alone; a cache without the extension says how to build it."""
     if not os.path.exists(qaq.LIB_PATH):
