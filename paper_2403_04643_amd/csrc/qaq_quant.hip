@@ -1356,8 +1356,10 @@ __global__ __launch_bounds__(kThreads, (listed_per_cu<D, ONE>())) void k_build_l
 // with the copies in host memory 16.1 | 12.0, outliers by thresholds, 3 x 16 x 2500, 15.4 | 11.3.
 // ---------------------------------------------------------------------------------
 constexpr int kMaxCopy = 8192;
-// Four wavefronts per tile side up to this many value sides per compute unit (28 of the 32 wavefronts it holds, 72 registers each).
-// Eight steps with their prompt, us, two | four: 5 (2 x 32 heads x 4100 tokens) 351.3 | 343.2, 6 (3 x 32 x 4000) 411.8 | 399.9,
+// Four wavefronts per tile side up to this many value sides per compute unit, where two have become as fast.  (Vector registers, 55 to 58,
+// would let eight sides of four wavefronts live on a compute unit; scalar ones, 112 and 16 for the trap handler of a SIMD's 800, let six.
+// With 96, by a launch bound of seven or asked for, seven live: where there are seven a step takes 6 % less, with up to three 1 % more,
+// and 4 x 32 heads of 3400, 3300, 1400 and 400 tokens 7 % more, 29.9 -> 32.1 us.)  Eight steps with their prompt, us, two | four: 5 (2 x 32 heads x 4100 tokens) 351.3 | 343.2, 6 (3 x 32 x 4000) 411.8 | 399.9,
 // 7 (4 x 32 x 3500 of 64 channels) 352.9 | 347.6, 8 (4 x 32 x 4000) 454.4 | 455.3, the same with spiked values 467.7 | 470.7.
 constexpr int kUpdFew = 7;
 constexpr int kUpdResident = 16;    // tile sides a compute unit takes: two wavefronts of at most 64 registers each
