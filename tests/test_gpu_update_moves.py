@@ -69,6 +69,86 @@ def test_both_forms_of_the_update(B, D, bit_set, n_o, thresholds):
     test_update_equals_separate_calls_when_many_tokens_move(B, 128, 1, D, 254, 5, bit_set, n_o, thresholds, 3, {})
 
 
+@pytest.mark.parametrize("wavefronts", [2, 4])
+@pytest.mark.parametrize("G,D,bit_set,n_o,thresholds,window,store,copies,ragged", [
+    (1, 128, (2, 3, 4, 8), 1, False, 2, {}, "device", True),
+    (2, 128, (2, 3, 4, 8), 1, False, 3, {"window_fp16": True}, "none", False),
+    (3, 64, (2, 3, 4, 8), 1, False, 5, {"window_bf16": True}, "host", True),
+    (6, 64, (1, 2, 3, 4, 8), 2, False, 1, {}, "none", True),
+    (2, 128, (2, 3, 4, 8), 4, True, 3, {"window_bf16": True}, "device", True),
+    (1, 64, (2, 3, 4, 8), 2, True, 8, {"window_fp16": True}, "host", True),
+    (8, 128, (1, 2, 8), 0, False, 4, {"window_fp16": True}, "device", False),
+])
+def test_both_forms_of_the_update_over_their_options(wavefronts, G, D, bit_set, n_o, thresholds, window, store, copies, ragged):
+    """Windows kept in 16 bits, several query heads per KV head, sequences that end in different tiles (one with its first
+    token there, one with its first token at all), copies in host memory and none, by two wavefronts per tile side (more than
+    seven value sides per compute unit) and by four."""
+    print(f"options: wavefronts={wavefronts} G={G} D={D} set={bit_set} n_o={n_o} thr={thresholds} window={window} {store} {copies} ragged={ragged}", flush=True)
+    T, steps, B = 2043 if ragged else 507, 9, 8                # from the sixth step on a tile more
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if ragged:                             # (at most 256 pairs of a sequence and a KV head)
+        Hkv = 32 if wavefronts == 2 else 4
+    else:
+        Hkv = cus // 2 if wavefronts == 2 else cus // 8
+    tiles = (T + 1 + 255) // 256
+    assert all((-(-B * Hkv * n // cus) > 7) == (wavefronts == 2) for n in (tiles, tiles + 1))
+    lens = [2043, 256, 255, 1, 2, 1800, 1279, 2036] if ragged else [T] * B
+    cap = T + steps
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(100 * G + D + window)
+    std = torch.exp(torch.rand((1, Hkv, 1, D), device="cuda", generator=gen) * 2.0)
+    k, v = ((torch.randn((B, Hkv, cap, D), device="cuda", generator=gen) * std).half() for _ in range(2))
+    thr = [_thresholds(k), _thresholds(v)] if thresholds else None
+    fused, apart = (qaq.Cache(qaq.make_config(B, Hkv * G, Hkv, D, cap, [1.0] * Hkv, bit_set=bit_set, n_outlier_per_side=n_o, window=window,
+                                              outlier_thresholds=thr, **store)) for _ in range(2))
+    for c in (fused, apart):
+        if ragged:
+            c.set_shortfall([T - n for n in lens])
+        c.quantize_append(k[:, :, :T].contiguous(), v[:, :, :T].contiguous())
+    # the caller's copies as far as the tokens are there; the call adds its own
+    have = torch.arange(cap, device="cuda")[None, :] < torch.tensor(lens, device="cuda")[:, None]
+    k_copy, v_copy = (torch.where(have[:, None, :, None], x, torch.zeros_like(x)) for x in (k, v))
+    given = {"device": (k_copy, v_copy), "none": (None, None)}.get(copies)
+    if copies == "host":
+        given = tuple(qaq.HostBuffer(tuple(k.shape), "float16") for _ in range(2))
+        for h, x in zip(given, (k_copy, v_copy)):
+            h.array[:] = x.cpu().numpy()
+    own = (k, v) if copies != "none" else (None, None)
+    likely = torch.rand((B, Hkv * G, cap), device="cuda", generator=gen).pow_(6)
+    for j in range(steps):                 # scores and hyper-parameters that move as they do while a model generates
+        n = [x + j + 1 for x in lens]
+        s = torch.full((B, Hkv * G, T + j + 1), float("nan"), device="cuda")        # nothing may read past a sequence's own
+        for b in range(B):
+            x = likely[b, :, :n[b]] * torch.exp(0.3 * torch.randn((Hkv * G, n[b]), device="cuda", generator=gen))
+            s[b, :, :n[b]] = x / x.sum(-1, keepdim=True)
+        for c in (fused, apart):
+            c.set_sigmas(*((2e-4, 1e-2), (1.97e-4, 9.8e-3), (2.02e-4, 1.01e-2))[j % 3])
+        kn, vn = (torch.stack([x[b, :, n[b] - 1] for b in range(B)]).contiguous() for x in (k, v))
+        kb, vb = fused.decode_update(s, kn, vn, *given, want_bits=True)
+        apart.quantize_append(kn[:, :, None].contiguous(), vn[:, :, None].contiguous())
+        kb2, vb2 = apart.select_bits(s)
+        apart.requantize(kb2, vb2, *own)
+        assert fused.lengths() == apart.lengths() == n
+        got, want = ([c.export_canonical(side) for side in (0, 1)] for c in (fused, apart))
+        for b in range(B):
+            assert torch.equal(kb[b, :, :n[b]], kb2[b, :, :n[b]]) and torch.equal(vb[b, :, :n[b]], vb2[b, :, :n[b]]), f"step {j}, sequence {b}: widths"
+            for side in (0, 1):
+                for name in got[side]:
+                    x, y = (e[side][name][b, :, :n[b]].contiguous().view(torch.uint8) for e in (got, want))
+                    assert torch.equal(x, y), f"step {j} side {side}, sequence {b}: {name}"
+    a, b = fused.stats(), apart.stats()
+    everything = 2 * Hkv * sum((x + 255) // 256 for x in n)
+    print(f"  handed over in the last step: {a.update_handovers} of {everything}; widenings served {a.served_upgrades}, refused {a.refused_upgrades}", flush=True)
+    assert a.update_handovers < everything // 4, "the general kernel did the step"
+    assert (a.served_upgrades, a.refused_upgrades) == (b.served_upgrades, b.refused_upgrades)
+    assert (a.served_upgrades == 0) == (copies == "none") and (a.refused_upgrades > 0) == (copies == "none")
+    if copies != "none":
+        have = torch.arange(cap, device="cuda")[None, :] < torch.tensor([x + steps for x in lens], device="cuda")[:, None]
+        for x, y in zip(given, (k, v)):
+            x = x if copies == "device" else torch.from_numpy(x.array.copy()).cuda()
+            assert torch.equal(x, torch.where(have[:, None, :, None], y, torch.zeros_like(y))), "the appended rows belong into the copies"
+
+
 @pytest.mark.parametrize("B,Hkv,D,T,bit_set,n_o,thresholds,staged", [
     (8, 32, 128, 3900, (2, 3, 4, 8), 1, False, "some"),        # sixteen sides per compute unit: the smallest staging
     (8, 32, 128, 1290, (1, 2, 3, 4, 8), 1, False, "some"),
