@@ -239,10 +239,14 @@ def test_score_rows_over_many_shares(D, Hkv, G, T, n, gain):
     (64, 1, 2, 20465, 2, (0, 4000)),
     (64, 1, 1, 16900, 2, (0, 600)),         # the shorter sequence's row ends inside the registers
     (64, 1, 2, 8300, 2, (0, 8200)),
+    (64, 1, 1, 32768, 1, None),             # the last row that sixteen wavefronts hold
+    (64, 1, 1, 32771, 2, (0, 900)),         # four wavefronts, 64 logits per thread and the others read again: both rows end in those,
+    (64, 1, 2, 33000, 2, (0, 20000)),       # the shorter one inside the registers
 ])
 def test_rows_at_the_borders_of_the_register_forms(D, Hkv, G, T, n, shortfall):
-    """The softmax keeps a row's logits in registers, 16, 32 or 64 per thread, and reads again what they do not hold: rows
-    and window around each border, sequences of one length and of two."""
+    """The softmax keeps a row's logits in registers: sixteen wavefronts 8, 16, 20 or 32 per thread, for rows that are few (as
+    nearly all here) or long; beyond 32768 tokens four wavefronts 64 per thread, and they read again what those do not hold.  Rows
+    and window around each border, sequences of one length and of two; the forms for many short rows against these: below."""
     B = len(shortfall) if shortfall else 1
     sh = W.shape(3, batch=B, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
     _log(f"prefill rows: {sh} rows={n} shortfall={shortfall}")
@@ -285,6 +289,34 @@ def test_a_row_does_not_depend_on_how_many_there_are(G, T):
     (few, kb, vb), (many, kbm, vbm) = got
     assert torch.equal(few.expand_as(many), many)
     assert torch.equal(kb.expand_as(kbm), kbm) and torch.equal(vb.expand_as(vbm), vbm)
+
+
+@pytest.mark.parametrize("T,shortfall", [(300, (0, 296, 100)), (4096, (0, 1, 4000)), (4097, (0, 1, 2)), (6000, (0, 1905, 5996)), (8192, (0, 4096, 8000))])
+@pytest.mark.parametrize("G", [1, 2])
+def test_a_shorter_row_does_not_depend_on_how_many_there_are(G, T, shortfall):
+    """The same with sequences of different lengths: four wavefronts per row, 16 and 32 logits per thread, against sixteen."""
+    import torch
+    Hkv, D, n = 8, 64, 4
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B, copies = len(shortfall), -(-2 * cus // (len(shortfall) * Hkv * n)) + 1
+    sh = W.shape(3, batch=B, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=D, context=T)
+    _log(f"few and many rows, ragged: {sh} copies={copies}")
+    K, V = (dev(x) for x in W.make_kv(3, sh))
+    q = dev(np.ascontiguousarray(W.make_queries(3, sh, n=n, seed_offset=4).transpose(1, 2, 0, 3) * F16(4.0)))
+    got = []
+    for c in (1, copies):
+        cache = qaq.Cache(qaq.make_config(c * B, Hkv * G, Hkv, D, T, [1.0] * Hkv, window=n, sigma_s_max=1e-3, sigma_x_max=1e-2))
+        cache.set_shortfall(list(shortfall) * c)
+        k, v, ql = (x.repeat(c, 1, 1, 1) for x in (K, V, q))
+        got.append((cache.prefill_window(ql, k), *cache.quantize_append_selected(k, v, want_bits=True)))
+    assert n * Hkv * G * B <= 2 * cus < n * Hkv * G * B * copies
+    (few, kb, vb), (many, kbm, vbm) = got
+    for c in range(copies):
+        assert torch.equal(few, many[:, c * B:(c + 1) * B])
+        for b in range(B):
+            length = T - shortfall[b]
+            assert (few[:, b, :, length:] == 0).all()
+            assert torch.equal(kb[b, :, :length], kbm[c * B + b, :, :length]) and torch.equal(vb[b, :, :length], vbm[c * B + b, :, :length])
 
 
 @pytest.mark.parametrize("T", [32767, 32768, 32769])
