@@ -93,11 +93,12 @@ __global__ __launch_bounds__(kThreads) void k_prefill_logits(QaqPrefillArgs a) {
 }
 
 // Softmax of the score rows in place: one workgroup per (query head, prompt row).  Bound by HBM: a thread keeps its
-// logits -- every 256th of the row -- in registers, KEEP of them (16, 32 or 64 by the row's length), so that up to
-// 16384 tokens a score is read once and written once.  The sum's order is part of what the scores are to the last bit:
+// logits -- every 256th of the row -- in registers, KEEP of them: 16 and 32 for many rows of up to 4096 and 8192 tokens, so
+// that a score is read once and written once; 64 for rows of more than 32768, whose others are read again, for the sum and for
+// the scores (what lies between: the wide form below).  The sum's order is part of what the scores are to the last bit:
 // a score that decides a width must not depend on how a row is shared out.  Before, one workgroup took the rows of all
 // G heads one after the other, with 16 logits in registers: 16 x 64 heads, 8192 tokens, 5 rows 256 us, now 59 (and 27 for
-// the window's rows); 8 x 32 heads, 4096 tokens 18 -> 13; 2 x 32 heads, 12001 tokens 37 -> 18.
+// the window's rows); 8 x 32 heads, 4096 tokens 18 -> 13.
 template <int KEEP>
 __global__ __launch_bounds__(kThreads) void k_prefill_softmax(QaqPrefillArgs a) {
   __shared__ float red[4];
